@@ -1,0 +1,129 @@
+// fp32 products on the 16-bit matrix unit: operands split into two halves.
+//
+// A value v is scaled by a power of two s that puts the largest magnitude of
+// its tensor into [2^14, 2^15) and split into two fp16 numbers,
+//   v s = hi + lo + e,   hi = fp16(v s),  lo = fp16(v s - hi),
+// |e| <= 2^-22 |v s| while |v| is above 2^-18 of the largest and <= 2^-25
+// absolutely (2^-40 of the largest) below that.  A product of two such
+// numbers is lo hi' + hi lo' + hi hi' (lo lo' is below 2^-22 of it): three
+// v_mfma_f32_16x16x32_f16, which multiply exactly and accumulate in fp32,
+// where v_mfma_f32_16x16x4_f32 needs eight instructions of twice the cycles
+// for the same K: 48 against 256 cycles.  The sum of 32 products is rounded
+// once instead of 32 times, so the result is closer to the exact one than the
+// fp32 instruction's: over 576 products of N(0,1) x U(-0.1,0.1) the relative
+// error (2-norm) is 2.7e-7 against 4.3e-7 (three bf16 parts with six products:
+// 3.5e-7).  The scales are exact and are undone on the sums.
+//
+// A split pair takes 4 bytes like the fp32 value: 8 channels are 16 bytes of
+// hi followed by 16 bytes of lo, in LDS and in the weight fragments.
+//
+// Where the scale comes from:
+//   h        |h| <= 1 (o tanh c): s = 2^15;
+//   weights  the largest magnitude of a gate row (per-row scale);
+//   x        the largest magnitude of the tensor.  A tensor that one scale
+//            does not serve (a value that is not finite, or more than 1 in
+//            1024 of its non-zero values below 2^-17 of the largest, where
+//            the split starts to lose bits) keeps the fp32 instruction: the
+//            step kernels then read the same 32 bytes as eight fp32 channels
+//            (ctl[0] = 1).
+#pragma once
+
+#include "common.h"
+
+namespace plstm {
+
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef float v4 __attribute__((ext_vector_type(4)));
+
+constexpr float kHScale = 32768.0f;     // 2^15
+constexpr int kStatBlocks = 256;
+constexpr unsigned kStatRange = 17u << 23;   // 2^-17 of the largest, in exponent bits
+
+struct Split8 {
+    h8 hi, lo;
+};
+// Two f4 (channels 0..3, 4..7), already scaled.
+__device__ inline Split8 split8(v4 a, v4 b)
+{
+    Split8 s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        s.hi[i] = (_Float16)a[i];
+        s.hi[4 + i] = (_Float16)b[i];
+        s.lo[i] = (_Float16)(a[i] - (float)s.hi[i]);
+        s.lo[4 + i] = (_Float16)(b[i] - (float)s.hi[4 + i]);
+    }
+    return s;
+}
+
+__device__ inline v4 mfma_h(h8 a, h8 b, v4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+
+// Exponent that brings magnitude bits `m` (a finite float's, sign cleared)
+// into [2^14, 2^15); 0 for m = 0.
+__device__ inline int scale_exp(unsigned m)
+{
+    if (m == 0) return 0;
+    const int e = 14 - ((int)(m >> 23) - 127);
+    return e > 110 ? 110 : e;           // (denormals count as 2^-127)
+}
+__device__ inline float exp2i(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
+
+// Statistics of a tensor, two passes: per block the largest finite magnitude
+// (bits) and whether a value is not finite; then, per block, how many values
+// are not zero and how many of those lie below 2^-17 of the tensor's largest.
+struct SplitStat {
+    unsigned max_bits, bad, nonzero, small;
+};
+struct SplitStats {
+    SplitStat first[kStatBlocks], second[kStatBlocks];
+};
+int split_stats(int dtype, const void *x, long long n, SplitStats *part, hipStream_t st);
+
+__device__ inline SplitStat stat_combine(SplitStat a, SplitStat b)
+{
+    SplitStat r;
+    r.max_bits = a.max_bits > b.max_bits ? a.max_bits : b.max_bits;
+    r.bad = a.bad | b.bad;
+    r.nonzero = a.nonzero + b.nonzero;      // (at most 2^31 values)
+    r.small = a.small + b.small;
+    return r;
+}
+__device__ inline SplitStat stat_wave(SplitStat s)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        SplitStat t;
+        t.max_bits = __shfl_xor(s.max_bits, o);
+        t.bad = __shfl_xor(s.bad, o);
+        t.nonzero = __shfl_xor(s.nonzero, o);
+        t.small = __shfl_xor(s.small, o);
+        s = stat_combine(s, t);
+    }
+    return s;
+}
+// The kStatBlocks partials of one pass, reduced by a workgroup's first wave
+// (`red`: one SplitStat of LDS); every thread returns the result.
+__device__ inline SplitStat stat_reduce(const SplitStat *part, SplitStat *red)
+{
+    if (threadIdx.x < 64) {
+        SplitStat s = part[threadIdx.x];
+#pragma unroll
+        for (int k = 1; k < kStatBlocks / 64; ++k)
+            s = stat_combine(s, part[threadIdx.x + 64 * k]);
+        s = stat_wave(s);
+        if (threadIdx.x == 0) *red = s;
+    }
+    __syncthreads();
+    return *red;
+}
+// One scale serves the tensor.
+__device__ inline bool stat_fits(const SplitStat &max, const SplitStat &count)
+{
+    return !max.bad && count.small <= count.nonzero / 1024u;
+}
+
+}  // namespace plstm

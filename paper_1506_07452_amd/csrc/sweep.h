@@ -36,6 +36,13 @@ size_t step_bwd_ws(const Geom &g);
 int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, const Saved &sv,
              const float *dh, float *dx, float *dwx, float *dwh, float *db, void *ws,
              hipStream_t st);
+// fp32 plane steps on the 16-bit matrix unit (split_step.hip, operands split
+// into two fp16 halves): the automatic choice of step_fwd outside the 2D line
+// blocks.  `cell`: c^d of every plane (cell_full) or room for the last two.
+size_t split_fwd_ws(const Geom &g);
+int split_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void *wh,
+              const void *b, float *hd, float *cell, bool cell_full, float *gates, void *ws,
+              hipStream_t st, int *launches);
 // dL/dx from the gate gradients dA [6][N][V][4O] on the MFMA (step_supported
 // shapes); `fragx` holds step_dx_ws bytes.
 size_t step_dx_ws(const Geom &g);

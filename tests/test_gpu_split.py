@@ -1,0 +1,76 @@
+"""fp32 contractions on the 16-bit matrix unit (operands split into two fp16
+halves) against the fp64 oracle, at the edges of their tiles, slots and
+launch shapes, and on inputs that one scale does not serve."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from paper_1506_07452_amd.network import layer_forward
+from tests.gpu_util import dev, host, layer_dev, saved_view, say
+
+pytestmark = pytest.mark.gpu
+
+# Splitting loses at most 2^-22 of an operand and a K-group's sum is rounded
+# once: over n products the error is within (2^-21 + n/32 2^-24) of the sum of
+# magnitudes, 3e-6 for the largest n here (5000); the cells, the direction
+# sum and the gate functions (1 ulp each) carry it over at most 13 planes.
+TOL = 2e-5
+# tanh as 1 - 2 / (e^2a + 1) is off by up to 2^-23 whatever its size: twice in a
+# cell, twice in h, over the six directions (one voxel's h is 1e-3 here)
+ABS = 6 * 4 * 2.0 ** -23
+
+
+def close(got, ref):
+    return np.abs(got - ref).max() <= TOL * np.abs(ref).max() + ABS
+
+
+# (N, D, H, W, C, O, K): one pixel; blocks cut by every border; channel counts
+# of one slot, several, and a padded last one; slots that end inside a
+# K-group; filters whose halo is larger than the plane; every launch shape.
+SHAPES = [(1, 1, 1, 1, 1, 32, 3), (1, 5, 9, 11, 6, 16, 3), (2, 3, 7, 40, 17, 16, 5),
+          (1, 1, 13, 1, 32, 32, 3), (2, 9, 17, 40, 32, 32, 3), (1, 4, 6, 70, 3, 64, 3),
+          (1, 6, 20, 33, 41, 64, 3), (1, 3, 12, 9, 25, 32, 7), (1, 7, 8, 13, 64, 64, 7),
+          (1, 3, 5, 4, 9, 16, 1), (1, 3, 120, 130, 8, 32, 3)]
+
+
+def make(shape, seed):
+    N, D, H, W, C, O, K = shape
+    return synth.make(synth.Workload("split", N, D, H, W, C, [O], seed=seed, K=K))
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_forward(shape):
+    inst = make(shape, 9000 + sum(shape))
+    L = inst.layers[0]
+    ref = oracle.forward(inst.x, L.wx, L.wh, L.b, want_hd=True, want_saved=True)
+    say("split forward", shape)
+    x, Ld = dev(inst.x), layer_dev(L)
+    h, saved = layer_forward(x, Ld, training=True)
+    h2, _ = layer_forward(x, Ld)
+    torch.cuda.synchronize()
+    assert torch.equal(h, h2)
+    assert close(host(h), ref["h"])
+    for name in ("hd", "cell", "gates"):
+        assert close(saved_view(saved, name, shape[:6]), ref[name]), name
+
+
+@pytest.mark.parametrize("outlier", [np.inf, -np.inf, 1e30, 1e6], ids=str)
+@pytest.mark.parametrize("shape", [(1, 5, 9, 11, 6, 16, 3), (1, 4, 12, 10, 32, 32, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_forward_with_an_outlier(shape, outlier):
+    """An infinite voxel saturates its neighbours' gates and one far above the
+    rest leaves their precision alone, as the fp32 instruction has it."""
+    inst = make(shape, 9100 + sum(shape))
+    L = inst.layers[0]
+    inst.x[0, 2, 4, 5, 1] = outlier
+    with np.errstate(over="ignore"):
+        ref = oracle.forward(inst.x, L.wx, L.wh, L.b)["h"]
+    say("split outlier", shape, outlier)
+    h, _ = layer_forward(dev(inst.x), layer_dev(L))
+    torch.cuda.synchronize()
+    assert np.isfinite(ref).all()
+    assert close(host(h), ref)
