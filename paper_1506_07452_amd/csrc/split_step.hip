@@ -428,11 +428,12 @@ k_step_fwd_h2(FwdH2Args a)
         h8 a[4][2];
         h8 b[NT][2];
     };
-    f4 acc[4][NT];
+    f4 sum[2][4][NT];                // lo hi' + hi lo', hi hi'
+    f4(&acc)[4][NT] = sum[1];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[i][nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int nt = 0; nt < NT; ++nt) sum[0][i][nt] = sum[1][i][nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
 
     __builtin_amdgcn_s_waitcnt(kWaitAllLds);
     __syncthreads();
@@ -453,8 +454,8 @@ k_step_fwd_h2(FwdH2Args a)
                 for (int i = 0; i < 4; ++i) {
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt)
-                        acc[i][nt] = mfma_h(cur.a[i][p == 0 ? 1 : 0], cur.b[nt][p == 1 ? 1 : 0],
-                                            acc[i][nt]);
+                        sum[p == 2][i][nt] = mfma_h(cur.a[i][p == 0 ? 1 : 0],
+                                                    cur.b[nt][p == 1 ? 1 : 0], sum[p == 2][i][nt]);
                     const int k = p * 4 + i;
                     if (k < 8) nxt.a[k >> 1][k & 1] = rd[(wm * 8 + k) * 64 + lane];
                     if (k < 2 * NT) nxt.b[k >> 1][k & 1] = stg[spb[k >> 1] + bn + (k & 1)];
@@ -487,7 +488,12 @@ k_step_fwd_h2(FwdH2Args a)
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    acc[i][nt] = mfma_h(X.a[i][p == 0 ? 1 : 0], X.b[nt][p == 1 ? 1 : 0], acc[i][nt]);
+                    sum[p == 2][i][nt] = mfma_h(X.a[i][p == 0 ? 1 : 0], X.b[nt][p == 1 ? 1 : 0],
+                                                sum[p == 2][i][nt]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) sum[1][i][nt] += sum[0][i][nt];
     } else {
         // fp32 channels: K-group kg is eight k-steps of the fp32 instruction,
         // lane group q supplying channel j of its slot
@@ -544,6 +550,419 @@ k_step_fwd_h2(FwdH2Args a)
             *(f4 *)(gp + 2 * O) = gg;
             *(f4 *)(gp + 3 * O) = go;
         }
+    }
+}
+
+// ---- reverse step -----------------------------------------------------------
+
+// A fragments frag[d][kg][rt][2][64]: row tile rt < U holds units 16 rt .. + 15
+// of W_h^T, the rest channels 16 (rt - U) .. + 15 of W_x^T (0 past C).  K-groups run
+// over passes of 64 gate-units, then taps, then halves: kg = (pass KK + tap) 2 +
+// half, lane group q taking gate-units 64 pass + 32 half + 8 q .. + 7.
+// One workgroup per (direction, row tile): the 16 rows' largest magnitudes and
+// their scale, then the fragments.
+struct PackBwdArgs {
+    int O, C, KK, RT, rt0, nrt;   // packs row tiles rt0 .. rt0 + nrt - 1
+    const float *wx, *wh;
+    h8 *frag;
+    float *rinv;              // [nd][16 RT]: 1 / scale of each row
+};
+constexpr int kPackBwdThreads = 1024;
+__global__ void __launch_bounds__(kPackBwdThreads)
+k_pack_bwd_h2(PackBwdArgs a)
+{
+    __shared__ unsigned mx[16];
+    __shared__ float fr[16];
+    const int O = a.O, U = O / 16, G = 4 * O, KK = a.KK, C = a.C, tid = threadIdx.x;
+    const int rt = a.rt0 + blockIdx.x % a.nrt, d = blockIdx.x / a.nrt;
+    const bool is_h = rt < U;
+    const float *w = (is_h ? a.wh : a.wx) + (long long)d * G * (is_h ? O : C) * KK;
+    const int cols = is_h ? O : C, r0 = (is_h ? rt : rt - U) * 16;
+    if (tid < 16) mx[tid] = 0u;
+    __syncthreads();
+    {
+        constexpr int TR = kPackBwdThreads / 16;
+        const int row = tid / TR;
+        unsigned m0 = 0;
+        if (r0 + row < cols)
+            for (int i = tid % TR; i < G * KK; i += TR) {
+                const int g = i / KK, tap = i - g * KK;
+                const unsigned m =
+                    __float_as_uint(w[((long long)g * cols + r0 + row) * KK + tap]) & 0x7fffffffu;
+                m0 = m > m0 && m < 0x7f800000u ? m : m0;
+            }
+        atomicMax(&mx[row], m0);
+    }
+    __syncthreads();
+    if (tid < 16) {
+        const int s = scale_exp(mx[tid]);
+        fr[tid] = exp2i(s);
+        a.rinv[(d * a.RT + rt) * 16 + tid] = exp2i(-s);
+    }
+    __syncthreads();
+    const int KG = KK * U * 2;
+    for (int e = tid; e < KG * 64; e += kPackBwdThreads) {
+        const int lane = e & 63, kg = e >> 6, q = lane >> 4, col = lane & 15;
+        const int half = kg & 1, pt = kg >> 1, pass = pt / KK, tap = pt - pass * KK;
+        const int g0 = pass * 64 + half * 32 + 8 * q;
+        f4 v[2];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            v[j >> 2][j & 3] =
+                r0 + col < cols ? w[((long long)(g0 + j) * cols + r0 + col) * KK + tap] * fr[col]
+                                : 0.0f;
+        const Split8 sp = split8(v[0], v[1]);
+        h8 *out = a.frag + (((long long)d * KG + kg) * a.RT + rt) * 128 + lane;
+        out[0] = sp.hi;
+        out[64] = sp.lo;
+    }
+}
+
+struct BwdH2Args {
+    Geom g;
+    int t;                    // plane (-1: dL/dx of plane 0 only)
+    int RT, KG;               // row tiles: U of units, then the channels'; K-groups of a pass
+    int k_mul;
+    int tab_off;
+    const h8 *frag;
+    const float *rinv;
+    unsigned *amax;           // largest finite |dA| (bits) of each plane's waves,
+                              // [N][T][nblk][waves] at aoff
+    long long aoff[kDirs + 1];
+    const float *gates, *cell, *dh;
+    float *dA;                // [nd][N][V][4O]
+    float *gcp;               // dL/dc f of the last two planes, [N][min(T,2)][P Q][O] at coff
+    float *dxd;               // [nd][N][V][C] or null
+    long long coff[kDirs];
+    int bp[kDirs], bq[kDirs], nbq[kDirs], nblk[kDirs];
+    int base[kDirs + 1];
+};
+
+// 1 KB fragment loads of a K-group: the row tiles' halves, rounded up to a
+// whole number per wave.
+constexpr int bwd_frags(int RTW, int WM) { return (RTW * WM * 2 + 4 * WM - 1) / (4 * WM) * (4 * WM); }
+constexpr int kBwdChunks = 18;           // staged pixel: 64 gate-units as 8 split slots, 2 pad
+
+// Reverse plane step: dL/dh_t = dL/dh + sum_taps W_h^T dA_{t+1}[p - tap] and, with
+// CT channel tiles, dL/dx_{t+1} = sum_taps W_x^T dA_{t+1}[p - tap] of the same
+// staged dA_{t+1}; then the gate gradients dA_t.  4 WM waves take at most 64 NT
+// pixels; wave (wm, wn) computes row tiles RTW wm .. + RTW - 1 for NT pixel tiles.
+// dA_{t+1} of the block and its filter halo is staged 64 gate-units at a time
+// (28 KB for 64 pixels, two to three workgroups share a CU), scaled by the
+// largest magnitude of the blocks it touches, which the launch before left in
+// amax (one word a wave: an atomic maximum per plane cost 0.4 us a launch); the
+// fragments stream as in the forward step.
+// Bound by the launches on small planes (37 us for 400 workgroups: staging twice
+// 4, K-groups 0.6 each, 36 of them, cell update 11 kilocycles) and by LDS reads and
+// barriers on large ones.  Measured against the fp32 instruction on 64-pixel
+// blocks, with dL/dx: 32 -> 32 units on 48 x 240 x 240 27.2 -> 14.3 ms, on 25 x 240 x
+// 240 17.4 -> 9.3; 64 -> 64 on 20 x 64 x 64 6.3 -> 2.7 (steps and a dL/dx pass); 7 x 7,
+// 25 -> 32 on 15 x 128 x 128 21.0 -> 8.5; 6 -> 16 on 19 x 101 x 75 1.39 -> 1.17.  Not
+// kept: 128-pixel blocks (15.7 ms on the first); the cell update's operands loaded
+// before the last pass (two instead of three workgroups a CU: 15.9).
+template <int RTW, int WM, int EU>
+__global__ void __launch_bounds__(256 * WM)
+k_step_bwd_h2(BwdH2Args a)
+{
+    constexpr int NT = 1;                // pixel tiles of a wave
+    constexpr int NW = 4 * WM, THREADS = 64 * NW, AT = bwd_frags(RTW, WM), NDMA = AT / NW;
+    constexpr int kWaitRingLds = 0x0070 | NDMA;
+    __shared__ h8 ring0[AT * 64], ring1[AT * 64], ring2[AT * 64];
+    extern __shared__ h8 stg[];
+    const int tid = threadIdx.x, lane = tid & 63, q4 = lane >> 4, col = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wv % WM, wn = wv / WM;
+    const int per_xcd = gridDim.x / kXcds;
+    const int blk = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    if (blk >= a.base[kDirs]) return;
+    const int d = item_dir(a.base, blk);
+    const DirGeom dg = a.g.dir[d];
+    int r = blk - a.base[d];
+    const int n = r / a.nblk[d];
+    r -= n * a.nblk[d];
+    const int BP = a.bp[d], BQ = a.bq[d];
+    const int bi = r / a.nbq[d], bj = r - bi * a.nbq[d];
+    const int p0 = bi * BP, q0 = bj * BQ;
+    const int t = a.t, O = a.g.O, G = 4 * O, U = O >> 4, RT = a.RT;
+    const int s = dg.sign > 0 ? t : dg.T - 1 - t;
+    const int ss = (int)dg.ss, sp = (int)dg.sp, sq = (int)dg.sq;
+    const int P = dg.P, Q = dg.Q, PQ = P * Q;
+    const long long V = a.g.V;
+    const bool do_h = t >= 0, has_next = t + 1 < dg.T;
+    const int noff = dg.sign * ss;       // voxel of plane t + 1 = voxel of plane t + noff
+    const int KQ = a.g.KQ, radp = a.g.KP >> 1, radq = KQ >> 1, KK = a.g.KP * KQ;
+    const int SW = BQ + 2 * radq, SH = BP + 2 * radp;
+    const long long sbase = ((long long)d * a.g.N + n) * V;
+    const int KG = a.KG;                 // of one pass
+    int *const tab = (int *)(stg + a.tab_off);
+    float *const rowp = (float *)(tab + (KK + 3) / 4 * 4);   // 1 / scale of the rows
+    unsigned *const am = a.amax + a.aoff[d] + (long long)n * dg.T * a.nblk[d] * NW;
+
+    // this lane's pixel of each tile
+    int spb[NT], evox[NT], epix[NT];
+    bool elive[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int e = (wn * NT + nt) * 16 + col;
+        const int ey = fdiv_floor(e, 1.0f / (float)BQ), ex = e - ey * BQ;
+        const bool in = ey < BP;
+        elive[nt] = in && on_plane(p0 + ey, q0 + ex, P, Q);
+        spb[nt] = (in ? (ey + radp) * SW + ex + radq : radp * SW + radq) * kBwdChunks + 2 * q4;
+        epix[nt] = elive[nt] ? (p0 + ey) * Q + q0 + ex : 0;
+        evox[nt] = s * ss + (elive[nt] ? (p0 + ey) * sp + (q0 + ex) * sq : 0);
+    }
+    f4 sum[2][RTW][NT];              // lo hi' + hi lo', hi hi'
+    f4(&acc)[RTW][NT] = sum[1];
+#pragma unroll
+    for (int i = 0; i < RTW; ++i)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) sum[0][i][nt] = sum[1][i][nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    float unscale = 1.0f;
+
+    if (has_next) {
+        // largest |dA_{t+1}| of the blocks the staged one touches: this lane's
+        // first word now, the rest (wide halos) and the reduction beside the
+        // staging loads
+        const unsigned *const an = am + (long long)(t + 1) * a.nblk[d] * NW;
+        const int i0 = fdiv_floor(max(p0 - radp, 0), 1.0f / (float)BP);
+        const int i1 = fdiv_floor(min(p0 + BP - 1 + radp, P - 1), 1.0f / (float)BP);
+        const int j0 = fdiv_floor(max(q0 - radq, 0), 1.0f / (float)BQ);
+        const int j1 = fdiv_floor(min(q0 + BQ - 1 + radq, Q - 1), 1.0f / (float)BQ);
+        const int nj = (j1 - j0 + 1) * NW, cnt = (i1 - i0 + 1) * nj;
+        auto top_word = [&](int e) {
+            const int i = fdiv_floor(e, 1.0f / (float)nj);
+            return an[((i0 + i) * a.nbq[d] + j0) * NW + e - i * nj];
+        };
+        unsigned top_next = top_word(min(lane, cnt - 1));
+        const auto rs_a =
+            rsrc_of(a.frag + (long long)d * KG * U * RT * 128, (long long)KG * U * RT * 2048);
+        const float *const dA_n = a.dA + sbase * G;
+        const float inv_sw = 1.0f / (float)SW;
+        const int nst = SH * SW * 8;
+        struct Ops {
+            h8 a[RTW][2];
+            h8 b[NT][2];
+        };
+        for (int pass = 0; pass < U; ++pass) {
+            // (rows past the last tile repeat it)
+            auto issue_a = [&](int kg, h8 *slot) {
+#pragma unroll
+                for (int j0 = 0; j0 < AT; j0 += NW) {
+                    const int j = j0 + wv;
+                    const int rt = min(j >> 1, RT - 1);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                        rs_a, (lds_void *)&slot[j * 64], 16,
+                        (int)((unsigned)((((pass * KG + kg) * RT + rt) * 2 + (j & 1)) * 64 + lane) *
+                              16u),
+                        0, 0, 0);
+                }
+            };
+            if (pass > 0) __syncthreads();   // every wave is done with the staged pass
+            issue_a(0, ring0);
+            issue_a(1, ring1);
+            if (KG > 2) issue_a(2, ring2);
+            constexpr int SB = 4;
+            for (int e0 = tid; e0 - tid < nst; e0 += SB * THREADS) {
+                f4 va[SB], vb[SB];
+                int dst[SB];
+                bool ok[SB];
+#pragma unroll
+                for (int u = 0; u < SB; ++u) {
+                    const int e = e0 + u * THREADS;
+                    const int spx = e >> 3, c = e & 7;
+                    const int sy = fdiv_floor(spx, inv_sw), sx = spx - sy * SW;
+                    const int pp = p0 - radp + sy, qq = q0 - radq + sx;
+                    dst[u] = e < nst ? spx * kBwdChunks + 2 * c : -1;
+                    ok[u] = e < nst && on_plane(pp, qq, P, Q);
+                    const int v = (s + dg.sign) * ss + pp * sp + qq * sq;
+                    const float *src = dA_n + (ok[u] ? (long long)v * G + pass * 64 + 8 * c : 0);
+                    va[u] = *(const f4 *)src;
+                    vb[u] = *(const f4 *)(src + 4);
+                }
+                if (pass == 0 && e0 == tid) {
+                    // the pixels that received this pixel's h (and x) through a tap
+                    for (int e = tid; e < KK; e += THREADS) {
+                        const int ka = ((e * a.k_mul) >> 16) - radp, kb = e - (ka + radp) * KQ - radq;
+                        tab[e] = (-ka * SW - kb) * kBwdChunks;
+                    }
+                    if (tid < RT * 16) rowp[tid] = a.rinv[d * RT * 16 + tid];
+                }
+                if (pass == 0 && e0 == tid) {
+                    for (int e = 64 + lane; e < cnt; e += 64) {
+                        const unsigned m = top_word(e);
+                        top_next = m > top_next ? m : top_next;
+                    }
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) {
+                        const unsigned m = __shfl_xor(top_next, o);
+                        top_next = m > top_next ? m : top_next;
+                    }
+                }
+                const float scale = exp2i(scale_exp(top_next));
+#pragma unroll
+                for (int u = 0; u < SB; ++u) {
+                    if (dst[u] < 0) continue;
+                    const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+                    const Split8 w = split8(ok[u] ? va[u] * scale : zero, ok[u] ? vb[u] * scale : zero);
+                    stg[dst[u]] = w.hi;
+                    stg[dst[u] + 1] = w.lo;
+                }
+            }
+            __builtin_amdgcn_s_waitcnt(kWaitAllLds);
+            __syncthreads();
+
+            Ops X, Y;
+#pragma unroll
+            for (int i = 0; i < 2 * RTW; ++i) X.a[i >> 1][i & 1] = ring0[((i >> 1) * WM * 2 + wm * 2 + (i & 1)) * 64 + lane];
+            {
+                const int bo = tab[0];
+#pragma unroll
+                for (int i = 0; i < 2 * NT; ++i) X.b[i >> 1][i & 1] = stg[spb[i >> 1] + bo + (i & 1)];
+            }
+            int bn = tab[0] + 8;             // offset of K-group kg + 1
+            auto step = [&](int kg, const Ops &cur, Ops &nxt, const h8 *rd, h8 *dm) {
+                const bool more = kg + 3 < KG;
+                const int bt = tab[min((kg + 2) >> 1, KK - 1)] + 8 * (kg & 1);
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+#pragma unroll
+                    for (int i = 0; i < RTW; ++i) {
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt)
+                            sum[p == 2][i][nt] =
+                                mfma_h(cur.a[i][p == 0 ? 1 : 0], cur.b[nt][p == 1 ? 1 : 0],
+                                       sum[p == 2][i][nt]);
+                        const int k = p * RTW + i;
+                        if (k < 2 * RTW) nxt.a[k >> 1][k & 1] = rd[((k >> 1) * WM * 2 + wm * 2 + (k & 1)) * 64 + lane];
+                        if (k < 2 * NT) nxt.b[k >> 1][k & 1] = stg[spb[k >> 1] + bn + (k & 1)];
+                        if (RTW * 3 < 2 * NT && k == RTW * 3 - 1) {
+#pragma unroll
+                            for (int m = RTW * 3; m < 2 * NT; ++m)
+                                nxt.b[m >> 1][m & 1] = stg[spb[m >> 1] + bn + (m & 1)];
+                        }
+                        if (k == RTW && more) issue_a(kg + 3, dm);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                bn = bt;
+                if (more)
+                    __builtin_amdgcn_s_waitcnt(kWaitRingLds);
+                else
+                    __builtin_amdgcn_s_waitcnt(kWaitAllLds);
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            };
+            __syncthreads();
+            for (int kg = 0; kg + 1 < KG; kg += 6) {
+                step(kg, X, Y, ring1, ring0);
+                if (kg + 2 < KG) step(kg + 1, Y, X, ring2, ring1);
+                if (kg + 3 < KG) step(kg + 2, X, Y, ring0, ring2);
+                if (kg + 4 < KG) step(kg + 3, Y, X, ring1, ring0);
+                if (kg + 5 < KG) step(kg + 4, X, Y, ring2, ring1);
+                if (kg + 6 < KG) step(kg + 5, Y, X, ring0, ring2);
+            }
+            // KG is even: the last K-group's operands are in Y
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+                for (int i = 0; i < RTW; ++i)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        sum[p == 2][i][nt] = mfma_h(Y.a[i][p == 0 ? 1 : 0], Y.b[nt][p == 1 ? 1 : 0],
+                                                    sum[p == 2][i][nt]);
+        }
+#pragma unroll
+        for (int i = 0; i < RTW; ++i)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) sum[1][i][nt] += sum[0][i][nt];
+        unscale = exp2i(-scale_exp(top_next));
+    }
+
+    const int np = dg.T > 1 ? 2 : 1;
+    float *const gc0 = a.gcp + a.coff[d] + (long long)n * np * PQ * O;
+    const float *const gcin = gc0 + (long long)((t + 1) & 1) * PQ * O;
+    float *const gcout = gc0 + (long long)(t & 1) * PQ * O;
+    // the cell update's operands of the wave's unit tiles (rt = wm, wm + WM,
+    // .. < U), all in flight at once
+    f4 e_g[EU][4], e_c[EU], e_cp[EU], e_gn[EU], e_dh[EU];
+    const long long vo = sbase + evox[0];
+#pragma unroll
+    for (int i = 0; i < EU; ++i) {
+        const int uo = min(i * WM + wm, U - 1) * 16 + 4 * q4;
+        const float *gp = a.gates + (do_h ? vo : sbase) * G + uo;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) e_g[i][k] = *(const f4 *)(gp + k * O);
+        e_c[i] = *(const f4 *)(a.cell + (do_h ? vo : sbase) * O + uo);
+        e_cp[i] = *(const f4 *)(a.cell + (t > 0 ? vo - noff : sbase) * O + uo);
+        e_gn[i] = *(const f4 *)((has_next ? gcin : gcout) + (long long)epix[0] * O + uo);
+        e_dh[i] = *(const f4 *)(a.dh + ((long long)n * V + (do_h ? evox[0] : 0)) * O + uo);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // (the scheduler would sink each load to its use)
+    unsigned top = 0;
+    if (elive[0]) {
+#pragma unroll
+        for (int i = 0; i < RTW; ++i) {
+            const int rt = i * WM + wm;
+            if (rt >= RT) continue;
+            if (rt >= U) {
+                // dL/dx of plane t + 1, this direction's share
+                if (!has_next) continue;
+                const f4 rinv = *(const f4 *)(rowp + rt * 16 + 4 * q4) * unscale;
+                const int C = a.g.C, c0 = (rt - U) * 16 + 4 * q4;
+                float *out = a.dxd + (vo + noff) * C;
+                const f4 v = acc[i][0] * rinv;
+                if ((C & 3) == 0 && c0 + 3 < C) {
+                    *(f4 *)(out + c0) = v;
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (c0 + k < C) out[c0 + k] = v[k];
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < EU; ++i) {
+            const int rt = i * WM + wm, uo = rt * 16 + 4 * q4;
+            if (!do_h || rt >= U) continue;
+            f4 rinv = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (has_next) rinv = *(const f4 *)(rowp + uo) * unscale;
+            const f4 gi = e_g[i][0], gf = e_g[i][1], gg = e_g[i][2], go = e_g[i][3], c = e_c[i];
+            f4 di, df, dgv, dov, gco;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float gh = __builtin_fmaf(acc[i][0][k], rinv[k], e_dh[i][k]);
+                const float tc = ftanh(c[k]);
+                const float gcv = gh * go[k] * (1.0f - tc * tc) + (has_next ? e_gn[i][k] : 0.0f);
+                di[k] = gcv * gg[k] * gi[k] * (1.0f - gi[k]);
+                df[k] = gcv * (t > 0 ? e_cp[i][k] : 0.0f) * gf[k] * (1.0f - gf[k]);
+                dgv[k] = gcv * gi[k] * (1.0f - gg[k] * gg[k]);
+                dov[k] = gh * tc * go[k] * (1.0f - go[k]);
+                gco[k] = gcv * gf[k];
+            }
+            float *dp = a.dA + vo * G + uo;
+            *(f4 *)dp = di;
+            *(f4 *)(dp + O) = df;
+            *(f4 *)(dp + 2 * O) = dgv;
+            *(f4 *)(dp + 3 * O) = dov;
+            *(f4 *)(gcout + (long long)epix[0] * O + uo) = gco;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float v4[4] = {di[k], df[k], dgv[k], dov[k]};
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const unsigned bits = __float_as_uint(v4[m]) & 0x7fffffffu;
+                    top = bits > top && bits < 0x7f800000u ? bits : top;
+                }
+            }
+        }
+    }
+    if (do_h) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const unsigned b = __shfl_xor(top, o);
+            top = b > top ? b : top;
+        }
+        if (lane == 0) am[((long long)t * a.nblk[d] + bi * a.nbq[d] + bj) * NW + wv] = top;
     }
 }
 
@@ -712,8 +1131,107 @@ FwdPlan plan_fwd(const Geom &g, const FwdK &k, int nchp)
     return best;
 }
 
-}  // namespace
+// Reverse steps: U unit tiles and, with dL/dx, the channels' row tiles, spread
+// over WM waves of RTW tiles.
+struct BwdShape {
+    int RT, RTW, WM;
+};
+BwdShape bwd_shape(const Geom &g, bool with_dx)
+{
+    BwdShape b;
+    b.RT = g.O / 16 + (with_dx ? (g.C + 15) / 16 : 0);
+    b.WM = b.RT > 4 || g.O == 64 ? 2 : 1;
+    b.RTW = (b.RT + b.WM - 1) / b.WM;
+    return b;
+}
 
+// tap table and row scales
+inline size_t bwd_table(const Geom &g, int RT)
+{
+    return (size_t)(g.KP * g.KQ + 3) / 4 * 16 + (size_t)RT * 64;
+}
+
+template <int RTW, int WM, int EU>
+int launch_bwd_h2(const Geom &g, BwdH2Args &a, const PixBlocks &b, bool with_dx, hipStream_t st)
+{
+    a.tab_off = b.max_staged * kBwdChunks;
+    const size_t lds = (size_t)a.tab_off * 16 + bwd_table(g, a.RT);
+    if (hipFuncSetAttribute((const void *)k_step_bwd_h2<RTW, WM, EU>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return PLSTM_EHIP;
+    for (int d = 0; d < kDirs; ++d) {
+        a.bp[d] = b.bp[d]; a.bq[d] = b.bq[d]; a.nbq[d] = b.nbq[d]; a.nblk[d] = b.nblk[d];
+    }
+    // with dL/dx, a last launch (t = -1) gives plane 0's share
+    for (int t = max_T(g) - 1; t >= (with_dx ? -1 : 0); --t) {
+        a.t = t;
+        int nb = 0;
+        for (int d = 0; d < kDirs; ++d) {
+            a.base[d] = nb;
+            if (t < g.dir[d].T && g.dir[d].T > 0) nb += g.N * a.nblk[d];
+        }
+        a.base[kDirs] = nb;
+        const int grid = (nb + kXcds - 1) / kXcds * kXcds;
+        k_step_bwd_h2<RTW, WM, EU><<<grid, 256 * WM, lds, st>>>(a);
+        PLSTM_LAUNCH_CHECK();
+    }
+    return PLSTM_OK;
+}
+
+int launch_bwd_shape(const Geom &g, BwdH2Args &a, const BwdShape &sh, const PixBlocks &b,
+                     bool with_dx, hipStream_t st)
+{
+    const int U = g.O / 16, EU = (U + sh.WM - 1) / sh.WM;    // unit tiles per wave
+    switch ((sh.WM * 8 + sh.RTW) * 4 + EU) {
+    case 37: return launch_bwd_h2<1, 1, 1>(g, a, b, with_dx, st);
+    case 41: return launch_bwd_h2<2, 1, 1>(g, a, b, with_dx, st);
+    case 42: return launch_bwd_h2<2, 1, 2>(g, a, b, with_dx, st);
+    case 45: return launch_bwd_h2<3, 1, 1>(g, a, b, with_dx, st);
+    case 46: return launch_bwd_h2<3, 1, 2>(g, a, b, with_dx, st);
+    case 49: return launch_bwd_h2<4, 1, 1>(g, a, b, with_dx, st);
+    case 50: return launch_bwd_h2<4, 1, 2>(g, a, b, with_dx, st);
+    case 74: return launch_bwd_h2<2, 2, 2>(g, a, b, with_dx, st);
+    case 77: return launch_bwd_h2<3, 2, 1>(g, a, b, with_dx, st);
+    case 78: return launch_bwd_h2<3, 2, 2>(g, a, b, with_dx, st);
+    case 82: return launch_bwd_h2<4, 2, 2>(g, a, b, with_dx, st);
+    default: return PLSTM_EUNSUPPORTED;
+    }
+}
+
+struct BwdWs {
+    float *dA, *gcp, *dxd, *rinv;
+    h8 *frag;
+    unsigned *amax;
+    long long aoff[kDirs + 1];
+    PixBlocks blocks;
+};
+BwdWs carve_bwd(Carve &cv, const Geom &g, bool with_dx)
+{
+    const BwdShape sh = bwd_shape(g, with_dx);
+    BwdWs w;
+    const long long lim = device_info().max_lds > 0 ? device_info().max_lds : 65536;
+    const long long fixed =
+        (long long)bwd_frags(sh.RTW, sh.WM) * 1024 * 3 + (long long)bwd_table(g, sh.RT);
+    w.blocks = pixel_blocks(g, 64, 0.35, (int)((lim - fixed) / (kBwdChunks * 16)));
+    w.dA = cv.take<float>((size_t)g.nd * g.N * g.V * 4 * g.O);
+    size_t planes = 0;
+    long long words = 0;
+    for (int d = 0; d < kDirs; ++d) {
+        w.aoff[d] = words;
+        if (d >= g.nd) continue;
+        planes += (size_t)(g.dir[d].T > 1 ? 2 : 1) * g.dir[d].P * g.dir[d].Q;
+        words += (long long)g.N * g.dir[d].T * w.blocks.nblk[d] * 4 * sh.WM;
+    }
+    w.aoff[kDirs] = words;
+    w.gcp = cv.take<float>(planes * g.N * g.O);
+    w.frag = cv.take<h8>((size_t)g.nd * g.KP * g.KQ * (g.O / 8) * sh.RT * 128);
+    w.rinv = cv.take<float>((size_t)g.nd * sh.RT * 16);
+    w.amax = cv.take<unsigned>((size_t)words);
+    w.dxd = with_dx ? cv.take<float>((size_t)g.nd * g.N * g.V * g.C) : nullptr;
+    return w;
+}
+
+}  // namespace
 
 int split_stats(int dtype, const void *x, long long n, SplitStats *part, hipStream_t st)
 {
@@ -809,6 +1327,64 @@ int split_fwd(const Geom &g, int dtype, const void *x, const void *wx, const voi
     case 17: return launch_fwd_h2<2, 1>(g, a, pl.blocks, st);
     default: return launch_fwd_h2<2, 2>(g, a, pl.blocks, st);
     }
+}
+
+size_t split_bwd_ws(const Geom &g)
+{
+    Carve cv(nullptr), cn(nullptr);
+    carve_bwd(cv, g, true);
+    carve_bwd(cn, g, false);
+    return cv.off > cn.off ? cv.off : cn.off;
+}
+
+int split_bwd(const Geom &g, const float *wx, const float *wh, const Saved &sv, const float *dh,
+              bool with_dx, void *ws, SplitBwd *out, hipStream_t st)
+{
+    Carve cv(ws);
+    const BwdWs w = carve_bwd(cv, g, with_dx);
+    const BwdShape sh = bwd_shape(g, with_dx);
+    const int KK = g.KP * g.KQ, U = g.O / 16;
+    PackBwdArgs pa;
+    pa.O = g.O; pa.C = g.C; pa.KK = KK; pa.RT = sh.RT;
+    pa.wx = wx; pa.wh = wh; pa.frag = w.frag; pa.rinv = w.rinv;
+    pa.rt0 = 0;
+    pa.nrt = sh.RT;
+    if (with_dx && sh.WM == 2) {
+        // row tiles of two waves: the channels' fragments count as dL/dx
+        timing_begin("dx_step", st);
+        pa.rt0 = U;
+        pa.nrt = sh.RT - U;
+        k_pack_bwd_h2<<<g.nd * pa.nrt, kPackBwdThreads, 0, st>>>(pa);
+        PLSTM_LAUNCH_CHECK();
+        timing_end(1, st);
+        pa.rt0 = 0;
+        pa.nrt = U;
+    }
+    timing_begin("sweep_bwd_step", st);
+    k_pack_bwd_h2<<<g.nd * pa.nrt, kPackBwdThreads, 0, st>>>(pa);
+    PLSTM_LAUNCH_CHECK();
+
+    BwdH2Args a;
+    a.g = g;
+    a.RT = sh.RT; a.KG = 2 * KK;
+    a.k_mul = (65536 + g.KQ - 1) / g.KQ;
+    a.frag = w.frag; a.rinv = w.rinv; a.amax = w.amax;
+    a.gates = sv.gates; a.cell = sv.cell; a.dh = dh;
+    a.dA = w.dA; a.gcp = w.gcp; a.dxd = w.dxd;
+    long long off = 0;
+    for (int d = 0; d < kDirs; ++d) {
+        a.coff[d] = off;
+        if (d < g.nd)
+            off += (long long)g.N * (g.dir[d].T > 1 ? 2 : 1) * g.dir[d].P * g.dir[d].Q * g.O;
+    }
+    for (int d = 0; d <= kDirs; ++d) a.aoff[d] = out->aoff[d] = w.aoff[d];
+    const int rc = launch_bwd_shape(g, a, sh, w.blocks, with_dx, st);
+    if (rc == PLSTM_OK) timing_end(1 + max_T(g) + (with_dx ? 1 : 0), st);
+    out->dA = w.dA;
+    out->dxd = w.dxd;
+    out->amax = w.amax;
+    out->used = cv.off;
+    return rc;
 }
 
 }  // namespace plstm

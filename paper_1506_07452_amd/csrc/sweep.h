@@ -43,6 +43,17 @@ size_t split_fwd_ws(const Geom &g);
 int split_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void *wh,
               const void *b, float *hd, float *cell, bool cell_full, float *gates, void *ws,
               hipStream_t st, int *launches);
+// Reverse steps the same way: dA, with_dx each direction's share of dL/dx, and the
+// largest finite |dA| of each wave of each step, all in the workspace.
+struct SplitBwd {
+    float *dA, *dxd;
+    unsigned *amax;           // finite |dA| maxima (bits), those of direction d at
+    long long aoff[kDirs + 1];   // aoff[d] .. aoff[d + 1]
+    size_t used;              // workspace bytes taken
+};
+size_t split_bwd_ws(const Geom &g);
+int split_bwd(const Geom &g, const float *wx, const float *wh, const Saved &sv, const float *dh,
+              bool with_dx, void *ws, SplitBwd *out, hipStream_t st);
 // dL/dx from the gate gradients dA [6][N][V][4O] on the MFMA (step_supported
 // shapes); `fragx` holds step_dx_ws bytes.
 size_t step_dx_ws(const Geom &g);

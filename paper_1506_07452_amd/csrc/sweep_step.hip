@@ -1682,15 +1682,6 @@ struct BwdStepArgs {
     float *gcf;               // [6][N][V][O]: dL/dc_t * f_t
     int npg[kDirs];
     int base[kDirs + 1];
-    // pixel blocks of the LDS-staged kernel (as in FwdStepArgs) and one
-    // wave's LDS region in 16-byte units (its staged block + filter halo, or
-    // its partial sums, whichever is larger)
-    int bp[kDirs], bq[kDirs], nbq[kDirs], nblk[kDirs];
-    int reg_f4;
-    // dL/dx inside the staged reverse step: W_x^T fragments
-    // [6][KK * 4U][CT][64][4] and each direction's share [6][N][V][C]
-    const float *fragx;
-    float *dxd;
 };
 
 // ---- line blocks of the 2D layer's reverse sweep (16 hidden units) ----------
@@ -2152,259 +2143,6 @@ k_step_bwd(BwdStepArgs a)
             *(f4 *)(dp + 3 * O) = dov;
             *(f4 *)(a.gcf + vo * O + uo) = gco;
         }
-    }
-}
-
-// Reverse step on LDS-staged pixel blocks (U = 1 or 2 unit tiles), with
-// this direction's share of dL/dx for the plane before it in sweep order when
-// CT > 0.  A workgroup takes a BP x BQ block of 64 pixels of one plane (the
-// blocks of the staged forward).  The K dimension of the contraction is (tap,
-// gate-unit block of 16): wave w takes the blocks mb = w + 4 j (j < U) of
-// every tap.  It stages those channels of dA_{t+1} for the block and its
-// filter halo in its own LDS region (16-byte chunks XOR-swizzled by the
-// pixel), so every tap's B operand comes from LDS, and contracts them with
-//   W_h^T (U unit tiles):     gh_t[p]     = sum_taps W_h^T dA_{t+1}[p - tap]
-//   W_x^T (CT channel tiles): dx_{t+1}[p] = sum_taps W_x^T dA_{t+1}[p - tap]
-// for the block's four pixel tiles: the input x_{t+1} entered plane t + 1's
-// gates through the same taps (Eq. (7)-(9), (11)), so its gradient is the
-// same transposed convolution of the same staged dA_{t+1}.  The partial sums
-// of the three tiles a wave does not finish then go to its region; after a
-// barrier wave w adds tile w's four partials in wave order, runs the
-// gate-gradient epilogue and stores dx_{t+1}.  t = -1 gives dL/dx of plane 0
-// only.
-template <int U, int CT>
-__global__ void __launch_bounds__(64 * kSW) __attribute__((amdgpu_waves_per_eu(3)))
-k_step_bwd_blk(BwdStepArgs a)
-{
-    constexpr int O = 16 * U, G = 4 * O, MB = 4 * U;
-    constexpr int NCH = 4 * U;                       // staged 16-byte chunks per pixel
-    constexpr int SWM = NCH >= 8 ? 7 : 3;
-    static_assert(kNT == kSW, "wave w finishes tile w");
-    extern __shared__ f4 lds[];
-    const int lane = threadIdx.x & 63, q4 = lane >> 4, col = lane & 15;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int blk = blockIdx.x;
-    if (blk >= a.base[kDirs]) return;
-    const int d = item_dir(a.base, blk);
-    const DirGeom dg = a.g.dir[d];
-    int r = blk - a.base[d];
-    const int n = r / a.nblk[d];
-    r -= n * a.nblk[d];
-    const int BP = a.bp[d], BQ = a.bq[d];
-    const int bi = r / a.nbq[d], bj = r - bi * a.nbq[d];
-    const int p0 = bi * BP, q0 = bj * BQ;
-    const int t = a.t;
-    const bool do_h = t >= 0;                        // plane t exists (t = -1: dL/dx only)
-    const int s = dg.sign > 0 ? t : dg.T - 1 - t;
-    const int ss = (int)dg.ss, sp = (int)dg.sp, sq = (int)dg.sq;
-    const int P = dg.P, Q = dg.Q;
-    const long long V = a.g.V;
-    const bool has_next = t + 1 < dg.T;
-    const int noff = dg.sign * ss;    // voxel of plane t + 1 = voxel of plane t + noff
-    const int KQ = a.g.KQ, radp = a.g.KP >> 1, radq = KQ >> 1, KK = a.g.KP * KQ;
-    const int KG = KK * MB;
-    const int SW = BQ + 2 * radq, SH = BP + 2 * radp;
-    const long long sbase = ((long long)d * a.g.N + n) * V;
-    f4 *mine = lds + (long long)wave * a.reg_f4;
-
-    // ---- the epilogue's pixel (tile `wave`)
-    const int lbq = 31 - __builtin_clz(BQ);
-    const int ee = wave * 16 + col;
-    const int ey = ee >> lbq, ex = ee & (BQ - 1);
-    const bool elive = on_plane(p0 + ey, q0 + ex, P, Q);
-    const int pix = elive ? (p0 + ey) * sp + (q0 + ex) * sq : 0;
-    const int evox = s * ss + pix;
-    const long long vo = sbase + evox;
-    const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-
-    // ---- contraction over this wave's gate-unit blocks of dA_{t+1}
-    f4 acc[U][kNT], accx[CT > 0 ? CT : 1][kNT];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int nt = 0; nt < kNT; ++nt) acc[u][nt] = zero;
-#pragma unroll
-    for (int c = 0; c < (CT > 0 ? CT : 1); ++c)
-#pragma unroll
-        for (int nt = 0; nt < kNT; ++nt) accx[c][nt] = zero;
-    if (has_next) {
-        // direct-to-LDS loads, all in flight at once: one instruction fills
-        // 64 consecutive 16-byte slots, slot p of pixel spx holding chunk
-        // p ^ (spx & SWM), each lane loading the chunk its slot holds
-        const auto rs_dA = slice_rsrc(a.dA + sbase * G, V * G);
-        const int nst = SH * SW * NCH;
-        for (int e0 = 0; e0 < nst; e0 += 64) {
-            const int e = e0 + lane;
-            const int spx = e / NCH, pos = e - spx * NCH;
-            const int c = pos ^ (spx & SWM);
-            const int sy = spx / SW, sx = spx - sy * SW;
-            const int pp = p0 - radp + sy, qq = q0 - radq + sx;
-            const int mb = wave + kSW * (c >> 2);
-            const int v = (s + dg.sign) * ss + pp * sp + qq * sq;
-            lds_void *dst = (lds_void *)&mine[e0];
-            if (e < nst)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rs_dA, dst, 16,
-                    (int)sel_off(on_plane(pp, qq, P, Q),
-                                 (unsigned)(v * G + mb * 16 + 4 * (c & 3)) * 4u),
-                    0, 0, 0);
-        }
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-    }
-    __syncthreads();
-    if (has_next) {
-        int spix[kNT];
-#pragma unroll
-        for (int nt = 0; nt < kNT; ++nt) {
-            const int e = nt * 16 + col;
-            spix[nt] = ((e >> lbq) + radp) * SW + (e & (BQ - 1)) + radq;
-        }
-        const float *fr = a.frag + (long long)d * U * KG * 256 + lane * 4;
-        const float *frx = a.fragx + (long long)d * KG * CT * 256 + lane * 4;
-        // K-steps in (tap, j) order; A fragments one K-group ahead
-        auto afrag = [&](int tap, int j, f4 *o, f4 *ox) {
-            const int kg = tap * MB + wave + kSW * j;
-#pragma unroll
-            for (int u = 0; u < U; ++u) o[u] = *(const f4 *)(fr + ((long long)u * KG + kg) * 256);
-#pragma unroll
-            for (int c = 0; c < CT; ++c) ox[c] = *(const f4 *)(frx + ((long long)kg * CT + c) * 256);
-        };
-        f4 acur[U], anxt[U], axc[CT > 0 ? CT : 1], axn[CT > 0 ? CT : 1];
-        afrag(0, 0, acur, axc);
-        const int nk = KK * U;
-        for (int k = 0; k < nk; ++k) {
-            const int tap = k / U, j = k - tap * U;
-            if (k + 1 < nk) afrag((k + 1) / U, (k + 1) - ((k + 1) / U) * U, anxt, axn);
-            const int row = tap_row(tap, a.k_mul), ka = row - radp, kb = tap - row * KQ - radq;
-            // the pixels that received this pixel's h (and x) through tap (ka, kb)
-            const int doff = -ka * SW - kb;
-            const int chunk = j * 4 + q4;
-            f4 bv[kNT];
-#pragma unroll
-            for (int nt = 0; nt < kNT; ++nt) {
-                const int spx = spix[nt] + doff;
-                bv[nt] = mine[spx * NCH + (chunk ^ (spx & SWM))];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int nt = 0; nt < kNT; ++nt)
-                        acc[u][nt] = mfma(acur[u][i], bv[nt][i], acc[u][nt]);
-#pragma unroll
-                for (int c = 0; c < CT; ++c)
-#pragma unroll
-                    for (int nt = 0; nt < kNT; ++nt)
-                        accx[c][nt] = mfma(axc[c][i], bv[nt][i], accx[c][nt]);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) acur[u] = anxt[u];
-#pragma unroll
-            for (int c = 0; c < CT; ++c) axc[c] = axn[c];
-        }
-    }
-    // the epilogue's operands of tile `wave`, in flight during the exchange
-    // of partial sums below
-    f4 e_g[U][4], e_c[U], e_cp[U], e_gn[U], e_dh[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) e_g[u][k] = zero;
-        e_c[u] = e_cp[u] = e_gn[u] = e_dh[u] = zero;
-    }
-    if (do_h && elive) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int uo = u * 16 + 4 * q4;
-            const float *gp = a.gates + vo * G + uo;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) e_g[u][k] = *(const f4 *)(gp + k * O);
-            e_c[u] = *(const f4 *)(a.cell + vo * O + uo);
-            if (t > 0) e_cp[u] = *(const f4 *)(a.cell + (vo - noff) * O + uo);
-            if (has_next) e_gn[u] = *(const f4 *)(a.gcf + (vo + noff) * O + uo);
-            e_dh[u] = *(const f4 *)(a.dh + ((long long)n * V + evox) * O + uo);
-        }
-    }
-    // partial sums of the tiles other waves finish, into this wave's own
-    // region (only this wave read it): slot nt - (nt > wave) of each M-tile
-#pragma unroll
-    for (int nt = 0; nt < kNT; ++nt) {
-        if (nt == wave) continue;
-        const int sl = nt - (nt > wave ? 1 : 0);
-#pragma unroll
-        for (int u = 0; u < U; ++u) mine[(u * (kNT - 1) + sl) * 64 + lane] = acc[u][nt];
-#pragma unroll
-        for (int c = 0; c < CT; ++c)
-            mine[((U + c) * (kNT - 1) + sl) * 64 + lane] = accx[c][nt];
-    }
-    __syncthreads();
-    if (!elive) return;
-    // tile `wave` of M-tile m: the four waves' partials in wave order
-    auto partial = [&](int m, f4 own) {
-        f4 v = zero;
-#pragma unroll
-        for (int w = 0; w < kSW; ++w) {
-            if (w == wave) {
-                v += own;
-            } else {
-                const int sl = wave - (wave > w ? 1 : 0);
-                v += lds[(long long)w * a.reg_f4 + (m * (kNT - 1) + sl) * 64 + lane];
-            }
-        }
-        return v;
-    };
-    f4 own_h[U], own_x[CT > 0 ? CT : 1];
-#pragma unroll
-    for (int nt = 0; nt < kNT; ++nt)
-        if (nt == wave) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) own_h[u] = acc[u][nt];
-#pragma unroll
-            for (int c = 0; c < CT; ++c) own_x[c] = accx[c][nt];
-        }
-
-    if (CT > 0 && has_next) {
-        const int C = a.g.C;
-        float *out = a.dxd + (sbase + evox + noff) * C;
-#pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            const f4 v = partial(U + c, own_x[c]);
-            const int c0 = c * 16 + 4 * q4;
-            if ((C & 3) == 0 && c0 + 3 < C) {
-                *(f4 *)(out + c0) = v;
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (c0 + i < C) out[c0 + i] = v[i];
-            }
-        }
-    }
-    if (!do_h) return;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int uo = u * 16 + 4 * q4;
-        const f4 gi = e_g[u][0], gf = e_g[u][1], gg = e_g[u][2], go = e_g[u][3];
-        const f4 c = e_c[u], cp = e_cp[u], gn = e_gn[u];
-        f4 ghv = partial(u, own_h[u]) + e_dh[u];
-        f4 di, df, dgv, dov, gco;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float gh = ghv[i];
-            const float tc = ftanh(c[i]);
-            const float gcv = gh * go[i] * (1.0f - tc * tc) + gn[i];
-            di[i] = gcv * gg[i] * gi[i] * (1.0f - gi[i]);
-            df[i] = gcv * cp[i] * gf[i] * (1.0f - gf[i]);
-            dgv[i] = gcv * gi[i] * (1.0f - gg[i] * gg[i]);
-            dov[i] = gh * tc * go[i] * (1.0f - go[i]);
-            gco[i] = gcv * gf[i];
-        }
-        float *dp = a.dA + vo * G + uo;
-        *(f4 *)dp = di;
-        *(f4 *)(dp + O) = df;
-        *(f4 *)(dp + 2 * O) = dgv;
-        *(f4 *)(dp + 3 * O) = dov;
-        *(f4 *)(a.gcf + vo * O + uo) = gco;
     }
 }
 
@@ -3213,60 +2951,9 @@ int launch_fwd_steps(const Geom &g, FwdStepArgs &a, hipStream_t st)
     return PLSTM_OK;
 }
 
-// One wave's LDS region of the staged reverse step, in 16-byte units: its
-// staged block (reg_px pixels of 4U chunks) or its partial sums (three
-// tiles of U + CT M-tiles, 64 lanes), whichever is larger.
-inline int bwd_blk_reg_f4(int U, int CT, int reg_px)
-{
-    const int st = reg_px * 4 * U, part = (U + CT) * (kNT - 1) * 64;
-    return st > part ? st : part;
-}
-
-// The staged reverse step for this shape: U <= 2 unit tiles and, with dL/dx
-// inside it, at most two channel tiles; `reg_px` the largest staged block.
-inline bool bwd_blk_ok(const Geom &g, bool with_dx, int reg_px)
-{
-    const int U = g.O / 16, CT = with_dx ? pad16(g.C) / 16 : 0;
-    if (g_step_split != 0 || U > 2 || CT > 2) return false;
-    return (size_t)kSW * bwd_blk_reg_f4(U, CT, reg_px) * 16 <= (size_t)device_info().max_lds;
-}
-
-template <int U, int CT>
-int launch_bwd_blk(const Geom &g, BwdStepArgs &a, hipStream_t st)
-{
-    const size_t lds = (size_t)kSW * a.reg_f4 * 16;
-    if (hipFuncSetAttribute((const void *)k_step_bwd_blk<U, CT>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-        return PLSTM_EHIP;
-    // with dL/dx, a last launch (t = -1) gives plane 0's share
-    for (int t = max_T(g) - 1; t >= (CT > 0 ? -1 : 0); --t) {
-        a.t = t;
-        int nb = 0;
-        for (int d = 0; d < kDirs; ++d) {
-            a.base[d] = nb;
-            if (t < g.dir[d].T && g.dir[d].T > 0) nb += g.N * a.nblk[d];
-        }
-        a.base[kDirs] = nb;
-        k_step_bwd_blk<U, CT><<<nb, 64 * kSW, lds, st>>>(a);
-        PLSTM_LAUNCH_CHECK();
-    }
-    return PLSTM_OK;
-}
-
 template <int U>
 int launch_bwd_steps(const Geom &g, BwdStepArgs &a, hipStream_t st)
 {
-    if constexpr (U <= 2) {
-        if (a.reg_f4 > 0) {
-            const int CT = a.dxd ? pad16(g.C) / 16 : 0;
-            switch (CT) {
-            case 0: return launch_bwd_blk<U, 0>(g, a, st);
-            case 1: return launch_bwd_blk<U, 1>(g, a, st);
-            case 2: return launch_bwd_blk<U, 2>(g, a, st);
-            default: return PLSTM_EUNSUPPORTED;
-            }
-        }
-    }
     // an item of the reverse step holds every unit group: split up to four
     // waves per SIMD
     const int few = g_step_split == 0 ? 2 * split_threshold() : split_threshold();
@@ -3801,9 +3488,6 @@ inline int line_nsegmax(const Geom &g)
     return m;
 }
 inline bool line_bwd_geom(const Geom &g) { return g.nd == 4 && g.KP == 1 && g.O == 16; }
-// Shapes whose reverse sweep may give dL/dx per direction (the 2D line blocks,
-// or the staged reverse step with at most 32 units and 32 input channels).
-inline bool bwd_dxd(const Geom &g) { return line_bwd_dx(g) || (g.O <= 32 && pad16(g.C) <= 32); }
 
 size_t step_bwd_ws(const Geom &g)
 {
@@ -3815,9 +3499,12 @@ size_t step_bwd_ws(const Geom &g)
     cv.take<float>((size_t)g.nd * U * KK * 4 * U * 256);           // W_h^T fragments
     cv.take<float>(wg_partial_floats(g));                           // weight-gradient partials
     cv.take<float>((size_t)g.nd * KK * 4 * U * (Cp / 16) * 256);   // W_x^T fragments
-    if (bwd_dxd(g)) cv.take<float>((size_t)g.nd * g.N * g.V * g.C);   // dL/dx per direction
+    if (line_bwd_dx(g)) cv.take<float>((size_t)g.nd * g.N * g.V * g.C);   // dL/dx per direction
     if (line_bwd_geom(g)) cv.take<float>((size_t)g.nd * g.N * line_nsegmax(g) * 64);  // db partials
-    return cv.off;
+    Carve sp(nullptr);                                             // split reverse steps
+    sp.off = split_bwd_ws(g);
+    sp.take<float>(wg_partial_floats(g));
+    return sp.off > cv.off ? sp.off : cv.off;
 }
 
 // dL/dx from the gate gradients of all six directions (any O in 16, 32, 64;
@@ -3870,21 +3557,46 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
     float *frag = cv.take<float>((size_t)g.nd * U * KK * 4 * U * 256);
     float *partial = cv.take<float>(wg_partial_floats(g));
     float *fragx = cv.take<float>((size_t)g.nd * KK * 4 * U * (Cp / 16) * 256);
-    float *dxd = bwd_dxd(g) ? cv.take<float>((size_t)g.nd * g.N * g.V * g.C) : nullptr;
+    float *dxd = line_bwd_dx(g) ? cv.take<float>((size_t)g.nd * g.N * g.V * g.C) : nullptr;
     float *dbl = line_bwd_geom(g) ? cv.take<float>((size_t)g.nd * g.N * line_nsegmax(g) * 64)
                                   : nullptr;
     bool db_done = false;
     const long long nvox = (long long)g.N * g.V;
     bool dx_done = false;
 
-    timing_begin("sweep_bwd_step", st);
-    k_pack_bwd<<<blocks_for((long long)g.nd * U * KK * 4 * U * 256, 256), 256, 0, st>>>(
-        g.nd, g.O, KK, wh, frag);
-    PLSTM_LAUNCH_CHECK();
     const bool fuse_dx = dx && dxd && line_bwd_dx(g);
     const size_t line_dyn = line_bwd_dyn_lds(g.KQ * 4, fuse_dx ? g.KQ * G * g.C : 0);
-    if (g.nd == 4 && g.KP == 1 && g.O == 16 && (g_step_split == 0 || g_step_split == 2) &&
-        line_dyn + 2 * kLineSlots * 64 + 4 * 64 * 16 + 4 * 4 * 4 * 16 <= (size_t)device_info().max_lds) {
+    const bool lines =
+        g.nd == 4 && g.KP == 1 && g.O == 16 && (g_step_split == 0 || g_step_split == 2) &&
+        line_dyn + 2 * kLineSlots * 64 + 4 * 64 * 16 + 4 * 4 * 4 * 16 <= (size_t)device_info().max_lds;
+    const bool split = !lines && g_step_split == 0;
+    if (!split) {
+        timing_begin("sweep_bwd_step", st);
+        k_pack_bwd<<<blocks_for((long long)g.nd * U * KK * 4 * U * 256, 256), 256, 0, st>>>(
+            g.nd, g.O, KK, wh, frag);
+        PLSTM_LAUNCH_CHECK();
+    }
+    if (split) {
+        SplitBwd sb;
+        const int rc = split_bwd(g, wx, wh, sv, dh, dx != nullptr, ws, &sb, st);
+        if (rc != PLSTM_OK) return rc;
+        if (dx) {
+            timing_begin("dx_step", st);
+            const long long ndx = nvox * g.C;
+            if ((ndx & 3) == 0)
+                k_sum_dxn4<<<blocks_for(ndx / 4, 256), 256, 0, st>>>(
+                    ndx / 4, g.nd, (const f4 *)sb.dxd, (f4 *)dx);
+            else
+                k_sum_dxn<<<blocks_for(ndx, 256), 256, 0, st>>>(ndx, g.nd, sb.dxd, dx);
+            PLSTM_LAUNCH_CHECK();
+            timing_end(1, st);
+            dx_done = true;
+        }
+        dA = sb.dA;
+        Carve rest(ws);
+        rest.off = sb.used;
+        partial = rest.take<float>(wg_partial_floats(g));
+    } else if (lines) {
         // 2D layers with 16 units: line blocks, S lines per launch (S r <= 16)
         LineBwdArgs la;
         la.g = g;
@@ -3944,24 +3656,6 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         a.gates = sv.gates; a.cell = sv.cell; a.dh = dh;
         a.dA = dA; a.gcf = gcf;
         for (int d = 0; d < kDirs; ++d) a.npg[d] = npg_of(g.dir[d]);
-        set_blocks(g, a.bp, a.bq, a.nbq, a.nblk);
-        int reg_px = 64;
-        for (int d = 0; d < g.nd; ++d) {
-            const int px = (a.bp[d] + 2 * (g.KP / 2)) * (a.bq[d] + 2 * (g.KQ / 2));
-            if (px > reg_px) reg_px = px;
-        }
-        // the staged reverse step, with dL/dx inside it where it takes it
-        const bool with_dx = dx && dxd && bwd_blk_ok(g, true, reg_px);
-        a.reg_f4 = bwd_blk_ok(g, with_dx, reg_px)
-                       ? bwd_blk_reg_f4(U, with_dx ? Cp / 16 : 0, reg_px) : 0;
-        a.fragx = fragx;
-        a.dxd = with_dx ? dxd : nullptr;
-        if (with_dx) {
-            const long long nf = (long long)g.nd * KK * 4 * U * (Cp / 16) * 256;
-            k_pack_dx<<<blocks_for(nf, 256), 256, 0, st>>>(g.nd, g.O, g.C, Cp / 16, KK, wx,
-                                                            fragx);
-            PLSTM_LAUNCH_CHECK();
-        }
         int rc;
         switch (U) {
         case 1: rc = launch_bwd_steps<1>(g, a, st); break;
@@ -3969,19 +3663,7 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         default: rc = launch_bwd_steps<4>(g, a, st); break;
         }
         if (rc != PLSTM_OK) return rc;
-        timing_end((with_dx ? 3 : 1) + max_T(g), st);
-        if (with_dx) {
-            timing_begin("dx_step", st);
-            const long long ndx = nvox * g.C;
-            if ((ndx & 3) == 0 && ((uintptr_t)dx & 15) == 0)
-                k_sum_dxn4<<<blocks_for(ndx / 4, 256), 256, 0, st>>>(ndx / 4, g.nd,
-                                                                      (const f4 *)dxd, (f4 *)dx);
-            else
-                k_sum_dxn<<<blocks_for(ndx, 256), 256, 0, st>>>(ndx, g.nd, dxd, dx);
-            PLSTM_LAUNCH_CHECK();
-            timing_end(1, st);
-            dx_done = true;
-        }
+        timing_end(1 + max_T(g), st);
     }
 
     timing_begin("wgrad_step", st);

@@ -9,7 +9,7 @@ import torch
 
 import oracle
 import synth
-from paper_1506_07452_amd.network import layer_forward
+from paper_1506_07452_amd.network import layer_backward, layer_forward
 from tests.gpu_util import dev, host, layer_dev, saved_view, say
 
 pytestmark = pytest.mark.gpu
@@ -74,3 +74,27 @@ def test_forward_with_an_outlier(shape, outlier):
     torch.cuda.synchronize()
     assert np.isfinite(ref).all()
     assert close(host(h), ref)
+
+
+@pytest.mark.parametrize("want_dx", [True, False], ids=["dx", "no-dx"])
+@pytest.mark.parametrize("shape", SHAPES + [(1, 4, 9, 7, 60, 16, 3), (1, 3, 6, 8, 20, 64, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_backward(shape, want_dx):
+    """Every spread of row tiles over the waves; dL/dh varies by 2^60 over the
+    volume, so that blocks and planes have scales of their own."""
+    inst = make(shape, 9200 + sum(shape))
+    L = inst.layers[0]
+    dh = synth.upstream_grad(inst.x.shape[:-1] + (shape[5],), 9300 + sum(shape))
+    rng = np.random.default_rng(5)
+    dh *= np.exp2(rng.integers(-30, 31, size=dh.shape[:2] + (1, 1, 1))).astype(np.float32)
+    ref = oracle.backward(inst.x, L.wx, L.wh, L.b, dh)
+    say("split backward", shape, want_dx)
+    x, Ld = dev(inst.x), layer_dev(L)
+    _, saved = layer_forward(x, Ld, training=True)
+    dx, dwx, dwh, db = layer_backward(x, Ld, saved, dev(dh), want_dx=want_dx)
+    torch.cuda.synchronize()
+    for name, got in (("dx", dx), ("dwx", dwx), ("dwh", dwh), ("db", db)):
+        if got is None:
+            continue
+        want = np.abs(ref[name]).max()
+        assert np.abs(host(got) - ref[name]).max() <= TOL * want, name
