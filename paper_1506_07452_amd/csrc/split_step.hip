@@ -717,6 +717,10 @@ k_step_bwd_h2(BwdH2Args a)
     for (int i = 0; i < RTW; ++i)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) sum[0][i][nt] = sum[1][i][nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    // neighbouring blocks and planes take opposite signs: what the instruction's
+    // rounding towards -inf leaves (1e-9 of the mean magnitude) then cancels in the
+    // bias gradients, which add it up over all voxels
+    const float flip = (bi + bj + t) & 1 ? -1.0f : 1.0f;
     float unscale = 1.0f;
 
     if (has_next) {
@@ -798,7 +802,7 @@ k_step_bwd_h2(BwdH2Args a)
                         top_next = m > top_next ? m : top_next;
                     }
                 }
-                const float scale = exp2i(scale_exp(top_next));
+                const float scale = flip * exp2i(scale_exp(top_next));
 #pragma unroll
                 for (int u = 0; u < SB; ++u) {
                     if (dst[u] < 0) continue;
@@ -875,7 +879,7 @@ k_step_bwd_h2(BwdH2Args a)
         for (int i = 0; i < RTW; ++i)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) sum[1][i][nt] += sum[0][i][nt];
-        unscale = exp2i(-scale_exp(top_next));
+        unscale = flip * exp2i(-scale_exp(top_next));
     }
 
     const int np = dg.T > 1 ? 2 : 1;
@@ -1244,6 +1248,13 @@ int split_stats(int dtype, const void *x, long long n, SplitStats *part, hipStre
         PLSTM_LAUNCH_CHECK();
         k_split_stats<float, true><<<kStatBlocks, 256, 0, st>>>(n, (const float *)x, part);
     }
+    PLSTM_LAUNCH_CHECK();
+    return PLSTM_OK;
+}
+
+int split_pad_x(long long nvox, int C, const float *x, float *xp, hipStream_t st)
+{
+    k_pad_x8<float><<<blocks_for(nvox * pad8(C), 256), 256, 0, st>>>(nvox, C, pad8(C), x, xp);
     PLSTM_LAUNCH_CHECK();
     return PLSTM_OK;
 }

@@ -32,6 +32,12 @@ size_t step_fwd_ws(const Geom &g);
 int step_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void *wh,
              const void *b, float *hd, float *cell, float *gates, void *h, void *ws,
              hipStream_t st);
+// Weight and bias gradients (db may be null) from dA; `amax`, `aoff`: maxima of
+// |dA| per direction as split_bwd leaves them, or null for the fp32 kernel.
+size_t step_wgrad_ws(const Geom &g);
+int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
+               const unsigned *amax, const long long *aoff, void *ws, float *dwx, float *dwh,
+               float *db, const char *phase, hipStream_t st);
 size_t step_bwd_ws(const Geom &g);
 int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, const Saved &sv,
              const float *dh, float *dx, float *dwx, float *dwh, float *db, void *ws,
@@ -54,6 +60,19 @@ struct SplitBwd {
 size_t split_bwd_ws(const Geom &g);
 int split_bwd(const Geom &g, const float *wx, const float *wh, const Saved &sv, const float *dh,
               bool with_dx, void *ws, SplitBwd *out, hipStream_t st);
+// Weight and bias gradients the same way (split_wgrad.hip): partial sums
+// [nd][kch][4O][16 NTt] of dA (x) [im2col(h) | im2col(x) | 1].  Where x has no one
+// scale it leaves them to the fp32 kernel, and *ctl (device) is 1.
+struct WgradSplit {
+    int kch;
+    size_t floats;            // of partial
+};
+WgradSplit split_wgrad_shape(const Geom &g);
+size_t split_wgrad_ws(const Geom &g);
+int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
+                const unsigned *amax, const long long *aoff, float *partial, void *ws,
+                const unsigned **ctl, hipStream_t st);
+int split_pad_x(long long nvox, int C, const float *x, float *xp, hipStream_t st);
 // dL/dx from the gate gradients dA [6][N][V][4O] on the MFMA (step_supported
 // shapes); `fragx` holds step_dx_ws bytes.
 size_t step_dx_ws(const Geom &g);
@@ -110,9 +129,8 @@ extern int g_step_split;
 // with pixel blocks staged in LDS (default), 2 = bf16 MFMA with operands read
 // from L1, 0 = on the fp32 MFMA.
 extern int g_step_bf16_mfma;
-// Weight gradients of the plane-step path: 1 = the LDS-staged GEMM where it
-// applies (at most 32 hidden units, C % 4 == 0; default), 0 = the
-// register-streamed kernel.
+// Weight gradients of the plane-step path: 1 = split products from staged
+// blocks (default), 0 = the register-streamed fp32 kernel.
 extern int g_wgrad_staged;
 
 }  // namespace plstm

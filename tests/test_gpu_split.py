@@ -98,3 +98,25 @@ def test_backward(shape, want_dx):
             continue
         want = np.abs(ref[name]).max()
         assert np.abs(host(got) - ref[name]).max() <= TOL * want, name
+
+
+@pytest.mark.parametrize("shape", [(1, 5, 9, 11, 6, 16, 3), (1, 4, 12, 10, 32, 32, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_weight_gradients_with_an_outlier(shape):
+    """An input with one value far above the rest keeps the fp32 products: the
+    other channels' gradients do not lose theirs."""
+    inst = make(shape, 9400 + sum(shape))
+    L = inst.layers[0]
+    inst.x[0, 2, 4, 5, 1] = 1e12
+    dh = synth.upstream_grad(inst.x.shape[:-1] + (shape[5],), 9500 + sum(shape))
+    ref = oracle.backward(inst.x, L.wx, L.wh, L.b, dh)
+    say("split outlier gradients", shape)
+    x, Ld = dev(inst.x), layer_dev(L)
+    _, saved = layer_forward(x, Ld, training=True)
+    _, dwx, dwh, db = layer_backward(x, Ld, saved, dev(dh))
+    torch.cuda.synchronize()
+    dwx, rest = host(dwx), [c for c in range(shape[4]) if c != 1]
+    assert np.abs(dwx[:, :, rest] - ref["dwx"][:, :, rest]).max() <= TOL * np.abs(ref["dwx"][:, :, rest]).max()
+    assert np.abs(dwx - ref["dwx"]).max() <= TOL * np.abs(ref["dwx"]).max()
+    for name, got in (("dwh", dwh), ("db", db)):
+        assert np.abs(host(got) - ref[name]).max() <= TOL * np.abs(ref[name]).max(), name
