@@ -54,6 +54,7 @@ int forward_dispatch(const Geom &g, int dtype, const void *x, const void *wx, co
         float *hd = sv ? sv->hd : cv.take<float>(saved_state_count(g));
         float *cellbuf = sv ? sv->cell : cv.take<float>(saved_state_count(g));
         int *flags = cv.take<int>(1024 + 1);
+        void *pack = cv.take<char>(sweep_fwd_pack_bytes());
         const float *xf = (const float *)x, *wxf = (const float *)wx, *whf = (const float *)wh,
                     *bf = (const float *)b;
         if (dtype == PLSTM_BF16) {
@@ -67,7 +68,7 @@ int forward_dispatch(const Geom &g, int dtype, const void *x, const void *wx, co
             xf = wd.x; wxf = wd.wx; whf = wd.wh; bf = wd.b;
         }
         const int rc = sweep_fwd(g, xf, wxf, whf, bf, hd, cellbuf, sv ? sv->gates : nullptr,
-                                 flags, st, path != 3);
+                                 flags, pack, st, path != 3);
         if (rc == PLSTM_OK) return sum_dirs(g, dtype, hd, h, st);
         // A grid that cannot be co-resident or a plane too wide for LDS runs
         // on another path instead.

@@ -14,26 +14,31 @@
 //     for each chunk of rows of the strip (sized to fit LDS):
 //       stage h_{t-1} (chunk + 1-pixel halo) and the input plane x_t into LDS
 //       each wave, per tile of 16 pixels:
-//         A = bias + im2col(x_t) W_x + im2col(h_{t-1}) W_h   (v_mfma_f32_16x16x4f32)
+//         A = bias + im2col(x_t) W_x + im2col(h_{t-1}) W_h   (split operands, split.h)
 //         gates, c_t = g i + c_{t-1} f, h_t = o tanh(c_t)    (in registers)
 //         write h_t, c_t (and the gates when training) to global memory
 //     publish: flag = t + 1 once the stores have completed
 //
-// The weight fragments (recurrent and input) and the bias live in LDS for
-// the whole kernel; h of every plane stays in the per-direction volume in
-// global memory, so a step only reads plane t-1 and writes plane t (no
-// write-after-read hazard).  MFMA layout (16x16x4 f32, one block): lane l
-// supplies A[m = l%16][k = l/16] and B[k = l/16][n = l%16] and receives
-// D[4(l/16) + i][l%16], i = 0..3.  Gate-units are on M (M-tile g = gate g of
-// the 16 units, the weights are the A operand) and pixels on N (B = im2col).
-// The K index of a tap is permuted so that lane group q = l/16 takes hidden
-// channels 4q..4q+3 of its pixel with one 16-byte LDS read; A uses the same
-// permutation.  Every lane ends with all four gates of units 4q..4q+3 of
-// pixel l%16, so the cell update needs no data exchange and its loads and
-// stores are 16-byte vectors.
+// The weight fragments (48 KB of split pairs, packed once per call with their row
+// scales), the bias and the scales live in LDS for the whole kernel; h of every
+// plane stays in the per-direction volume in global memory, so a step only reads
+// plane t-1 and writes plane t (no write-after-read hazard).  MFMA layout
+// (16x16x32 f16): lane l supplies A[m = l%16][k = 8 (l/16) + j] and B[k][n = l%16],
+// j = 0..7, and receives D[4(l/16) + i][l%16], i = 0..3.  Gate-units are on M
+// (M-tile g = gate g of the 16 units, the weights are the A operand) and pixels
+// on N (B = im2col in slots of eight channels).  Every lane ends with all four
+// gates of units 4q..4q+3 of pixel l%16, so the cell update needs no data exchange
+// and its loads and stores are 16-byte vectors.
+//
+// A tile is 72 products of 16 cycles (172 of 32 on the fp32 instruction), 60 LDS
+// reads of 16 bytes a lane and the cell update of about a thousand cycles, which
+// the four waves of a SIMD overlap.  Measured against the fp32 instruction, one
+// launch: 48 x 240 x 240 x 3 inference 3.67 -> 2.01 ms, training (with the stores of the gates) 4.0 -> 3.0; 30 x 512 x 512 x 1 8.9 -> 4.5 and
+// 10.6 -> 8.5; 2 x 8 x 64 x 64 x 1, bound by the hand-over between strips, 0.37 -> 0.32.
 #include "common.h"
 #include "coherent.h"
 #include "sweep.h"
+#include "split.h"
 #include "strip_plan.h"
 #include "timing.h"
 
@@ -45,7 +50,8 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr int kO = 16;
 constexpr int kG = 4 * kO;
 constexpr int kWaves = 16;         // four waves per SIMD: gate math of some overlaps the MFMAs of others
-constexpr int kWhFloats = 9 * 4 * 64 * 4;   // recurrent A fragments in LDS
+constexpr int kKG = 6;             // K-groups: 18 slots of h (9 taps x 2), 6 of x (3 x 2 tap pairs)
+constexpr int kAFloats = kKG * 4 * 2 * 256;   // A fragments in LDS: 48 KB
 constexpr int kThreads = 64 * kWaves;
 constexpr int kHS = 20;          // LDS floats per staged h pixel (16 + 4 pad)
 constexpr int kWaitVmcnt0 = 0x0F70;   // s_waitcnt vmcnt(0), other counters unconstrained
@@ -55,7 +61,10 @@ constexpr int kResX = 4;         // x_t staging registers per thread (resident s
 
 struct SweepArgs {
     Geom g;
-    const float *x, *wx, *wh, *b;
+    const float *x;
+    const h8 *frag;     // [6][kKG][4 gates][2][64] A fragments (k_pack_sweep)
+    const float *rows;  // [6][2][64] bias, 1 / scale of the gate rows
+    const unsigned *ctl;    // [0] 1: fp32 channels instead of split pairs, [1] scale of x (bits)
     float *hd;          // [6][N][V][16] per-direction h^d
     float *cell;        // [6][N][V][16] c^d
     float *gates;       // [6][N][V][64] or null
@@ -117,53 +126,208 @@ __device__ inline void publish(const SweepArgs &a, int step)
     __hip_atomic_store(&a.flags[blockIdx.x], step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Gate pre-activations of one 16-pixel tile: bias + W_x im2col(x_t) +
-// W_h im2col(h_{t-1}); `base` is the LDS pixel index of this lane's pixel in
-// the staged (halo-padded) tile whose rows are `rs` and columns `cs` pixels
-// apart.
-template <int C>
-__device__ __forceinline__ void tile_preact(const float *whs, const float *hsrc,
-                                            const float *xs, const float *wxs, const float *bs,
-                                            int base, int rs, int cs, const int *xoff, int q4,
-                                            int lane, f4 (&acc)[4])
+// Staged h of a pixel: 16 units as two split slots (8 hi, 8 lo fp16 each), or
+// as 16 fp32 values in the same 64 bytes.  Units 4 qd .. 4 qd + 3:
+__device__ inline void put_h(float *px, int qd, f4 v, bool f32)
 {
-    constexpr int KXS = (9 * C + 3) / 4;
+    char *p = (char *)px + (qd >> 1) * 32;
+    if (f32) {
+        *(f4 *)(p + (qd & 1) * 16) = v;
+        return;
+    }
+    h4 hi, lo;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) acc[g] = *(const f4 *)&bs[g * kO + 4 * q4];
+    for (int i = 0; i < 4; ++i) {
+        const float s = v[i] * kHScale;
+        hi[i] = (_Float16)s;
+        lo[i] = (_Float16)(s - (float)hi[i]);
+    }
+    *(h4 *)(p + (qd & 1) * 8) = hi;
+    *(h4 *)(p + 16 + (qd & 1) * 8) = lo;
+}
+// Staged x: 8 bytes of a pixel in each of two planes `xlo` bytes apart, four
+// channels' hi and lo, or channels 0, 1 and 2, 3 in fp32.
+__device__ inline void put_x(char *xs, int xlo, int px, int c, float v, float scale, bool f32)
+{
+    if (f32) {
+        *(float *)(xs + (c >> 1) * xlo + px * 8 + (c & 1) * 4) = v;
+        return;
+    }
+    const float s = v * scale;
+    const _Float16 hi = (_Float16)s;
+    *(_Float16 *)(xs + px * 8 + c * 2) = hi;
+    *(_Float16 *)(xs + xlo + px * 8 + c * 2) = (_Float16)(s - (float)hi);
+}
+// 16 bytes that are only 8-byte aligned (two neighbouring pixels of x).
+__device__ inline h8 read_pair(const char *p)
+{
+    const h4 a = *(const h4 *)p, b = *(const h4 *)(p + 8);
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// A tile's contraction, the sums of Eq. (7)-(9), (11) times their rows' scales.
+// Lane group q of K-group kg takes slot 4 kg + q: slot 2 tap + half of h, or slot 18
+// + 2 r + j of x, the pixels -1, 0 (j = 0) or 1, 2 (j = 1, the second with zero
+// weights) along the axis that is contiguous in LDS, r - 1 across it.  `h` and
+// `x` are this lane's pixel; off[kg] its slot's byte offset.
+struct SlotOff {
+    int h[5];      // K-groups 0 .. 3, and 4 for q < 2
+    int x[2];      // K-groups 4 (q >= 2) and 5
+    int xlo;       // plane distance of x
+};
+__device__ __forceinline__ void tile_preact(const float *afr, const char *h, const char *x,
+                                            const SlotOff &o, int q4, int lane, bool f32,
+                                            f4 (&acc)[4])
+{
+    f4 cross[4];
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-        const int o = (tap / 3 - 1) * rs + (tap % 3 - 1) * cs;
-        const f4 hv = *(const f4 *)&hsrc[(base + o) * kHS + 4 * q4];
-        f4 w[4];
+    for (int g = 0; g < 4; ++g) acc[g] = cross[g] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    const h8 *ap = (const h8 *)afr + lane;
 #pragma unroll
-        for (int s2 = 0; s2 < 4; ++s2) w[s2] = *(const f4 *)&whs[((tap * 4 + s2) * 64 + lane) * 4];
+    for (int kg = 0; kg < kKG; ++kg) {
+        h8 bh, bl;
+        if (kg < 4) {
+            bh = *(const h8 *)(h + o.h[kg]);
+            bl = *(const h8 *)(h + o.h[kg] + 16);
+        } else {
+            const bool is_h = kg == 4 && q4 < 2;
+            const char *p = is_h ? h + o.h[4] : x + o.x[kg - 4];
+            bh = read_pair(p);
+            bl = read_pair(p + (is_h ? 16 : o.xlo));
+        }
+        if (!f32) {
 #pragma unroll
-        for (int s2 = 0; s2 < 4; ++s2)
+            for (int g = 0; g < 4; ++g) {
+                const h8 ah = ap[(kg * 4 + g) * 128], al = ap[(kg * 4 + g) * 128 + 64];
+                cross[g] = mfma_h(al, bh, cross[g]);
+                acc[g] = mfma_h(ah, bh, acc[g]);
+                cross[g] = mfma_h(ah, bl, cross[g]);
+            }
+        } else {
+            f4 b0 = __builtin_bit_cast(f4, bh), b1 = __builtin_bit_cast(f4, bl);
+            // (the pixel with zero weights may hold an infinity)
+            const bool one = kg == 5 ? (q4 & 1) : kg == 4 && q4 == 3;
+            if (kg >= 4) b0[2] = one ? 0.0f : b0[2], b0[3] = one ? 0.0f : b0[3];
+            if (kg >= 4) b1[2] = one ? 0.0f : b1[2], b1[3] = one ? 0.0f : b1[3];
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s2][g], hv[s2], acc[g], 0,
-                                                            0, 0);
+            for (int g = 0; g < 4; ++g) {
+                const f4 a0 = __builtin_bit_cast(f4, ap[(kg * 4 + g) * 128]);
+                const f4 a1 = __builtin_bit_cast(f4, ap[(kg * 4 + g) * 128 + 64]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[i], b0[i], acc[g], 0, 0, 0);
+                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[i], b1[i], acc[g], 0, 0, 0);
+                }
+            }
+        }
     }
 #pragma unroll
-    for (int ks = 0; ks < KXS; ++ks) {
-        const float xv = (4 * ks + q4 < 9 * C) ? xs[base * C + xoff[ks]] : 0.0f;
-        const f4 wxv = *(const f4 *)&wxs[(ks * 64 + lane) * 4];
+    for (int g = 0; g < 4; ++g) acc[g] += cross[g];
+}
+
+// A fragments and row scales (split.h), one workgroup per (direction, gate); x
+// slots pair the taps of the axis that is contiguous in the direction's strips.
+struct PackSweepArgs {
+    int C;
+    const float *wx, *wh, *b;
+    const SplitStats *part;
+    unsigned *ctl;
+    h8 *frag;
+    float *rows;
+    int resident[kDirs];
+};
+__global__ void __launch_bounds__(256) k_pack_sweep(PackSweepArgs a)
+{
+    __shared__ SplitStat red[2];
+    __shared__ unsigned mx[16], mh[16];
+    __shared__ float fx[16], fh[16];
+    const int gate = blockIdx.x & 3, d = blockIdx.x >> 2, tid = threadIdx.x, C = a.C;
+    if (tid < 16) mx[tid] = mh[tid] = 0u;
+    const SplitStat st = stat_reduce(a.part->first, &red[0]);
+    const bool split = stat_fits(st, stat_reduce(a.part->second, &red[1]));
+    const int ex = scale_exp(st.max_bits), gu0 = d * kG + gate * kO;
+    {
+        const int row = tid >> 4;
+        unsigned m0 = 0, m1 = 0;
+        for (int i = tid & 15; i < C * 9; i += 16) {
+            const unsigned m = __float_as_uint(a.wx[(gu0 + row) * C * 9 + i]) & 0x7fffffffu;
+            m0 = m > m0 && m < 0x7f800000u ? m : m0;
+        }
+        for (int i = tid & 15; i < kO * 9; i += 16) {
+            const unsigned m = __float_as_uint(a.wh[(gu0 + row) * kO * 9 + i]) & 0x7fffffffu;
+            m1 = m > m1 && m < 0x7f800000u ? m : m1;
+        }
+        atomicMax(&mx[row], m0);
+        atomicMax(&mh[row], m1);
+    }
+    __syncthreads();
+    if (tid < 16) {
+        int s = 100;
+        if (mx[tid]) s = min(s, ex + scale_exp(mx[tid]));
+        if (mh[tid]) s = min(s, 15 + scale_exp(mh[tid]));
+        if (s < -100) s = -100;
+        fx[tid] = split ? ldexpf(1.0f, s - ex) : 1.0f;
+        fh[tid] = split ? ldexpf(1.0f, s - 15) : 1.0f;
+        a.rows[d * 128 + gate * kO + tid] = a.b[gu0 + tid];
+        a.rows[d * 128 + 64 + gate * kO + tid] = split ? ldexpf(1.0f, -s) : 1.0f;
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        a.ctl[0] = split ? 0u : 1u;
+        a.ctl[1] = __float_as_uint(split ? exp2i(ex) : 1.0f);
+    }
+    __syncthreads();
+    for (int e = tid; e < kKG * 64; e += 256) {
+        const int lane = e & 63, kg = e >> 6, q = lane >> 4, col = lane & 15, slot = 4 * kg + q;
+        f4 w[2];
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-            acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(wxv[g], xv, acc[g], 0, 0, 0);
+        for (int j = 0; j < 8; ++j) {
+            float v = 0.0f;
+            if (slot < 18) {
+                v = a.wh[((gu0 + col) * kO + 8 * (slot & 1) + j) * 9 + (slot >> 1)] * fh[col];
+            } else {
+                // pixel and channel of element j: four channels of each pixel, or in
+                // fp32 two of each pixel per plane
+                const int r = (slot - 18) >> 1, jj = (slot - 18) & 1;
+                const int px = split ? j >> 2 : (j >> 1) & 1;
+                const int c = split ? j & 3 : (j >> 2) * 2 + (j & 1);
+                const int k = 2 * jj + px;                 // tap along the contiguous axis
+                if (k < 3 && c < C)
+                    v = a.wx[((gu0 + col) * C + c) * 9 + (a.resident[d] ? k * 3 + r : r * 3 + k)] *
+                        fx[col];
+            }
+            w[j >> 2][j & 3] = v;
+        }
+        h8 *out = a.frag + (((long long)d * kKG + kg) * 4 + gate) * 128 + lane;
+        if (split) {
+            const Split8 sp = split8(w[0], w[1]);
+            out[0] = sp.hi;
+            out[64] = sp.lo;
+        } else {
+            out[0] = __builtin_bit_cast(h8, w[0]);
+            out[64] = __builtin_bit_cast(h8, w[1]);
+        }
     }
 }
 
 // Gates, cell and hidden update of four units of one pixel (Eq. (7)-(12)).
-__device__ __forceinline__ void lstm_cell(const f4 (&acc)[4], f4 cprev, bool has_prev, f4 &gi,
-                                          f4 &gf, f4 &gg, f4 &go, f4 &cn, f4 &hn)
+// `bs`: biases of the gate rows, then 1 / their scales.
+__device__ __forceinline__ void lstm_cell(const f4 (&acc)[4], const float *bs, int q4, f4 cprev,
+                                          bool has_prev, f4 &gi, f4 &gf, f4 &gg, f4 &go, f4 &cn,
+                                          f4 &hn)
 {
+    f4 pre[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const f4 b = *(const f4 *)&bs[g * kO + 4 * q4], r = *(const f4 *)&bs[kG + g * kO + 4 * q4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pre[g][i] = __builtin_fmaf(acc[g][i], r[i], b[i]);
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        gi[i] = fsig(acc[0][i]);
-        gf[i] = fsig(acc[1][i]);
-        gg[i] = ftanh(acc[2][i]);
-        go[i] = fsig(acc[3][i]);
+        gi[i] = fsig(pre[0][i]);
+        gf[i] = fsig(pre[1][i]);
+        gg[i] = ftanh(pre[2][i]);
+        go[i] = fsig(pre[3][i]);
         cn[i] = gg[i] * gi[i] + (has_prev ? cprev[i] : 0.0f) * gf[i];
         hn[i] = go[i] * ftanh(cn[i]);
     }
@@ -190,9 +354,10 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int q4 = lane >> 4, col = lane & 15;
-    constexpr int KXS = (9 * C + 3) / 4;    // MFMA k-steps of the input convolution
-    float *wxs = smem;                       // [KXS][64 lanes][4 M-tiles] A fragments
-    float *bs = wxs + KXS * 256;             // [64] bias
+    float *whs = smem;                       // [kKG][4 gates][2][64 lanes] A fragments
+    float *bs = whs + kAFloats;              // [64] bias, [64] 1 / scale
+    const bool f32 = a.ctl[0] != 0;
+    const float xscale = __uint_as_float(a.ctl[1]);
     const bool resident = a.resident[d] != 0;
     const int P = dg.P;
     // LDS pixel strides of a staged tile: chunked strips are row-major,
@@ -200,41 +365,22 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
     // so the columns next to a neighbour strip form their own tiles).
     const int rs = resident ? 1 : W2, cs = resident ? P + 2 : 1;
 
-    // ---- recurrent weights as MFMA A fragments (resident for the sweep) ---
     const long long V = a.g.V;
-    // Recurrent weights as MFMA A fragments in LDS: entry (tap, s, lane)
-    // holds the four gates' weights of gate-unit lane%16 for hidden unit
-    // 4 (lane/16) + s, one 16-byte read per k-step (LDS keeps the waves at
-    // about 110 VGPRs, so four share a SIMD).
-    float *whs = bs + kG;
-    for (int e = threadIdx.x; e < 9 * 4 * 64; e += kThreads) {
-        const int l = e & 63, s = (e >> 6) & 3, tap = e >> 8;
-        const int lq = l >> 4, lc = l & 15;
-        f4 v;
+    for (int e = threadIdx.x; e < kAFloats / 4; e += kThreads)
+        *(f4 *)&whs[e * 4] = ((const f4 *)(a.frag + (long long)d * kKG * 512))[e];
+    if (threadIdx.x < 2 * kG) bs[threadIdx.x] = a.rows[d * 2 * kG + threadIdx.x];
+    // byte offsets of this lane's slots from its pixel
+    SlotOff so;
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-            v[g] = a.wh[(((long long)d * kG + g * kO + lc) * kO + 4 * lq + s) * 9 + tap];
-        *(f4 *)&whs[e * 4] = v;
+    for (int kg = 0; kg < 5; ++kg) {
+        const int slot = min(4 * kg + q4, 17), tap = slot >> 1;
+        so.h[kg] = ((tap / 3 - 1) * rs + (tap % 3 - 1) * cs) * kHS * 4 + (slot & 1) * 32;
     }
-    // Input-convolution A fragments in LDS as well (they feed few MFMAs).
-    int xoff[KXS];
 #pragma unroll
-    for (int ks = 0; ks < KXS; ++ks) {
-        const int k = 4 * ks + q4;
-        const int tap = k < 9 * C ? k / C : 0, c = k % C;   // padding lanes read tap 0
-        xoff[ks] = k < 9 * C ? ((tap / 3 - 1) * rs + (tap % 3 - 1) * cs) * C + c : 0;
-        if (wave == 0) {
-            f4 w4;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int gn = g * kO + col;
-                const float w = a.wx[(((long long)d * kG + gn) * C + c) * 9 + tap];
-                w4[g] = k < 9 * C ? w : 0.0f;
-            }
-            *(f4 *)&wxs[(ks * 64 + lane) * 4] = w4;
-        }
+    for (int k = 0; k < 2; ++k) {
+        const int xsl = k ? 2 + q4 : (q4 & 1), r = xsl >> 1;
+        so.x[k] = ((r - 1) * (resident ? cs : rs) + ((xsl & 1) ? 1 : -1)) * 8;
     }
-    if (threadIdx.x < kG) bs[threadIdx.x] = a.b[d * kG + threadIdx.x];
 
     // Base pointers of this (direction, batch element); element offsets inside
     // a slice fit in 32 bits (V * 64 < 2^31 is checked at the boundary).
@@ -266,14 +412,16 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
         const int npl = P2 * W2;
         const int npx = P * TQ;
         const int nmt = (npx + 15) >> 4;
-        float *hb0 = whs + kWhFloats;
+        float *hb0 = bs + 2 * kG;
         float *hb1 = hb0 + npl * kHS;
-        float *xs = hb1 + npl * kHS;
-        float *cb = xs + ((npl * C + 3) & ~3);     // [npx][kCS] cell states (16-byte aligned)
+        char *xs = (char *)(hb1 + npl * kHS);      // two planes of 8 bytes a pixel (+ 2 pixels read past)
+        so.xlo = (npl * 8 + 31) & ~15;
+        float *cb = (float *)(xs + 2 * so.xlo);    // [npx][kCS] cell states
         int *order = (int *)(cb + npx * kCS);      // tile order, edge tiles first
         int *cnt = order + nmt;                    // edge tiles stored this step
         const float inv_p = 1.0f / (float)P;
         for (int e = threadIdx.x; e < 2 * npl * kHS; e += kThreads) hb0[e] = 0.0f;
+        for (int e = threadIdx.x; e < so.xlo / 2; e += kThreads) ((float *)xs)[e] = 0.0f;
         if (threadIdx.x == 0) {
             int k = 0;
             for (int pass = 0; pass < 2; ++pass)
@@ -313,7 +461,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
                 const int e = threadIdx.x + u * kThreads;
                 const int pix = e / C, c = e - (e / C) * C;
                 const int rr = fdiv_floor(pix, inv_w2);
-                if (e < npl * C) xs[((pix - rr * W2) * P2 + rr) * C + c] = xr[u];
+                if (e < npl * C) put_x(xs, so.xlo, (pix - rr * W2) * P2 + rr, c, xr[u], xscale, f32);
             }
         };
         issue_x((dg.sign > 0 ? 0 : dg.T - 1) * ss);
@@ -336,7 +484,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
                     if (pc >= 0 && pc < dg.Q) {
                         const f4 v =
                             load_coherent(hd_rs, (pplane + r * sp + pc * sq) * kO + qd * 4);
-                        *(f4 *)&hprev[((side ? TQ + 1 : 0) * P2 + r + 1) * kHS + qd * 4] = v;
+                        put_h(&hprev[((side ? TQ + 1 : 0) * P2 + r + 1) * kHS], qd, v, f32);
                     }
                 }
             }
@@ -351,12 +499,12 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
                 const int v = splane + ra * sp + (q0 + ca) * sq;
                 const f4 cv = *(const f4 *)&cb[pa * kCS + 4 * q4];
                 f4 acc[4];
-                tile_preact<C>(whs, hprev, xs, wxs, bs, base, 1, P2, xoff, q4, lane, acc);
+                tile_preact(whs, (const char *)&hprev[base * kHS], xs + base * 8, so, q4, lane, f32, acc);
                 f4 gi, gf, gg, go, cn, hn;
-                lstm_cell(acc, cv, t > 0, gi, gf, gg, go, cn, hn);
+                lstm_cell(acc, bs, q4, cv, t > 0, gi, gf, gg, go, cn, hn);
                 if (mt * 16 + col < npx) {
                     *(f4 *)&cb[pa * kCS + 4 * q4] = cn;
-                    *(f4 *)&hcur[base * kHS + 4 * q4] = hn;
+                    put_h(&hcur[base * kHS], q4, hn, f32);
                     if (is_shared_col(q0 + ca))
                         store_coherent(hd_rs, v * kO + 4 * q4, hn);
                     else
@@ -395,8 +543,11 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
 
     // ================= chunked strip: rows staged per step =================
     const int chunk_rows = a.chunk_rows[d];
-    float *hs = whs + kWhFloats;
-    float *xs = hs + (chunk_rows + 2) * (a.max_w[d] + 2) * kHS;
+    float *hs = bs + 2 * kG;
+    const int max_px = (chunk_rows + 2) * (a.max_w[d] + 2);
+    char *xs = (char *)(hs + max_px * kHS);
+    so.xlo = (max_px * 8 + 31) & ~15;
+    for (int e = threadIdx.x; e < so.xlo / 2; e += kThreads) ((float *)xs)[e] = 0.0f;
     const float inv_tq = 1.0f / (float)TQ;
     __syncthreads();
     for (int t = 0; t < dg.T; ++t) {
@@ -448,8 +599,8 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) {
                     const int e = e0 + u * kThreads;
-                    if (e < nh) *(f4 *)&hs[(e >> 2) * kHS + (e & 3) * 4] = hv[u];
-                    if (e < nx) xs[e] = xv[u];
+                    if (e < nh) put_h(&hs[(e >> 2) * kHS], e & 3, hv[u], f32);
+                    if (e < nx) put_x(xs, so.xlo, e / C, e % C, xv[u], xscale, f32);
                 }
             }
             __syncthreads();
@@ -470,10 +621,10 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
                 // otherwise sink it to its use and expose its latency)
                 __builtin_amdgcn_sched_barrier(0);
                 f4 acc[4];
-                tile_preact<C>(whs, hs, xs, wxs, bs, base, W2, 1, xoff, q4, lane, acc);
+                tile_preact(whs, (const char *)&hs[base * kHS], xs + base * 8, so, q4, lane, f32, acc);
                 if (mt * 16 + col >= npx) continue;
                 f4 gi, gf, gg, go, cn, hn;
-                lstm_cell(acc, cv, t > 0, gi, gf, gg, go, cn, hn);
+                lstm_cell(acc, bs, q4, cv, t > 0, gi, gf, gg, go, cn, hn);
                 *(f4 *)&cell_dn[v * kO + 4 * q4] = cn;
                 if (is_shared_col(pa - ra * TQ + q0))
                     store_coherent(hd_rs, v * kO + 4 * q4, hn);
@@ -508,15 +659,14 @@ __global__ void k_fill_zero(int *p, int n)
 StripCostModel fwd_model(int C)
 {
     StripCostModel m;
-    // wx fragments, bias, recurrent fragments
-    m.fixed_bytes = (size_t)(((9 * C + 3) / 4) * 256 + kG + kWhFloats) * sizeof(float);
-    m.px_bytes = (size_t)(kHS + C) * sizeof(float);                     // h + x per pixel
+    m.fixed_bytes = (size_t)(kAFloats + 2 * kG) * sizeof(float) + 64;   // fragments, rows, x padding
+    m.px_bytes = (size_t)kHS * sizeof(float) + 16;                      // h + x per pixel
     m.c_sync = 3.0;
-    m.c_tile = 3.2;
+    m.c_tile = 1.1;
     m.c_stage0 = 1.0;
     m.c_stage_px = 0.0031;
     m.allow_resident = true;
-    m.res_px_bytes = (size_t)(2 * kHS + C) * sizeof(float);   // two h buffers + x
+    m.res_px_bytes = (size_t)2 * kHS * sizeof(float) + 16;   // two h buffers + x
     m.res_own_bytes = (size_t)kCS * sizeof(float) + 1 * sizeof(int);   // c + tile order
     m.res_fixed_bytes = 16 * sizeof(int);                      // counters + alignment of c
     m.res_max_staged = kResX * kThreads / C;                   // x_t fits the registers
@@ -550,6 +700,28 @@ bool sweep_fwd_supported(const Geom &g, int dtype)
            g.KQ == 3 && g.O == kO && g.C >= 1 && g.C <= 4;
 }
 
+struct SweepPack {
+    h8 *frag;
+    float *rows;
+    SplitStats *part;
+    unsigned *ctl;
+};
+static SweepPack carve_pack(Carve &cv)
+{
+    SweepPack k;
+    k.frag = cv.take<h8>((size_t)kDirs * kKG * 512);
+    k.rows = cv.take<float>((size_t)kDirs * 2 * kG);
+    k.part = cv.take<SplitStats>(1);
+    k.ctl = cv.take<unsigned>(2);
+    return k;
+}
+size_t sweep_fwd_pack_bytes()
+{
+    Carve cv(nullptr);
+    carve_pack(cv);
+    return cv.off;
+}
+
 size_t sweep_fwd_ws(const Geom &g, bool training)
 {
     Carve cv(nullptr);
@@ -558,11 +730,12 @@ size_t sweep_fwd_ws(const Geom &g, bool training)
         cv.take<float>(saved_state_count(g));   // c^d
     }
     cv.take<int>(1024 + 1);                     // flags + err
+    cv.take<char>(sweep_fwd_pack_bytes());
     return cv.off;
 }
 
 int sweep_fwd(const Geom &g, const float *x, const float *wx, const float *wh, const float *b,
-              float *hd, float *cell, float *gates, int *flags, hipStream_t st,
+              float *hd, float *cell, float *gates, int *flags, void *pack, hipStream_t st,
               bool allow_resident)
 {
     const DevInfo di = device_info();
@@ -583,7 +756,9 @@ int sweep_fwd(const Geom &g, const float *x, const float *wx, const float *wh, c
 
     SweepArgs args;
     args.g = g;
-    args.x = x; args.wx = wx; args.wh = wh; args.b = b;
+    Carve cv(pack);
+    const SweepPack pk = carve_pack(cv);
+    args.x = x; args.frag = pk.frag; args.rows = pk.rows; args.ctl = pk.ctl;
     args.hd = hd; args.cell = cell; args.gates = gates;
     args.flags = flags;
     args.err = flags + 1024;
@@ -601,8 +776,16 @@ int sweep_fwd(const Geom &g, const float *x, const float *wx, const float *wh, c
 
     k_fill_zero<<<(1025 + 255) / 256, 256, 0, st>>>(flags, 1025);
     PLSTM_LAUNCH_CHECK();
+    int rc = split_stats(PLSTM_F32, x, (long long)g.N * g.V * g.C, pk.part, st);
+    if (rc != PLSTM_OK) return rc;
+    PackSweepArgs pa;
+    pa.C = g.C;
+    pa.wx = wx; pa.wh = wh; pa.b = b;
+    pa.part = pk.part; pa.ctl = pk.ctl; pa.frag = pk.frag; pa.rows = pk.rows;
+    for (int d = 0; d < kDirs; ++d) pa.resident[d] = pl.resident[d];
+    k_pack_sweep<<<kDirs * 4, 256, 0, st>>>(pa);
+    PLSTM_LAUNCH_CHECK();
     timing_begin("sweep_fwd_mfma", st);
-    int rc;
     switch (g.C) {
     case 1: rc = launch_sweep<1>(pl, args, st); break;
     case 2: rc = launch_sweep<2>(pl, args, st); break;

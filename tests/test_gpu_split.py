@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import oracle
+import paper_1506_07452_amd as P
 import synth
 from paper_1506_07452_amd.network import layer_backward, layer_forward
 from tests.gpu_util import dev, host, layer_dev, saved_view, say
@@ -120,3 +121,28 @@ def test_weight_gradients_with_an_outlier(shape):
     assert np.abs(dwx - ref["dwx"]).max() <= TOL * np.abs(ref["dwx"]).max()
     for name, got in (("dwh", dwh), ("db", db)):
         assert np.abs(host(got) - ref[name]).max() <= TOL * np.abs(ref[name]).max(), name
+
+
+@pytest.fixture(params=[0, 3], ids=["whole", "chunked"])
+def strips(request):
+    P.pyramid_lstm_set_forward_path(request.param)
+    yield
+    P.pyramid_lstm_set_forward_path(0)
+
+
+@pytest.mark.parametrize("outlier", [None, np.inf, 1e30], ids=str)
+@pytest.mark.parametrize("shape", [(1, 5, 9, 11, 3, 16, 3), (2, 7, 3, 40, 1, 16, 3), (1, 1, 1, 2, 4, 16, 3),
+                                   (1, 17, 40, 21, 2, 16, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_persistent_forward(shape, outlier, strips):
+    """Strips kept whole in LDS and staged by chunks: their tap pairs lie along
+    different axes, and the pixel with zero weights may hold an infinity."""
+    inst = make(shape, 9600 + sum(shape))
+    L = inst.layers[0]
+    if outlier is not None:
+        inst.x[-1, -1, -1, -1, 0] = outlier
+    with np.errstate(over="ignore"):
+        ref = oracle.forward(inst.x, L.wx, L.wh, L.b)["h"]
+    say("split sweep", shape, outlier)
+    h, _ = layer_forward(dev(inst.x), layer_dev(L))
+    torch.cuda.synchronize()
+    assert close(host(h), ref)
