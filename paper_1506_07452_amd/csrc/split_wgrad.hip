@@ -114,7 +114,10 @@ struct WgH2Args {
 // memory), with the reduction: 32 -> 32 units on 48 x 240 x 240 24.1 -> 9.7 ms, on
 // 25 x 240 x 240 12.6 -> 5.7; 64 -> 64 on 20 x 64 x 64 3.2 -> 1.2; 7 x 7, 25 -> 32 on
 // 15 x 128 x 128 10.7 -> 4.5; 16 -> 16, 5 x 5 on 2 x 61 x 132 x 144 19.0 -> 5.1; error
-// against 64 bits 4.6e-6 -> 9e-7.  Generic pointers into LDS and values hoisted out
+// against 64 bits 4.6e-6 -> 9e-7.  After the persistent reverse sweep (16 units, 3
+// channels on 48 x 240 x 240, training step of two layers) 49.9 -> 47.9 ms and after
+// the 2D line blocks (30 x 512 x 512 x 1, forward and backward) 17.7 -> 16.6, where
+// a wave streamed operands from memory for fp32 products.  Generic pointers into LDS and values hoisted out
 // of the block loop cost 120 spilled registers (15.1 ms on the second).
 template <int NT, int DB>
 __global__ void __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_eu(2, 2)))

@@ -15,10 +15,10 @@
 //     in LDS, and each lane ends with four consecutive units of one
 //     pixel, so every epilogue load and store is a 16-byte vector.  The
 //     product gc_t f_t is what plane t - 1 needs, so that is what is kept.
-//     dA of every voxel is kept for (2) and for dL/dx.
-// (2) k_wgrad_rows: dW = sum over voxels of dA (x) [im2col(h_{t-1}),
-//     im2col(x_t), 1], a register-streamed implicit GEMM (see there), and
-//     (3) k_wgrad_reduce sums the per-wave partials in a fixed order.
+//     dA of every voxel is kept for (2) and for dL/dx, and each wave leaves the
+//     largest finite |dA| it stored, from which (2) scales its split operands.
+// (2) dW = sum over voxels of dA (x) [im2col(h_{t-1}), im2col(x_t), 1]: the
+//     plane-step path's kernels (split_wgrad.hip).
 #include "common.h"
 #include "coherent.h"
 #include "strip_plan.h"
@@ -56,12 +56,31 @@ struct BwdArgs {
     const float *dh;             // dL/dh [N][V][16]
     float *dA;                   // [6][N][V][64] gate pre-activation gradients
     float *gcf;                  // [6][N][V][16] dL/dc_t * f_t, carried to plane t - 1
+    unsigned *amax;              // [blocks][kWaves] largest finite |dA| (bits)
     int *flags, *err;
     int max_spin;                // polls before a wait gives up
     int wait_bias;               // added to the awaited step (0; failure-path test mode only)
     int nstrip[kDirs], first[kDirs], chunk_rows[kDirs], max_w[kDirs];
     int resident[kDirs];         // 1: the strip's dA stays in LDS for the sweep
 };
+
+// The largest of `top` and the finite |v|: one comparison of the sixteen values'
+// maximum, and each value's own where that is not finite.
+__device__ inline float top_finite(float top, f4 a, f4 b, f4 c, f4 d)
+{
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        m = fmaxf(fmaxf(m, fmaxf(fabsf(a[i]), fabsf(b[i]))), fmaxf(fabsf(c[i]), fabsf(d[i])));
+    if (__builtin_expect(m < __builtin_inff(), 1)) return fmaxf(top, m);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float v[4] = {fabsf(a[i]), fabsf(b[i]), fabsf(c[i]), fabsf(d[i])};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) top = v[k] < __builtin_inff() ? fmaxf(top, v[k]) : top;
+    }
+    return top;
+}
 
 // Epilogue operands of one tile (this lane's pixel, units 4 q4 .. 4 q4 + 3).
 struct BwdEpi {
@@ -163,6 +182,13 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
     auto is_shared_col = [&](int pc) {
         return (pc == q0 - 1) | (pc == q1) | ((pc == q0) & (nb_lo >= 0)) |
                ((pc == q1 - 1) & (nb_hi >= 0));
+    };
+
+    float top = 0.0f;            // largest finite |dA| of this lane
+    auto leave_max = [&]() {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+        if (lane == 0) a.amax[blockIdx.x * kWaves + wave] = __float_as_uint(top);
     };
 
     if (a.resident[d]) {
@@ -295,6 +321,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                         dAg[i] = gcs * e.gi[i] * (1.0f - e.gg[i] * e.gg[i]);
                         dAo[i] = gh * tc * e.go[i] * (1.0f - e.go[i]);
                     }
+                    top = top_finite(top, dAi, dAf, dAg, dAo);
                     const int o4 = vo * kG + 4 * q4;
                     if (shared) {
                         store_coherent(dA_rs, o4 + 0 * kO, dAi);
@@ -345,6 +372,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
             // the next step's first barrier orders these LDS writes before
             // its contractions
         }
+        leave_max();
         return;
     }
 
@@ -445,6 +473,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     dAg[i] = gcs * e.gi[i] * (1.0f - e.gg[i] * e.gg[i]);
                     dAo[i] = gh * tc * e.go[i] * (1.0f - e.go[i]);
                 }
+                top = top_finite(top, dAi, dAf, dAg, dAo);
                 const int o4 = vo * kG + 4 * q4;
                 float *dst = &dA_dn[o4];
                 if (shared) {
@@ -482,261 +511,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
             __hip_atomic_store(&a.flags[blockIdx.x], r + 1, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
     }
-}
-
-// ---- parameter gradients, register-streamed --------------------------------
-// dW[d] = sum over voxels v of dA[v] (x) [im2col(h_{t-1})(v), im2col(x_t)(v), 1],
-// an implicit GEMM with M = 64 gate-units, N = 144 + 9C + 1 and K = voxels.
-// One wave owns a contiguous range of units (16 voxels of a row: four MFMA
-// k-steps) of one direction, walking each column group down the rows of a
-// plane, and holds all 4 x ceil(N / 16) output tiles (in AGPRs; one wave per
-// SIMD).  Operands come straight from global memory into registers
-// (lane col takes a gate-unit (A) or an im2col column (B), so every load is
-// 64 contiguous bytes per voxel), the
-// next group's loads are in flight while the current group's MFMAs run,
-// and the accumulators stay in VGPRs for the whole launch: no LDS, no
-// barriers.  Zero padding (off-plane taps, h_{-1}) comes from the buffer
-// range check.
-constexpr int kWgWaves = 4;                    // one team (wave) per SIMD
-constexpr int kWgTeamsPerDir = 170;
-
-struct WgRowArgs {
-    Geom g;
-    const float *x, *hd, *dA;
-    float *partial;     // [6][tpd][64][KCp]
-    int tpd;            // teams per direction
-    int KCp;            // columns padded to 16
-};
-
-template <int C> struct WgN {
-    static constexpr int NT = (144 + 9 * C + 1 + 15) / 16;   // N-tiles
-};
-
-// Cursor of a team: batch element, sweep step, row, group of 16 columns.
-struct WgCursor {
-    int n, t, p, qg;
-};
-
-template <int C, int NT0, int NTC>
-__device__ inline void wg_rows_team(const WgRowArgs &a, int d, long long r0, long long r1, int q,
-                                    int col, float *out)
-{
-    const DirGeom dg = a.g.dir[d];
-    const long long V = a.g.V;
-    const int ss = (int)dg.ss, sp = (int)dg.sp, sq = (int)dg.sq;
-    const int ngrp = (dg.Q + 15) >> 4;
-    // per-lane constants of the input-tap columns (tiles 9, 10, ...)
-    int xtap_dp[NTC], xtap_dq[NTC], xtap_c[NTC], xkind[NTC];   // kind 0: x, 1: one, 2: zero
-#pragma unroll
-    for (int j = 0; j < NTC; ++j) {
-        const int nt = NT0 + j;
-        const int kk = (nt - 9) * 16 + col;
-        const int tap = kk < 9 * C && kk >= 0 ? kk / C : 4;
-        xtap_dp[j] = tap / 3 - 1;
-        xtap_dq[j] = tap % 3 - 1;
-        xtap_c[j] = kk >= 0 && kk < 9 * C ? kk % C : 0;
-        xkind[j] = kk < 9 * C ? 0 : (kk == 9 * C ? 1 : 2);
-    }
-    f4 acc[4][NTC];
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int j = 0; j < NTC; ++j) acc[g][j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-
-    // Operands of one group of 16 voxels.  K order inside the group: lane
-    // group q takes voxels 4q .. 4q+3 (k-step ks: voxel 4q + ks), so the
-    // three column taps of an h_{t-1} row read a sliding window of six
-    // loads per lane: tap (r, dq) at k-step ks is hv[r][ks + dq].
-    constexpr int NX = NT0 + NTC > 9 ? NT0 + NTC - (NT0 > 9 ? NT0 : 9) : 0;   // input tiles
-    constexpr int JX = NT0 > 9 ? 0 : 9 - NT0;                                  // first input j
-    struct Ops {
-        float a[4][4];                 // [k-step][gate]: dA
-        float hv[3][6];                // [row p-1, p, p+1][column 4q-1 .. 4q+4]: h_{t-1}
-        float bx[4][NX > 0 ? NX : 1];  // [k-step][input tile]: x_t
-    };
-    constexpr bool kRow[3] = {NT0 < 3, NT0 < 6 && NT0 + NTC > 3, NT0 + NTC > 6};
-    // Row-uniform state of the group being loaded: buffer resources of the
-    // slice, planes, row validity.  An invalid lane (off the plane, past the
-    // row, h_{-1}) gets an out-of-range offset and the hardware returns 0,
-    // so no mask touches a loaded value before its MFMA.
-    constexpr int kOOB = 0x7ffffff0;
-    struct Row {
-        __amdgpu_buffer_rsrc_t rs_a, rs_h, rs_x;
-        int s, p, colbase;
-        bool live, hok[3];
-    };
-    auto row_of = [&](const WgCursor &cu, bool live) {
-        Row w;
-        const long long dn = ((long long)d * a.g.N + cu.n) * V;
-        // slice resources (byte sizes fit 31 bits: checked on the host)
-        w.rs_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.dA + dn * kG), (short)0,
-                                                   (int)(V * kG * 4), kBufferRsrcWord3);
-        w.rs_h = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.hd + dn * kO), (short)0,
-                                                   (int)(V * kO * 4), kBufferRsrcWord3);
-        w.rs_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.x + (long long)cu.n * V * C),
-                                                   (short)0, (int)(V * C * 4), kBufferRsrcWord3);
-        w.s = dg.sign > 0 ? cu.t : dg.T - 1 - cu.t;
-        w.p = cu.p;
-        w.colbase = cu.qg * 16 + 4 * q;
-        w.live = live;
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-            w.hok[r] = live & (cu.t > 0) & ((unsigned)(cu.p + r - 1) < (unsigned)dg.P);
-        return w;
-    };
-    // bounds as non-short-circuit unsigned compares: no branches
-    auto load_a = [&](const Row &w, int ks, Ops &o) {
-        const int qq = w.colbase + ks;
-        const bool vq = w.live & ((unsigned)qq < (unsigned)dg.Q);
-        const int off = (w.s * ss + w.p * sp + qq * sq) * kG + col;
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-            o.a[ks][g] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                w.rs_a, vq ? (off + g * 16) * 4 : kOOB, 0, 0));
-    };
-    auto load_h = [&](const Row &w, int m, Ops &o) {
-        const int c = w.colbase - 1 + m;
-        const bool okc = (unsigned)c < (unsigned)dg.Q;
-        const int sprev = w.s - dg.sign;
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            if (!kRow[r]) continue;
-            const int off = (sprev * ss + (w.p + r - 1) * sp + c * sq) * kO + col;
-            o.hv[r][m] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                w.rs_h, (w.hok[r] & okc) ? off * 4 : kOOB, 0, 0));
-        }
-    };
-    auto load_x = [&](const Row &w, int ks, Ops &o) {
-#pragma unroll
-        for (int jx = 0; jx < NX; ++jx) {
-            const int j = JX + jx;
-            const int pp = w.p + xtap_dp[j], c = w.colbase + ks + xtap_dq[j];
-            const bool ok = w.live & (xkind[j] == 0) & ((unsigned)pp < (unsigned)dg.P) &
-                            ((unsigned)c < (unsigned)dg.Q);
-            const int off = (w.s * ss + pp * sp + c * sq) * C + xtap_c[j];
-            o.bx[ks][jx] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                w.rs_x, ok ? off * 4 : kOOB, 0, 0));
-        }
-    };
-    // ones of the bias column (1 for a voxel on the plane, else 0: its dA
-    // is 0 then anyway)
-    float bias_one[NTC];
-#pragma unroll
-    for (int j = 0; j < NTC; ++j) bias_one[j] = (NT0 + j >= 9 && xkind[j] == 1) ? 1.0f : 0.0f;
-    auto mfma_k = [&](const Ops &o, int ks) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int j = 0; j < NTC; ++j) {
-                const int nt = NT0 + j;
-                const float b = nt < 9 ? o.hv[nt / 3][ks + nt % 3] : o.bx[ks][j - JX] + bias_one[j];
-                acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.a[ks][g], b, acc[g][j], 0, 0, 0);
-            }
-    };
-    // Cursor over units u = ((n T + t) ngrp + qg) P + p: a column group
-    // walks down the rows, so the h_{t-1} and x rows of one group are
-    // re-read (as p + 1, p, p - 1) by the next two groups from cache.  Past
-    // the end it stays on a valid unit and the loads are masked to zero.
-    WgCursor cu;
-    {
-        long long rest = r0;
-        cu.p = (int)(rest % dg.P);
-        rest /= dg.P;
-        cu.qg = (int)(rest % ngrp);
-        rest /= ngrp;
-        cu.t = (int)(rest % dg.T);
-        cu.n = (int)(rest / dg.T);
-    }
-    auto advance = [&]() {
-        if (++cu.p == dg.P) {
-            cu.p = 0;
-            if (++cu.qg == ngrp) {
-                cu.qg = 0;
-                if (++cu.t == dg.T) {
-                    cu.t = 0;
-                    if (cu.n + 1 < a.g.N) ++cu.n;
-                }
-            }
-        }
-    };
-    const long long total = r1 - r0;
-    Ops o;
-    {
-        const Row w = row_of(cu, total > 0);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            load_a(w, ks, o);
-            load_x(w, ks, o);
-        }
-#pragma unroll
-        for (int m = 0; m < 6; ++m) load_h(w, m, o);
-    }
-    // Each operand register is refilled with the next group's value right
-    // after its last use by this group's MFMAs: one group of operands is
-    // live, and every load has a whole group of MFMAs to arrive.
-    for (long long it = 0; it < total; ++it) {
-        advance();
-        const Row w = row_of(cu, it + 1 < total);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            mfma_k(o, ks);
-            load_a(w, ks, o);
-            load_x(w, ks, o);
-            load_h(w, ks, o);          // hv[.][ks] was last used at k-step ks
-            if (ks == 3) {
-                load_h(w, 4, o);
-                load_h(w, 5, o);
-            }
-        }
-    }
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int j = 0; j < NTC; ++j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                out[(g * 16 + 4 * q + i) * a.KCp + (NT0 + j) * 16 + col] = acc[g][j][i];
-}
-
-template <int C>
-__global__ void __launch_bounds__(64 * kWgWaves) __attribute__((amdgpu_waves_per_eu(1)))
-k_wgrad_rows(WgRowArgs a)
-{
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int q = lane >> 4, col = lane & 15;
-    const int team = blockIdx.x * kWgWaves + wave;
-    if (team >= kDirs * a.tpd) return;
-    const int d = team / a.tpd, tin = team % a.tpd;
-    const DirGeom dg = a.g.dir[d];
-    const long long units = (long long)a.g.N * dg.T * ((dg.Q + 15) / 16) * dg.P;
-    const long long r0 = units * tin / a.tpd, r1 = units * (tin + 1) / a.tpd;
-    float *out = a.partial + (long long)team * kG * a.KCp;
-    wg_rows_team<C, 0, WgN<C>::NT>(a, d, r0, r1, q, col, out);
-}
-
-// dW = sum of the per-workgroup partials in workgroup order.
-__global__ void __launch_bounds__(256)
-k_wgrad_reduce(int C, int bpd, int KCp, const float *__restrict__ partial,
-               float *__restrict__ dwx, float *__restrict__ dwh, float *__restrict__ db)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    const int KC = 144 + 9 * C + 1;
-    if (i >= kDirs * kG * KC) return;
-    const int k = i % KC;
-    const int gn = (i / KC) % kG;
-    const int d = i / (KC * kG);
-    float acc = 0.0f;
-    for (int b = 0; b < bpd; ++b) acc += partial[(((long long)d * bpd + b) * kG + gn) * KCp + k];
-    if (k < 144) {
-        const int tap = k / 16, j = k % 16;
-        dwh[(((long long)d * kG + gn) * kO + j) * 9 + tap] = acc;
-    } else if (k < 144 + 9 * C) {
-        const int kk = k - 144, tap = kk / C, c = kk % C;
-        dwx[(((long long)d * kG + gn) * C + c) * 9 + tap] = acc;
-    } else {
-        db[d * kG + gn] = acc;
-    }
+    leave_max();
 }
 
 __global__ void k_fill_zero(int *p, int n)
@@ -764,33 +539,13 @@ StripCostModel bwd_model(bool allow_resident)
     return m;
 }
 
-inline int wgrad_kcp(int C) { return (144 + 9 * C + 1 + 15) / 16 * 16; }
-constexpr int kWgradBlocksPerDir = 42;
-
-template <int C>
-int launch_wgrad(const Geom &g, const float *x, const float *hd, const float *dA, float *partial,
-                 hipStream_t st)
-{
-    WgRowArgs wa;
-    wa.g = g;
-    wa.x = x; wa.hd = hd; wa.dA = dA;
-    wa.partial = partial;
-    wa.tpd = kWgTeamsPerDir;
-    wa.KCp = wgrad_kcp(C);
-    const int teams = kDirs * kWgTeamsPerDir;
-    const int per_block = kWgWaves;
-    k_wgrad_rows<C><<<(teams + per_block - 1) / per_block, 64 * kWgWaves, 0, st>>>(wa);
-    PLSTM_LAUNCH_CHECK();
-    return PLSTM_OK;
-}
-
 }  // namespace
 
 bool sweep_bwd_supported(const Geom &g)
 {
     // dA slices are addressed as buffer resources: bytes must fit 32 bits
-    return g.nd == kDirs && g.KP == 3 && g.KQ == 3 && g.O == kO && g.C >= 1 && g.C <= 4 &&
-           g.V * kG * (long long)sizeof(float) < (1LL << 31);
+    return step_supported(g) && g.nd == kDirs && g.KP == 3 && g.KQ == 3 && g.O == kO && g.C >= 1 &&
+           g.C <= 4 && g.V * kG * (long long)sizeof(float) < (1LL << 31);
 }
 
 size_t sweep_bwd_ws(const Geom &g)
@@ -799,8 +554,9 @@ size_t sweep_bwd_ws(const Geom &g)
     cv.take<float>((size_t)kDirs * g.N * g.V * kG);                     // dA
     cv.take<float>((size_t)kDirs * g.N * g.V * kO);                     // dL/dc * f
     cv.take<int>(1024 + 1);                                              // flags + err
-    cv.take<float>((size_t)kDirs * kWgTeamsPerDir * kG * wgrad_kcp(g.C));   // partials
-    if (step_supported(g)) cv.take<char>(step_dx_ws(g));                     // dL/dx fragments
+    cv.take<unsigned>(1024 * kWaves);                                    // maxima of |dA|
+    cv.take<char>(step_wgrad_ws(g));                                     // weight gradients
+    cv.take<char>(step_dx_ws(g));                                        // dL/dx fragments
     return cv.off;
 }
 
@@ -825,8 +581,9 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
     float *dA = cv.take<float>((size_t)kDirs * g.N * g.V * kG);
     float *gcf = cv.take<float>((size_t)kDirs * g.N * g.V * kO);
     int *flags = cv.take<int>(1024 + 1);
-    float *partial = cv.take<float>((size_t)kDirs * kWgTeamsPerDir * kG * wgrad_kcp(g.C));
-    float *fragx = step_supported(g) ? (float *)cv.take<char>(step_dx_ws(g)) : nullptr;
+    unsigned *amax = cv.take<unsigned>(1024 * kWaves);
+    void *wgws = cv.take<char>(step_wgrad_ws(g));
+    float *fragx = (float *)cv.take<char>(step_dx_ws(g));
 
     BwdArgs args;
     args.g = g;
@@ -834,6 +591,7 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
     args.gates = sv.gates; args.cell = sv.cell;
     args.dh = dh;
     args.dA = dA; args.gcf = gcf;
+    args.amax = amax;
     args.flags = flags; args.err = flags + 1024;
     args.max_spin = g_wait_spin_limit;
     args.wait_bias = g_wait_bias;
@@ -861,22 +619,13 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
         return PLSTM_EHIP;
     timing_end(1, st);
 
-    timing_begin("wgrad_mfma", st);
-    int rc;
-    switch (g.C) {
-    case 1: rc = launch_wgrad<1>(g, x, sv.hd, dA, partial, st); break;
-    case 2: rc = launch_wgrad<2>(g, x, sv.hd, dA, partial, st); break;
-    case 3: rc = launch_wgrad<3>(g, x, sv.hd, dA, partial, st); break;
-    default: rc = launch_wgrad<4>(g, x, sv.hd, dA, partial, st); break;
-    }
+    long long aoff[kDirs + 1];
+    for (int d = 0; d < kDirs; ++d) aoff[d] = (long long)pl.first[d] * kWaves;
+    aoff[kDirs] = (long long)pl.blocks * kWaves;
+    int rc = step_wgrad(g, x, sv.hd, dA, amax, aoff, wgws, dwx, dwh, db, "wgrad_mfma", st);
     if (rc != PLSTM_OK) return rc;
-    const int nout = kDirs * kG * (144 + 9 * g.C + 1);
-    k_wgrad_reduce<<<(nout + 255) / 256, 256, 0, st>>>(g.C, kWgTeamsPerDir, wgrad_kcp(g.C),
-                                                       partial, dwx, dwh, db);
-    PLSTM_LAUNCH_CHECK();
-    timing_end(2, st);
     if (dx) {
-        rc = fragx ? step_dx(g, wx, dA, fragx, dx, st) : generic_dx(g, wx, dA, dx, st);
+        rc = step_dx(g, wx, dA, fragx, dx, st);
         if (rc != PLSTM_OK) return rc;
     }
     PoisonList poison;

@@ -1717,6 +1717,8 @@ struct LineBwdArgs {
     float *dxd;                 // [4][N][V][C] per-direction dL/dx, or null
     float *dbp;                 // [4][N][nsegmax][4O] bias-gradient partials, or null
     int nsegmax;                // segments of the longest line
+    unsigned *amax;             // largest finite |dA| (bits) of each wave of a segment over
+    int aoff[kDirs];            // the launches so far, [N][nseg][4] at aoff
     int nseg[kDirs];
     int base[kDirs + 1];
 };
@@ -1838,6 +1840,7 @@ k_line_bwd(LineBwdArgs a)
         }
     };
     int s_dx = -1;                              // line whose partials wait in dxr
+    float top = 0.0f;                           // largest finite |dA| of this lane
     for (int j = 0; j < nlines; ++j) {
         const int t = T - 1 - (r0 + j);
         const int s = dg.sign > 0 ? t : T - 1 - t;
@@ -1901,6 +1904,13 @@ k_line_bwd(LineBwdArgs a)
             if (on && qq >= q0 && qq < q0 + kLineSeg) {
 #pragma unroll
                 for (int g = 0; g < 4; ++g) dbacc[g] += dv[k][g];
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const float m = fabsf(dv[k][g][u]);
+                        top = m < __builtin_inff() ? fmaxf(top, m) : top;
+                    }
                 const long long vo = sbase + vox;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) *(f4 *)(a.dA + vo * G + g * O + 4 * q4) = dv[k][g];
@@ -1936,6 +1946,13 @@ k_line_bwd(LineBwdArgs a)
     if (want_dx && s_dx >= 0) {
         __syncthreads();
         store_dx(s_dx);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+    if (lane == 0) {
+        unsigned *e = a.amax + a.aoff[d] + (n * a.nseg[d] + seg) * 4 + wave;
+        const unsigned m = __float_as_uint(top);
+        *e = r0 == 0 || m > *e ? m : *e;
     }
     if (a.dbp) {
         // over the 16 lanes of a unit group (pixels), then the four waves
@@ -3283,7 +3300,10 @@ size_t step_bwd_ws(const Geom &g)
     cv.take<char>(step_wgrad_ws(g));                                // weight gradients
     cv.take<float>((size_t)g.nd * KK * 4 * U * (Cp / 16) * 256);   // W_x^T fragments
     if (line_bwd_dx(g)) cv.take<float>((size_t)g.nd * g.N * g.V * g.C);   // dL/dx per direction
-    if (line_bwd_geom(g)) cv.take<float>((size_t)g.nd * g.N * line_nsegmax(g) * 64);  // db partials
+    if (line_bwd_geom(g)) {
+        cv.take<float>((size_t)g.nd * g.N * line_nsegmax(g) * 64);        // db partials
+        cv.take<unsigned>((size_t)g.nd * g.N * line_nsegmax(g) * 4);      // maxima of |dA|
+    }
     Carve sp(nullptr);                                             // split reverse steps
     sp.off = split_bwd_ws(g);
     sp.take<char>(step_wgrad_ws(g));
@@ -3342,7 +3362,9 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
     float *dxd = line_bwd_dx(g) ? cv.take<float>((size_t)g.nd * g.N * g.V * g.C) : nullptr;
     float *dbl = line_bwd_geom(g) ? cv.take<float>((size_t)g.nd * g.N * line_nsegmax(g) * 64)
                                   : nullptr;
-    const unsigned *amax = nullptr;      // maxima of |dA| (split steps)
+    unsigned *aml = line_bwd_geom(g) ? cv.take<unsigned>((size_t)g.nd * g.N * line_nsegmax(g) * 4)
+                                     : nullptr;
+    const unsigned *amax = nullptr;      // maxima of |dA| (split steps, line blocks)
     long long aoff[kDirs + 1] = {};
     bool db_done = false;
     const long long nvox = (long long)g.N * g.V;
@@ -3397,6 +3419,12 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         la.dbp = dbl;
         la.nsegmax = line_nsegmax(g);
         for (int d = 0; d < kDirs; ++d) la.nseg[d] = (g.dir[d].Q + kLineSeg - 1) / kLineSeg;
+        la.amax = aml;
+        for (int d = 0; d < kDirs; ++d) {
+            la.aoff[d] = (int)aoff[d];
+            aoff[d + 1] = aoff[d] + (d < g.nd ? (long long)g.N * la.nseg[d] * 4 : 0);
+        }
+        amax = aml;
         const size_t dyn = line_dyn;
         if (hipFuncSetAttribute((const void *)k_line_bwd, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)dyn) != hipSuccess)

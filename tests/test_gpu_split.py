@@ -8,9 +8,11 @@ import pytest
 import torch
 
 import oracle
+import oracle.layer2d as o2d
 import paper_1506_07452_amd as P
 import synth
-from paper_1506_07452_amd.network import layer_backward, layer_forward
+from paper_1506_07452_amd.network import (LayerW, layer2d_backward, layer2d_forward, layer_backward,
+                                          layer_forward)
 from tests.gpu_util import dev, host, layer_dev, saved_view, say
 
 pytestmark = pytest.mark.gpu
@@ -146,3 +148,61 @@ def test_persistent_forward(shape, outlier, strips):
     h, _ = layer_forward(dev(inst.x), layer_dev(L))
     torch.cuda.synchronize()
     assert close(host(h), ref)
+
+
+def check_weights(ref, dwx, dwh, db, channels=None):
+    for name, got in (("dwx", dwx), ("dwh", dwh), ("db", db)):
+        got, want = host(got), ref[name]
+        if name == "dwx" and channels is not None:
+            got, want = got[:, :, channels], want[:, :, channels]
+        assert np.abs(got - want).max() <= TOL * np.abs(want).max(), name
+
+
+@pytest.mark.parametrize("outlier", [None, 1e12], ids=str)
+@pytest.mark.parametrize("path", [0, 2], ids=["whole", "chunked"])
+@pytest.mark.parametrize("shape", [(1, 5, 9, 11, 3, 16, 3), (2, 7, 3, 40, 1, 16, 3), (1, 1, 1, 2, 4, 16, 3),
+                                   (1, 17, 40, 21, 2, 16, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_persistent_weight_gradients(shape, path, outlier):
+    """The reverse sweep's own maxima of |dA| scale the products (dL/dh varies by
+    2^60 between planes); an input that one scale does not serve keeps fp32."""
+    inst = make(shape, 9700 + sum(shape))
+    L = inst.layers[0]
+    if outlier is not None:
+        inst.x[-1, -1, -1, -1, 0] = outlier
+    dh = synth.upstream_grad(inst.x.shape[:-1] + (16,), 9800 + sum(shape))
+    if outlier is None:
+        rng = np.random.default_rng(6)
+        dh *= np.exp2(rng.integers(-30, 31, size=dh.shape[:2] + (1, 1, 1))).astype(np.float32)
+    ref = oracle.backward(inst.x, L.wx, L.wh, L.b, dh)
+    say("split sweep gradients", shape, path, outlier)
+    x, Ld = dev(inst.x), layer_dev(L)
+    P.pyramid_lstm_set_backward_path(path)
+    _, saved = layer_forward(x, Ld, training=True)
+    _, dwx, dwh, db = layer_backward(x, Ld, saved, dev(dh), want_dx=False)
+    torch.cuda.synchronize()
+    P.pyramid_lstm_set_backward_path(0)
+    check_weights(ref, dwx, dwh, db)
+    if outlier is not None and shape[4] > 1:
+        check_weights(ref, dwx, dwh, db, list(range(1, shape[4])))
+
+
+@pytest.mark.parametrize("outlier", [None, 1e12], ids=str)
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1, 1), (2, 33, 40, 1, 3), (1, 9, 129, 4, 5), (3, 70, 6, 17, 7),
+                                   (1, 40, 64, 3, 1)], ids=lambda s: "x".join(map(str, s)))
+def test_line_weight_gradients(shape, outlier):
+    """Lines of one block and several, and those of the reverse line blocks'
+    segments over more than one launch."""
+    N, H, W, C, K = shape
+    x, wx, wh, b = synth.image2d(N, H, W, C, 16, K, 9900 + sum(shape), "f32")
+    if outlier is not None:
+        x[-1, -1, -1, 0] = outlier
+    dh = synth.upstream_grad((N, H, W, 16), 9950 + sum(shape))
+    ref = o2d.backward2d(x, wx, wh, b, dh)
+    say("split line gradients", shape, outlier)
+    xd, L = dev(x), LayerW(dev(wx), dev(wh), dev(b))
+    _, saved = layer2d_forward(xd, L, training=True)
+    _, dwx, dwh, db = layer2d_backward(xd, L, saved, dev(dh), want_dx=False)
+    torch.cuda.synchronize()
+    check_weights(ref, dwx, dwh, db)
+    if outlier is not None and C > 1:
+        check_weights(ref, dwx, dwh, db, list(range(1, C)))
