@@ -8,12 +8,16 @@
 //       gc   = gh o (1 - tanh^2 c_t) + gc_{t+1} f_{t+1}
 //       dA_o = gh tanh(c_t) o (1 - o)     dA_i = gc g i (1 - i)
 //       dA_g = gc i (1 - g^2)             dA_f = gc c_{t-1} f (1 - f)
-//     The transposed 3x3 convolution is an MFMA contraction of K = 9 x 64
-//     (tap, gate-unit) with units on M and pixels on N: lane l takes pixel
-//     l%16 and gate l/16 (16 units = 4 LDS reads of 16 bytes per tap) for the
-//     B operand, the transposed recurrent weights are the A operand, resident
-//     in LDS, and each lane ends with four consecutive units of one
-//     pixel, so every epilogue load and store is a 16-byte vector.  The
+//     The transposed 3x3 convolution is a contraction of K = 9 x 64
+//     (tap, gate-unit) on split operands (split.h) with units on M and pixels
+//     on N: a tap is two K-groups of 32, lane l takes pixel l%16 and eight
+//     gate-units (hi and lo, two LDS reads of 16 bytes) for the B operand, the
+//     transposed recurrent weights are the A operand, resident in LDS, and each
+//     lane ends with four consecutive units of one pixel, so every epilogue
+//     load and store is a 16-byte vector.  dA_{t+1} has one scale per strip and
+//     step, from its own largest |dA| and those its neighbours publish with
+//     their flags.  Its sign alternates from step to step and strip to strip,
+//     so that the instruction's rounding towards -inf cancels in db.  The
 //     product gc_t f_t is what plane t - 1 needs, so that is what is kept.
 //     dA of every voxel is kept for (2) and for dL/dx, and each wave leaves the
 //     largest finite |dA| it stored, from which (2) scales its split operands.
@@ -21,6 +25,7 @@
 //     plane-step path's kernels (split_wgrad.hip).
 #include "common.h"
 #include "coherent.h"
+#include "split.h"
 #include "strip_plan.h"
 #include "sweep.h"
 #include "timing.h"
@@ -33,11 +38,13 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr int kO = 16;
 constexpr int kG = 4 * kO;
 constexpr int kWaves = 16;             // four waves per SIMD
-constexpr int kWaFloats = 9 * 4 * 64 * 4;  // W_h^T fragments in LDS
+constexpr int kKG = 18;                    // K-groups: 9 taps x 2 halves of 64 gate-units
+constexpr int kWaFloats = kKG * 2 * 64 * 4 + 32;   // W_h^T fragments in LDS; 1 / row scales, 16 words of state
 constexpr int kThreads = 64 * kWaves;
-// A staged dA pixel is 64 floats in LDS; its 16-byte chunk c sits at
-// position c ^ (pixel & 15), so the 16 pixels a read instruction touches
-// hit 16 different bank groups.
+// A staged dA pixel is 256 bytes in LDS, eight gate-units after eight: their hi
+// halves (16 bytes) and their lo halves.  Its 16-byte chunk c sits at position
+// c ^ (pixel & 15), so the 16 pixels a read instruction touches hit 16 different
+// bank groups.
 __device__ inline int swz(int c, int pix) { return c ^ (pix & 15); }
 constexpr int kOutOfRange = 0x7ffffff0;    // buffer offset past any resource: reads zero
 typedef __attribute__((address_space(3))) void lds_void;
@@ -57,7 +64,9 @@ struct BwdArgs {
     float *dA;                   // [6][N][V][64] gate pre-activation gradients
     float *gcf;                  // [6][N][V][16] dL/dc_t * f_t, carried to plane t - 1
     unsigned *amax;              // [blocks][kWaves] largest finite |dA| (bits)
-    int *flags, *err;
+    // [blocks] steps done << 32 | (exponent of the plane before the last) << 8 | of the last
+    unsigned long long *flags;
+    int *err;
     int max_spin;                // polls before a wait gives up
     int wait_bias;               // added to the awaited step (0; failure-path test mode only)
     int nstrip[kDirs], first[kDirs], chunk_rows[kDirs], max_w[kDirs];
@@ -87,43 +96,51 @@ struct BwdEpi {
     f4 dh, gi, gf, gg, go, c, gcfn, cp;
 };
 
-// sum over taps of dA_{t+1}[p - tap] W_h^T for one 16-pixel tile, on the
-// MFMA: `base` is the lane's LDS pixel, whose row and column neighbours are
-// `rs` and `cs` LDS pixels apart.  The K loop runs in quarters of a tap
-// (quarter j = 4 tap + s: gate-units 16 q4 + 4 s .. + 3 of the lane's pixel
-// as B, the matching W_h^T fragment as A, four MFMAs); each quarter's two LDS
-// reads are issued three quarters (twelve MFMAs) before their use, in a
-// ring of four register slots, so a wave alone keeps the matrix unit busy.
-__device__ __forceinline__ void contract_bwd(const float *as, const float *was, int base, int rs,
-                                             int cs, int q4, int lane, f4 (&acc)[4])
+// sum over taps of dA_{t+1}[p - tap] W_h^T for one 16-pixel tile, times the scales:
+// `base` is the lane's LDS pixel, whose row and column neighbours are `rs` and
+// `cs` LDS pixels apart.  K-group 2 tap + half: gate-units 32 half + 8 q4 .. + 7 of
+// the lane's pixel as B, read one K-group ahead, the matching W_h^T fragment as A
+// (read ahead too, the resident strips' 128 registers would not do); the four
+// waves of a SIMD hide the rest.
+__device__ __forceinline__ f4 contract_bwd(const float *as, const float *was, int base, int rs,
+                                           int cs, int q4, int lane)
 {
-    constexpr int kQuarters = 36;
-    constexpr int kAhead = 2;
-    f4 bq[kAhead + 1], aq[kAhead + 1];
-    auto load = [&](int j) {
-        const int tap = j >> 2, sq = j & 3;
+    h8 b[2][2];
+    auto load = [&](int kg) {
+        const int tap = kg >> 1, half = kg & 1, k = kg & 1;
         // h_t at pixel p fed A_{t+1} at p - (tap offset)
         const int pp = base - ((tap / 3 - 1) * rs + (tap % 3 - 1) * cs);
-        bq[j % (kAhead + 1)] = *(const f4 *)&as[pp * kG + 4 * swz(4 * q4 + sq, pp)];
-        aq[j % (kAhead + 1)] = *(const f4 *)&was[((tap * 4 + sq) * 64 + lane) * 4];
+        // (chunks 8 half + 2 q4 and the next: bits 3 and 0 of the position)
+        const int o = (pp * kG + 4 * swz(2 * q4, pp)) ^ (half * 32);
+        b[k][0] = *(const h8 *)&as[o];
+        b[k][1] = *(const h8 *)&as[o ^ 4];
     };
+    f4 acc = {0.0f, 0.0f, 0.0f, 0.0f}, x0 = acc, x1 = acc;
+    load(0);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) acc[k] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int j = 0; j < kAhead; ++j) load(j);
-#pragma unroll
-    for (int j = 0; j < kQuarters; ++j) {
-        if (j + kAhead < kQuarters) load(j + kAhead);
-        // keep the reads ahead of this quarter's MFMAs
+    for (int kg = 0; kg < kKG; ++kg) {
+        const h8 wl = *(const h8 *)&was[((kg * 2 + 1) * 64 + lane) * 4];
+        const h8 wh = *(const h8 *)&was[((kg * 2 + 0) * 64 + lane) * 4];
+        if (kg + 1 < kKG) load(kg + 1);
+        // keep the reads ahead of this K-group's products
         __builtin_amdgcn_sched_barrier(0);
-        const int sl = j % (kAhead + 1);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[sl][i], bq[sl][i], acc[i], 0, 0, 0);
+        const int k = kg & 1;
+        x0 = mfma_h(wl, b[k][0], x0);
+        acc = mfma_h(wh, b[k][0], acc);
+        x1 = mfma_h(wh, b[k][1], x1);
         __builtin_amdgcn_sched_barrier(0);
     }
+    return acc + (x0 + x1);
 }
 
+// Scale exponent of a plane whose largest |dA| has the biased exponent `e` (not more
+// than 2^110: denormals, or all zero).
+__device__ inline int plane_exp(int e) { return min(14 - (e - 127), 110); }
+
+// One launch, against the contraction on v_mfma_f32_16x16x4 (144 instructions of 32
+// cycles a tile; now 54 of 16): 48 x 240 x 240 3.75 -> 3.05 ms, which is 15.6 GB of
+// activations and dA at 5.1 TB/s; 2 x 8 x 64 x 64 x 1, forward and backward, 0.836 ->
+// 0.798 ms (bound by the hand-over between strips).
 __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
 {
     extern __shared__ float smem[];
@@ -144,22 +161,86 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int q4 = lane >> 4, col = lane & 15;
     const int chunk_rows = a.chunk_rows[d];
-    // A fragments of W_h^T in LDS (registers stay free for four waves per
-    // SIMD): entry (tap, s4, lane) holds, for lane l, the gate-units
-    // 16 (l/16) + 4 s4 .. + 3 of output unit l%16; the tap's K index
-    // k = (s, q4) -> gate-unit 16 q4 + s.  The first staging barrier orders
-    // these stores before their reads.
+    // A fragments of W_h^T in LDS (registers stay free for four waves per SIMD):
+    // entry (K-group, hi or lo, lane) holds, for lane l, gate-units
+    // 32 half + 8 (l/16) .. + 7 of output unit l%16, times the unit's scale.
+    // Then 1 / the scales, and the state of the step:
     float *was = smem;
+    float *winv = was + kKG * 2 * 64 * 4;
+    unsigned *state = (unsigned *)(winv + 16);
+    unsigned *mx = state, *emx = state + 2;  // by step parity: largest |dA| (bits) of the strip, of its edge tiles
+    unsigned *nbe = state + 4;               // exponents of the neighbours' planes
     float *as = smem + kWaFloats;
-    for (int e = threadIdx.x; e < 9 * 4 * 64; e += kThreads) {
-        const int l = e & 63, s4 = (e >> 6) & 3, tap = e >> 8;
-        const int lq = l >> 4, lc = l & 15;
-        f4 v;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            v[j] = a.wh[(((long long)d * kG + 16 * lq + 4 * s4 + j) * kO + lc) * 9 + tap];
-        *(f4 *)&was[e * 4] = v;
+    unsigned *wmx = (unsigned *)as;          // the weights' largest magnitudes, only here
+    if (threadIdx.x < 16) wmx[threadIdx.x] = state[threadIdx.x] = 0u;
+    __syncthreads();
+    for (int e = threadIdx.x; e < kG * kO * 9; e += kThreads) {
+        const unsigned m = __float_as_uint(a.wh[(long long)d * kG * kO * 9 + e]) & 0x7fffffffu;
+        if (m < 0x7f800000u) atomicMax(&wmx[e / 9 % kO], m);
     }
+    __syncthreads();
+    if (threadIdx.x < 16) winv[threadIdx.x] = exp2i(-scale_exp(wmx[threadIdx.x]));
+    for (int e = threadIdx.x; e < kKG * 64; e += kThreads) {
+        const int l = e & 63, kg = e >> 6;
+        const int lq = l >> 4, lc = l & 15, tap = kg >> 1;
+        const float sc = exp2i(scale_exp(wmx[lc]));
+        f4 v[2];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            v[j >> 2][j & 3] =
+                a.wh[(((long long)d * kG + 32 * (kg & 1) + 8 * lq + j) * kO + lc) * 9 + tap] * sc;
+        const Split8 sp = split8(v[0], v[1]);
+        *(h8 *)&was[((kg * 2 + 0) * 64 + l) * 4] = sp.hi;
+        *(h8 *)&was[((kg * 2 + 1) * 64 + l) * 4] = sp.lo;
+    }
+    __syncthreads();                         // (wmx's words are staged over next)
+    // Waits (bounded) for the neighbours' step r and leaves the exponents of the
+    // planes they then finished; a neighbour may be one step further.
+    auto wait_neighbours = [&](int r) {
+        const int nb = threadIdx.x == 0 ? nb_lo : (threadIdx.x == 1 ? nb_hi : -1);
+        if (nb < 0) return;
+        int spins = 0;
+        unsigned long long w;
+        while ((int)((w = __hip_atomic_load(&a.flags[nb], __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT)) >> 32) < r + a.wait_bias) {
+            __builtin_amdgcn_s_sleep(1);
+            if (++spins > a.max_spin) {
+                __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+            if ((spins & 1023) == 0 &&
+                __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                break;
+        }
+        nbe[threadIdx.x] = ((int)(w >> 32) > r ? w >> 8 : w) & 255u;
+    };
+    // Publishes r + 1 steps with the exponents of this plane and the one before
+    // (`m`: the maxima by step parity).
+    auto publish = [&](int r, const unsigned *m) {
+        const unsigned cur = m[r & 1] >> 23, before = m[(r & 1) ^ 1] >> 23;
+        const unsigned long long w =
+            (unsigned long long)(r + 1) << 32 | before << 8 | cur;
+        __hip_atomic_store(&a.flags[blockIdx.x], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    // Exponent of dA_{t+1}'s scale at step r (all threads, after the wait's barrier).
+    auto step_exp = [&](int r) {
+        int e = (int)(mx[(r & 1) ^ 1] >> 23);
+        e = max(e, max((int)nbe[0], (int)nbe[1]));
+        return __builtin_amdgcn_readfirstlane(plane_exp(e));
+    };
+    auto step_sign = [&](int r) { return (strip + r) & 1 ? -1.0f : 1.0f; };
+    auto wave_max = [&](float v) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+        return __float_as_uint(v);
+    };
+    // fp32 slot `sl` of LDS pixel `pix`, split in place
+    auto split_slot = [&](int pix, int sl, float scale) {
+        float *p0 = &as[pix * kG + 4 * swz(2 * sl, pix)], *p1 = &as[pix * kG + 4 * swz(2 * sl + 1, pix)];
+        const Split8 sp = split8(*(const f4 *)p0 * scale, *(const f4 *)p1 * scale);
+        *(h8 *)p0 = sp.hi;
+        *(h8 *)p1 = sp.lo;
+    };
 
     const long long V = a.g.V;
     const long long dn = ((long long)d * a.g.N + n) * V;
@@ -186,17 +267,16 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
 
     float top = 0.0f;            // largest finite |dA| of this lane
     auto leave_max = [&]() {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
-        if (lane == 0) a.amax[blockIdx.x * kWaves + wave] = __float_as_uint(top);
+        const unsigned m = wave_max(top);
+        if (lane == 0) a.amax[blockIdx.x * kWaves + wave] = m;
     };
 
     if (a.resident[d]) {
         // ============ resident strip: dA of the whole strip stays in LDS ============
         // dA_t overwrites dA_{t+1} in place: each wave keeps its tiles' dA in
-        // registers until every wave's contraction has read dA_{t+1} (one
-        // barrier), then writes them.  Only the two halo columns come from
-        // the neighbours each step.  Pixels are numbered column by column
+        // registers until every wave's contraction has read dA_{t+1} and the
+        // neighbours' exponents are there (one barrier), then writes them split.
+        // Only the two halo columns come from the neighbours each step.  Pixels are numbered column by column
         // (LDS pixel (column + 1) (P + 2) + row + 1); the tiles touching a
         // column next to a neighbour strip run first and the step is
         // published as soon as they are stored.  At most two tiles per wave
@@ -229,8 +309,13 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
         // the next step's c_t, in registers: neither is loaded again and gc f
         // is never stored.
         f4 carry_gcf[2], carry_c[2];
+        f4 hold[2][4];               // dA_{t+1} of this lane's pixel
+        int hbase[2];
 #pragma unroll
-        for (int it = 0; it < 2; ++it) carry_gcf[it] = carry_c[it] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int it = 0; it < 2; ++it) {
+            carry_gcf[it] = carry_c[it] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            hbase[it] = -1;
+        }
         for (int r = 0; r < dg.T; ++r) {
             const int t = dg.T - 1 - r;
             const int s = dg.sign > 0 ? t : dg.T - 1 - t;
@@ -238,29 +323,39 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
             const int splane = s * ss;
             const int nplane = has_next ? (s + dg.sign) * ss : splane;
             const int pplane = has_prev ? (s - dg.sign) * ss : splane;
+            float inv = 0.0f;
             if (r > 0) {
-                // ---- the neighbours' edge columns of dA_{t+1} -> halo columns
-                const int nb = threadIdx.x == 0 ? nb_lo : (threadIdx.x == 1 ? nb_hi : -1);
-                if (nb >= 0) {
-                    int spins = 0;
-                    while (__hip_atomic_load(&a.flags[nb], __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT) < r + a.wait_bias) {
-                        __builtin_amdgcn_s_sleep(1);
-                        if (++spins > a.max_spin) {
-                            __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-                            break;
+                wait_neighbours(r);
+                __syncthreads();
+                const int ex = step_exp(r);
+                const float scale = step_sign(r) * exp2i(ex);
+                inv = step_sign(r) * exp2i(-ex);
+                // every contraction has read dA_{t+2}: overwrite it with dA_{t+1}
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    if (hbase[it] < 0) continue;
+                    const int pb = hbase[it];
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        h4 hi, lo;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float v = hold[it][g][i] * scale;
+                            hi[i] = (_Float16)v;
+                            lo[i] = (_Float16)(v - (float)hi[i]);
                         }
-                        if ((spins & 1023) == 0 &&
-                            __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                            break;
+                        // gate-units 16 g + 4 q4 .. + 3: half of slot 2 g + q4 / 2
+                        const int c = 2 * (2 * g + (q4 >> 1)), o = 2 * (q4 & 1);
+                        *(h4 *)&as[pb * kG + 4 * swz(c, pb) + o] = hi;
+                        *(h4 *)&as[pb * kG + 4 * swz(c + 1, pb) + o] = lo;
                     }
                 }
-                __syncthreads();
+                // ---- the neighbours' edge columns of dA_{t+1} -> halo columns
                 // One instruction moves four consecutive rows of a halo
                 // column (lane l: chunk position l%16 of row 4 j + l/16);
                 // lanes past the last row are inactive, so the halo rows
-                // above and below the plane keep their zeros.
+                // above and below the plane keep their zeros.  The wave then
+                // splits what it moved.
                 const int nslot = (P + 3) >> 2;
                 for (int i = wave; i < 2 * nslot; i += kWaves) {
                     const int side = i >= nslot ? 1 : 0;
@@ -279,10 +374,19 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                                                                  kCachePolicySC1);
                 }
                 __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+                asm volatile("" ::: "memory");
+                for (int i = wave; i < 2 * nslot; i += kWaves) {
+                    const int side = i >= nslot ? 1 : 0;
+                    const int row = 4 * (i - side * nslot) + (lane >> 3);
+                    if ((side ? nb_hi : nb_lo) < 0 || lane >= 32 || row >= P) continue;
+                    split_slot((side ? TQ + 1 : 0) * P2 + 1 + row, lane & 7, scale);
+                }
+                if (threadIdx.x == 0) {
+                    cnt[0] = 0;
+                    mx[r & 1] = emx[r & 1] = 0u;
+                }
                 __syncthreads();
             }
-            f4 hold[2][4];
-            int hbase[2];
 #pragma unroll
             for (int it = 0; it < 2; ++it) {
                 const int k = wave + it * kWaves;
@@ -291,7 +395,10 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     const int mt = order[k];
                     const int pa = min(mt * 16 + col, npx - 1);
                     const int ca = fdiv_floor(pa, inv_p), ra = pa - ca * P;
-                    const int base = (ca + 1) * P2 + ra + 1;
+                    // (hidden from the compiler, which would keep every tap's address
+                    // of both tiles in registers over the steps: 22 spilled)
+                    int base = (ca + 1) * P2 + ra + 1;
+                    asm volatile("" : "+v"(base));
                     const int vo = splane + ra * sp + (ca + q0) * sq;
                     const bool shared = is_shared_col(ca + q0);
                     BwdEpi e;
@@ -305,12 +412,14 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     e.gcfn = carry_gcf[it];
                     e.cp = *(const f4 *)&cell_dn[vop * kO + 4 * q4];
                     __builtin_amdgcn_sched_barrier(0);
-                    f4 acc[4];
-                    contract_bwd(as, was, base, 1, P2, q4, lane, acc);
+                    f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+                    if (has_next)
+                        acc = contract_bwd(as, was, base, 1, P2, q4, lane) * inv *
+                              *(const f4 *)&winv[4 * q4];
                     f4 dAi, dAf, dAg, dAo, gcf;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float gh = acc[0][i] + acc[1][i] + acc[2][i] + acc[3][i] + e.dh[i];
+                        const float gh = acc[i] + e.dh[i];
                         const float tc = ftanh(e.c[i]);
                         const float gcs = gh * e.go[i] * (1.0f - tc * tc) +
                                           (has_next ? e.gcfn[i] : 0.0f);
@@ -321,7 +430,13 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                         dAg[i] = gcs * e.gi[i] * (1.0f - e.gg[i] * e.gg[i]);
                         dAo[i] = gh * tc * e.go[i] * (1.0f - e.go[i]);
                     }
-                    top = top_finite(top, dAi, dAf, dAg, dAo);
+                    const float tm = top_finite(0.0f, dAi, dAf, dAg, dAo);
+                    const unsigned tmax = wave_max(tm);
+                    top = fmaxf(top, tm);
+                    if (lane == 0) {
+                        atomicMax(&mx[r & 1], tmax);
+                        if (k < n_edge) atomicMax(&emx[r & 1], tmax);
+                    }
                     const int o4 = vo * kG + 4 * q4;
                     if (shared) {
                         store_coherent(dA_rs, o4 + 0 * kO, dAi);
@@ -346,31 +461,15 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                         // this edge tile's coherent stores have completed:
                         // count it; the wave that counts the last publishes
                         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-                        if (lane == 0 && atomicAdd(cnt, 1) == n_edge - 1)
-                            __hip_atomic_store(&a.flags[blockIdx.x], r + 1, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
+                        __threadfence_block();
+                        if (lane == 0 && atomicAdd(cnt, 1) == n_edge - 1) {
+                            __threadfence_block();
+                            publish(r, emx);
+                        }
                     }
                 }
             }
-            // every contraction has read dA_{t+1}: overwrite it with dA_t
-            __syncthreads();
-#pragma unroll
-            for (int it = 0; it < 2; ++it) {
-                if (hbase[it] >= 0) {
-                    const int pb = hbase[it];
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        *(f4 *)&as[pb * kG + 4 * swz(4 * g + q4, pb)] = hold[it][g];
-                }
-            }
-            if (threadIdx.x == 0) {
-                if (n_edge == 0)
-                    __hip_atomic_store(&a.flags[blockIdx.x], r + 1, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                cnt[0] = 0;
-            }
-            // the next step's first barrier orders these LDS writes before
-            // its contractions
+            // (a strip without neighbours is waited for by none)
         }
         leave_max();
         return;
@@ -381,23 +480,15 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
         const int s = dg.sign > 0 ? t : dg.T - 1 - t;
         const bool has_next = t + 1 < dg.T, has_prev = t > 0;
         // ---- wait for the neighbours' dA_{t+1} --------------------------
+        float scale = 0.0f, inv = 0.0f, step_top = 0.0f;
         if (r > 0) {
-            const int nb = threadIdx.x == 0 ? nb_lo : (threadIdx.x == 1 ? nb_hi : -1);
-            if (nb >= 0) {
-                int spins = 0;
-                while (__hip_atomic_load(&a.flags[nb], __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT) < r + a.wait_bias) {
-                    __builtin_amdgcn_s_sleep(1);
-                    if (++spins > a.max_spin) {
-                        __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        break;
-                    }
-                    if ((spins & 1023) == 0 &&
-                        __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                        break;
-                }
-            }
+            wait_neighbours(r);
             __syncthreads();
+            const int ex = step_exp(r);
+            scale = step_sign(r) * exp2i(ex);
+            inv = step_sign(r) * exp2i(-ex);
+            if (threadIdx.x == 0) mx[r & 1] = 0u;
+            // (ordered before this step's maxima by the chunks' barriers)
         }
         const int splane = s * ss;
         const int nplane = has_next ? (s + dg.sign) * ss : splane;   // in-slice when read
@@ -432,6 +523,13 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                 }
             }
             __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+            asm volatile("" ::: "memory");
+            // each wave splits the pixels it moved (eight slots a pixel)
+            if (has_next)
+                for (int i = wave + (lane >> 5) * kWaves; i < nslots; i += 2 * kWaves) {
+                    const int pix = 4 * i + ((lane >> 3) & 3);
+                    if (pix < npl) split_slot(pix, lane & 7, scale);
+                }
             __syncthreads();
             // ---- 16-pixel tiles ------------------------------------------
             // Each tile's epilogue operands are loaded before its contraction.
@@ -458,11 +556,11 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                 e.gcfn = *(const f4 *)&gcf_dn[von * kO + 4 * q4];
                 e.cp = *(const f4 *)&cell_dn[vop * kO + 4 * q4];
             };
-            auto epilogue = [&](int vo, bool shared, const f4 (&acc)[4], const BwdEpi &e) {
+            auto epilogue = [&](int vo, bool shared, f4 acc, const BwdEpi &e) {
                 f4 dAi, dAf, dAg, dAo, gcf;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float gh = acc[0][i] + acc[1][i] + acc[2][i] + acc[3][i] + e.dh[i];
+                    const float gh = acc[i] + e.dh[i];
                     const float tc = ftanh(e.c[i]);
                     const float gcs = gh * e.go[i] * (1.0f - tc * tc) +
                                       (has_next ? e.gcfn[i] : 0.0f);
@@ -473,7 +571,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     dAg[i] = gcs * e.gi[i] * (1.0f - e.gg[i] * e.gg[i]);
                     dAo[i] = gh * tc * e.go[i] * (1.0f - e.go[i]);
                 }
-                top = top_finite(top, dAi, dAf, dAg, dAo);
+                step_top = top_finite(step_top, dAi, dAf, dAg, dAo);
                 const int o4 = vo * kG + 4 * q4;
                 float *dst = &dA_dn[o4];
                 if (shared) {
@@ -498,18 +596,21 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                 // keep the loads above the contraction (the scheduler would
                 // otherwise sink them to their use and expose their latency)
                 __builtin_amdgcn_sched_barrier(0);
-                f4 acc[4];
-                contract_bwd(as, was, base, W2, 1, q4, lane, acc);
+                f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+                if (has_next)
+                    acc = contract_bwd(as, was, base, W2, 1, q4, lane) * inv *
+                          *(const f4 *)&winv[4 * q4];
                 epilogue(vo, shared, acc, e);
             }
             __syncthreads();
         }
         // ---- publish dA_t: every wave's coherent stores have completed ---
+        top = fmaxf(top, step_top);
+        const unsigned smax = wave_max(step_top);
+        if (lane == 0) atomicMax(&mx[r & 1], smax);
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         __syncthreads();
-        if (threadIdx.x == 0)
-            __hip_atomic_store(&a.flags[blockIdx.x], r + 1, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) publish(r, mx);
     }
     leave_max();
 }
@@ -553,7 +654,7 @@ size_t sweep_bwd_ws(const Geom &g)
     Carve cv(nullptr);
     cv.take<float>((size_t)kDirs * g.N * g.V * kG);                     // dA
     cv.take<float>((size_t)kDirs * g.N * g.V * kO);                     // dL/dc * f
-    cv.take<int>(1024 + 1);                                              // flags + err
+    cv.take<int>(2 * 1024 + 1);                                          // flags + err
     cv.take<unsigned>(1024 * kWaves);                                    // maxima of |dA|
     cv.take<char>(step_wgrad_ws(g));                                     // weight gradients
     cv.take<char>(step_dx_ws(g));                                        // dL/dx fragments
@@ -580,7 +681,7 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
     Carve cv(ws);
     float *dA = cv.take<float>((size_t)kDirs * g.N * g.V * kG);
     float *gcf = cv.take<float>((size_t)kDirs * g.N * g.V * kO);
-    int *flags = cv.take<int>(1024 + 1);
+    int *flags = cv.take<int>(2 * 1024 + 1);     // (256-byte aligned: 64-bit words)
     unsigned *amax = cv.take<unsigned>(1024 * kWaves);
     void *wgws = cv.take<char>(step_wgrad_ws(g));
     float *fragx = (float *)cv.take<char>(step_dx_ws(g));
@@ -592,7 +693,7 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
     args.dh = dh;
     args.dA = dA; args.gcf = gcf;
     args.amax = amax;
-    args.flags = flags; args.err = flags + 1024;
+    args.flags = (unsigned long long *)flags; args.err = flags + 2 * 1024;
     args.max_spin = g_wait_spin_limit;
     args.wait_bias = g_wait_bias;
     for (int d = 0; d < kDirs; ++d) {
@@ -610,7 +711,7 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
     (void)hipFuncSetAttribute((const void *)k_sweep_bwd,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds);
 
-    k_fill_zero<<<(1025 + 255) / 256, 256, 0, st>>>(flags, 1025);
+    k_fill_zero<<<(2049 + 255) / 256, 256, 0, st>>>(flags, 2049);
     PLSTM_LAUNCH_CHECK();
     timing_begin("sweep_bwd_mfma", st);
     void *kargs[] = {&args};

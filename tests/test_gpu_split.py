@@ -206,3 +206,28 @@ def test_line_weight_gradients(shape, outlier):
     check_weights(ref, dwx, dwh, db)
     if outlier is not None and C > 1:
         check_weights(ref, dwx, dwh, db, list(range(1, C)))
+
+
+@pytest.mark.parametrize("path", [0, 2], ids=["whole", "chunked"])
+@pytest.mark.parametrize("axis", [1, 2, 3], ids=["planes", "rows", "columns"])
+def test_persistent_reverse_scales(path, axis):
+    """dL/dh that jumps by up to 2^60 from one plane, row or column to the next: a strip's
+    scale has to cover what its neighbours hand over, also when they are a step ahead."""
+    shape = (1, 19, 40, 52, 2, 16, 3)
+    inst = make(shape, 9990 + axis)
+    L = inst.layers[0]
+    dh = synth.upstream_grad(inst.x.shape[:-1] + (16,), 9995 + axis)
+    rng = np.random.default_rng(axis)
+    n = [1] * 5
+    n[axis] = dh.shape[axis]
+    dh *= np.exp2(rng.integers(-30, 31, size=n)).astype(np.float32)
+    ref = oracle.backward(inst.x, L.wx, L.wh, L.b, dh)
+    say("split reverse scales", path, axis)
+    x, Ld = dev(inst.x), layer_dev(L)
+    P.pyramid_lstm_set_backward_path(path)
+    _, saved = layer_forward(x, Ld, training=True)
+    dx, dwx, dwh, db = layer_backward(x, Ld, saved, dev(dh))
+    torch.cuda.synchronize()
+    P.pyramid_lstm_set_backward_path(0)
+    check_weights(ref, dwx, dwh, db)
+    assert np.abs(host(dx) - ref["dx"]).max() <= TOL * np.abs(ref["dx"]).max()
