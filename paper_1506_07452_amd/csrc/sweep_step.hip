@@ -37,6 +37,7 @@
 // im2col(x_t), 1] with K = voxels, and dL/dx = sum_d sum_taps W_x^T dA.
 #include "common.h"
 #include "strip_plan.h"
+#include "split.h"
 #include "sweep.h"
 #include "timing.h"
 
@@ -550,46 +551,84 @@ k_step_fwd_blk(FwdStepArgs a)
 // j + 1 reads, so h_{t-1} and c stay in LDS across the S lines; only the
 // segment itself is stored.  The widened pixels are the neighbours' own
 // pixels, recomputed.  Pixels past the line keep h = 0 (zero padding).
+// h is kept in LDS as split pairs (split.h; |h| <= 1, so its scale is fixed): the
+// 3 x 16 products of a 3-tap recurrence are 24 matrix instructions of 16 cycles,
+// where the fp32 instruction took 48 of 32.  x, a K-group or two of few channels,
+// stays on the fp32 instruction. 
 constexpr int kLineSeg = 64;       // stored pixels of a segment
 constexpr int kLineSlots = 112;    // LDS pixel slots: segment + 2 S r (S r <= 16) + a tile
 struct LineFwdArgs {
     Geom g;
     int t0, S;                  // first line of this launch, lines per launch
-    int Cp, KX, KG;             // padded channels; K-groups of the taps of x (dense), all
+    int Cp, KX;                 // channels in memory; K-groups of the taps of x (dense)
     int c_mul;                  // ceil(2^16 / C): (tap, channel) of a dense K index
-    const float *xp, *frag, *bias;
+    const float *xp, *frag, *bias;   // bias: [nd][64], then 1 / scale of the recurrent rows
     float *hd, *cell, *gates;
     int nseg[kDirs];            // segments per line
     int base[kDirs + 1];        // first workgroup of each direction
 };
 
-// A fragments of k_line_fwd, frag[d][kg][gate][lane][4] (16 units): the input
-// taps packed densely, K index kk = 16 kg + 4 q + i of the first KX groups
-// being (tap, channel) = (kk / C, kk % C) (zero past K C); then one group per
-// recurrent tap.  Entry i of lane (q, col) weighs gate-unit gate*16 + col.
+// A fragments of k_line_fwd (16 units), (KX + K) 1024 floats per direction.  First
+// frag[kg][gate][lane][4], the input taps packed densely, K index
+// kk = 16 kg + 4 q + i being (tap, channel) = (kk / C, kk % C) (zero past K C): entry
+// i of lane (q, col) weighs gate-unit gate*16 + col.  Then the recurrent taps as
+// split pairs [slot][gate][hi, lo][col][8 halves], slot 2 tap + half: units 8 half ..
+// + 7 times the scale of the gate-unit's row.
 template <typename TS>
 __global__ void __launch_bounds__(256)
-k_pack_line(int nd, int C, int KQ, int KX, int KG, const TS *__restrict__ wx,
+k_pack_line(int nd, int C, int KQ, int KX, const TS *__restrict__ wx,
             const TS *__restrict__ wh, const TS *__restrict__ b, float *__restrict__ frag,
             float *__restrict__ bias)
 {
     constexpr int O = 16, G = 64;
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i < (long long)nd * G) bias[i] = Store<TS>::load(b, i);
-    if (i >= (long long)nd * KG * 1024) return;
-    const int i4 = (int)(i & 3), lane = (int)((i >> 2) & 63), gate = (int)((i >> 8) & 3);
-    const long long r = i >> 10;
-    const int kg = (int)(r % KG), d = (int)(r / KG);
-    const int q = lane >> 4, col = lane & 15;
-    const long long gu = (long long)d * G + gate * O + col;
-    float v = 0.0f;
-    if (kg < KX) {
+    const int per = KX * 1024 + KQ * 128;      // input entries, then slots of 8 units
+    if (i >= (long long)nd * per) return;
+    const int d = (int)(i / per), r = (int)(i - (long long)d * per);
+    float *out = frag + (long long)d * (KX + KQ) * 1024;
+    if (r < KX * 1024) {
+        const int i4 = r & 3, lane = (r >> 2) & 63, gate = (r >> 8) & 3, kg = r >> 10;
+        const int q = lane >> 4, col = lane & 15;
+        const long long gu = (long long)d * G + gate * O + col;
         const int kk = 16 * kg + 4 * q + i4;
-        if (kk < KQ * C) v = Store<TS>::load(wx, (gu * C + kk % C) * KQ + kk / C);
-    } else {
-        v = Store<TS>::load(wh, (gu * O + 4 * q + i4) * KQ + (kg - KX));
+        out[r] = kk < KQ * C ? Store<TS>::load(wx, (gu * C + kk % C) * KQ + kk / C) : 0.0f;
+        return;
     }
-    frag[i] = v;
+    const int e = r - KX * 1024, col = e & 15, gate = (e >> 4) & 3, slot = e >> 6;
+    const long long gu = (long long)d * G + gate * O + col;
+    unsigned m = 0;
+    for (int k = 0; k < O * KQ; ++k) {
+        const unsigned v = __float_as_uint(Store<TS>::load(wh, gu * O * KQ + k)) & 0x7fffffffu;
+        m = v > m && v < 0x7f800000u ? v : m;
+    }
+    const int ex = scale_exp(m);
+    const float sc = exp2i(ex);
+    f4 w[2];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        w[j >> 2][j & 3] = Store<TS>::load(wh, (gu * O + 8 * (slot & 1) + j) * KQ + (slot >> 1)) * sc;
+    const Split8 sp = split8(w[0], w[1]);
+    h8 *hf = (h8 *)(out + KX * 1024) + (slot * 4 + gate) * 32 + col;
+    hf[0] = sp.hi;
+    hf[16] = sp.lo;
+    if (slot == 0) {
+        bias[gu] = Store<TS>::load(b, gu);
+        bias[nd * G + gu] = exp2i(-ex) / kHScale;
+    }
+}
+// A pixel of a line's h in LDS: units 8 half .. + 7 as hi, lo (16 bytes each).
+__device__ inline void put_line_h(f4 *px, int q4, f4 v)
+{
+    h4 hi, lo;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float f = v[i] * kHScale;
+        hi[i] = (_Float16)f;
+        lo[i] = (_Float16)(f - (float)hi[i]);
+    }
+    h4 *p = (h4 *)(px + (q4 >> 1) * 2) + (q4 & 1);
+    p[0] = hi;
+    p[2] = lo;
 }
 
 // LDS bytes of k_line_fwd beyond its static arrays: the launch's A fragments
@@ -620,13 +659,14 @@ k_line_fwd(LineFwdArgs a)
     const int ss = (int)dg.ss, sq = (int)dg.sq;
     const long long V = a.g.V;
     const long long sbase = ((long long)d * a.g.N + n) * V;
-    const int C = a.g.C, Cp = a.Cp, KX = a.KX, KG = a.KG, KC = a.g.KQ * C;
+    const int C = a.g.C, Cp = a.Cp, KX = a.KX, KQ = a.g.KQ, KG = KX + KQ, KC = KQ * C;
     const auto rs_x = slice_rsrc(a.xp + (long long)n * V * Cp, V * Cp);
     const auto rs_h = slice_rsrc(a.hd + sbase * O, V * O);
     const auto rs_c = slice_rsrc(a.cell + sbase * O, V * O);
     const int t0 = a.t0;
     const int nlines = min(S, dg.T - t0);
-    f4 *afr = dyn;                                 // [KG][4 gates][64 lanes]
+    f4 *afr = dyn;                                 // (see k_pack_line)
+    const h8 *hfr = (const h8 *)(dyn + KX * 256) + col;
     float *xbuf = (float *)(dyn + KG * 256);       // [2][kLineSlots][C]
 
     // x of line t (pixels pbase + slot, C channels) into buffer b: 4-byte
@@ -658,11 +698,17 @@ k_line_fwd(LineFwdArgs a)
             const int qq = pbase + slot;
             const bool ok = t0 > 0 && slot < nsl && (unsigned)qq < (unsigned)Q;
             const unsigned off = (unsigned)(((sprev * ss + qq * sq) * O + 4 * part) * 4);
-            hbuf[0][slot][part] = bload4(rs_h, sel_off(ok, off));
+            put_line_h(hbuf[0][slot], part, bload4(rs_h, sel_off(ok, off)));
             cbuf[slot][part] = bload4(rs_c, sel_off(ok, off));
         }
         stage_x(t0, 0);
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    }
+    f4 bi[4], ri[4];                               // bias and 1 / scale of this lane's rows
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        bi[g] = *(const f4 *)(a.bias + d * G + g * O + 4 * q4);
+        ri[g] = *(const f4 *)(a.bias + (a.g.nd + d) * G + g * O + 4 * q4);
     }
     __syncthreads();
 
@@ -676,7 +722,7 @@ k_line_fwd(LineFwdArgs a)
         const f4 (*hp)[4] = hbuf[j & 1];
         f4 (*hc)[4] = hbuf[(j + 1) & 1];
         const float *xb = xbuf + (size_t)(j & 1) * kLineSlots * C;
-        const int kgn = t > 0 ? KG : KX;
+        const int nsl = t > 0 ? 2 * KQ : 0;
         for (int i = wave; i < ntl; i += 4) {               // wave-uniform
             const int slot = lo + 16 * i + col;
             const int qq = pbase + slot;
@@ -684,21 +730,17 @@ k_line_fwd(LineFwdArgs a)
             f4 acc[4];
 #pragma unroll
             for (int g = 0; g < 4; ++g) acc[g] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            for (int kg = 0; kg < kgn; ++kg) {
+            for (int kg = 0; kg < KX; ++kg) {
                 f4 bv;
-                if (kg < KX) {
-                    // dense (tap, channel) K indices of this lane's four k-steps
+                // dense (tap, channel) K indices of this lane's four k-steps
 #pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4) {
-                        const int kk = 16 * kg + 4 * q4 + i4;
-                        const bool real = kk < KC;          // padding reads tap 0, channel 0
-                        const int tap = real ? (kk * a.c_mul) >> 16 : 0;
-                        const int c = real ? kk - tap * C : 0;
-                        const float xv = xb[(slot + tap - rq) * C + c];
-                        bv[i4] = real ? xv : 0.0f;
-                    }
-                } else {
-                    bv = hp[slot + (kg - KX) - rq][q4];
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const int kk = 16 * kg + 4 * q4 + i4;
+                    const bool real = kk < KC;              // padding reads tap 0, channel 0
+                    const int tap = real ? (kk * a.c_mul) >> 16 : 0;
+                    const int c = real ? kk - tap * C : 0;
+                    const float xv = xb[(slot + tap - rq) * C + c];
+                    bv[i4] = real ? xv : 0.0f;
                 }
                 const f4 *ak = afr + kg * 256 + lane;
 #pragma unroll
@@ -708,20 +750,41 @@ k_line_fwd(LineFwdArgs a)
                     for (int i4 = 0; i4 < 4; ++i4) acc[g] = mfma(av[i4], bv[i4], acc[g]);
                 }
             }
+            f4 hh[4], hx[4];                                // hi hi, and the cross products
+#pragma unroll
+            for (int g = 0; g < 4; ++g) hh[g] = hx[g] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int k0 = 0; k0 < nsl; k0 += 4) {
+                const int sl = min(k0 + q4, nsl - 1);
+                const h8 *px = (const h8 *)&hp[slot + (sl >> 1) - rq][(sl & 1) * 2];
+                h8 bh = px[0], bl = px[1];
+                if (k0 + q4 >= nsl) bh = bl = h8{};         // (past the last slot)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const h8 ah = hfr[(sl * 4 + g) * 32], al = hfr[(sl * 4 + g) * 32 + 16];
+                    hx[g] = mfma_h(al, bh, hx[g]);
+                    hh[g] = mfma_h(ah, bh, hh[g]);
+                    hx[g] = mfma_h(ah, bl, hx[g]);
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    acc[g][u] += __builtin_fmaf(hh[g][u] + hx[g][u], ri[g][u], bi[g][u]);
             f4 gi, gf, gg, go, c, h;
             const f4 cp = cbuf[slot][q4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                gi[u] = fsig(acc[0][u] + a.bias[d * G + 0 * O + 4 * q4 + u]);
-                gf[u] = fsig(acc[1][u] + a.bias[d * G + 1 * O + 4 * q4 + u]);
-                gg[u] = ftanh(acc[2][u] + a.bias[d * G + 2 * O + 4 * q4 + u]);
-                go[u] = fsig(acc[3][u] + a.bias[d * G + 3 * O + 4 * q4 + u]);
+                gi[u] = fsig(acc[0][u]);
+                gf[u] = fsig(acc[1][u]);
+                gg[u] = ftanh(acc[2][u]);
+                go[u] = fsig(acc[3][u]);
                 c[u] = gg[u] * gi[u] + (t > 0 ? cp[u] : 0.0f) * gf[u];
                 h[u] = go[u] * ftanh(c[u]);
             }
             const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
             cbuf[slot][q4] = on ? c : zero;
-            hc[slot][q4] = on ? h : zero;
+            put_line_h(hc[slot], q4, on ? h : zero);
             if (on && qq >= q0 && qq < q0 + kLineSeg) {
                 const long long vo = sbase + s * ss + qq * sq;
                 *(f4 *)(a.cell + vo * O + 4 * q4) = c;
@@ -2809,7 +2872,7 @@ size_t step_fwd_ws(const Geom &g)
     Carve cv(nullptr);
     cv.take<float>((size_t)g.N * g.V * Cp);          // padded x
     cv.take<float>((size_t)g.nd * U * KG * 1024);    // A fragments
-    cv.take<float>((size_t)g.nd * 4 * g.O);          // bias
+    cv.take<float>((size_t)g.nd * 8 * g.O);          // bias, row scales
     size_t need = cv.off;
     if (g.O % 32 == 0 || b16_packed(g)) {           // bf16 variant
         const B16K k = b16_k(g);
@@ -3114,7 +3177,7 @@ int step_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void
     Carve cv(ws);
     float *xp = cv.take<float>((size_t)g.N * g.V * Cp);
     float *frag = cv.take<float>((size_t)g.nd * U * KG * 1024);
-    float *bias = cv.take<float>((size_t)g.nd * 4 * g.O);
+    float *bias = cv.take<float>((size_t)g.nd * 8 * g.O);   // (line blocks: and row scales)
     const long long nvox = (long long)g.N * g.V;
     const long long nfrag = (long long)g.nd * U * KG * 1024;
 
@@ -3139,21 +3202,21 @@ int step_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void
             pad_x();
             PLSTM_LAUNCH_CHECK();
         }
-        const long long nfl = (long long)g.nd * KGL * 1024;
+        const long long nfl = (long long)g.nd * (KXL * 1024 + g.KQ * 128);
         if (dtype == PLSTM_BF16)
             k_pack_line<uint16_t><<<blocks_for(nfl, 256), 256, 0, st>>>(
-                g.nd, g.C, g.KQ, KXL, KGL, (const uint16_t *)wx, (const uint16_t *)wh,
+                g.nd, g.C, g.KQ, KXL, (const uint16_t *)wx, (const uint16_t *)wh,
                 (const uint16_t *)b, frag, bias);
         else
             k_pack_line<float><<<blocks_for(nfl, 256), 256, 0, st>>>(
-                g.nd, g.C, g.KQ, KXL, KGL, (const float *)wx, (const float *)wh,
+                g.nd, g.C, g.KQ, KXL, (const float *)wx, (const float *)wh,
                 (const float *)b, frag, bias);
         PLSTM_LAUNCH_CHECK();
         LineFwdArgs la;
         la.g = g;
         const int rq = g.KQ / 2;
         la.S = rq == 0 ? 16 : (16 / rq < 16 ? 16 / rq : 16);
-        la.Cp = x_direct ? g.C : Cp; la.KX = KXL; la.KG = KGL;
+        la.Cp = x_direct ? g.C : Cp; la.KX = KXL;
         la.c_mul = (65536 + g.C - 1) / g.C;
         la.xp = x_direct ? (const float *)x : xp; la.frag = frag; la.bias = bias;
         la.hd = hd; la.cell = cell; la.gates = gates;
