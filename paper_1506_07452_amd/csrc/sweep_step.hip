@@ -554,7 +554,8 @@ k_step_fwd_blk(FwdStepArgs a)
 // h is kept in LDS as split pairs (split.h; |h| <= 1, so its scale is fixed): the
 // 3 x 16 products of a 3-tap recurrence are 24 matrix instructions of 16 cycles,
 // where the fp32 instruction took 48 of 32.  x, a K-group or two of few channels,
-// stays on the fp32 instruction. 
+// stays on the fp32 instruction.  Four workgroups a CU by LDS.  30 x 512 x 512 x 1: 5.35
+// -> 4.19 ms for the 32 launches, which write 12 GB.
 constexpr int kLineSeg = 64;       // stored pixels of a segment
 constexpr int kLineSlots = 112;    // LDS pixel slots: segment + 2 S r (S r <= 16) + a tile
 struct LineFwdArgs {
@@ -1752,8 +1753,8 @@ struct BwdStepArgs {
 // back S lines per launch with overlapped tiles.  At reverse line j it
 // computes the segment widened by (S - j) r pixels on each side: line j + 1
 // reads all but the outer r of them (the outer r serve dL/dx).  dA_{t+1} (64
-// gate-units per pixel, 16-byte chunks XOR-swizzled by the pixel; overwritten
-// after a barrier) and gc_{t+1} f_{t+1} (in place) stay in LDS, and so does
+// gate-units per pixel as split pairs (split.h) scaled by the line's largest |dA|,
+// 16-byte chunks XOR-swizzled by the pixel; overwritten after a barrier) and gc_{t+1} f_{t+1} (in place) stay in LDS, and so does
 // the c_{t-1} read at line t, which is the next line's c.  The saved gates and
 // dL/dh are read per tile; only the segment's own dA_t is stored, and gc_t f_t
 // on the launch's last line.  Pixels past the line keep dA = 0.
@@ -1764,19 +1765,23 @@ struct BwdStepArgs {
 // With dxd (C <= 4) the line also gives this direction's share of dL/dx,
 //   dxd[p] = sum_taps W_x^T dA_t[p - tap],
 // from dA_t in LDS: the computed range is one radius wider than the next
-// line needs, so the segment's taps are all there.  Wave w sums gate w's 16
-// units for the segment's 64 pixels; the four partials meet in LDS and are
-// added, in order, after the next barrier.
+// line needs, so the segment's taps are all there.  Wave w contracts pixels 16 w ..
+// + 15 of the segment (channels are four of the instruction's 16 rows).
+// 18 matrix instructions of 16 cycles a tile, for gh as for dL/dx, where the fp32 ones
+// were 48 of 32 and dL/dx was summed on the vector unit by wave and gate: 30 x 512 x 512
+// x 1, forward and backward, 15.5 -> 15.0 ms (two workgroups a CU by LDS; 22 GB).
+// The sign of a line's scale alternates from line to line and segment to segment, so
+// that the instruction's rounding towards -inf cancels in db.
 // With dbp the segment's dA_t columns are summed too (db): per lane over its
 // central pixels, then over the lanes and waves in a fixed order, and added
 // to the (image, segment) partial of the earlier launches.
 struct LineBwdArgs {
     Geom g;
     int r0, S;                  // first reverse step of this launch, steps per launch
-    const float *frag;          // [6][KK * 4][64][4] W_h^T fragments
+    const h8 *frag, *fragx;     // W_h^T and W_x^T fragments (k_pack_line_bwd)
+    const float *rinv;          // [4][32] 1 / scales of W_h^T's 16 rows, W_x^T's 4
     const float *gates, *cell, *dh;
     float *dA, *gcf;
-    const float *wx;            // [4][4O][C][K] input filters (dxd only)
     float *dxd;                 // [4][N][V][C] per-direction dL/dx, or null
     float *dbp;                 // [4][N][nsegmax][4O] bias-gradient partials, or null
     int nsegmax;                // segments of the longest line
@@ -1786,41 +1791,59 @@ struct LineBwdArgs {
     int base[kDirs + 1];
 };
 
-// LDS bytes of k_line_bwd beyond its static arrays: W_h^T fragments, one line
-// of dA and, for dL/dx, the input filters.
-inline size_t line_bwd_dyn_lds(int KG, int wx_floats)
+// A fragments of k_line_bwd, one workgroup per direction: K-group 2 tap + half covers
+// gate-units 32 half .. + 31.  frag[d][kg][hi, lo][lane]: gate-units 8 (l / 16) .. + 7 of
+// output unit l % 16; fragx[d][kg][hi, lo][l / 16][4]: of input channel 0 .. 3 (zero
+// past C).
+__global__ void __launch_bounds__(256)
+k_pack_line_bwd(int C, int KQ, const float *__restrict__ wx, const float *__restrict__ wh,
+                h8 *__restrict__ frag, h8 *__restrict__ fragx, float *__restrict__ rinv)
 {
-    return (size_t)KG * 64 * 16 + (size_t)kLineSlots * 256 + (size_t)(wx_floats + 3) / 4 * 16;
-}
-
-// One wave's share of a segment pixel's dL/dx in the reverse line blocks:
-// gate w's 16 units over the taps, CC channels.  dab: one line of dA (16
-// chunks of 4 gate-units per pixel, chunk ^ (slot & 15)); wxl: [K][4O][CC]
-// input filters (wave-uniform reads); cs: the pixel's slot.
-template <int CC>
-__device__ inline f4 line_dx_px(const f4 *dab, const float *wxl, int cs, int rq, int KQ, int wave)
-{
-    constexpr int G = 64;
-    f4 px = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int tap = 0; tap < KQ; ++tap) {
-        const int sx = cs - (tap - rq);
-        const f4 *wp = (const f4 *)(wxl + (tap * G + wave * 16) * CC);
+    constexpr int O = 16, G = 64;
+    __shared__ unsigned mx[20];
+    const int d = blockIdx.x, tid = threadIdx.x, NK = 2 * KQ, Cx = min(C, 4);
+    if (tid < 20) mx[tid] = 0u;
+    __syncthreads();
+    for (int e = tid; e < G * O * KQ; e += 256) {
+        const unsigned m = __float_as_uint(wh[(long long)d * G * O * KQ + e]) & 0x7fffffffu;
+        if (m < 0x7f800000u) atomicMax(&mx[e / KQ % O], m);
+    }
+    for (int e = tid; e < G * Cx * KQ; e += 256) {
+        const int gu = e / (Cx * KQ), c = e / KQ % Cx, tap = e % KQ;
+        const unsigned m = __float_as_uint(wx[(((long long)d * G + gu) * C + c) * KQ + tap]) & 0x7fffffffu;
+        if (m < 0x7f800000u) atomicMax(&mx[16 + c], m);
+    }
+    __syncthreads();
+    if (tid < 32) rinv[d * 32 + tid] = tid < 20 ? exp2i(-scale_exp(mx[tid])) : 0.0f;
+    for (int e = tid; e < NK * 64; e += 256) {
+        const int l = e & 63, kg = e >> 6, col = l & 15, g0 = 32 * (kg & 1) + 8 * (l >> 4);
+        f4 w[2], v[2];
 #pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            const f4 v = dab[sx * 16 + ((wave * 4 + h) ^ (sx & 15))];
-            f4 w[CC];                       // units 4h .. 4h + 3, CC channels each
-#pragma unroll
-            for (int k = 0; k < CC; ++k) w[k] = wp[h * CC + k];
-#pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4)
-#pragma unroll
-                for (int c = 0; c < CC; ++c) {
-                    const int e = i4 * CC + c;
-                    px[c] += v[i4] * w[e >> 2][e & 3];
-                }
+        for (int j = 0; j < 8; ++j) {
+            const long long gu = (long long)d * G + g0 + j;
+            w[j >> 2][j & 3] = wh[(gu * O + col) * KQ + (kg >> 1)] * exp2i(scale_exp(mx[col]));
+            v[j >> 2][j & 3] = col < Cx ? wx[(gu * C + col) * KQ + (kg >> 1)] *
+                                              exp2i(scale_exp(mx[16 + (col & 3)]))
+                                        : 0.0f;
+        }
+        const Split8 sw = split8(w[0], w[1]);
+        h8 *o = frag + ((long long)d * NK + kg) * 128 + l;
+        o[0] = sw.hi;
+        o[64] = sw.lo;
+        if (col < 4) {
+            const Split8 sv = split8(v[0], v[1]);
+            h8 *ox = fragx + ((long long)d * NK + kg) * 32 + (l >> 4) * 4 + col;
+            ox[0] = sv.hi;
+            ox[16] = sv.lo;
         }
     }
-    return px;
+}
+
+// LDS bytes of k_line_bwd beyond its static arrays: W_h^T fragments, one line
+// of dA and, for dL/dx, the W_x^T fragments.
+inline size_t line_bwd_dyn_lds(int KQ, bool dx)
+{
+    return (size_t)KQ * 4096 + (size_t)kLineSlots * 256 + (dx ? (size_t)KQ * 1024 : 0);
 }
 
 __global__ void __launch_bounds__(256)
@@ -1828,7 +1851,7 @@ k_line_bwd(LineBwdArgs a)
 {
     constexpr int O = 16, G = 64;
     __shared__ f4 gcb[kLineSlots][4];           // gc f, chunk ^ (slot & 3)
-    __shared__ f4 dxr[4][64];                   // dL/dx partials of the four waves
+    __shared__ unsigned lmx[2];                 // largest finite |dA| of a line, by parity
     __shared__ f4 cl[kLineSlots][4];            // c_{t-1} read at line t: line t - 1's c
     __shared__ f4 dbr[4][4][4];                 // bias-gradient sums [wave][gate][q4]
     extern __shared__ f4 dyn[];
@@ -1840,13 +1863,13 @@ k_line_bwd(LineBwdArgs a)
     const DirGeom dg = a.g.dir[d];
     int r = blk - a.base[d];
     const int n = r / a.nseg[d], seg = r - n * a.nseg[d];
-    const int Q = dg.Q, rq = a.g.KQ >> 1, S = a.S, KG = a.g.KQ * 4;
+    const int Q = dg.Q, rq = a.g.KQ >> 1, S = a.S, NK = a.g.KQ * 2;
     const int q0 = seg * kLineSeg;
     const int pbase = q0 - (S + 1) * rq;       // pixel of LDS slot 0
     const int ss = (int)dg.ss, sq = (int)dg.sq, T = dg.T;
     const long long V = a.g.V;
     const long long sbase = ((long long)d * a.g.N + n) * V;
-    const int C = a.g.C, KQ = a.g.KQ;
+    const int C = a.g.C;
     const bool want_dx = a.dxd != nullptr;
     f4 dbacc[4] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f},
                    {0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
@@ -1858,52 +1881,89 @@ k_line_bwd(LineBwdArgs a)
     const int r0 = a.r0;
     const int nlines = min(S, T - r0);
     const int noff = dg.sign * ss;             // plane t + 1 = plane t + noff
-    f4 *afr = dyn;                              // [KG][64 lanes]
-    f4 *dab = dyn + KG * 64;                    // [kLineSlots][16], chunk ^ (slot & 15)
-    float *wxl = (float *)(dab + kLineSlots * 16);  // [K][4O][C] input filters
-
-    // W_h^T fragments, the input filters; dA and gc f of line t + 1 over the
-    // widest range (zero after the last line and past the line's ends)
-    {
-        const f4 *src = (const f4 *)(a.frag + (long long)d * KG * 256);
-        for (int e = threadIdx.x; e < KG * 64; e += 256) afr[e] = src[e];
-        if (want_dx) {
-            const int nw = KQ * G * C;
-            for (int e = threadIdx.x; e < nw; e += 256) {
-                const int tap = e / (G * C), mc = e - tap * (G * C);
-                wxl[e] = a.wx[((long long)d * G * C + mc) * KQ + tap];
-            }
+    h8 *afr = (h8 *)dyn;                        // [NK][hi, lo][64 lanes]
+    f4 *dab = dyn + NK * 128;                   // [kLineSlots][16], chunk ^ (slot & 15)
+    h8 *xfr = (h8 *)(dab + kLineSlots * 16);    // [NK][hi, lo][4][4]
+    float top = 0.0f;                           // largest finite |dA| of this lane's segment
+    auto finite_max = [](float m, f4 v) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float x = fabsf(v[u]);
+            m = x < __builtin_inff() ? fmaxf(m, x) : m;
         }
+        return m;
+    };
+    auto wave_max = [&](float v) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+        return __float_as_uint(v);
+    };
+    auto line_sign = [&](int t) { return (t + seg) & 1 ? -1.0f : 1.0f; };
+    const f4 ri = *(const f4 *)(a.rinv + d * 32 + 4 * q4), rx = *(const f4 *)(a.rinv + d * 32 + 16);
+    float scale, inv;                           // of the line in dab
+
+    // the fragments; dA and gc f of line t + 1 over the widest range (zero after
+    // the last line and past the line's ends)
+    {
+        const h8 *src = a.frag + (long long)d * NK * 128;
+        for (int e = threadIdx.x; e < NK * 128; e += 256) afr[e] = src[e];
+        if (want_dx)
+            for (int e = threadIdx.x; e < NK * 32; e += 256) xfr[e] = a.fragx[(long long)d * NK * 32 + e];
+        if (threadIdx.x < 2) lmx[threadIdx.x] = 0u;
+        __syncthreads();
         const int tn = T - r0;                  // line t + 1 for t = T - 1 - r0
         const int sn = dg.sign > 0 ? tn : T - 1 - tn;
         const int nsl = kLineSeg + 2 * (S + 1) * rq;
-        for (int e = threadIdx.x; e < kLineSlots * 16; e += 256) {
-            const int slot = e >> 4, ch = e & 15;
+        constexpr int kIt = (kLineSlots * 8 + 255) / 256;
+        f4 v[kIt][2];
+        float m = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) {
+            const int e = threadIdx.x + 256 * k, slot = e >> 3, ch = e & 7;
             const int qq = pbase + slot;
             const bool ok = r0 > 0 && slot < nsl && (unsigned)qq < (unsigned)Q;
-            const int v = sn * ss + qq * sq;
-            dab[slot * 16 + (ch ^ (slot & 15))] =
-                bload4(rs_dA, sel_off(ok, (unsigned)((v * G + 4 * ch) * 4)));
-            if (ch < 4)
-                gcb[slot][ch ^ (slot & 3)] = bload4(rs_gcf, sel_off(ok, (unsigned)((v * O + 4 * ch) * 4)));
+            const int vx = sn * ss + qq * sq;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                v[k][h] = bload4(rs_dA, sel_off(ok, (unsigned)((vx * G + 8 * ch + 4 * h) * 4)));
+                m = finite_max(m, v[k][h]);
+            }
+            if (ch < 4 && slot < kLineSlots)
+                gcb[slot][ch ^ (slot & 3)] = bload4(rs_gcf, sel_off(ok, (unsigned)((vx * O + 4 * ch) * 4)));
+        }
+        const unsigned wm = wave_max(m);
+        if (lane == 0) atomicMax(&lmx[1], wm);
+        __syncthreads();
+        const int ex = scale_exp(lmx[1]);
+        scale = line_sign(tn) * exp2i(ex);
+        inv = line_sign(tn) * exp2i(-ex);
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) {
+            const int e = threadIdx.x + 256 * k, slot = e >> 3, ch = e & 7;
+            if (slot >= kLineSlots) continue;
+            const Split8 sp = split8(v[k][0] * scale, v[k][1] * scale);
+            ((h8 *)dab)[slot * 16 + ((2 * ch) ^ (slot & 15))] = sp.hi;
+            ((h8 *)dab)[slot * 16 + ((2 * ch + 1) ^ (slot & 15))] = sp.lo;
         }
     }
     __syncthreads();
+    if (threadIdx.x == 0) lmx[1] = 0u;          // (line j = 0 uses lmx[0]; ordered by its barriers)
 
     const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    // the segment's dL/dx of line s: the four waves' partials, added in order
-    auto store_dx = [&](int s) {
-        if (threadIdx.x < kLineSeg) {
-            const int p = threadIdx.x, qq = q0 + p;
-            if (qq < Q) {
-                const f4 v = ((dxr[0][p] + dxr[1][p]) + dxr[2][p]) + dxr[3][p];
-                float *out = a.dxd + (sbase + s * ss + qq * sq) * C;
-                for (int c = 0; c < C; ++c) out[c] = v[c];
-            }
+    // sum over the taps of W^T dA[slot - (tap - r)], 64 gate-units of one line, scaled
+    auto contract = [&](int slot, auto weight) {
+        f4 acc = zero, x0 = zero, x1 = zero;
+        for (int kg = 0; kg < NK; ++kg) {
+            const int sx = slot - ((kg >> 1) - rq);
+            const int o = sx * 16 + ((8 * (kg & 1) + 2 * q4) ^ (sx & 15));
+            const h8 bh = ((const h8 *)dab)[o], bl = ((const h8 *)dab)[o ^ 1];
+            const h8 wh = weight(kg, 0), wl = weight(kg, 1);
+            x0 = mfma_h(wl, bh, x0);
+            acc = mfma_h(wh, bh, acc);
+            x1 = mfma_h(wh, bl, x1);
         }
+        return (acc + (x0 + x1)) * inv;
     };
-    int s_dx = -1;                              // line whose partials wait in dxr
-    float top = 0.0f;                           // largest finite |dA| of this lane
     for (int j = 0; j < nlines; ++j) {
         const int t = T - 1 - (r0 + j);
         const int s = dg.sign > 0 ? t : T - 1 - t;
@@ -1915,6 +1975,7 @@ k_line_bwd(LineBwdArgs a)
         // the one LDS buffer
         f4 dv[2][4];
         bool onv[2];
+        float lm = 0.0f;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int i = wave + 4 * k;
@@ -1937,16 +1998,8 @@ k_line_bwd(LineBwdArgs a)
             const f4 cp = bload4(rs_c, sel_off(on && t > 0, (unsigned)(((vox - noff) * O + 4 * q4) * 4)));
             const f4 dhv = bload4(rs_dh, sel_off(on, (unsigned)((vox * O + 4 * q4) * 4)));
             f4 acc = zero;
-            if (has_next) {
-                for (int kg = 0; kg < KG; ++kg) {
-                    const int tap = kg >> 2, mb = kg & 3;
-                    const int sx = slot - (tap - rq);
-                    const f4 bv = dab[sx * 16 + ((mb * 4 + q4) ^ (sx & 15))];
-                    const f4 av = afr[kg * 64 + lane];
-#pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4) acc = mfma(av[i4], bv[i4], acc);
-                }
-            }
+            if (has_next)
+                acc = contract(slot, [&](int kg, int hl) { return afr[(kg * 2 + hl) * 64 + lane]; }) * ri;
             // gc f and c are read and rewritten by their own lane only
             const f4 gn = has_next ? gcb[slot][gsw] : zero;
             cl[slot][gsw] = cp;
@@ -1964,16 +2017,15 @@ k_line_bwd(LineBwdArgs a)
                 gco[u] = gc * gf;
             }
             gcb[slot][gsw] = on ? gco : zero;
+            if (on) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) lm = finite_max(lm, dv[k][g]);
+            }
             if (on && qq >= q0 && qq < q0 + kLineSeg) {
 #pragma unroll
                 for (int g = 0; g < 4; ++g) dbacc[g] += dv[k][g];
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const float m = fabsf(dv[k][g][u]);
-                        top = m < __builtin_inff() ? fmaxf(top, m) : top;
-                    }
+                for (int g = 0; g < 4; ++g) top = finite_max(top, dv[k][g]);
                 const long long vo = sbase + vox;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) *(f4 *)(a.dA + vo * G + g * O + 4 * q4) = dv[k][g];
@@ -1981,34 +2033,47 @@ k_line_bwd(LineBwdArgs a)
                 if (j == nlines - 1) *(f4 *)(a.gcf + vo * O + 4 * q4) = gco;
             }
         }
+        const unsigned wm = wave_max(lm);
+        if (lane == 0) atomicMax(&lmx[j & 1], wm);
         __syncthreads();
-        if (want_dx && s_dx >= 0) store_dx(s_dx);
+        const int ex = scale_exp(lmx[j & 1]);
+        scale = line_sign(t) * exp2i(ex);
+        inv = line_sign(t) * exp2i(-ex);
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int i = wave + 4 * k;
             if (i >= ntl) continue;
             const int slot = lo + 16 * i + col;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) dab[slot * 16 + ((g * 4 + q4) ^ (slot & 15))] = onv[k] ? dv[k][g] : zero;
+            for (int g = 0; g < 4; ++g) {
+                h4 hi, lo4;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float v = onv[k] ? dv[k][g][u] * scale : 0.0f;
+                    hi[u] = (_Float16)v;
+                    lo4[u] = (_Float16)(v - (float)hi[u]);
+                }
+                // gate-units 16 g + 4 q4 .. + 3: half of the chunks of units 8 (2 g + q4 / 2) .. + 7
+                const int ch = slot * 16 + ((4 * g + 2 * (q4 >> 1)) ^ (slot & 15));
+                ((h4 *)&dab[ch])[q4 & 1] = hi;
+                ((h4 *)&dab[ch ^ 1])[q4 & 1] = lo4;
+            }
         }
+        if (threadIdx.x == 0) lmx[(j & 1) ^ 1] = 0u;    // (read before the barrier above)
         __syncthreads();
         if (want_dx) {
-            // lane = pixel of the segment; wave = gate; taps from dA_t in LDS
-            const int cs = (S + 1) * rq + lane;
-            f4 px;
-            switch (C) {
-            case 1: px = line_dx_px<1>(dab, wxl, cs, rq, KQ, wave); break;
-            case 2: px = line_dx_px<2>(dab, wxl, cs, rq, KQ, wave); break;
-            case 3: px = line_dx_px<3>(dab, wxl, cs, rq, KQ, wave); break;
-            default: px = line_dx_px<4>(dab, wxl, cs, rq, KQ, wave); break;
+            // the segment's dL/dx of this line: channels are rows 0 .. 3 (lanes q4 = 0)
+            const h8 none = {};
+            const f4 px = contract((S + 1) * rq + 16 * wave + col, [&](int kg, int hl) {
+                const h8 w = xfr[(kg * 2 + hl) * 16 + q4 * 4 + (col & 3)];
+                return col < 4 ? w : none;
+            }) * rx;
+            const int qq = q0 + 16 * wave + col;
+            if (q4 == 0 && qq < Q) {
+                float *out = a.dxd + (sbase + s * ss + qq * sq) * C;
+                for (int c = 0; c < C; ++c) out[c] = px[c];
             }
-            dxr[wave][lane] = px;
-            s_dx = s;
         }
-    }
-    if (want_dx && s_dx >= 0) {
-        __syncthreads();
-        store_dx(s_dx);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
@@ -3434,14 +3499,18 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
     bool dx_done = false;
 
     const bool fuse_dx = dx && dxd && line_bwd_dx(g);
-    const size_t line_dyn = line_bwd_dyn_lds(g.KQ * 4, fuse_dx ? g.KQ * G * g.C : 0);
+    const size_t line_dyn = line_bwd_dyn_lds(g.KQ, fuse_dx);
     const bool lines =
         g.nd == 4 && g.KP == 1 && g.O == 16 && (g_step_split == 0 || g_step_split == 2) &&
-        line_dyn + 2 * kLineSlots * 64 + 4 * 64 * 16 + 4 * 4 * 4 * 16 <= (size_t)device_info().max_lds;
+        line_dyn + 2 * kLineSlots * 64 + 4 * 4 * 4 * 16 + 16 <= (size_t)device_info().max_lds;
     const bool split = !lines && g_step_split == 0;
     if (!split) {
         timing_begin("sweep_bwd_step", st);
-        k_pack_bwd<<<blocks_for((long long)g.nd * U * KK * 4 * U * 256, 256), 256, 0, st>>>(
+        if (lines)
+            k_pack_line_bwd<<<g.nd, 256, 0, st>>>(g.C, g.KQ, wx, wh, (h8 *)frag, (h8 *)fragx,
+                                                  fragx + g.nd * g.KQ * 256);
+        else
+            k_pack_bwd<<<blocks_for((long long)g.nd * U * KK * 4 * U * 256, 256), 256, 0, st>>>(
             g.nd, g.O, KK, wh, frag);
         PLSTM_LAUNCH_CHECK();
     }
@@ -3474,10 +3543,10 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         const int rq = g.KQ / 2;
         la.S = rq == 0 ? 16 : (16 / rq < 16 ? 16 / rq : 16);
         if (kLineSeg + 2 * la.S * rq > 96) return PLSTM_EUNSUPPORTED;   // two tiles per wave
-        la.frag = frag;
+        la.frag = (const h8 *)frag; la.fragx = (const h8 *)fragx;
+        la.rinv = fragx + g.nd * g.KQ * 256;
         la.gates = sv.gates; la.cell = sv.cell; la.dh = dh;
         la.dA = dA; la.gcf = gcf;
-        la.wx = wx;
         la.dxd = fuse_dx ? dxd : nullptr;
         la.dbp = dbl;
         la.nsegmax = line_nsegmax(g);
