@@ -21,7 +21,6 @@ namespace {
 typedef v4 f4;
 
 constexpr int kXcds = 8;                 // XCDs: workgroup b runs on XCD b % 8
-constexpr int kOOB = 0x7ffffff0;         // byte offset past any buffer: loads return 0
 constexpr int kRsrcWord3 = 0x00020000;   // raw buffer, 32-bit data
 constexpr int kWaitAllLds = 0x0070;      // s_waitcnt vmcnt(0) lgkmcnt(0)
 
@@ -35,18 +34,6 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void *p, long long bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes,
                                              kRsrcWord3);
-}
-__device__ inline f4 bload4(__amdgpu_buffer_rsrc_t rs, unsigned off)
-{
-    return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
-}
-// `off` if `ok`, else an offset past the buffer (the load returns zero); the
-// empty asm keeps the select from becoming a branch around the load.
-__device__ inline unsigned sel_off(bool ok, unsigned off)
-{
-    unsigned o = ok ? off : (unsigned)kOOB;
-    asm volatile("" : "+v"(o));
-    return o;
 }
 __device__ inline int item_dir(const int *base, int item)
 {

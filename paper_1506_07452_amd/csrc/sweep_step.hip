@@ -3,6 +3,11 @@
 // channels: the layers of the stacked networks whose recurrent weights do
 // not fit a workgroup's LDS next to its staged planes.
 //
+// This file holds the bf16 steps, the 2D line blocks, the fp32 fallback of the weight
+// gradients, dL/dx after the persistent sweep, and the fp32 steps on the fp32
+// instruction, which a launch-shape knob selects; the default fp32 steps and weight
+// gradients are split_step.hip and split_wgrad.hip.
+//
 // The sweeps run one launch per plane step t.  Within a launch every
 // direction with t < T_d updates its whole plane t as independent GEMM
 // tiles on v_mfma_f32_16x16x4f32:
@@ -1754,7 +1759,8 @@ struct BwdStepArgs {
 // computes the segment widened by (S - j) r pixels on each side: line j + 1
 // reads all but the outer r of them (the outer r serve dL/dx).  dA_{t+1} (64
 // gate-units per pixel as split pairs (split.h) scaled by the line's largest |dA|,
-// 16-byte chunks XOR-swizzled by the pixel; overwritten after a barrier) and gc_{t+1} f_{t+1} (in place) stay in LDS, and so does
+// 16-byte chunks XOR-swizzled by the pixel; overwritten after a barrier) and
+// gc_{t+1} f_{t+1} (in place) stay in LDS, and so does
 // the c_{t-1} read at line t, which is the next line's c.  The saved gates and
 // dL/dh are read per tile; only the segment's own dA_t is stored, and gc_t f_t
 // on the launch's last line.  Pixels past the line keep dA = 0.
