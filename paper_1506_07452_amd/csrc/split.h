@@ -2,10 +2,14 @@
 //
 // A value v is scaled by a power of two s that puts the largest magnitude of
 // its tensor into [2^14, 2^15) and split into two fp16 numbers,
-//   v s = hi + lo + e,   hi = fp16(v s),  lo = fp16(v s - hi),
-// |e| <= 2^-22 |v s| while |v| is above 2^-18 of the largest and <= 2^-25
-// absolutely (2^-40 of the largest) below that.  A product of two such
-// numbers is lo hi' + hi lo' + hi hi' (lo lo' is below 2^-22 of it): three
+//   v s = hi + 2^-11 lo + e,   hi = fp16(v s),  lo = fp16(2^11 (v s - hi)),
+// |e| <= 2^-22 |v s| while |v s| is at least 2^-14, that is |v| 2^-28 of the
+// largest, and <= 2^-36 absolutely (2^-50 of the largest) below that.  The
+// residual of an fp16 number is below 2^-11 of it, so it is kept 2^11 times
+// larger, in the range of hi itself; at its own size it would sink into the
+// subnormals from 2^-17 of the largest on and a value 2^-40 of it would be lost.
+// A product of two such numbers is 2^-11 (lo hi' + hi lo') + hi hi' (lo lo' is
+// below 2^-22 of it): three
 // v_mfma_f32_16x16x32_f16, which multiply exactly and accumulate in fp32,
 // where v_mfma_f32_16x16x4_f32 needs eight instructions of twice the cycles
 // for the same K: 48 against 256 cycles.  The sum of 32 products is rounded
@@ -15,7 +19,7 @@
 // the sums.
 //
 // The cross products lo hi' + hi lo' have an accumulator of their own, added
-// last: the instruction drops the bits of a product below the accumulator's
+// last (join): the instruction drops the bits of a product below the accumulator's
 // last ones towards -inf, which on one accumulator leaves every sum low by
 // 1.1e-8 of the mean magnitude (288 products; error 2.0e-7).  That is nothing for
 // one sum, but the bias gradients add millions of them with cancelling signs
@@ -29,7 +33,7 @@
 //   weights  the largest magnitude of a gate row (per-row scale);
 //   x        the largest magnitude of the tensor.  A tensor that one scale
 //            does not serve (a value that is not finite, or more than 1 in
-//            1024 of its non-zero values below 2^-17 of the largest, where
+//            1024 of its non-zero values below 2^-28 of the largest, where
 //            the split starts to lose bits) keeps the fp32 instruction: the
 //            step kernels then read the same 32 bytes as eight fp32 channels
 //            (ctl[0] = 1).
@@ -45,23 +49,48 @@ typedef float v4 __attribute__((ext_vector_type(4)));
 
 constexpr float kHScale = 32768.0f;     // 2^15
 constexpr int kStatBlocks = 256;
-constexpr unsigned kStatRange = 17u << 23;   // 2^-17 of the largest, in exponent bits
+constexpr unsigned kStatRange = 28u << 23;   // 2^-28 of the largest, in exponent bits
+constexpr float kLo = 2048.0f, kLoInv = 1.0f / 2048.0f;   // scale of lo
 
+// One value, already scaled.
+__device__ inline void split1(float v, _Float16 &hi, _Float16 &lo)
+{
+    hi = (_Float16)v;
+    lo = (_Float16)__builtin_fmaf((float)hi, -kLo, v * kLo);
+}
+struct Split4 {
+    h4 hi, lo;
+};
+__device__ inline Split4 split4(v4 v)
+{
+    Split4 s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        _Float16 h, l;
+        split1(v[i], h, l);
+        s.hi[i] = h;
+        s.lo[i] = l;
+    }
+    return s;
+}
 struct Split8 {
     h8 hi, lo;
 };
 // Two f4 (channels 0..3, 4..7), already scaled.
 __device__ inline Split8 split8(v4 a, v4 b)
 {
+    const Split4 x = split4(a), y = split4(b);
     Split8 s;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        s.hi[i] = (_Float16)a[i];
-        s.hi[4 + i] = (_Float16)b[i];
-        s.lo[i] = (_Float16)(a[i] - (float)s.hi[i]);
-        s.lo[4 + i] = (_Float16)(b[i] - (float)s.hi[4 + i]);
-    }
+    s.hi = __builtin_shufflevector(x.hi, y.hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    s.lo = __builtin_shufflevector(x.lo, y.lo, 0, 1, 2, 3, 4, 5, 6, 7);
     return s;
+}
+// The sums of hi hi' and of the cross products.
+__device__ inline v4 join(v4 sum, v4 cross)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum[i] = __builtin_fmaf(cross[i], kLoInv, sum[i]);
+    return sum;
 }
 
 __device__ inline v4 mfma_h(h8 a, h8 b, v4 c)
@@ -81,7 +110,7 @@ __device__ inline float exp2i(int e) { return __uint_as_float((unsigned)(e + 127
 
 // Statistics of a tensor, two passes: per block the largest finite magnitude
 // (bits) and whether a value is not finite; then, per block, how many values
-// are not zero and how many of those lie below 2^-17 of the tensor's largest.
+// are not zero and how many of those lie below 2^-28 of the tensor's largest.
 struct SplitStat {
     unsigned max_bits, bad, nonzero, small;
 };

@@ -480,7 +480,7 @@ k_step_fwd_h2(FwdH2Args a)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) sum[1][i][nt] += sum[0][i][nt];
+            for (int nt = 0; nt < NT; ++nt) sum[1][i][nt] = join(sum[1][i][nt], sum[0][i][nt]);
     } else {
         // fp32 channels: K-group kg is eight k-steps of the fp32 instruction,
         // lane group q supplying channel j of its slot
@@ -865,7 +865,7 @@ k_step_bwd_h2(BwdH2Args a)
 #pragma unroll
         for (int i = 0; i < RTW; ++i)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) sum[1][i][nt] += sum[0][i][nt];
+            for (int nt = 0; nt < NT; ++nt) sum[1][i][nt] = join(sum[1][i][nt], sum[0][i][nt]);
         unscale = flip * exp2i(-scale_exp(top_next));
     }
 

@@ -291,8 +291,8 @@ k_wgrad_h2(WgH2Args a)
                 f4 y0 = mfma_h(av[m][0], bh, zero), y1 = mfma_h(av[m + 1][0], bh, zero);
                 x0 = mfma_h(av[m][0], bl, x0);
                 x1 = mfma_h(av[m + 1][0], bl, x1);
-                acc[m][j] += y0 + x0;
-                acc[m + 1][j] += y1 + x1;
+                acc[m][j] += join(y0, x0);
+                acc[m + 1][j] += join(y1, x1);
             }
             bh = nh;
             bl = nl;

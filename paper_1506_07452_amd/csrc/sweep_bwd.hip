@@ -130,7 +130,7 @@ __device__ __forceinline__ f4 contract_bwd(const float *as, const float *was, in
         x1 = mfma_h(wh, b[k][1], x1);
         __builtin_amdgcn_sched_barrier(0);
     }
-    return acc + (x0 + x1);
+    return join(acc, x0 + x1);
 }
 
 // Scale exponent of a plane whose largest |dA| has the biased exponent `e` (not more
@@ -337,17 +337,11 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     const int pb = hbase[it];
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
-                        h4 hi, lo;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float v = hold[it][g][i] * scale;
-                            hi[i] = (_Float16)v;
-                            lo[i] = (_Float16)(v - (float)hi[i]);
-                        }
+                        const Split4 sp = split4(hold[it][g] * scale);
                         // gate-units 16 g + 4 q4 .. + 3: half of slot 2 g + q4 / 2
                         const int c = 2 * (2 * g + (q4 >> 1)), o = 2 * (q4 & 1);
-                        *(h4 *)&as[pb * kG + 4 * swz(c, pb) + o] = hi;
-                        *(h4 *)&as[pb * kG + 4 * swz(c + 1, pb) + o] = lo;
+                        *(h4 *)&as[pb * kG + 4 * swz(c, pb) + o] = sp.hi;
+                        *(h4 *)&as[pb * kG + 4 * swz(c + 1, pb) + o] = sp.lo;
                     }
                 }
                 // ---- the neighbours' edge columns of dA_{t+1} -> halo columns

@@ -135,15 +135,9 @@ __device__ inline void put_h(float *px, int qd, f4 v, bool f32)
         *(f4 *)(p + (qd & 1) * 16) = v;
         return;
     }
-    h4 hi, lo;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float s = v[i] * kHScale;
-        hi[i] = (_Float16)s;
-        lo[i] = (_Float16)(s - (float)hi[i]);
-    }
-    *(h4 *)(p + (qd & 1) * 8) = hi;
-    *(h4 *)(p + 16 + (qd & 1) * 8) = lo;
+    const Split4 s = split4(v * kHScale);
+    *(h4 *)(p + (qd & 1) * 8) = s.hi;
+    *(h4 *)(p + 16 + (qd & 1) * 8) = s.lo;
 }
 // Staged x: 8 bytes of a pixel in each of two planes `xlo` bytes apart, four
 // channels' hi and lo, or channels 0, 1 and 2, 3 in fp32.
@@ -153,10 +147,10 @@ __device__ inline void put_x(char *xs, int xlo, int px, int c, float v, float sc
         *(float *)(xs + (c >> 1) * xlo + px * 8 + (c & 1) * 4) = v;
         return;
     }
-    const float s = v * scale;
-    const _Float16 hi = (_Float16)s;
+    _Float16 hi, lo;
+    split1(v * scale, hi, lo);
     *(_Float16 *)(xs + px * 8 + c * 2) = hi;
-    *(_Float16 *)(xs + xlo + px * 8 + c * 2) = (_Float16)(s - (float)hi);
+    *(_Float16 *)(xs + xlo + px * 8 + c * 2) = lo;
 }
 // 16 bytes that are only 8-byte aligned (two neighbouring pixels of x).
 __device__ inline h8 read_pair(const char *p)
@@ -222,7 +216,7 @@ __device__ __forceinline__ void tile_preact(const float *afr, const char *h, con
         }
     }
 #pragma unroll
-    for (int g = 0; g < 4; ++g) acc[g] += cross[g];
+    for (int g = 0; g < 4; ++g) acc[g] = join(acc[g], cross[g]);
 }
 
 // A fragments and row scales (split.h), one workgroup per (direction, gate); x

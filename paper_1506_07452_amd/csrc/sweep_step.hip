@@ -625,16 +625,10 @@ k_pack_line(int nd, int C, int KQ, int KX, const TS *__restrict__ wx,
 // A pixel of a line's h in LDS: units 8 half .. + 7 as hi, lo (16 bytes each).
 __device__ inline void put_line_h(f4 *px, int q4, f4 v)
 {
-    h4 hi, lo;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float f = v[i] * kHScale;
-        hi[i] = (_Float16)f;
-        lo[i] = (_Float16)(f - (float)hi[i]);
-    }
+    const Split4 s = split4(v * kHScale);
     h4 *p = (h4 *)(px + (q4 >> 1) * 2) + (q4 & 1);
-    p[0] = hi;
-    p[2] = lo;
+    p[0] = s.hi;
+    p[2] = s.lo;
 }
 
 // LDS bytes of k_line_fwd beyond its static arrays: the launch's A fragments
@@ -773,10 +767,11 @@ k_line_fwd(LineFwdArgs a)
                 }
             }
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
+            for (int g = 0; g < 4; ++g) {
+                const f4 sum = join(hh[g], hx[g]);
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    acc[g][u] += __builtin_fmaf(hh[g][u] + hx[g][u], ri[g][u], bi[g][u]);
+                for (int u = 0; u < 4; ++u) acc[g][u] += __builtin_fmaf(sum[u], ri[g][u], bi[g][u]);
+            }
             f4 gi, gf, gg, go, c, h;
             const f4 cp = cbuf[slot][q4];
 #pragma unroll
@@ -1968,7 +1963,7 @@ k_line_bwd(LineBwdArgs a)
             acc = mfma_h(wh, bh, acc);
             x1 = mfma_h(wh, bl, x1);
         }
-        return (acc + (x0 + x1)) * inv;
+        return join(acc, x0 + x1) * inv;
     };
     for (int j = 0; j < nlines; ++j) {
         const int t = T - 1 - (r0 + j);
@@ -2052,17 +2047,11 @@ k_line_bwd(LineBwdArgs a)
             const int slot = lo + 16 * i + col;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                h4 hi, lo4;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float v = onv[k] ? dv[k][g][u] * scale : 0.0f;
-                    hi[u] = (_Float16)v;
-                    lo4[u] = (_Float16)(v - (float)hi[u]);
-                }
+                const Split4 sp = split4(onv[k] ? dv[k][g] * scale : zero);
                 // gate-units 16 g + 4 q4 .. + 3: half of the chunks of units 8 (2 g + q4 / 2) .. + 7
                 const int ch = slot * 16 + ((4 * g + 2 * (q4 >> 1)) ^ (slot & 15));
-                ((h4 *)&dab[ch])[q4 & 1] = hi;
-                ((h4 *)&dab[ch ^ 1])[q4 & 1] = lo4;
+                ((h4 *)&dab[ch])[q4 & 1] = sp.hi;
+                ((h4 *)&dab[ch ^ 1])[q4 & 1] = sp.lo;
             }
         }
         if (threadIdx.x == 0) lmx[(j & 1) ^ 1] = 0u;    // (read before the barrier above)

@@ -231,3 +231,95 @@ def test_persistent_reverse_scales(path, axis):
     P.pyramid_lstm_set_backward_path(0)
     check_weights(ref, dwx, dwh, db)
     assert np.abs(host(dx) - ref["dx"]).max() <= TOL * np.abs(ref["dx"]).max()
+
+
+def without_neighbours(w):
+    """Recurrent filters with their centre tap only: dL/dh of a voxel then reaches the
+    voxels of its three axis lines and no others."""
+    c = np.zeros_like(w)
+    c[..., w.shape[-1] // 2] = w[..., w.shape[-1] // 2]
+    if w.ndim == 5:
+        c[..., [r for r in range(w.shape[-2]) if r != w.shape[-2] // 2], :] = 0
+    return c
+
+
+def out_of_reach(extents, at, r):
+    """Voxels whose dL/dx takes nothing from dL/dh of voxel `at` (at most one coordinate
+    within the input filters' radius of it)."""
+    near = np.zeros(extents, int)
+    for ax, (n, c) in enumerate(zip(extents, at)):
+        near += (np.abs(np.arange(n) - c) <= r).reshape([-1 if a == ax else 1 for a in range(len(extents))])
+    return near <= len(extents) - 2
+
+
+@pytest.mark.parametrize("loud", [20, 28])
+@pytest.mark.parametrize("path", [0, 2], ids=["whole", "chunked"])
+@pytest.mark.parametrize("shape", [(1, 5, 9, 11, 6, 16, 3), (1, 5, 12, 10, 32, 32, 3), (1, 5, 8, 9, 16, 64, 3),
+                                   (1, 5, 9, 11, 3, 16, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_reverse_beside_a_loud_voxel(shape, path, loud):
+    """Voxels that take nothing from one 2^loud times louder keep their precision, though
+    its block or strip has one scale: the residual half reaches as far down as the first."""
+    inst = make(shape, 9100 + sum(shape))
+    L = inst.layers[0]
+    L.wh = without_neighbours(L.wh)
+    dh = synth.upstream_grad(inst.x.shape[:-1] + (shape[5],), 77)
+    dh[0, 2, 4, 5] *= 2.0 ** loud
+    ref = oracle.backward(inst.x, L.wx, L.wh, L.b, dh)["dx"][0]
+    quiet = out_of_reach(shape[1:4], (2, 4, 5), 1)
+    say("split loud voxel", shape, path, loud)
+    x, Ld = dev(inst.x), layer_dev(L)
+    P.pyramid_lstm_set_backward_path(path)
+    try:
+        _, saved = layer_forward(x, Ld, training=True)
+        dx, _, _, _ = layer_backward(x, Ld, saved, dev(dh))
+        torch.cuda.synchronize()
+    finally:
+        P.pyramid_lstm_set_backward_path(0)
+    assert np.abs(host(dx)[0][quiet] - ref[quiet]).max() <= TOL * np.abs(ref[quiet]).max()
+
+
+@pytest.mark.parametrize("loud", [20, 28])
+@pytest.mark.parametrize("shape", [(1, 21, 30, 3, 3), (1, 12, 70, 1, 5), (2, 40, 9, 6, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_line_reverse_beside_a_loud_pixel(shape, loud):
+    N, H, W, C, K = shape
+    x, wx, wh, b = synth.image2d(N, H, W, C, 16, K, 9900 + sum(shape), "f32")
+    wh = without_neighbours(wh)
+    dh = synth.upstream_grad((N, H, W, 16), 78)
+    dh[0, 5, 4] *= 2.0 ** loud
+    ref = o2d.backward2d(x, wx, wh, b, dh)["dx"][0]
+    quiet = out_of_reach((H, W), (5, 4), K // 2)
+    say("split loud pixel", shape, loud)
+    xd, L = dev(x), LayerW(dev(wx), dev(wh), dev(b))
+    _, saved = layer2d_forward(xd, L, training=True)
+    dx, _, _, _ = layer2d_backward(xd, L, saved, dev(dh))
+    torch.cuda.synchronize()
+    assert np.abs(host(dx)[0][quiet] - ref[quiet]).max() <= TOL * np.abs(ref[quiet]).max()
+
+
+def closed_gate_error(ref, got, O, unit):
+    """Largest error of the rows of an input gate relative to the row's own largest."""
+    worst = 0.0
+    for name in ("dwx", "dwh"):
+        r, g = ref[name][:, unit].reshape(6, -1), host(got[name])[:, unit].reshape(6, -1)
+        worst = max(worst, (np.abs(g - r).max(1) / np.abs(r).max(1)).max())
+    return worst
+
+
+@pytest.mark.parametrize("bias", [-18])
+@pytest.mark.parametrize("shape", [(1, 5, 9, 11, 6, 16, 3), (1, 4, 12, 10, 32, 32, 3), (1, 5, 9, 11, 3, 16, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_weight_gradients_of_a_closed_gate(shape, bias):
+    """An input gate shut by its bias has gradients e^bias of the others'; its rows of dW
+    keep their precision beside theirs."""
+    inst = make(shape, 9100 + sum(shape))
+    L = inst.layers[0]
+    L.b[:, 5] = bias
+    dh = synth.upstream_grad(inst.x.shape[:-1] + (shape[5],), 79)
+    ref = oracle.backward(inst.x, L.wx, L.wh, L.b, dh)
+    say("split closed gate", shape, bias)
+    x, Ld = dev(inst.x), layer_dev(L)
+    _, saved = layer_forward(x, Ld, training=True)
+    _, dwx, dwh, _ = layer_backward(x, Ld, saved, dev(dh))
+    torch.cuda.synchronize()
+    assert closed_gate_error(ref, {"dwx": dwx, "dwh": dwh}, shape[5], 5) <= TOL
