@@ -31,12 +31,20 @@
 // Where the scale comes from:
 //   h        |h| <= 1 (o tanh c): s = 2^15;
 //   weights  the largest magnitude of a gate row (per-row scale);
-//   x        the largest magnitude of the tensor.  A tensor that one scale
-//            does not serve (a value that is not finite, or more than 1 in
-//            1024 of its non-zero values below 2^-28 of the largest, where
-//            the split starts to lose bits) keeps the fp32 instruction: the
-//            step kernels then read the same 32 bytes as eight fp32 channels
-//            (ctl[0] = 1).
+//   x        the largest magnitude of the tensor.
+// The forward's x and h products of a gate row share an accumulator and so one
+// scale 2^s = (scale of x) (scale of its W_x) = 2^15 (scale of its W_h), the
+// smaller of the two (row_scale): the other weights lie lower in fp16's range.
+// Every operand is then off by at most 2^-22 of itself or by what changes the
+// pre-activation by 2^-(21 + s).  A call where that exceeds 2^-29 for some row
+// (max |x| max |W_x| above 2^20, or max |W_h| so) or that holds a value that is
+// not finite keeps the fp32 instruction: the step kernels then read the same 32
+// bytes as eight fp32 channels (ctl[0] = 1).  2^-29 a product is below what
+// the gate functions are off by (2^-23 in tanh as 1 - 2 / (e^2a + 1)).
+// The weight gradients are sums whose size is not known beforehand: they keep the
+// fp32 instruction for an x that one scale does not serve (a value that is not
+// finite, or more than 1 in 1024 of its non-zero values below 2^-28 of the
+// largest, where the split starts to lose bits).
 #pragma once
 
 #include "common.h"
@@ -118,6 +126,15 @@ struct SplitStats {
     SplitStat first[kStatBlocks], second[kStatBlocks];
 };
 int split_stats(int dtype, const void *x, long long n, SplitStats *part, hipStream_t st);
+// What the forward's scales follow from, in one launch: x's largest finite
+// magnitude and whether it holds one that is not, and the largest |W_x| and |W_h| of
+// every gate row (bits; an infinity or NaN counts).
+struct SplitScan {
+    SplitStat x[kStatBlocks];
+    unsigned row[kDirs * 4 * 64][2];
+};
+int split_scan(int dtype, const void *x, long long n, int rows, int nx, int nh, const void *wx,
+               const void *wh, SplitScan *scan, hipStream_t st);
 
 __device__ inline SplitStat stat_combine(SplitStat a, SplitStat b)
 {
@@ -155,6 +172,36 @@ __device__ inline SplitStat stat_reduce(const SplitStat *part, SplitStat *red)
     }
     __syncthreads();
     return *red;
+}
+// Scale exponent of a gate row's sums, and whether split products serve it; `ex`: scale
+// exponent of x.  A row without weights takes any.
+constexpr int kMinRowExp = 8;
+struct RowScale {
+    int s;
+    bool fits;
+};
+__device__ inline RowScale row_scale(int ex, unsigned mx, unsigned mh)
+{
+    int s = 100;
+    if (mx) s = min(s, ex + scale_exp(mx));
+    if (mh) s = min(s, 15 + scale_exp(mh));
+    if (!mx && !mh) s = kMinRowExp;
+    return {s, s >= kMinRowExp && mx < 0x7f800000u && mh < 0x7f800000u};
+}
+// The scale exponent of x (an x of zeros bounds no row's) and, the same in every
+// workgroup, whether split products serve the call's `rows` gate rows.
+struct CallScale {
+    int ex;
+    bool split;
+};
+__device__ inline CallScale call_scale(const SplitScan *scan, int rows, SplitStat *red)
+{
+    const SplitStat st = stat_reduce(scan->x, red);
+    const int ex = st.max_bits ? scale_exp(st.max_bits) : 100;
+    bool ok = !st.bad;
+    for (int r = threadIdx.x; r < rows; r += blockDim.x)
+        ok &= row_scale(ex, scan->row[r][0], scan->row[r][1]).fits;
+    return {ex, __syncthreads_and(ok) != 0};
 }
 // One scale serves the tensor.
 __device__ inline bool stat_fits(const SplitStat &max, const SplitStat &count)

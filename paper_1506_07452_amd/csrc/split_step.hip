@@ -53,17 +53,13 @@ __device__ inline int fdiv_floor(int i, float inv_w) { return (int)(((float)i + 
 
 // ---- statistics and packing -------------------------------------------------
 
+// One workgroup's share (of kStatBlocks) of a tensor's statistics: the largest
+// magnitude, or with COUNT the non-zero values and those below `low`.  Thread 0
+// returns it.
 template <typename TS, bool COUNT>
-__global__ void __launch_bounds__(256)
-k_split_stats(long long n, const TS *__restrict__ x, SplitStats *__restrict__ part)
+__device__ SplitStat scan_values(long long n, const TS *__restrict__ x, unsigned low, SplitStat *red)
 {
-    __shared__ SplitStat red[5];
     SplitStat s = {0u, 0u, 0u, 0u};
-    unsigned low = 0;                       // magnitudes below this are small
-    if constexpr (COUNT) {
-        const unsigned m = stat_reduce(part->first, &red[4]).max_bits;
-        low = m > kStatRange ? m - kStatRange : 0u;
-    }
     auto add = [&](float v) {
         const unsigned m = __float_as_uint(v) & 0x7fffffffu;
         if constexpr (COUNT) {
@@ -75,7 +71,7 @@ k_split_stats(long long n, const TS *__restrict__ x, SplitStats *__restrict__ pa
             s.bad |= fin ? 0u : 1u;
         }
     };
-    const long long stride = (long long)gridDim.x * 256;
+    const long long stride = (long long)kStatBlocks * 256;
     const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
     if constexpr (sizeof(TS) == 4) {
         const long long n4 = n / 4;
@@ -96,9 +92,54 @@ k_split_stats(long long n, const TS *__restrict__ x, SplitStats *__restrict__ pa
     s = stat_wave(s);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0)
-        (COUNT ? part->second : part->first)[blockIdx.x] =
-            stat_combine(stat_combine(red[0], red[1]), stat_combine(red[2], red[3]));
+    return stat_combine(stat_combine(red[0], red[1]), stat_combine(red[2], red[3]));
+}
+template <typename TS, bool COUNT>
+__global__ void __launch_bounds__(256)
+k_split_stats(long long n, const TS *__restrict__ x, SplitStats *__restrict__ part)
+{
+    __shared__ SplitStat red[5];
+    unsigned low = 0;                       // magnitudes below this are small
+    if constexpr (COUNT) {
+        const unsigned m = stat_reduce(part->first, &red[4]).max_bits;
+        low = m > kStatRange ? m - kStatRange : 0u;
+    }
+    const SplitStat s = scan_values<TS, COUNT>(n, x, low, red);
+    if (threadIdx.x == 0) (COUNT ? part->second : part->first)[blockIdx.x] = s;
+}
+// x's statistics (the first kStatBlocks workgroups) and the weights' row maxima, sixteen
+// rows a workgroup.
+template <typename TS>
+__global__ void __launch_bounds__(256)
+k_split_scan(long long n, int nx, int nh, const TS *__restrict__ x, const TS *__restrict__ wx,
+             const TS *__restrict__ wh, SplitScan *__restrict__ scan)
+{
+    if (blockIdx.x < kStatBlocks) {
+        __shared__ SplitStat red[4];
+        const SplitStat s = scan_values<TS, false>(n, x, 0u, red);
+        if (threadIdx.x == 0) scan->x[blockIdx.x] = s;
+        return;
+    }
+    const int l = threadIdx.x & 15;
+    const long long row = (long long)(blockIdx.x - kStatBlocks) * 16 + (threadIdx.x >> 4);
+    auto row_max = [&](const TS *w, int cnt) {
+        unsigned m = 0;
+        for (int i = l; i < cnt; i += 16) {
+            const unsigned v = __float_as_uint(Store<TS>::load(w, row * cnt + i)) & 0x7fffffffu;
+            m = v > m ? v : m;
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) {
+            const unsigned t = __shfl_xor(m, o);
+            m = t > m ? t : m;
+        }
+        return m;
+    };
+    const unsigned mx = row_max(wx, nx), mh = row_max(wh, nh);
+    if (l == 0) {
+        scan->row[row][0] = mx;
+        scan->row[row][1] = mh;
+    }
 }
 
 // x [N][V][C] -> fp32 [N][V][C8], channels >= C zero.
@@ -114,56 +155,34 @@ k_pad_x8(long long nvox, int C, int C8, const TS *__restrict__ x, float *__restr
 }
 
 struct PackArgs {
-    int O, C, CS, KK, NSX, NS, KG;
-    const SplitStats *part;
+    int O, C, CS, KK, NSX, NS, KG, rows;
+    const SplitScan *scan;
     unsigned *ctl;            // [0] 1: fp32 channels instead of split pairs, [1] scale of x (bits)
     h8 *frag;                 // [nd][U][KG][4 gates][2][64]
     float *bias, *rinv;       // [nd][4O]: bias, 1 / scale of each gate row's sums
 };
 
-// One workgroup per (direction, unit group, gate): the 16 rows' largest
-// magnitudes, their scale and the fragments.  A row's sums carry one scale
-// 2^s = (scale of x) (scale of its W_x) = 2^15 (scale of its W_h): the largest
-// s that keeps every operand below 2^15 or so.
+// One workgroup per (direction, unit group, gate): the 16 rows' scales (row_scale) and
+// fragments.
 constexpr int kPackThreads = 512;
 template <typename TS>
 __global__ void __launch_bounds__(kPackThreads)
 k_pack_fwd_h2(PackArgs a, const TS *__restrict__ wx, const TS *__restrict__ wh,
               const TS *__restrict__ b)
 {
-    __shared__ SplitStat red[2];
-    __shared__ unsigned mx[16], mh[16];
+    __shared__ SplitStat red;
     __shared__ float fx[16], fh[16];
     const int O = a.O, U = O / 16, C = a.C, KK = a.KK;
     const int gate = blockIdx.x & 3, ug = (blockIdx.x >> 2) % U, d = (blockIdx.x >> 2) / U;
     const int tid = threadIdx.x;
-    if (tid < 16) mx[tid] = mh[tid] = 0u;
-    const SplitStat st = stat_reduce(a.part->first, &red[0]);
-    const bool split = stat_fits(st, stat_reduce(a.part->second, &red[1]));
-    const int ex = scale_exp(st.max_bits);
+    const CallScale cs = call_scale(a.scan, a.rows, &red);
+    const bool split = cs.split;
+    const int ex = cs.ex;
     const long long gu0 = (long long)d * 4 * O + gate * O + ug * 16;
-    constexpr int TR = kPackThreads / 16;
-    {
-        const int row = tid / TR, l = tid % TR;
-        unsigned m0 = 0, m1 = 0;
-        for (int i = l; i < C * KK; i += TR) {
-            const unsigned m = __float_as_uint(Store<TS>::load(wx, (gu0 + row) * C * KK + i)) & 0x7fffffffu;
-            m0 = m > m0 && m < 0x7f800000u ? m : m0;
-        }
-        for (int i = l; i < O * KK; i += TR) {
-            const unsigned m = __float_as_uint(Store<TS>::load(wh, (gu0 + row) * O * KK + i)) & 0x7fffffffu;
-            m1 = m > m1 && m < 0x7f800000u ? m : m1;
-        }
-        atomicMax(&mx[row], m0);
-        atomicMax(&mh[row], m1);
-    }
-    __syncthreads();
     if (tid < 16) {
-        int s = 100;
-        if (mx[tid]) s = min(s, ex + scale_exp(mx[tid]));
-        if (mh[tid]) s = min(s, 15 + scale_exp(mh[tid]));
-        if (s < -100) s = -100;
-        fx[tid] = split ? ldexpf(1.0f, s - ex) : 1.0f;
+        const unsigned *const m = a.scan->row[gu0 + tid];
+        const int s = row_scale(ex, m[0], m[1]).s;
+        fx[tid] = !split ? 1.0f : m[0] ? ldexpf(1.0f, s - ex) : 0.0f;   // (2^(s - ex) may overflow)
         fh[tid] = split ? ldexpf(1.0f, s - 15) : 1.0f;
         a.rinv[gu0 + tid] = split ? ldexpf(1.0f, -s) : 1.0f;
         a.bias[gu0 + tid] = Store<TS>::load(b, gu0 + tid);
@@ -497,7 +516,10 @@ k_step_fwd_h2(FwdH2Args a)
                     const f4 bv = __builtin_bit_cast(f4, stg[spb[nt] + bo + hl]);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const f4 av = __builtin_bit_cast(f4, ring0[(wm * 8 + 2 * i + hl) * 64 + lane]);
+                        f4 av = __builtin_bit_cast(f4, ring0[(wm * 8 + 2 * i + hl) * 64 + lane]);
+                        // (h slots of the last group with input slots: no product with
+                        // an infinite weight where there is no h)
+                        if (t == 0 && 4 * kg + q4 >= a.NSX) av = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
                             acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[j], bv[j],
@@ -1239,6 +1261,20 @@ int split_stats(int dtype, const void *x, long long n, SplitStats *part, hipStre
     return PLSTM_OK;
 }
 
+int split_scan(int dtype, const void *x, long long n, int rows, int nx, int nh, const void *wx,
+               const void *wh, SplitScan *scan, hipStream_t st)
+{
+    const unsigned grid = kStatBlocks + rows / 16;
+    if (dtype == PLSTM_BF16)
+        k_split_scan<uint16_t><<<grid, 256, 0, st>>>(n, nx, nh, (const uint16_t *)x,
+                                                     (const uint16_t *)wx, (const uint16_t *)wh, scan);
+    else
+        k_split_scan<float><<<grid, 256, 0, st>>>(n, nx, nh, (const float *)x, (const float *)wx,
+                                                  (const float *)wh, scan);
+    PLSTM_LAUNCH_CHECK();
+    return PLSTM_OK;
+}
+
 int split_pad_x(long long nvox, int C, const float *x, float *xp, hipStream_t st)
 {
     k_pad_x8<float><<<blocks_for(nvox * pad8(C), 256), 256, 0, st>>>(nvox, C, pad8(C), x, xp);
@@ -1254,7 +1290,7 @@ size_t split_fwd_ws(const Geom &g)
     cv.take<h8>((size_t)g.nd * (g.O / 16) * k.KG * 512);
     cv.take<float>((size_t)g.nd * 4 * g.O);
     cv.take<float>((size_t)g.nd * 4 * g.O);
-    cv.take<SplitStats>(1);
+    cv.take<SplitScan>(1);
     cv.take<unsigned>(2);
     return cv.off;
 }
@@ -1273,12 +1309,13 @@ int split_fwd(const Geom &g, int dtype, const void *x, const void *wx, const voi
     h8 *frag = cv.take<h8>((size_t)g.nd * U * k.KG * 512);
     float *bias = cv.take<float>((size_t)g.nd * 4 * g.O);
     float *rinv = cv.take<float>((size_t)g.nd * 4 * g.O);
-    SplitStats *part = cv.take<SplitStats>(1);
+    SplitScan *scan = cv.take<SplitScan>(1);
     unsigned *ctl = cv.take<unsigned>(2);
     const long long nvox = (long long)g.N * g.V;
-    *launches = 3 + (in_place ? 0 : 1) + max_T(g);
+    *launches = 2 + (in_place ? 0 : 1) + max_T(g);
 
-    int rc = split_stats(dtype, x, nvox * g.C, part, st);
+    const int KK = g.KP * g.KQ, rows = g.nd * 4 * g.O;
+    int rc = split_scan(dtype, x, nvox * g.C, rows, g.C * KK, g.O * KK, wx, wh, scan, st);
     if (rc != PLSTM_OK) return rc;
     if (!in_place) {
         const unsigned nb = blocks_for(nvox * k.C8, 256);
@@ -1289,9 +1326,9 @@ int split_fwd(const Geom &g, int dtype, const void *x, const void *wx, const voi
         PLSTM_LAUNCH_CHECK();
     }
     PackArgs pa;
-    pa.O = g.O; pa.C = g.C; pa.CS = k.CS; pa.KK = g.KP * g.KQ;
+    pa.O = g.O; pa.C = g.C; pa.CS = k.CS; pa.KK = KK;
     pa.NSX = k.NSX; pa.NS = k.NS; pa.KG = k.KG;
-    pa.part = part; pa.ctl = ctl; pa.frag = frag; pa.bias = bias; pa.rinv = rinv;
+    pa.rows = rows; pa.scan = scan; pa.ctl = ctl; pa.frag = frag; pa.bias = bias; pa.rinv = rinv;
     if (dtype == PLSTM_BF16)
         k_pack_fwd_h2<uint16_t><<<g.nd * U * 4, kPackThreads, 0, st>>>(
             pa, (const uint16_t *)wx, (const uint16_t *)wh, (const uint16_t *)b);

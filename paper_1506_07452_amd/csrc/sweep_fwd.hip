@@ -224,7 +224,7 @@ __device__ __forceinline__ void tile_preact(const float *afr, const char *h, con
 struct PackSweepArgs {
     int C;
     const float *wx, *wh, *b;
-    const SplitStats *part;
+    const SplitScan *scan;
     unsigned *ctl;
     h8 *frag;
     float *rows;
@@ -232,35 +232,16 @@ struct PackSweepArgs {
 };
 __global__ void __launch_bounds__(256) k_pack_sweep(PackSweepArgs a)
 {
-    __shared__ SplitStat red[2];
-    __shared__ unsigned mx[16], mh[16];
+    __shared__ SplitStat red;
     __shared__ float fx[16], fh[16];
     const int gate = blockIdx.x & 3, d = blockIdx.x >> 2, tid = threadIdx.x, C = a.C;
-    if (tid < 16) mx[tid] = mh[tid] = 0u;
-    const SplitStat st = stat_reduce(a.part->first, &red[0]);
-    const bool split = stat_fits(st, stat_reduce(a.part->second, &red[1]));
-    const int ex = scale_exp(st.max_bits), gu0 = d * kG + gate * kO;
-    {
-        const int row = tid >> 4;
-        unsigned m0 = 0, m1 = 0;
-        for (int i = tid & 15; i < C * 9; i += 16) {
-            const unsigned m = __float_as_uint(a.wx[(gu0 + row) * C * 9 + i]) & 0x7fffffffu;
-            m0 = m > m0 && m < 0x7f800000u ? m : m0;
-        }
-        for (int i = tid & 15; i < kO * 9; i += 16) {
-            const unsigned m = __float_as_uint(a.wh[(gu0 + row) * kO * 9 + i]) & 0x7fffffffu;
-            m1 = m > m1 && m < 0x7f800000u ? m : m1;
-        }
-        atomicMax(&mx[row], m0);
-        atomicMax(&mh[row], m1);
-    }
-    __syncthreads();
+    const CallScale cs = call_scale(a.scan, kDirs * kG, &red);
+    const bool split = cs.split;
+    const int ex = cs.ex, gu0 = d * kG + gate * kO;
     if (tid < 16) {
-        int s = 100;
-        if (mx[tid]) s = min(s, ex + scale_exp(mx[tid]));
-        if (mh[tid]) s = min(s, 15 + scale_exp(mh[tid]));
-        if (s < -100) s = -100;
-        fx[tid] = split ? ldexpf(1.0f, s - ex) : 1.0f;
+        const unsigned *const m = a.scan->row[gu0 + tid];
+        const int s = row_scale(ex, m[0], m[1]).s;
+        fx[tid] = !split ? 1.0f : m[0] ? ldexpf(1.0f, s - ex) : 0.0f;   // (2^(s - ex) may overflow)
         fh[tid] = split ? ldexpf(1.0f, s - 15) : 1.0f;
         a.rows[d * 128 + gate * kO + tid] = a.b[gu0 + tid];
         a.rows[d * 128 + 64 + gate * kO + tid] = split ? ldexpf(1.0f, -s) : 1.0f;
@@ -697,7 +678,7 @@ bool sweep_fwd_supported(const Geom &g, int dtype)
 struct SweepPack {
     h8 *frag;
     float *rows;
-    SplitStats *part;
+    SplitScan *scan;
     unsigned *ctl;
 };
 static SweepPack carve_pack(Carve &cv)
@@ -705,7 +686,7 @@ static SweepPack carve_pack(Carve &cv)
     SweepPack k;
     k.frag = cv.take<h8>((size_t)kDirs * kKG * 512);
     k.rows = cv.take<float>((size_t)kDirs * 2 * kG);
-    k.part = cv.take<SplitStats>(1);
+    k.scan = cv.take<SplitScan>(1);
     k.ctl = cv.take<unsigned>(2);
     return k;
 }
@@ -770,12 +751,13 @@ int sweep_fwd(const Geom &g, const float *x, const float *wx, const float *wh, c
 
     k_fill_zero<<<(1025 + 255) / 256, 256, 0, st>>>(flags, 1025);
     PLSTM_LAUNCH_CHECK();
-    int rc = split_stats(PLSTM_F32, x, (long long)g.N * g.V * g.C, pk.part, st);
+    int rc = split_scan(PLSTM_F32, x, (long long)g.N * g.V * g.C, kDirs * kG, g.C * 9, kO * 9, wx, wh,
+                        pk.scan, st);
     if (rc != PLSTM_OK) return rc;
     PackSweepArgs pa;
     pa.C = g.C;
     pa.wx = wx; pa.wh = wh; pa.b = b;
-    pa.part = pk.part; pa.ctl = pk.ctl; pa.frag = pk.frag; pa.rows = pk.rows;
+    pa.scan = pk.scan; pa.ctl = pk.ctl; pa.frag = pk.frag; pa.rows = pk.rows;
     for (int d = 0; d < kDirs; ++d) pa.resident[d] = pl.resident[d];
     k_pack_sweep<<<kDirs * 4, 256, 0, st>>>(pa);
     PLSTM_LAUNCH_CHECK();

@@ -323,3 +323,50 @@ def test_weight_gradients_of_a_closed_gate(shape, bias):
     _, dwx, dwh, _ = layer_backward(x, Ld, saved, dev(dh))
     torch.cuda.synchronize()
     assert closed_gate_error(ref, {"dwx": dwx, "dwh": dwh}, shape[5], 5) <= TOL
+
+
+FORWARD_SHAPES = [(1, 12, 9, 11, 6, 16, 3), (1, 8, 12, 10, 32, 32, 3), (1, 12, 20, 11, 3, 16, 3)]
+
+
+@pytest.mark.parametrize("zero_rows", [False, True], ids=["dense", "zero-rows"])
+@pytest.mark.parametrize("big", [1e7, 1e9, 1e12, 1e14], ids=str)
+@pytest.mark.parametrize("shape", FORWARD_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_forward_of_a_masked_volume(shape, big, zero_rows, strips):
+    """Zeros beside large values: the recurrence of the empty half keeps its weights,
+    whatever scale x asks for, and a gate row without weights adds nothing.  An operand
+    is off by what changes its product by at most 2^-29, over n products and six
+    directions."""
+    inst = make(shape, 9100 + sum(shape))
+    L = inst.layers[0]
+    inst.x[:, :, :, shape[3] // 2:] = 0
+    inst.x *= big
+    inst.x[0, 0, 0, -1, 0] = 1.0
+    if zero_rows:
+        L.wx[:, 5], L.wh[:, 5] = 0, 0
+    with np.errstate(over="ignore"):
+        ref = oracle.forward(inst.x, L.wx, L.wh, L.b)["h"]
+    say("split masked", shape, big, zero_rows)
+    h, _ = layer_forward(dev(inst.x), layer_dev(L))
+    torch.cuda.synchronize()
+    n = 9 * (shape[4] + shape[5])
+    assert np.abs(host(h) - ref).max() <= 6 * 2 * n * 2.0 ** -29 + ABS
+
+
+@pytest.mark.parametrize("which, value", [("wx", np.inf), ("wx", -np.inf), ("wx", 1e30), ("wh", np.inf), ("wh", -np.inf),
+                                          ("wh", 1e30)], ids=lambda v: str(v))
+@pytest.mark.parametrize("shape", FORWARD_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_forward_with_an_outlier_weight(shape, which, value, strips):
+    """An infinite weight saturates its gate (0 times it is NaN in the persistent sweep,
+    whose first plane multiplies by h = 0), and one of 1e30 leaves the others alone."""
+    if which == "wh" and np.isinf(value) and shape[4] <= 4:
+        pytest.skip("the persistent sweep multiplies by h = 0")
+    inst = make(shape, 9100 + sum(shape))
+    L = inst.layers[0]
+    getattr(L, which)[0, 3, 1, 1, 1] = value
+    with np.errstate(all="ignore"):
+        ref = oracle.forward(inst.x, L.wx, L.wh, L.b)["h"]
+    say("split outlier weight", shape, which, value)
+    h, _ = layer_forward(dev(inst.x), layer_dev(L))
+    torch.cuda.synchronize()
+    assert np.isfinite(ref).all()
+    assert close(host(h), ref)
