@@ -579,7 +579,9 @@ struct LineFwdArgs {
 // kk = 16 kg + 4 q + i being (tap, channel) = (kk / C, kk % C) (zero past K C): entry
 // i of lane (q, col) weighs gate-unit gate*16 + col.  Then the recurrent taps as
 // split pairs [slot][gate][hi, lo][col][8 halves], slot 2 tap + half: units 8 half ..
-// + 7 times the scale of the gate-unit's row.
+// + 7 times the scale of the gate-unit's row, or, where one of the call's rows has
+// weights that split products do not serve (row_scale), as eight fp32 values, the
+// rows' scales being 1 then (a split row's is at least 2^kMinRowExp).
 template <typename TS>
 __global__ void __launch_bounds__(256)
 k_pack_line(int nd, int C, int KQ, int KX, const TS *__restrict__ wx,
@@ -589,6 +591,12 @@ k_pack_line(int nd, int C, int KQ, int KX, const TS *__restrict__ wx,
     constexpr int O = 16, G = 64;
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     const int per = KX * 1024 + KQ * 128;      // input entries, then slots of 8 units
+    unsigned wild = 0;                         // the call's largest |W_h|
+    for (int e = threadIdx.x; e < nd * G * O * KQ; e += 256) {
+        const unsigned v = __float_as_uint(Store<TS>::load(wh, e)) & 0x7fffffffu;
+        wild = v > wild ? v : wild;
+    }
+    const bool split = __syncthreads_and(row_scale(100, 0u, wild).fits) != 0;
     if (i >= (long long)nd * per) return;
     const int d = (int)(i / per), r = (int)(i - (long long)d * per);
     float *out = frag + (long long)d * (KX + KQ) * 1024;
@@ -608,23 +616,27 @@ k_pack_line(int nd, int C, int KQ, int KX, const TS *__restrict__ wx,
         m = v > m && v < 0x7f800000u ? v : m;
     }
     const int ex = scale_exp(m);
-    const float sc = exp2i(ex);
+    const float sc = split ? exp2i(ex) : 1.0f;
     f4 w[2];
 #pragma unroll
     for (int j = 0; j < 8; ++j)
         w[j >> 2][j & 3] = Store<TS>::load(wh, (gu * O + 8 * (slot & 1) + j) * KQ + (slot >> 1)) * sc;
     const Split8 sp = split8(w[0], w[1]);
     h8 *hf = (h8 *)(out + KX * 1024) + (slot * 4 + gate) * 32 + col;
-    hf[0] = sp.hi;
-    hf[16] = sp.lo;
+    hf[0] = split ? sp.hi : __builtin_bit_cast(h8, w[0]);
+    hf[16] = split ? sp.lo : __builtin_bit_cast(h8, w[1]);
     if (slot == 0) {
         bias[gu] = Store<TS>::load(b, gu);
-        bias[nd * G + gu] = exp2i(-ex) / kHScale;
+        bias[nd * G + gu] = split ? exp2i(-ex) / kHScale : 1.0f;
     }
 }
-// A pixel of a line's h in LDS: units 8 half .. + 7 as hi, lo (16 bytes each).
-__device__ inline void put_line_h(f4 *px, int q4, f4 v)
+// A pixel of a line's h in LDS: units 8 half .. + 7 as hi, lo (16 bytes each), or fp32.
+__device__ inline void put_line_h(f4 *px, int q4, f4 v, bool f32)
 {
+    if (f32) {
+        px[q4] = v;
+        return;
+    }
     const Split4 s = split4(v * kHScale);
     h4 *p = (h4 *)(px + (q4 >> 1) * 2) + (q4 & 1);
     p[0] = s.hi;
@@ -667,6 +679,7 @@ k_line_fwd(LineFwdArgs a)
     const int nlines = min(S, dg.T - t0);
     f4 *afr = dyn;                                 // (see k_pack_line)
     const h8 *hfr = (const h8 *)(dyn + KX * 256) + col;
+    const bool f32 = a.bias[a.g.nd * G] == 1.0f;   // (see k_pack_line)
     float *xbuf = (float *)(dyn + KG * 256);       // [2][kLineSlots][C]
 
     // x of line t (pixels pbase + slot, C channels) into buffer b: 4-byte
@@ -698,7 +711,7 @@ k_line_fwd(LineFwdArgs a)
             const int qq = pbase + slot;
             const bool ok = t0 > 0 && slot < nsl && (unsigned)qq < (unsigned)Q;
             const unsigned off = (unsigned)(((sprev * ss + qq * sq) * O + 4 * part) * 4);
-            put_line_h(hbuf[0][slot], part, bload4(rs_h, sel_off(ok, off)));
+            put_line_h(hbuf[0][slot], part, bload4(rs_h, sel_off(ok, off)), f32);
             cbuf[slot][part] = bload4(rs_c, sel_off(ok, off));
         }
         stage_x(t0, 0);
@@ -753,7 +766,27 @@ k_line_fwd(LineFwdArgs a)
             f4 hh[4], hx[4];                                // hi hi, and the cross products
 #pragma unroll
             for (int g = 0; g < 4; ++g) hh[g] = hx[g] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            for (int k0 = 0; k0 < nsl; k0 += 4) {
+            if (f32) {
+                for (int k0 = 0; k0 < nsl; k0 += 4) {
+                    const int sl = min(k0 + q4, nsl - 1);
+                    const f4 *px = &hp[slot + (sl >> 1) - rq][(sl & 1) * 2];
+                    const f4 none = {0.0f, 0.0f, 0.0f, 0.0f};
+                    const bool real = k0 + q4 < nsl;
+                    const f4 b0 = real ? px[0] : none, b1 = real ? px[1] : none;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        f4 a0 = __builtin_bit_cast(f4, hfr[(sl * 4 + g) * 32]);
+                        f4 a1 = __builtin_bit_cast(f4, hfr[(sl * 4 + g) * 32 + 16]);
+                        if (!real) a0 = a1 = none;
+#pragma unroll
+                        for (int i4 = 0; i4 < 4; ++i4) {
+                            hh[g] = mfma(a0[i4], b0[i4], hh[g]);
+                            hh[g] = mfma(a1[i4], b1[i4], hh[g]);
+                        }
+                    }
+                }
+            }
+            for (int k0 = f32 ? nsl : 0; k0 < nsl; k0 += 4) {
                 const int sl = min(k0 + q4, nsl - 1);
                 const h8 *px = (const h8 *)&hp[slot + (sl >> 1) - rq][(sl & 1) * 2];
                 h8 bh = px[0], bl = px[1];
@@ -785,7 +818,7 @@ k_line_fwd(LineFwdArgs a)
             }
             const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
             cbuf[slot][q4] = on ? c : zero;
-            put_line_h(hc[slot], q4, on ? h : zero);
+            put_line_h(hc[slot], q4, on ? h : zero, f32);
             if (on && qq >= q0 && qq < q0 + kLineSeg) {
                 const long long vo = sbase + s * ss + qq * sq;
                 *(f4 *)(a.cell + vo * O + 4 * q4) = c;

@@ -370,3 +370,20 @@ def test_forward_with_an_outlier_weight(shape, which, value, strips):
     torch.cuda.synchronize()
     assert np.isfinite(ref).all()
     assert close(host(h), ref)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, 1e12], ids=str)
+@pytest.mark.parametrize("shape", [(1, 20, 70, 2, 3), (2, 35, 33, 5, 7)], ids=lambda s: "x".join(map(str, s)))
+def test_line_forward_with_an_outlier_weight(shape, value):
+    """As above for the 2D line blocks, over more than one launch; the volume with D = 1 that
+    computes the layer has no product with h before the first line."""
+    N, H, W, C, K = shape
+    x, wx, wh, b = synth.image2d(N, H, W, C, 16, K, 9910 + sum(shape), "f32")
+    wh[:, 3, 1, K // 2] = value
+    with np.errstate(all="ignore"):
+        ref = o2d.forward2d_via_volume(x, wx, wh, b)
+    say("split outlier line weight", shape, value)
+    h, _ = layer2d_forward(dev(x), LayerW(dev(wx), dev(wh), dev(b)))
+    torch.cuda.synchronize()
+    assert np.isfinite(ref).all()
+    assert close(host(h), ref)
