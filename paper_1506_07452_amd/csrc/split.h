@@ -53,7 +53,9 @@ namespace plstm {
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float v4 __attribute__((ext_vector_type(4)));
+typedef float v2 __attribute__((ext_vector_type(2)));
 
 constexpr float kHScale = 32768.0f;     // 2^15
 constexpr int kStatBlocks = 256;
@@ -66,6 +68,9 @@ __device__ inline void split1(float v, _Float16 &hi, _Float16 &lo)
     hi = (_Float16)v;
     lo = (_Float16)__builtin_fmaf((float)hi, -kLo, v * kLo);
 }
+// Four values, already scaled.  (Two at a time, and hi hidden from the compiler, which
+// would fold the scaling into the conversion and convert every value twice: 30 instead
+// of 36 instructions per eight values.)
 struct Split4 {
     h4 hi, lo;
 };
@@ -73,11 +78,14 @@ __device__ inline Split4 split4(v4 v)
 {
     Split4 s;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        _Float16 h, l;
-        split1(v[i], h, l);
-        s.hi[i] = h;
-        s.lo[i] = l;
+    for (int i = 0; i < 4; i += 2) {
+        h2 h = __builtin_convertvector(v2{v[i], v[i + 1]}, h2);
+        asm("" : "+v"(h));
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            s.hi[i + k] = h[k];
+            s.lo[i + k] = (_Float16)__builtin_fmaf((float)h[k], -kLo, v[i + k] * kLo);
+        }
     }
     return s;
 }
