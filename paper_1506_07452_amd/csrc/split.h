@@ -45,6 +45,11 @@
 // fp32 instruction for an x that one scale does not serve (a value that is not
 // finite, or more than 1 in 1024 of its non-zero values below 2^-28 of the
 // largest, where the split starts to lose bits).
+// The reverse steps scale dA by the largest magnitude of the pixels they stage
+// and keep the fp32 instruction where the loudest gate-unit of some pixel is
+// below 2^-28 of it or a value is not finite (da_wide): a pixel's products are
+// then off by at most 2^-22 of its own largest.  The weights of a unit (a row of W_h^T,
+// W_x^T) count as x does, 1 in 64.
 #pragma once
 
 #include "common.h"
@@ -133,7 +138,8 @@ struct SplitStat {
 struct SplitStats {
     SplitStat first[kStatBlocks], second[kStatBlocks];
 };
-int split_stats(int dtype, const void *x, long long n, SplitStats *part, hipStream_t st);
+// (of fp32 values; clears nctl words of ctl too)
+int split_stats(const float *x, long long n, SplitStats *part, unsigned *ctl, int nctl, hipStream_t st);
 // What the forward's scales follow from, in one launch: x's largest finite
 // magnitude and whether it holds one that is not, and the largest |W_x| and |W_h| of
 // every gate row (bits; an infinity or NaN counts).
@@ -210,6 +216,51 @@ __device__ inline CallScale call_scale(const SplitScan *scan, int rows, SplitSta
     for (int r = threadIdx.x; r < rows; r += blockDim.x)
         ok &= row_scale(ex, scan->row[r][0], scan->row[r][1]).fits;
     return {ex, __syncthreads_and(ok) != 0};
+}
+// Magnitudes of a stretch of dA, as biased exponents: x the largest (255: a value is
+// not finite), y 255 minus the smallest of the pixels' largest (pixels of zeros apart;
+// 0: none).  Stretches join by the maximum of each.
+typedef unsigned short DaRange __attribute__((ext_vector_type(2)));
+__device__ inline DaRange da_join(DaRange a, DaRange b) { return __builtin_elementwise_max(a, b); }
+__device__ inline DaRange da_shuffle(DaRange r, int o)
+{
+    return __builtin_bit_cast(DaRange, __shfl_xor(__builtin_bit_cast(int, r), o));
+}
+// Over a wave whose lanes l, l + 16, l + 32, l + 48 hold one pixel's largest (bits).
+__device__ inline DaRange da_wave(unsigned m)
+{
+#pragma unroll
+    for (int o = 32; o > 8; o >>= 1) {
+        const unsigned t = __shfl_xor(m, o);
+        m = t > m ? t : m;
+    }
+    DaRange r = {(unsigned short)(m >> 23), (unsigned short)(m ? 255u - (m >> 23) : 0u)};
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) r = da_join(r, da_shuffle(r, o));
+    return r;
+}
+// One scale does not serve it.
+__device__ inline bool da_wide(DaRange r)
+{
+    return r.x == 255 || (int)r.x + (int)r.y - 255 > (int)(kStatRange >> 23);
+}
+// Exponent of its scale (a range of zeros takes any).
+__device__ inline int da_exp(DaRange r) { return min(14 - ((int)r.x - 127), 110); }
+// Eight weights as fp32 values, from their fragment's two halves: split pairs (the
+// value to 22 bits, still scaled), or, `raw`, the values themselves.
+struct Wide8 {
+    v4 a, b;
+};
+__device__ inline Wide8 widen8(h8 hi, h8 lo, bool raw)
+{
+    if (raw) return {__builtin_bit_cast(v4, hi), __builtin_bit_cast(v4, lo)};
+    Wide8 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        w.a[i] = __builtin_fmaf((float)lo[i], kLoInv, (float)hi[i]);
+        w.b[i] = __builtin_fmaf((float)lo[4 + i], kLoInv, (float)hi[4 + i]);
+    }
+    return w;
 }
 // One scale serves the tensor.
 __device__ inline bool stat_fits(const SplitStat &max, const SplitStat &count)

@@ -94,9 +94,10 @@ __device__ SplitStat scan_values(long long n, const TS *__restrict__ x, unsigned
     __syncthreads();
     return stat_combine(stat_combine(red[0], red[1]), stat_combine(red[2], red[3]));
 }
-template <typename TS, bool COUNT>
+template <bool COUNT>
 __global__ void __launch_bounds__(256)
-k_split_stats(long long n, const TS *__restrict__ x, SplitStats *__restrict__ part)
+k_split_stats(long long n, const float *__restrict__ x, SplitStats *__restrict__ part,
+              unsigned *__restrict__ ctl, int nctl)
 {
     __shared__ SplitStat red[5];
     unsigned low = 0;                       // magnitudes below this are small
@@ -104,11 +105,12 @@ k_split_stats(long long n, const TS *__restrict__ x, SplitStats *__restrict__ pa
         const unsigned m = stat_reduce(part->first, &red[4]).max_bits;
         low = m > kStatRange ? m - kStatRange : 0u;
     }
-    const SplitStat s = scan_values<TS, COUNT>(n, x, low, red);
+    const SplitStat s = scan_values<float, COUNT>(n, x, low, red);
+    if (!COUNT && blockIdx.x == 0 && (int)threadIdx.x < nctl) ctl[threadIdx.x] = 0u;
     if (threadIdx.x == 0) (COUNT ? part->second : part->first)[blockIdx.x] = s;
 }
-// x's statistics (the first kStatBlocks workgroups) and the weights' row maxima, sixteen
-// rows a workgroup.
+// x's statistics (the first kStatBlocks workgroups) and the weights' row maxima, a row a
+// wave.
 template <typename TS>
 __global__ void __launch_bounds__(256)
 k_split_scan(long long n, int nx, int nh, const TS *__restrict__ x, const TS *__restrict__ wx,
@@ -120,16 +122,17 @@ k_split_scan(long long n, int nx, int nh, const TS *__restrict__ x, const TS *__
         if (threadIdx.x == 0) scan->x[blockIdx.x] = s;
         return;
     }
-    const int l = threadIdx.x & 15;
-    const long long row = (long long)(blockIdx.x - kStatBlocks) * 16 + (threadIdx.x >> 4);
+    const int l = threadIdx.x & 63;
+    const long long row = (long long)(blockIdx.x - kStatBlocks) * 4 + (threadIdx.x >> 6);
     auto row_max = [&](const TS *w, int cnt) {
         unsigned m = 0;
-        for (int i = l; i < cnt; i += 16) {
+#pragma unroll 4
+        for (int i = l; i < cnt; i += 64) {
             const unsigned v = __float_as_uint(Store<TS>::load(w, row * cnt + i)) & 0x7fffffffu;
             m = v > m ? v : m;
         }
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {
+        for (int o = 32; o > 0; o >>= 1) {
             const unsigned t = __shfl_xor(m, o);
             m = t > m ? t : m;
         }
@@ -569,45 +572,69 @@ k_step_fwd_h2(FwdH2Args a)
 // over passes of 64 gate-units, then taps, then halves: kg = (pass KK + tap) 2 +
 // half, lane group q taking gate-units 64 pass + 32 half + 8 q .. + 7.
 // One workgroup per (direction, row tile): the 16 rows' largest magnitudes and
-// their scale, then the fragments.
+// their scale, then the fragments.  Rows that one scale does not serve leave fp32
+// values instead (raw[d][rt] = 1).
 struct PackBwdArgs {
     int O, C, KK, RT, rt0, nrt;   // packs row tiles rt0 .. rt0 + nrt - 1
     const float *wx, *wh;
     h8 *frag;
     float *rinv;              // [nd][16 RT]: 1 / scale of each row
+    unsigned *raw;            // [nd][RT]
 };
 constexpr int kPackBwdThreads = 1024;
 __global__ void __launch_bounds__(kPackBwdThreads)
 k_pack_bwd_h2(PackBwdArgs a)
 {
-    __shared__ unsigned mx[16];
+    __shared__ unsigned mx[16], mn[16], nonzero[16], small[16];
     __shared__ float fr[16];
     const int O = a.O, U = O / 16, G = 4 * O, KK = a.KK, C = a.C, tid = threadIdx.x;
     const int rt = a.rt0 + blockIdx.x % a.nrt, d = blockIdx.x / a.nrt;
     const bool is_h = rt < U;
     const float *w = (is_h ? a.wh : a.wx) + (long long)d * G * (is_h ? O : C) * KK;
     const int cols = is_h ? O : C, r0 = (is_h ? rt : rt - U) * 16;
-    if (tid < 16) mx[tid] = 0u;
+    if (tid < 16) {
+        mx[tid] = nonzero[tid] = small[tid] = 0u;
+        mn[tid] = ~0u;
+    }
     __syncthreads();
-    {
-        constexpr int TR = kPackBwdThreads / 16;
-        const int row = tid / TR;
-        unsigned m0 = 0;
+    constexpr int TR = kPackBwdThreads / 16;
+    const int row = tid / TR;
+    auto each = [&](auto use) {              // magnitudes of this thread's share of its row
         if (r0 + row < cols)
             for (int i = tid % TR; i < G * KK; i += TR) {
                 const int g = i / KK, tap = i - g * KK;
-                const unsigned m =
-                    __float_as_uint(w[((long long)g * cols + r0 + row) * KK + tap]) & 0x7fffffffu;
-                m0 = m > m0 && m < 0x7f800000u ? m : m0;
+                use(__float_as_uint(w[((long long)g * cols + r0 + row) * KK + tap]) & 0x7fffffffu);
             }
+    };
+    {
+        unsigned m0 = 0, m1 = ~0u;
+        each([&](unsigned m) {
+            m0 = m > m0 ? m : m0;
+            m1 = m - 1u < m1 ? m - 1u : m1;      // (zeros apart)
+        });
         atomicMax(&mx[row], m0);
+        atomicMin(&mn[row], m1);
     }
     __syncthreads();
+    const unsigned low = mx[row] > kStatRange ? mx[row] - kStatRange : 0u;
+    if (__syncthreads_or(mn[row] != ~0u && mn[row] + 1u < low)) {   // (seldom: counted then only)
+        unsigned nz = 0, sm = 0;
+        each([&](unsigned m) {
+            nz += m != 0 ? 1u : 0u;
+            sm += m != 0 && m < low ? 1u : 0u;
+        });
+        atomicAdd(&nonzero[row], nz);
+        atomicAdd(&small[row], sm);
+    }
+    __syncthreads();
+    const int r16 = tid & 15;
+    const bool raw = __syncthreads_or(mx[r16] >= 0x7f800000u || small[r16] > nonzero[r16] / 64u) != 0;
     if (tid < 16) {
-        const int s = scale_exp(mx[tid]);
+        const int s = raw ? 0 : scale_exp(mx[tid]);
         fr[tid] = exp2i(s);
         a.rinv[(d * a.RT + rt) * 16 + tid] = exp2i(-s);
     }
+    if (tid == 0) a.raw[d * a.RT + rt] = raw ? 1u : 0u;
     __syncthreads();
     const int KG = KK * U * 2;
     for (int e = tid; e < KG * 64; e += kPackBwdThreads) {
@@ -622,8 +649,8 @@ k_pack_bwd_h2(PackBwdArgs a)
                                 : 0.0f;
         const Split8 sp = split8(v[0], v[1]);
         h8 *out = a.frag + (((long long)d * KG + kg) * a.RT + rt) * 128 + lane;
-        out[0] = sp.hi;
-        out[64] = sp.lo;
+        out[0] = raw ? __builtin_bit_cast(h8, v[0]) : sp.hi;
+        out[64] = raw ? __builtin_bit_cast(h8, v[1]) : sp.lo;
     }
 }
 
@@ -635,8 +662,8 @@ struct BwdH2Args {
     int tab_off;
     const h8 *frag;
     const float *rinv;
-    unsigned *amax;           // largest finite |dA| (bits) of each plane's waves,
-                              // [N][T][nblk][waves] at aoff
+    const unsigned *raw;
+    DaRange *amax;            // range of each plane's waves, [N][T][nblk][waves] at aoff
     long long aoff[kDirs + 1];
     const float *gates, *cell, *dh;
     float *dA;                // [nd][N][V][4O]
@@ -659,8 +686,10 @@ constexpr int kBwdChunks = 18;           // staged pixel: 64 gate-units as 8 spl
 // dA_{t+1} of the block and its filter halo is staged 64 gate-units at a time
 // (28 KB for 64 pixels, two to three workgroups share a CU), scaled by the
 // largest magnitude of the blocks it touches, which the launch before left in
-// amax (one word a wave: an atomic maximum per plane cost 0.4 us a launch); the
-// fragments stream as in the forward step.
+// amax (one range a wave: an atomic maximum per plane cost 0.4 us a launch); the
+// fragments stream as in the forward step.  Blocks that one scale does not serve
+// (da_wide, raw weights) stage dA as it is and take the fp32 instruction, one
+// K-group at a time.
 // Bound by the launches on small planes (37 us for 400 workgroups: staging twice
 // 4, K-groups 0.6 each, 36 of them, cell update 11 kilocycles) and by LDS reads and
 // barriers on large ones.  Measured against the fp32 instruction on 64-pixel
@@ -705,7 +734,7 @@ k_step_bwd_h2(BwdH2Args a)
     const int KG = a.KG;                 // of one pass
     int *const tab = (int *)(stg + a.tab_off);
     float *const rowp = (float *)(tab + (KK + 3) / 4 * 4);   // 1 / scale of the rows
-    unsigned *const am = a.amax + a.aoff[d] + (long long)n * dg.T * a.nblk[d] * NW;
+    DaRange *const am = a.amax + a.aoff[d] + (long long)n * dg.T * a.nblk[d] * NW;
 
     // this lane's pixel of each tile
     int spb[NT], evox[NT], epix[NT];
@@ -731,12 +760,14 @@ k_step_bwd_h2(BwdH2Args a)
     // bias gradients, which add it up over all voxels
     const float flip = (bi + bj + t) & 1 ? -1.0f : 1.0f;
     float unscale = 1.0f;
+    unsigned raw = 0;                // row tiles with fp32 weights
+    bool f32 = false;
 
     if (has_next) {
-        // largest |dA_{t+1}| of the blocks the staged one touches: this lane's
-        // first word now, the rest (wide halos) and the reduction beside the
+        // range of dA_{t+1} of the blocks the staged one touches: this lane's
+        // first wave now, the rest (wide halos) and the reduction beside the
         // staging loads
-        const unsigned *const an = am + (long long)(t + 1) * a.nblk[d] * NW;
+        const DaRange *const an = am + (long long)(t + 1) * a.nblk[d] * NW;
         const int i0 = fdiv_floor(max(p0 - radp, 0), 1.0f / (float)BP);
         const int i1 = fdiv_floor(min(p0 + BP - 1 + radp, P - 1), 1.0f / (float)BP);
         const int j0 = fdiv_floor(max(q0 - radq, 0), 1.0f / (float)BQ);
@@ -746,7 +777,8 @@ k_step_bwd_h2(BwdH2Args a)
             const int i = fdiv_floor(e, 1.0f / (float)nj);
             return an[((i0 + i) * a.nbq[d] + j0) * NW + e - i * nj];
         };
-        unsigned top_next = top_word(min(lane, cnt - 1));
+        DaRange range = top_word(min(lane, cnt - 1));
+        const unsigned raw_tile = a.raw[d * RT + min(lane, RT - 1)];
         const auto rs_a =
             rsrc_of(a.frag + (long long)d * KG * U * RT * 128, (long long)KG * U * RT * 2048);
         const float *const dA_n = a.dA + sbase * G;
@@ -801,21 +833,24 @@ k_step_bwd_h2(BwdH2Args a)
                     if (tid < RT * 16) rowp[tid] = a.rinv[d * RT * 16 + tid];
                 }
                 if (pass == 0 && e0 == tid) {
-                    for (int e = 64 + lane; e < cnt; e += 64) {
-                        const unsigned m = top_word(e);
-                        top_next = m > top_next ? m : top_next;
-                    }
+                    for (int e = 64 + lane; e < cnt; e += 64) range = da_join(range, top_word(e));
 #pragma unroll
-                    for (int o = 32; o > 0; o >>= 1) {
-                        const unsigned m = __shfl_xor(top_next, o);
-                        top_next = m > top_next ? m : top_next;
-                    }
+                    for (int o = 32; o > 0; o >>= 1) range = da_join(range, da_shuffle(range, o));
+                    range = __builtin_bit_cast(
+                        DaRange, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, range)));
+                    raw = (unsigned)__ballot(raw_tile != 0 && lane < RT);
+                    f32 = raw != 0 || da_wide(range);
                 }
-                const float scale = flip * exp2i(scale_exp(top_next));
+                const float scale = flip * exp2i(da_exp(range));
 #pragma unroll
                 for (int u = 0; u < SB; ++u) {
                     if (dst[u] < 0) continue;
                     const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+                    if (f32) {
+                        stg[dst[u]] = __builtin_bit_cast(h8, ok[u] ? va[u] : zero);
+                        stg[dst[u] + 1] = __builtin_bit_cast(h8, ok[u] ? vb[u] : zero);
+                        continue;
+                    }
                     const Split8 w = split8(ok[u] ? va[u] * scale : zero, ok[u] ? vb[u] * scale : zero);
                     stg[dst[u]] = w.hi;
                     stg[dst[u] + 1] = w.lo;
@@ -824,6 +859,34 @@ k_step_bwd_h2(BwdH2Args a)
             __builtin_amdgcn_s_waitcnt(kWaitAllLds);
             __syncthreads();
 
+            if (f32) {
+                // fp32 values: K-group kg is eight k-steps of the fp32 instruction
+                for (int kg = 0; kg < KG; ++kg) {
+                    __syncthreads();
+                    issue_a(kg, ring0);
+                    __builtin_amdgcn_s_waitcnt(kWaitAllLds);
+                    __syncthreads();
+                    const int bo = tab[kg >> 1] + 8 * (kg & 1);
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const f4 b0 = __builtin_bit_cast(f4, stg[spb[nt] + bo]);
+                        const f4 b1 = __builtin_bit_cast(f4, stg[spb[nt] + bo + 1]);
+#pragma unroll
+                        for (int i = 0; i < RTW; ++i) {
+                            const h8 *ap = &ring0[(i * WM * 2 + wm * 2) * 64 + lane];
+                            const Wide8 w = widen8(ap[0], ap[64], raw >> min(i * WM + wm, RT - 1) & 1);
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.a[j], b0[j],
+                                                                                  acc[i][nt], 0, 0, 0);
+                                acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.b[j], b1[j],
+                                                                                  acc[i][nt], 0, 0, 0);
+                            }
+                        }
+                    }
+                }
+                continue;
+            }
             Ops X, Y;
 #pragma unroll
             for (int i = 0; i < 2 * RTW; ++i) X.a[i >> 1][i & 1] = ring0[((i >> 1) * WM * 2 + wm * 2 + (i & 1)) * 64 + lane];
@@ -888,7 +951,7 @@ k_step_bwd_h2(BwdH2Args a)
         for (int i = 0; i < RTW; ++i)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) sum[1][i][nt] = join(sum[1][i][nt], sum[0][i][nt]);
-        unscale = flip * exp2i(-scale_exp(top_next));
+        unscale = f32 ? 1.0f : flip * exp2i(-da_exp(range));
     }
 
     const int np = dg.T > 1 ? 2 : 1;
@@ -964,18 +1027,14 @@ k_step_bwd_h2(BwdH2Args a)
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
                     const unsigned bits = __float_as_uint(v4[m]) & 0x7fffffffu;
-                    top = bits > top && bits < 0x7f800000u ? bits : top;
+                    top = bits > top ? bits : top;
                 }
             }
         }
     }
     if (do_h) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned b = __shfl_xor(top, o);
-            top = b > top ? b : top;
-        }
-        if (lane == 0) am[((long long)t * a.nblk[d] + bi * a.nbq[d] + bj) * NW + wv] = top;
+        const DaRange range = da_wave(top);
+        if (lane == 0) am[((long long)t * a.nblk[d] + bi * a.nbq[d] + bj) * NW + wv] = range;
     }
 }
 
@@ -1214,7 +1273,8 @@ int launch_bwd_shape(const Geom &g, BwdH2Args &a, const BwdShape &sh, const PixB
 struct BwdWs {
     float *dA, *gcp, *dxd, *rinv;
     h8 *frag;
-    unsigned *amax;
+    DaRange *amax;
+    unsigned *raw;
     long long aoff[kDirs + 1];
     PixBlocks blocks;
 };
@@ -1239,24 +1299,19 @@ BwdWs carve_bwd(Carve &cv, const Geom &g, bool with_dx)
     w.gcp = cv.take<float>(planes * g.N * g.O);
     w.frag = cv.take<h8>((size_t)g.nd * g.KP * g.KQ * (g.O / 8) * sh.RT * 128);
     w.rinv = cv.take<float>((size_t)g.nd * sh.RT * 16);
-    w.amax = cv.take<unsigned>((size_t)words);
+    w.raw = cv.take<unsigned>((size_t)g.nd * sh.RT);
+    w.amax = cv.take<DaRange>((size_t)words);
     w.dxd = with_dx ? cv.take<float>((size_t)g.nd * g.N * g.V * g.C) : nullptr;
     return w;
 }
 
 }  // namespace
 
-int split_stats(int dtype, const void *x, long long n, SplitStats *part, hipStream_t st)
+int split_stats(const float *x, long long n, SplitStats *part, unsigned *ctl, int nctl, hipStream_t st)
 {
-    if (dtype == PLSTM_BF16) {
-        k_split_stats<uint16_t, false><<<kStatBlocks, 256, 0, st>>>(n, (const uint16_t *)x, part);
-        PLSTM_LAUNCH_CHECK();
-        k_split_stats<uint16_t, true><<<kStatBlocks, 256, 0, st>>>(n, (const uint16_t *)x, part);
-    } else {
-        k_split_stats<float, false><<<kStatBlocks, 256, 0, st>>>(n, (const float *)x, part);
-        PLSTM_LAUNCH_CHECK();
-        k_split_stats<float, true><<<kStatBlocks, 256, 0, st>>>(n, (const float *)x, part);
-    }
+    k_split_stats<false><<<kStatBlocks, 256, 0, st>>>(n, x, part, ctl, nctl);
+    PLSTM_LAUNCH_CHECK();
+    k_split_stats<true><<<kStatBlocks, 256, 0, st>>>(n, x, part, ctl, nctl);
     PLSTM_LAUNCH_CHECK();
     return PLSTM_OK;
 }
@@ -1264,7 +1319,7 @@ int split_stats(int dtype, const void *x, long long n, SplitStats *part, hipStre
 int split_scan(int dtype, const void *x, long long n, int rows, int nx, int nh, const void *wx,
                const void *wh, SplitScan *scan, hipStream_t st)
 {
-    const unsigned grid = kStatBlocks + rows / 16;
+    const unsigned grid = kStatBlocks + rows / 4;
     if (dtype == PLSTM_BF16)
         k_split_scan<uint16_t><<<grid, 256, 0, st>>>(n, nx, nh, (const uint16_t *)x,
                                                      (const uint16_t *)wx, (const uint16_t *)wh, scan);
@@ -1381,7 +1436,7 @@ int split_bwd(const Geom &g, const float *wx, const float *wh, const Saved &sv, 
     const int KK = g.KP * g.KQ, U = g.O / 16;
     PackBwdArgs pa;
     pa.O = g.O; pa.C = g.C; pa.KK = KK; pa.RT = sh.RT;
-    pa.wx = wx; pa.wh = wh; pa.frag = w.frag; pa.rinv = w.rinv;
+    pa.wx = wx; pa.wh = wh; pa.frag = w.frag; pa.rinv = w.rinv; pa.raw = w.raw;
     pa.rt0 = 0;
     pa.nrt = sh.RT;
     if (with_dx && sh.WM == 2) {
@@ -1403,7 +1458,7 @@ int split_bwd(const Geom &g, const float *wx, const float *wh, const Saved &sv, 
     a.g = g;
     a.RT = sh.RT; a.KG = 2 * KK;
     a.k_mul = (65536 + g.KQ - 1) / g.KQ;
-    a.frag = w.frag; a.rinv = w.rinv; a.amax = w.amax;
+    a.frag = w.frag; a.rinv = w.rinv; a.raw = w.raw; a.amax = w.amax;
     a.gates = sv.gates; a.cell = sv.cell; a.dh = dh;
     a.dA = w.dA; a.gcp = w.gcp; a.dxd = w.dxd;
     long long off = 0;
@@ -1412,12 +1467,12 @@ int split_bwd(const Geom &g, const float *wx, const float *wh, const Saved &sv, 
         if (d < g.nd)
             off += (long long)g.N * (g.dir[d].T > 1 ? 2 : 1) * g.dir[d].P * g.dir[d].Q * g.O;
     }
-    for (int d = 0; d <= kDirs; ++d) a.aoff[d] = out->aoff[d] = w.aoff[d];
+    for (int d = 0; d <= kDirs; ++d) a.aoff[d] = out->am.off[d] = w.aoff[d];
     const int rc = launch_bwd_shape(g, a, sh, w.blocks, with_dx, st);
     if (rc == PLSTM_OK) timing_end(1 + max_T(g) + (with_dx ? 1 : 0), st);
     out->dA = w.dA;
     out->dxd = w.dxd;
-    out->amax = w.amax;
+    out->am.p = (const unsigned *)w.amax;
     out->used = cv.off;
     return rc;
 }

@@ -39,14 +39,13 @@ __device__ inline h8 tr8(lds_char *base, int o0, int o1)
 }
 
 // Maxima of |dA| per direction (kMaxWords workgroups each) and, last workgroup,
-// whether one scale serves x and its exponent.
+// whether one scale serves x and its exponent.  A dA that is not finite keeps fp32 too.
 struct PrepArgs {
     int nd;
-    const unsigned *amax;
-    long long aoff[kDirs + 1];
+    DaMaxima am;
     const SplitStats *part;
     unsigned *dmax;           // [nd][kMaxWords]
-    unsigned *ctl;            // [0] 1: x keeps fp32 products, [1] its largest magnitude (bits)
+    unsigned *ctl;            // [0] 1: fp32 products (cleared before), [1] x's largest magnitude (bits)
 };
 __global__ void __launch_bounds__(256) k_wg_prep(PrepArgs a)
 {
@@ -57,14 +56,16 @@ __global__ void __launch_bounds__(256) k_wg_prep(PrepArgs a)
         const SplitStat m = stat_reduce(a.part->first, &red[0]);
         const SplitStat c = stat_reduce(a.part->second, &red[1]);
         if (threadIdx.x == 0) {
-            a.ctl[0] = stat_fits(m, c) ? 0u : 1u;
+            if (!stat_fits(m, c)) atomicOr(&a.ctl[0], 1u);
             a.ctl[1] = m.max_bits;
         }
         return;
     }
     unsigned m = 0;
-    for (long long i = a.aoff[d] + b * 256 + threadIdx.x; i < a.aoff[d + 1]; i += kMaxWords * 256)
-        m = a.amax[i] > m ? a.amax[i] : m;
+    for (long long i = a.am.off[d] + b * 256 + threadIdx.x; i < a.am.off[d + 1]; i += kMaxWords * 256) {
+        const unsigned v = a.am.p[i] & 0xffffu;
+        m = v > m ? v : m;
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const unsigned t = __shfl_xor(m, o);
@@ -74,7 +75,8 @@ __global__ void __launch_bounds__(256) k_wg_prep(PrepArgs a)
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < 4; ++w) m = top[w] > m ? top[w] : m;
-        a.dmax[d * kMaxWords + b] = m;
+        a.dmax[d * kMaxWords + b] = m << 23;
+        if (m == 255u) atomicOr(&a.ctl[0], 1u);
     }
 }
 
@@ -501,14 +503,14 @@ size_t split_wgrad_ws(const Geom &g)
 }
 
 int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-                const unsigned *amax, const long long *aoff, float *partial, void *ws,
-                const unsigned **ctl, hipStream_t st)
+                const DaMaxima &am, float *partial, void *ws, const unsigned **ctl,
+                hipStream_t st)
 {
     Carve cv(ws);
     const WgWs s = carve_wg(cv, g);
     const WgPlan w = wg_plan(g);
     const long long nvox = (long long)g.N * g.V;
-    int rc = split_stats(PLSTM_F32, x, nvox * g.C, s.part, st);
+    int rc = split_stats(x, nvox * g.C, s.part, s.ctl, 2, st);
     if (rc != PLSTM_OK) return rc;
     if (s.xp) {
         rc = split_pad_x(nvox, g.C, x, s.xp, st);
@@ -516,8 +518,7 @@ int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
     }
     PrepArgs pa;
     pa.nd = g.nd;
-    pa.amax = amax;
-    for (int d = 0; d <= kDirs; ++d) pa.aoff[d] = aoff[d];
+    pa.am = am;
     pa.part = s.part; pa.dmax = s.dmax; pa.ctl = s.ctl;
     k_wg_prep<<<g.nd * kMaxWords + 1, 256, 0, st>>>(pa);
     PLSTM_LAUNCH_CHECK();

@@ -33,12 +33,17 @@ size_t step_fwd_ws(const Geom &g);
 int step_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void *wh,
              const void *b, float *hd, float *cell, float *gates, void *h, void *ws,
              hipStream_t st);
-// Weight and bias gradients (db may be null) from dA; `amax`, `aoff`: maxima of
-// |dA| per direction as split_bwd leaves them, or null for the fp32 kernel.
+// Weight and bias gradients (db may be null) from dA; `am`: the largest biased exponents
+// of dA (255: not finite), those of direction d in the lower halves of words am.off[d] ..
+// am.off[d + 1], or null for the fp32 kernel.
+struct DaMaxima {
+    const unsigned *p = nullptr;
+    long long off[kDirs + 1] = {};
+};
 size_t step_wgrad_ws(const Geom &g);
 int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-               const unsigned *amax, const long long *aoff, void *ws, float *dwx, float *dwh,
-               float *db, const char *phase, hipStream_t st);
+               const DaMaxima &am, void *ws, float *dwx, float *dwh, float *db,
+               const char *phase, hipStream_t st);
 size_t step_bwd_ws(const Geom &g);
 int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, const Saved &sv,
              const float *dh, float *dx, float *dwx, float *dwh, float *db, void *ws,
@@ -51,11 +56,10 @@ int split_fwd(const Geom &g, int dtype, const void *x, const void *wx, const voi
               const void *b, float *hd, float *cell, bool cell_full, float *gates, void *ws,
               hipStream_t st, int *launches);
 // Reverse steps the same way: dA, with_dx each direction's share of dL/dx, and the
-// largest finite |dA| of each wave of each step, all in the workspace.
+// largest |dA| of each wave of each step, all in the workspace.
 struct SplitBwd {
     float *dA, *dxd;
-    unsigned *amax;           // finite |dA| maxima (bits), those of direction d at
-    long long aoff[kDirs + 1];   // aoff[d] .. aoff[d + 1]
+    DaMaxima am;
     size_t used;              // workspace bytes taken
 };
 size_t split_bwd_ws(const Geom &g);
@@ -71,8 +75,8 @@ struct WgradSplit {
 WgradSplit split_wgrad_shape(const Geom &g);
 size_t split_wgrad_ws(const Geom &g);
 int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-                const unsigned *amax, const long long *aoff, float *partial, void *ws,
-                const unsigned **ctl, hipStream_t st);
+                const DaMaxima &am, float *partial, void *ws, const unsigned **ctl,
+                hipStream_t st);
 int split_pad_x(long long nvox, int C, const float *x, float *xp, hipStream_t st);
 // dL/dx from the gate gradients dA [6][N][V][4O] on the MFMA (step_supported
 // shapes); `fragx` holds step_dx_ws bytes.

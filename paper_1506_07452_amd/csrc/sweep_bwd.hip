@@ -63,7 +63,7 @@ struct BwdArgs {
     const float *dh;             // dL/dh [N][V][16]
     float *dA;                   // [6][N][V][64] gate pre-activation gradients
     float *gcf;                  // [6][N][V][16] dL/dc_t * f_t, carried to plane t - 1
-    unsigned *amax;              // [blocks][kWaves] largest finite |dA| (bits)
+    unsigned *amax;              // [blocks][kWaves] exponent of the largest finite |dA|
     // [blocks] steps done << 32 | (exponent of the plane before the last) << 8 | of the last
     unsigned long long *flags;
     int *err;
@@ -268,7 +268,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
     float top = 0.0f;            // largest finite |dA| of this lane
     auto leave_max = [&]() {
         const unsigned m = wave_max(top);
-        if (lane == 0) a.amax[blockIdx.x * kWaves + wave] = m;
+        if (lane == 0) a.amax[blockIdx.x * kWaves + wave] = m >> 23;
     };
 
     if (a.resident[d]) {
@@ -714,10 +714,11 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
         return PLSTM_EHIP;
     timing_end(1, st);
 
-    long long aoff[kDirs + 1];
-    for (int d = 0; d < kDirs; ++d) aoff[d] = (long long)pl.first[d] * kWaves;
-    aoff[kDirs] = (long long)pl.blocks * kWaves;
-    int rc = step_wgrad(g, x, sv.hd, dA, amax, aoff, wgws, dwx, dwh, db, "wgrad_mfma", st);
+    DaMaxima am;
+    am.p = amax;
+    for (int d = 0; d < kDirs; ++d) am.off[d] = (long long)pl.first[d] * kWaves;
+    am.off[kDirs] = (long long)pl.blocks * kWaves;
+    int rc = step_wgrad(g, x, sv.hd, dA, am, wgws, dwx, dwh, db, "wgrad_mfma", st);
     if (rc != PLSTM_OK) return rc;
     if (dx) {
         rc = step_dx(g, wx, dA, fragx, dx, st);

@@ -1819,7 +1819,7 @@ struct LineBwdArgs {
     float *dxd;                 // [4][N][V][C] per-direction dL/dx, or null
     float *dbp;                 // [4][N][nsegmax][4O] bias-gradient partials, or null
     int nsegmax;                // segments of the longest line
-    unsigned *amax;             // largest finite |dA| (bits) of each wave of a segment over
+    unsigned *amax;             // exponent of the largest finite |dA| of each wave of a segment over
     int aoff[kDirs];            // the launches so far, [N][nseg][4] at aoff
     int nseg[kDirs];
     int base[kDirs + 1];
@@ -2107,7 +2107,7 @@ k_line_bwd(LineBwdArgs a)
     for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
     if (lane == 0) {
         unsigned *e = a.amax + a.aoff[d] + (n * a.nseg[d] + seg) * 4 + wave;
-        const unsigned m = __float_as_uint(top);
+        const unsigned m = __float_as_uint(top) >> 23;
         *e = r0 == 0 || m > *e ? m : *e;
     }
     if (a.dbp) {
@@ -3404,8 +3404,8 @@ size_t step_wgrad_ws(const Geom &g)
 }
 
 int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-               const unsigned *amax, const long long *aoff, void *ws, float *dwx, float *dwh,
-               float *db, const char *phase, hipStream_t st)
+               const DaMaxima &am, void *ws, float *dwx, float *dwh, float *db,
+               const char *phase, hipStream_t st)
 {
     const int U = g.O / 16, KK = g.KP * g.KQ, G = 4 * g.O;
     const WgShape w = wg_shape(g);
@@ -3416,9 +3416,9 @@ int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
     // split products, and the fp32 kernel for an input they do not serve (known
     // on the device only: it returns at once where it has no work)
     const unsigned *ctl = nullptr;
-    const bool split = g_wgrad_staged && amax;
+    const bool split = g_wgrad_staged && am.p;
     if (split) {
-        const int rc = split_wgrad(g, x, hd, dA, amax, aoff, partial, rest, &ctl, st);
+        const int rc = split_wgrad(g, x, hd, dA, am, partial, rest, &ctl, st);
         if (rc != PLSTM_OK) return rc;
     }
     WgStepArgs wa;
@@ -3520,8 +3520,7 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
                                   : nullptr;
     unsigned *aml = line_bwd_geom(g) ? cv.take<unsigned>((size_t)g.nd * g.N * line_nsegmax(g) * 4)
                                      : nullptr;
-    const unsigned *amax = nullptr;      // maxima of |dA| (split steps, line blocks)
-    long long aoff[kDirs + 1] = {};
+    DaMaxima am;                          // maxima of |dA| (split steps, line blocks)
     bool db_done = false;
     const long long nvox = (long long)g.N * g.V;
     bool dx_done = false;
@@ -3562,8 +3561,7 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         Carve rest(ws);
         rest.off = sb.used;
         wgws = rest.take<char>(step_wgrad_ws(g));
-        amax = sb.amax;
-        for (int d = 0; d <= kDirs; ++d) aoff[d] = sb.aoff[d];
+        am = sb.am;
     } else if (lines) {
         // 2D layers with 16 units: line blocks, S lines per launch (S r <= 16)
         LineBwdArgs la;
@@ -3581,10 +3579,10 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         for (int d = 0; d < kDirs; ++d) la.nseg[d] = (g.dir[d].Q + kLineSeg - 1) / kLineSeg;
         la.amax = aml;
         for (int d = 0; d < kDirs; ++d) {
-            la.aoff[d] = (int)aoff[d];
-            aoff[d + 1] = aoff[d] + (d < g.nd ? (long long)g.N * la.nseg[d] * 4 : 0);
+            la.aoff[d] = (int)am.off[d];
+            am.off[d + 1] = am.off[d] + (d < g.nd ? (long long)g.N * la.nseg[d] * 4 : 0);
         }
-        amax = aml;
+        am.p = aml;
         const size_t dyn = line_dyn;
         if (hipFuncSetAttribute((const void *)k_line_bwd, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)dyn) != hipSuccess)
@@ -3640,7 +3638,7 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         timing_end(1 + max_T(g), st);
     }
 
-    const int rc = step_wgrad(g, x, sv.hd, dA, amax, aoff, wgws, dwx, dwh, db_done ? nullptr : db,
+    const int rc = step_wgrad(g, x, sv.hd, dA, am, wgws, dwx, dwh, db_done ? nullptr : db,
                               "wgrad_step", st);
     if (rc != PLSTM_OK) return rc;
     if (dx && !dx_done) return step_dx(g, wx, dA, fragx, dx, st);

@@ -252,13 +252,17 @@ def out_of_reach(extents, at, r):
     return near <= len(extents) - 2
 
 
-@pytest.mark.parametrize("loud", [20, 28])
-@pytest.mark.parametrize("path", [0, 2], ids=["whole", "chunked"])
-@pytest.mark.parametrize("shape", [(1, 5, 9, 11, 6, 16, 3), (1, 5, 12, 10, 32, 32, 3), (1, 5, 8, 9, 16, 64, 3),
-                                   (1, 5, 9, 11, 3, 16, 3)], ids=lambda s: "x".join(map(str, s)))
+STEP_REVERSE = [(1, 5, 9, 11, 6, 16, 3), (1, 5, 12, 10, 32, 32, 3), (1, 5, 8, 9, 16, 64, 3), (1, 5, 8, 9, 40, 64, 3)]
+SWEEP_REVERSE = [(1, 5, 9, 11, 3, 16, 3)]
+LOUD = [(s, 0, p) for s in STEP_REVERSE for p in (20, 28, 45, 100)]
+LOUD += [(s, path, p) for s in SWEEP_REVERSE for path in (0, 2) for p in (20, 28)]
+
+
+@pytest.mark.parametrize("shape, path, loud", LOUD, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_reverse_beside_a_loud_voxel(shape, path, loud):
     """Voxels that take nothing from one 2^loud times louder keep their precision, though
-    its block or strip has one scale: the residual half reaches as far down as the first."""
+    its block or strip has one scale: the residual half reaches as far down as the first,
+    and where that is not enough the block keeps fp32."""
     inst = make(shape, 9100 + sum(shape))
     L = inst.layers[0]
     L.wh = without_neighbours(L.wh)
@@ -276,6 +280,49 @@ def test_reverse_beside_a_loud_voxel(shape, path, loud):
     finally:
         P.pyramid_lstm_set_backward_path(0)
     assert np.abs(host(dx)[0][quiet] - ref[quiet]).max() <= TOL * np.abs(ref[quiet]).max()
+
+
+@pytest.mark.parametrize("which, at", [("wh", (0, 3, 1)), ("wx", (2, 18, 2))], ids=["wh", "wx"])
+@pytest.mark.parametrize("shape", STEP_REVERSE, ids=lambda s: "x".join(map(str, s)))
+def test_reverse_with_an_outlier_weight(shape, which, at):
+    """A weight of 1e30 shuts its gate, whose gradient is 0: the other weights of that unit
+    or channel keep theirs."""
+    inst = make(shape, 9100 + sum(shape))
+    L = inst.layers[0]
+    getattr(L, which)[at + (1, 1)] = 1e30
+    dh = synth.upstream_grad(inst.x.shape[:-1] + (shape[5],), 77)
+    with np.errstate(all="ignore"):
+        ref = oracle.backward(inst.x, L.wx, L.wh, L.b, dh)
+    say("split reverse outlier weight", shape, which)
+    x, Ld = dev(inst.x), layer_dev(L)
+    _, saved = layer_forward(x, Ld, training=True)
+    dx, dwx, dwh, db = layer_backward(x, Ld, saved, dev(dh))
+    torch.cuda.synchronize()
+    check_weights(ref, dwx, dwh, db)
+    dx, want = host(dx), ref["dx"]
+    for c in range(shape[4]):
+        assert np.abs(dx[..., c] - want[..., c]).max() <= TOL * np.abs(want[..., c]).max(), c
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 9, 11, 6, 16, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_weight_gradients_of_an_infinite_dh(shape):
+    """Rows of a gate with an infinite gradient are infinite where 64 bits have them so (a
+    residual of infinity makes them NaN)."""
+    inst = make(shape, 9100 + sum(shape))
+    L = inst.layers[0]
+    L.wh[:] = 0
+    dh = synth.upstream_grad(inst.x.shape[:-1] + (shape[5],), 79)
+    dh[0, 0, 4, 5, 7] = np.inf
+    with np.errstate(all="ignore"):
+        ref = oracle.backward(inst.x, L.wx, L.wh, L.b, dh)
+    x, Ld = dev(inst.x), layer_dev(L)
+    say("split infinite dh", shape)
+    _, saved = layer_forward(x, Ld, training=True)
+    _, dwx, _, db = layer_backward(x, Ld, saved, dev(dh))
+    torch.cuda.synchronize()
+    for got, want in ((dwx, ref["dwx"]), (db, ref["db"])):
+        assert np.isinf(want).any()
+        assert (host(got)[np.isinf(want)] == want[np.isinf(want)]).all()
 
 
 @pytest.mark.parametrize("loud", [20, 28])
