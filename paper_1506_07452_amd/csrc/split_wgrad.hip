@@ -45,7 +45,7 @@ struct PrepArgs {
     DaMaxima am;
     const SplitStats *part;
     unsigned *dmax;           // [nd][kMaxWords]
-    unsigned *ctl;            // [0] 1: fp32 products (cleared before), [1] x's largest magnitude (bits)
+    unsigned *ctl;            // [kWgCtl], cleared before
 };
 __global__ void __launch_bounds__(256) k_wg_prep(PrepArgs a)
 {
@@ -87,7 +87,8 @@ struct WgH2Args {
     int nct;                  // parts along the column tiles
     int kch, NTt;             // voxel chunks per part, N-tiles of a row of partial
     const float *x, *hd, *dA;
-    const unsigned *dmax, *ctl;
+    const unsigned *dmax;
+    unsigned *ctl;            // [kWgCtl]
     float *partial;           // [nd][kch][4O][16 NTt]
     int rowB;                 // bytes of a staged [h | x] pixel
     int bufb;                 // bytes of one stage buffer
@@ -163,6 +164,10 @@ k_wgrad_h2(WgH2Args a)
         }
     }
     const int ea = scale_exp(dm), exx = scale_exp(a.ctl[1]);
+    // groups of this wave's staged dA, and the bound below which a value is small, as
+    // (bits << 1) - 1, where zeros are the largest
+    const unsigned low = dm > kStatRange ? ((dm - kStatRange) << 1) - 1u : 0u;
+    int groups = 0, small = 0;
     const float sa = exp2i(ea), sx = exp2i(exx);
 
     // this wave's taps and its lane's rows of a piece (voxel 16 j + 4 q + i of the
@@ -242,6 +247,12 @@ k_wgrad_h2(WgH2Args a)
             const f4 v0 = oka[u] ? ra[u][0] : zero, v1 = oka[u] ? ra[u][1] : zero;
             dbs[0] += v0;
             dbs[1] += v1;
+            unsigned least = ~0u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                least = min(least, min((__float_as_uint(v0[k]) << 1) - 1u, (__float_as_uint(v1[k]) << 1) - 1u));
+            groups += __popcll(__ballot(least != ~0u));
+            small += __popcll(__ballot(least < low));
             const Split8 w = split8(v0 * sa, v1 * sa);
             const int c = ti & 7;
             char *p = buf + ((ti >> 3) + 64 * u) * kRowA + (c >> 1) * 64 + (c & 1) * 16;
@@ -333,6 +344,11 @@ k_wgrad_h2(WgH2Args a)
             if (u + 1 < u1) commit(smem + (((u - u0) & 1) ^ 1) * a.bufb);
             __syncthreads();
         }
+    }
+
+    if (cp == 0 && lane == 0) {
+        atomicAdd(&a.ctl[2 + d], (unsigned)groups);
+        if (small) atomicAdd(&a.ctl[2 + kDirs + d], (unsigned)small);
     }
 
     // the KS waves of an item, summed in order through LDS, one row tile at a time
@@ -483,7 +499,7 @@ WgWs carve_wg(Carve &cv, const Geom &g)
     w.xp = pad8(g.C) != g.C ? cv.take<float>((size_t)g.N * g.V * pad8(g.C)) : nullptr;
     w.part = cv.take<SplitStats>(1);
     w.dmax = cv.take<unsigned>((size_t)g.nd * kMaxWords);
-    w.ctl = cv.take<unsigned>(2);
+    w.ctl = cv.take<unsigned>(kWgCtl);
     return w;
 }
 
@@ -510,7 +526,7 @@ int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
     const WgWs s = carve_wg(cv, g);
     const WgPlan w = wg_plan(g);
     const long long nvox = (long long)g.N * g.V;
-    int rc = split_stats(x, nvox * g.C, s.part, s.ctl, 2, st);
+    int rc = split_stats(x, nvox * g.C, s.part, s.ctl, kWgCtl, st);
     if (rc != PLSTM_OK) return rc;
     if (s.xp) {
         rc = split_pad_x(nvox, g.C, x, s.xp, st);

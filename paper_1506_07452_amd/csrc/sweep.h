@@ -66,8 +66,8 @@ size_t split_bwd_ws(const Geom &g);
 int split_bwd(const Geom &g, const float *wx, const float *wh, const Saved &sv, const float *dh,
               bool with_dx, void *ws, SplitBwd *out, hipStream_t st);
 // Weight and bias gradients the same way (split_wgrad.hip): partial sums
-// [nd][kch][4O][16 NTt] of dA (x) [im2col(h) | im2col(x) | 1].  Where x has no one
-// scale it leaves them to the fp32 kernel, and *ctl (device) is 1.
+// [nd][kch][4O][16 NTt] of dA (x) [im2col(h) | im2col(x) | 1], and the control words
+// (device) that say whether the fp32 kernel is to make them instead (wgrad_keeps_f32).
 struct WgradSplit {
     int kch;
     size_t floats;            // of partial

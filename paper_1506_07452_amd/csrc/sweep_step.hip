@@ -2388,7 +2388,7 @@ struct WgStepArgs {
     int k_mul;                // ceil(2^16 / K)
     const float *xp, *hd, *dA;  // xp: the input x [N][V][Cp] (read one channel per lane)
     float *partial;           // [6][kch][4O][16 NTt]
-    const unsigned *only_if;  // run only where this word is set (null: always)
+    const unsigned *ctl;      // run only where wgrad_keeps_f32 (null: always)
 };
 
 // The wave's share: NTL tiles (compile time) of which `ntl` are real; ONES:
@@ -2552,7 +2552,7 @@ template <int U>
 __global__ void __launch_bounds__(64 * kSW) __attribute__((amdgpu_waves_per_eu(2)))
 k_wgrad_step(WgStepArgs a)
 {
-    if (a.only_if && !*a.only_if) return;
+    if (a.ctl && !wgrad_keeps_f32(a.ctl)) return;
     const int per_xcd = gridDim.x / kXcds;
     const int lblk = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
     const int item = lblk * kSW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -2615,7 +2615,7 @@ k_wgrad_step_reduce(int nd, int O, int C, int Cp, int KK, int NTt, int kch, int 
     const int gu = (int)((i / KC) % G);
     const int d = (int)(i / ((long long)KC * G));
     float acc = 0.0f;
-    if (ctl && *ctl) kch = kch_f32;        // the fp32 kernel's chunks
+    if (ctl && wgrad_keeps_f32(ctl)) kch = kch_f32;        // the fp32 kernel's chunks
     for (int c = 0; c < kch; ++c) acc += partial[(((long long)d * kch + c) * G + gu) * KCp + k];
     if (k < KK * O) {
         dwh[(((long long)d * G + gu) * O + k % O) * KK + k / O] = acc;
@@ -3413,7 +3413,7 @@ int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
     float *partial = cv.take<float>(wg_partial_floats(g));
     void *rest = cv.take<char>(split_wgrad_ws(g));
     timing_begin(phase, st);
-    // split products, and the fp32 kernel for an input they do not serve (known
+    // split products, and the fp32 kernel for an x or dA they do not serve (known
     // on the device only: it returns at once where it has no work)
     const unsigned *ctl = nullptr;
     const bool split = g_wgrad_staged && am.p;
@@ -3428,7 +3428,7 @@ int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
     wa.xp = x; wa.hd = hd; wa.dA = dA;
     wa.partial = partial;
     wa.k_mul = k_mul_of(g);
-    wa.only_if = ctl;
+    wa.ctl = ctl;
     const long long witems = (long long)g.nd * U * w.nblk * w.kch;
     const long long wblocks = (blocks_for(witems, kSW) + kXcds - 1) / kXcds * kXcds;
     switch (U) {

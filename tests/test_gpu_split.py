@@ -353,12 +353,12 @@ def closed_gate_error(ref, got, O, unit):
     return worst
 
 
-@pytest.mark.parametrize("bias", [-18])
+@pytest.mark.parametrize("bias", [-18, -22, -30, -60])
 @pytest.mark.parametrize("shape", [(1, 5, 9, 11, 6, 16, 3), (1, 4, 12, 10, 32, 32, 3), (1, 5, 9, 11, 3, 16, 3)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_weight_gradients_of_a_closed_gate(shape, bias):
     """An input gate shut by its bias has gradients e^bias of the others'; its rows of dW
-    keep their precision beside theirs."""
+    keep their precision beside theirs, in fp32 where one scale does not serve both."""
     inst = make(shape, 9100 + sum(shape))
     L = inst.layers[0]
     L.b[:, 5] = bias
