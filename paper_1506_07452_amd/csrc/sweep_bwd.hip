@@ -15,12 +15,13 @@
 //     transposed recurrent weights are the A operand, resident in LDS, and each
 //     lane ends with four consecutive units of one pixel, so every epilogue
 //     load and store is a 16-byte vector.  dA_{t+1} has one scale per strip and
-//     step, from its own largest |dA| and those its neighbours publish with
-//     their flags.  Its sign alternates from step to step and strip to strip,
+//     step, from its own range of |dA| and those its neighbours publish with
+//     their flags; a step that one scale does not serve (da_wide), or weights,
+//     keep the fp32 instruction on the same LDS.  The scale's sign alternates from step to step and strip to strip,
 //     so that the instruction's rounding towards -inf cancels in db.  The
 //     product gc_t f_t is what plane t - 1 needs, so that is what is kept.
 //     dA of every voxel is kept for (2) and for dL/dx, and each wave leaves the
-//     largest finite |dA| it stored, from which (2) scales its split operands.
+//     largest |dA| it stored, from which (2) scales its split operands.
 // (2) dW = sum over voxels of dA (x) [im2col(h_{t-1}), im2col(x_t), 1]: the
 //     plane-step path's kernels (split_wgrad.hip).
 #include "common.h"
@@ -63,8 +64,9 @@ struct BwdArgs {
     const float *dh;             // dL/dh [N][V][16]
     float *dA;                   // [6][N][V][64] gate pre-activation gradients
     float *gcf;                  // [6][N][V][16] dL/dc_t * f_t, carried to plane t - 1
-    unsigned *amax;              // [blocks][kWaves] exponent of the largest finite |dA|
-    // [blocks] steps done << 32 | (exponent of the plane before the last) << 8 | of the last
+    unsigned *amax;              // [blocks][kWaves] exponent of the largest |dA|
+    // [blocks] steps done << 32 | (range of the plane before the last) << 16 | of the last, a
+    // range being DaRange's two exponents in a byte each
     unsigned long long *flags;
     int *err;
     int max_spin;                // polls before a wait gives up
@@ -73,22 +75,14 @@ struct BwdArgs {
     int resident[kDirs];         // 1: the strip's dA stays in LDS for the sweep
 };
 
-// The largest of `top` and the finite |v|: one comparison of the sixteen values'
-// maximum, and each value's own where that is not finite.
-__device__ inline float top_finite(float top, f4 a, f4 b, f4 c, f4 d)
+// The largest of sixteen magnitudes (a NaN apart: it spreads whichever way it is multiplied).
+__device__ inline float top_of(f4 a, f4 b, f4 c, f4 d)
 {
     float m = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
         m = fmaxf(fmaxf(m, fmaxf(fabsf(a[i]), fabsf(b[i]))), fmaxf(fabsf(c[i]), fabsf(d[i])));
-    if (__builtin_expect(m < __builtin_inff(), 1)) return fmaxf(top, m);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float v[4] = {fabsf(a[i]), fabsf(b[i]), fabsf(c[i]), fabsf(d[i])};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) top = v[k] < __builtin_inff() ? fmaxf(top, v[k]) : top;
-    }
-    return top;
+    return m;
 }
 
 // Epilogue operands of one tile (this lane's pixel, units 4 q4 .. 4 q4 + 3).
@@ -133,9 +127,29 @@ __device__ __forceinline__ f4 contract_bwd(const float *as, const float *was, in
     return join(acc, x0 + x1);
 }
 
-// Scale exponent of a plane whose largest |dA| has the biased exponent `e` (not more
-// than 2^110: denormals, or all zero).
-__device__ inline int plane_exp(int e) { return min(14 - (e - 127), 110); }
+// The same of dA as it is, with the fp32 instruction: a gate-unit a lane group and step.
+// Seldom taken, so nothing is read ahead and little is kept in registers.
+__device__ __forceinline__ f4 contract_bwd_f32(const float *as, const float *was, bool raw, int base,
+                                               int rs, int cs, int q4, int lane)
+{
+    f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int k = 0; k < 2 * kKG; ++k) {
+        const int kg = k >> 1, j = k & 1, tap = kg >> 1, half = kg & 1, ta = (tap * 11) >> 5;
+        const int pp = base - ((ta - 1) * rs + (tap - 3 * ta - 1) * cs);
+        const int o = ((pp * kG + 4 * swz(2 * q4, pp)) ^ (half * 32)) ^ (4 * j);
+        const f4 b = *(const f4 *)&as[o];
+        const h4 hi = *(const h4 *)&was[((kg * 2 + 0) * 64 + lane) * 4 + 2 * j];
+        const h4 lo = *(const h4 *)&was[((kg * 2 + 1) * 64 + lane) * 4 + 2 * j];
+        f4 w = *(const f4 *)&was[((kg * 2 + j) * 64 + lane) * 4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            w[i] = raw ? w[i] : __builtin_fmaf((float)lo[i], kLoInv, (float)hi[i]);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i], b[i], acc, 0, 0, 0);
+        }
+    }
+    return acc;
+}
 
 // One launch, against the contraction on v_mfma_f32_16x16x4 (144 instructions of 32
 // cycles a tile; now 54 of 16): 48 x 240 x 240 3.75 -> 3.05 ms, which is 15.6 GB of
@@ -168,33 +182,60 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
     float *was = smem;
     float *winv = was + kKG * 2 * 64 * 4;
     unsigned *state = (unsigned *)(winv + 16);
-    unsigned *mx = state, *emx = state + 2;  // by step parity: largest |dA| (bits) of the strip, of its edge tiles
-    unsigned *nbe = state + 4;               // exponents of the neighbours' planes
+    // by step parity: range of |dA| (DaRange's x and y) of the strip, of its edge tiles
+    unsigned *mx = state, *emx = state + 4;
+    unsigned *nbe = state + 8;               // ranges of the neighbours' planes, x | y << 8
     float *as = smem + kWaFloats;
-    unsigned *wmx = (unsigned *)as;          // the weights' largest magnitudes, only here
-    if (threadIdx.x < 16) wmx[threadIdx.x] = state[threadIdx.x] = 0u;
-    __syncthreads();
-    for (int e = threadIdx.x; e < kG * kO * 9; e += kThreads) {
-        const unsigned m = __float_as_uint(a.wh[(long long)d * kG * kO * 9 + e]) & 0x7fffffffu;
-        if (m < 0x7f800000u) atomicMax(&wmx[e / 9 % kO], m);
+    // the weights' largest and smallest magnitudes and counts by unit, only here
+    unsigned *wmx = (unsigned *)as, *wmn = wmx + 16, *wnz = wmx + 32, *wsm = wmx + 48;
+    if (threadIdx.x < 16) {
+        wmx[threadIdx.x] = wnz[threadIdx.x] = wsm[threadIdx.x] = state[threadIdx.x] = 0u;
+        wmn[threadIdx.x] = ~0u;
     }
     __syncthreads();
-    if (threadIdx.x < 16) winv[threadIdx.x] = exp2i(-scale_exp(wmx[threadIdx.x]));
+    const float *const wh_d = a.wh + (long long)d * kG * kO * 9;
+    const int wrow = threadIdx.x & 15;               // a unit's nine taps of one gate-unit a thread
+    static_assert(kThreads == kG * kO, "");
+    auto tap_bits = [&](int tap) {
+        return __float_as_uint(wh_d[threadIdx.x * 9 + tap]) & 0x7fffffffu;
+    };
+    {
+        unsigned m0 = 0u, m1 = ~0u;
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+            m0 = max(m0, tap_bits(tap));
+            m1 = min(m1, tap_bits(tap) - 1u);        // (zeros apart)
+        }
+        atomicMax(&wmx[wrow], m0);
+        atomicMin(&wmn[wrow], m1);
+    }
+    __syncthreads();
+    bool wild = wmx[wrow] >= 0x7f800000u;
+    if (__syncthreads_or(wmn[wrow] != ~0u && wmn[wrow] + 1u + kStatRange < wmx[wrow])) {   // (seldom)
+        for (int tap = 0; tap < 9; ++tap) {
+            const unsigned m = tap_bits(tap);
+            if (m) atomicAdd(&wnz[wrow], 1u);
+            if (m && m + kStatRange < wmx[wrow]) atomicAdd(&wsm[wrow], 1u);
+        }
+        __syncthreads();
+        wild |= wsm[wrow] > wnz[wrow] / 64u;
+    }
+    const bool raw = __syncthreads_or(wild) != 0;    // fp32 weights
+    if (threadIdx.x < 16) winv[threadIdx.x] = raw ? 1.0f : exp2i(-scale_exp(wmx[threadIdx.x]));
     for (int e = threadIdx.x; e < kKG * 64; e += kThreads) {
         const int l = e & 63, kg = e >> 6;
         const int lq = l >> 4, lc = l & 15, tap = kg >> 1;
-        const float sc = exp2i(scale_exp(wmx[lc]));
+        const float sc = raw ? 1.0f : exp2i(scale_exp(wmx[lc]));
         f4 v[2];
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            v[j >> 2][j & 3] =
-                a.wh[(((long long)d * kG + 32 * (kg & 1) + 8 * lq + j) * kO + lc) * 9 + tap] * sc;
+            v[j >> 2][j & 3] = wh_d[((32 * (kg & 1) + 8 * lq + j) * kO + lc) * 9 + tap] * sc;
         const Split8 sp = split8(v[0], v[1]);
-        *(h8 *)&was[((kg * 2 + 0) * 64 + l) * 4] = sp.hi;
-        *(h8 *)&was[((kg * 2 + 1) * 64 + l) * 4] = sp.lo;
+        *(h8 *)&was[((kg * 2 + 0) * 64 + l) * 4] = raw ? __builtin_bit_cast(h8, v[0]) : sp.hi;
+        *(h8 *)&was[((kg * 2 + 1) * 64 + l) * 4] = raw ? __builtin_bit_cast(h8, v[1]) : sp.lo;
     }
     __syncthreads();                         // (wmx's words are staged over next)
-    // Waits (bounded) for the neighbours' step r and leaves the exponents of the
+    // Waits (bounded) for the neighbours' step r and leaves the ranges of the
     // planes they then finished; a neighbour may be one step further.
     auto wait_neighbours = [&](int r) {
         const int nb = threadIdx.x == 0 ? nb_lo : (threadIdx.x == 1 ? nb_hi : -1);
@@ -212,21 +253,29 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                 __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
                 break;
         }
-        nbe[threadIdx.x] = ((int)(w >> 32) > r ? w >> 8 : w) & 255u;
+        nbe[threadIdx.x] = ((int)(w >> 32) > r ? w >> 16 : w) & 0xffffu;
     };
-    // Publishes r + 1 steps with the exponents of this plane and the one before
-    // (`m`: the maxima by step parity).
+    // Publishes r + 1 steps with the ranges of this plane and the one before
+    // (`m`: by step parity).
     auto publish = [&](int r, const unsigned *m) {
-        const unsigned cur = m[r & 1] >> 23, before = m[(r & 1) ^ 1] >> 23;
+        const int p = 2 * (r & 1), q = p ^ 2;
+        const unsigned cur = m[p] | m[p + 1] << 8, before = m[q] | m[q + 1] << 8;
         const unsigned long long w =
-            (unsigned long long)(r + 1) << 32 | before << 8 | cur;
+            (unsigned long long)(r + 1) << 32 | before << 16 | cur;
         __hip_atomic_store(&a.flags[blockIdx.x], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    // Exponent of dA_{t+1}'s scale at step r (all threads, after the wait's barrier).
-    auto step_exp = [&](int r) {
-        int e = (int)(mx[(r & 1) ^ 1] >> 23);
-        e = max(e, max((int)nbe[0], (int)nbe[1]));
-        return __builtin_amdgcn_readfirstlane(plane_exp(e));
+    // Range of dA_{t+1} at step r (all threads, after the wait's barrier).
+    auto step_range = [&](int r) {
+        const int q = 2 * ((r & 1) ^ 1);
+        DaRange v = {(unsigned short)mx[q], (unsigned short)mx[q + 1]};
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            v = da_join(v, DaRange{(unsigned short)(nbe[k] & 255u), (unsigned short)(nbe[k] >> 8)});
+        return __builtin_bit_cast(DaRange, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+    };
+    auto widen = [&](unsigned *m, DaRange v) {           // (one lane of a wave)
+        atomicMax(&m[0], (unsigned)v.x);
+        atomicMax(&m[1], (unsigned)v.y);
     };
     auto step_sign = [&](int r) { return (strip + r) & 1 ? -1.0f : 1.0f; };
     auto wave_max = [&](float v) {
@@ -265,7 +314,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                ((pc == q1 - 1) & (nb_hi >= 0));
     };
 
-    float top = 0.0f;            // largest finite |dA| of this lane
+    float top = 0.0f;            // largest |dA| of this lane
     auto leave_max = [&]() {
         const unsigned m = wave_max(top);
         if (lane == 0) a.amax[blockIdx.x * kWaves + wave] = m >> 23;
@@ -324,12 +373,15 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
             const int nplane = has_next ? (s + dg.sign) * ss : splane;
             const int pplane = has_prev ? (s - dg.sign) * ss : splane;
             float inv = 0.0f;
+            bool f32 = false;
             if (r > 0) {
                 wait_neighbours(r);
                 __syncthreads();
-                const int ex = step_exp(r);
+                const DaRange range = step_range(r);
+                const int ex = da_exp(range);
                 const float scale = step_sign(r) * exp2i(ex);
-                inv = step_sign(r) * exp2i(-ex);
+                f32 = raw || da_wide(range);
+                inv = f32 ? 1.0f : step_sign(r) * exp2i(-ex);
                 // every contraction has read dA_{t+2}: overwrite it with dA_{t+1}
 #pragma unroll
                 for (int it = 0; it < 2; ++it) {
@@ -337,6 +389,10 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     const int pb = hbase[it];
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
+                        if (f32) {
+                            *(f4 *)&as[pb * kG + 4 * swz(4 * g + q4, pb)] = hold[it][g];
+                            continue;
+                        }
                         const Split4 sp = split4(hold[it][g] * scale);
                         // gate-units 16 g + 4 q4 .. + 3: half of slot 2 g + q4 / 2
                         const int c = 2 * (2 * g + (q4 >> 1)), o = 2 * (q4 & 1);
@@ -369,7 +425,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                 }
                 __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
                 asm volatile("" ::: "memory");
-                for (int i = wave; i < 2 * nslot; i += kWaves) {
+                for (int i = f32 ? 2 * nslot : wave; i < 2 * nslot; i += kWaves) {
                     const int side = i >= nslot ? 1 : 0;
                     const int row = 4 * (i - side * nslot) + (lane >> 3);
                     if ((side ? nb_hi : nb_lo) < 0 || lane >= 32 || row >= P) continue;
@@ -377,7 +433,8 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                 }
                 if (threadIdx.x == 0) {
                     cnt[0] = 0;
-                    mx[r & 1] = emx[r & 1] = 0u;
+                    const int p = 2 * (r & 1);
+                    mx[p] = mx[p + 1] = emx[p] = emx[p + 1] = 0u;
                 }
                 __syncthreads();
             }
@@ -407,9 +464,13 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     e.cp = *(const f4 *)&cell_dn[vop * kO + 4 * q4];
                     __builtin_amdgcn_sched_barrier(0);
                     f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-                    if (has_next)
-                        acc = contract_bwd(as, was, base, 1, P2, q4, lane) * inv *
-                              *(const f4 *)&winv[4 * q4];
+                    if (has_next) {
+                        if (__builtin_expect(f32, 0))
+                            acc = contract_bwd_f32(as, was, raw, base, 1, P2, q4, lane);
+                        else
+                            acc = contract_bwd(as, was, base, 1, P2, q4, lane);
+                        acc = acc * inv * *(const f4 *)&winv[4 * q4];
+                    }
                     f4 dAi, dAf, dAg, dAo, gcf;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
@@ -424,13 +485,6 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                         dAg[i] = gcs * e.gi[i] * (1.0f - e.gg[i] * e.gg[i]);
                         dAo[i] = gh * tc * e.go[i] * (1.0f - e.go[i]);
                     }
-                    const float tm = top_finite(0.0f, dAi, dAf, dAg, dAo);
-                    const unsigned tmax = wave_max(tm);
-                    top = fmaxf(top, tm);
-                    if (lane == 0) {
-                        atomicMax(&mx[r & 1], tmax);
-                        if (k < n_edge) atomicMax(&emx[r & 1], tmax);
-                    }
                     const int o4 = vo * kG + 4 * q4;
                     if (shared) {
                         store_coherent(dA_rs, o4 + 0 * kO, dAi);
@@ -443,6 +497,14 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                         *(f4 *)&dst[1 * kO] = dAf;
                         *(f4 *)&dst[2 * kO] = dAg;
                         *(f4 *)&dst[3 * kO] = dAo;
+                    }
+                    // (beside the stores)
+                    const float tm = top_of(dAi, dAf, dAg, dAo);
+                    const DaRange tr = da_wave(__float_as_uint(tm));
+                    top = fmaxf(top, tm);
+                    if (lane == 0) {
+                        widen(&mx[2 * (r & 1)], tr);
+                        if (k < n_edge) widen(&emx[2 * (r & 1)], tr);
                     }
                     carry_gcf[it] = gcf;
                     carry_c[it] = e.cp;
@@ -474,14 +536,18 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
         const int s = dg.sign > 0 ? t : dg.T - 1 - t;
         const bool has_next = t + 1 < dg.T, has_prev = t > 0;
         // ---- wait for the neighbours' dA_{t+1} --------------------------
-        float scale = 0.0f, inv = 0.0f, step_top = 0.0f;
+        float scale = 0.0f, inv = 0.0f;
+        DaRange wave_range = {0, 0};        // of this wave's tiles
+        bool f32 = false;
         if (r > 0) {
             wait_neighbours(r);
             __syncthreads();
-            const int ex = step_exp(r);
+            const DaRange range = step_range(r);
+            const int ex = da_exp(range);
             scale = step_sign(r) * exp2i(ex);
-            inv = step_sign(r) * exp2i(-ex);
-            if (threadIdx.x == 0) mx[r & 1] = 0u;
+            f32 = raw || da_wide(range);
+            inv = f32 ? 1.0f : step_sign(r) * exp2i(-ex);
+            if (threadIdx.x == 0) mx[2 * (r & 1)] = mx[2 * (r & 1) + 1] = 0u;
             // (ordered before this step's maxima by the chunks' barriers)
         }
         const int splane = s * ss;
@@ -519,7 +585,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
             __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
             asm volatile("" ::: "memory");
             // each wave splits the pixels it moved (eight slots a pixel)
-            if (has_next)
+            if (has_next && !f32)
                 for (int i = wave + (lane >> 5) * kWaves; i < nslots; i += 2 * kWaves) {
                     const int pix = 4 * i + ((lane >> 3) & 3);
                     if (pix < npl) split_slot(pix, lane & 7, scale);
@@ -565,7 +631,9 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     dAg[i] = gcs * e.gi[i] * (1.0f - e.gg[i] * e.gg[i]);
                     dAo[i] = gh * tc * e.go[i] * (1.0f - e.go[i]);
                 }
-                step_top = top_finite(step_top, dAi, dAf, dAg, dAo);
+                const float tm = top_of(dAi, dAf, dAg, dAo);
+                wave_range = da_join(wave_range, da_wave(__float_as_uint(tm)));
+                top = fmaxf(top, tm);
                 const int o4 = vo * kG + 4 * q4;
                 float *dst = &dA_dn[o4];
                 if (shared) {
@@ -591,17 +659,19 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                 // otherwise sink them to their use and expose their latency)
                 __builtin_amdgcn_sched_barrier(0);
                 f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (has_next)
-                    acc = contract_bwd(as, was, base, W2, 1, q4, lane) * inv *
-                          *(const f4 *)&winv[4 * q4];
+                if (has_next) {
+                    if (__builtin_expect(f32, 0))
+                        acc = contract_bwd_f32(as, was, raw, base, W2, 1, q4, lane);
+                    else
+                        acc = contract_bwd(as, was, base, W2, 1, q4, lane);
+                    acc = acc * inv * *(const f4 *)&winv[4 * q4];
+                }
                 epilogue(vo, shared, acc, e);
             }
             __syncthreads();
         }
         // ---- publish dA_t: every wave's coherent stores have completed ---
-        top = fmaxf(top, step_top);
-        const unsigned smax = wave_max(step_top);
-        if (lane == 0) atomicMax(&mx[r & 1], smax);
+        if (lane == 0) widen(&mx[2 * (r & 1)], wave_range);
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         __syncthreads();
         if (threadIdx.x == 0) publish(r, mx);

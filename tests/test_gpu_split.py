@@ -253,9 +253,9 @@ def out_of_reach(extents, at, r):
 
 
 STEP_REVERSE = [(1, 5, 9, 11, 6, 16, 3), (1, 5, 12, 10, 32, 32, 3), (1, 5, 8, 9, 16, 64, 3), (1, 5, 8, 9, 40, 64, 3)]
-SWEEP_REVERSE = [(1, 5, 9, 11, 3, 16, 3)]
+SWEEP_REVERSE = [(1, 5, 9, 11, 3, 16, 3), (1, 19, 40, 52, 2, 16, 3)]    # one strip a direction, several
 LOUD = [(s, 0, p) for s in STEP_REVERSE for p in (20, 28, 45, 100)]
-LOUD += [(s, path, p) for s in SWEEP_REVERSE for path in (0, 2) for p in (20, 28)]
+LOUD += [(s, path, p) for s in SWEEP_REVERSE for path in (0, 2) for p in (20, 28, 45, 100)]
 
 
 @pytest.mark.parametrize("shape, path, loud", LOUD, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
@@ -283,28 +283,33 @@ def test_reverse_beside_a_loud_voxel(shape, path, loud):
 
 
 @pytest.mark.parametrize("which, at", [("wh", (0, 3, 1)), ("wx", (2, 18, 2))], ids=["wh", "wx"])
-@pytest.mark.parametrize("shape", STEP_REVERSE, ids=lambda s: "x".join(map(str, s)))
-def test_reverse_with_an_outlier_weight(shape, which, at):
+@pytest.mark.parametrize("shape, path", [(s, 0) for s in STEP_REVERSE] + [(s, p) for s in SWEEP_REVERSE for p in (0, 2)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_reverse_with_an_outlier_weight(shape, path, which, at):
     """A weight of 1e30 shuts its gate, whose gradient is 0: the other weights of that unit
     or channel keep theirs."""
     inst = make(shape, 9100 + sum(shape))
     L = inst.layers[0]
-    getattr(L, which)[at + (1, 1)] = 1e30
+    getattr(L, which)[at[:2] + (min(at[2], getattr(L, which).shape[2] - 1), 1, 1)] = 1e30
     dh = synth.upstream_grad(inst.x.shape[:-1] + (shape[5],), 77)
     with np.errstate(all="ignore"):
         ref = oracle.backward(inst.x, L.wx, L.wh, L.b, dh)
-    say("split reverse outlier weight", shape, which)
+    say("split reverse outlier weight", shape, path, which)
     x, Ld = dev(inst.x), layer_dev(L)
-    _, saved = layer_forward(x, Ld, training=True)
-    dx, dwx, dwh, db = layer_backward(x, Ld, saved, dev(dh))
-    torch.cuda.synchronize()
+    P.pyramid_lstm_set_backward_path(path)
+    try:
+        _, saved = layer_forward(x, Ld, training=True)
+        dx, dwx, dwh, db = layer_backward(x, Ld, saved, dev(dh))
+        torch.cuda.synchronize()
+    finally:
+        P.pyramid_lstm_set_backward_path(0)
     check_weights(ref, dwx, dwh, db)
     dx, want = host(dx), ref["dx"]
     for c in range(shape[4]):
         assert np.abs(dx[..., c] - want[..., c]).max() <= TOL * np.abs(want[..., c]).max(), c
 
 
-@pytest.mark.parametrize("shape", [(1, 1, 9, 11, 6, 16, 3)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [(1, 1, 9, 11, 6, 16, 3), (1, 1, 9, 11, 3, 16, 3)], ids=lambda s: "x".join(map(str, s)))
 def test_weight_gradients_of_an_infinite_dh(shape):
     """Rows of a gate with an infinite gradient are infinite where 64 bits have them so (a
     residual of infinity makes them NaN)."""
