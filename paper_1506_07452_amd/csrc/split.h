@@ -230,6 +230,11 @@ __device__ inline DaRange da_shuffle(DaRange r, int o)
 {
     return __builtin_bit_cast(DaRange, __shfl_xor(__builtin_bit_cast(int, r), o));
 }
+// Of one pixel whose largest is `m` (bits).
+__device__ inline DaRange da_of(unsigned m)
+{
+    return {(unsigned short)(m >> 23), (unsigned short)(m ? 255u - (m >> 23) : 0u)};
+}
 // Over a wave whose lanes l, l + 16, l + 32, l + 48 hold one pixel's largest (bits).
 __device__ inline DaRange da_wave(unsigned m)
 {
@@ -238,7 +243,7 @@ __device__ inline DaRange da_wave(unsigned m)
         const unsigned t = __shfl_xor(m, o);
         m = t > m ? t : m;
     }
-    DaRange r = {(unsigned short)(m >> 23), (unsigned short)(m ? 255u - (m >> 23) : 0u)};
+    DaRange r = da_of(m);
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) r = da_join(r, da_shuffle(r, o));
     return r;

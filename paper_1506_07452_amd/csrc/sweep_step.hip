@@ -1786,8 +1786,9 @@ struct BwdStepArgs {
 // back S lines per launch with overlapped tiles.  At reverse line j it
 // computes the segment widened by (S - j) r pixels on each side: line j + 1
 // reads all but the outer r of them (the outer r serve dL/dx).  dA_{t+1} (64
-// gate-units per pixel as split pairs (split.h) scaled by the line's largest |dA|,
-// 16-byte chunks XOR-swizzled by the pixel; overwritten after a barrier) and
+// gate-units per pixel as split pairs (split.h) scaled by the line's largest |dA|, or as
+// they are where one scale does not serve the line (da_wide) or the weights, 16-byte
+// chunks XOR-swizzled by the pixel; overwritten after a barrier) and
 // gc_{t+1} f_{t+1} (in place) stay in LDS, and so does
 // the c_{t-1} read at line t, which is the next line's c.  The saved gates and
 // dL/dh are read per tile; only the segment's own dA_t is stored, and gc_t f_t
@@ -1813,13 +1814,13 @@ struct LineBwdArgs {
     Geom g;
     int r0, S;                  // first reverse step of this launch, steps per launch
     const h8 *frag, *fragx;     // W_h^T and W_x^T fragments (k_pack_line_bwd)
-    const float *rinv;          // [4][32] 1 / scales of W_h^T's 16 rows, W_x^T's 4
+    const float *rinv;          // [4][32] 1 / scales of W_h^T's 16 rows, W_x^T's 4; whether they are fp32
     const float *gates, *cell, *dh;
     float *dA, *gcf;
     float *dxd;                 // [4][N][V][C] per-direction dL/dx, or null
     float *dbp;                 // [4][N][nsegmax][4O] bias-gradient partials, or null
     int nsegmax;                // segments of the longest line
-    unsigned *amax;             // exponent of the largest finite |dA| of each wave of a segment over
+    unsigned *amax;             // exponent of the largest |dA| of each wave of a segment over
     int aoff[kDirs];            // the launches so far, [N][nseg][4] at aoff
     int nseg[kDirs];
     int base[kDirs + 1];
@@ -1828,47 +1829,62 @@ struct LineBwdArgs {
 // A fragments of k_line_bwd, one workgroup per direction: K-group 2 tap + half covers
 // gate-units 32 half .. + 31.  frag[d][kg][hi, lo][lane]: gate-units 8 (l / 16) .. + 7 of
 // output unit l % 16; fragx[d][kg][hi, lo][l / 16][4]: of input channel 0 .. 3 (zero
-// past C).
+// past C).  Either holds fp32 values where one of its rows has no one scale (rinv[20],
+// rinv[21] are 1).
 __global__ void __launch_bounds__(256)
 k_pack_line_bwd(int C, int KQ, const float *__restrict__ wx, const float *__restrict__ wh,
                 h8 *__restrict__ frag, h8 *__restrict__ fragx, float *__restrict__ rinv)
 {
     constexpr int O = 16, G = 64;
-    __shared__ unsigned mx[20];
+    __shared__ unsigned mx[20], nonzero[20], small[20];
     const int d = blockIdx.x, tid = threadIdx.x, NK = 2 * KQ, Cx = min(C, 4);
-    if (tid < 20) mx[tid] = 0u;
+    if (tid < 20) mx[tid] = nonzero[tid] = small[tid] = 0u;
     __syncthreads();
-    for (int e = tid; e < G * O * KQ; e += 256) {
-        const unsigned m = __float_as_uint(wh[(long long)d * G * O * KQ + e]) & 0x7fffffffu;
-        if (m < 0x7f800000u) atomicMax(&mx[e / KQ % O], m);
-    }
-    for (int e = tid; e < G * Cx * KQ; e += 256) {
-        const int gu = e / (Cx * KQ), c = e / KQ % Cx, tap = e % KQ;
-        const unsigned m = __float_as_uint(wx[(((long long)d * G + gu) * C + c) * KQ + tap]) & 0x7fffffffu;
-        if (m < 0x7f800000u) atomicMax(&mx[16 + c], m);
-    }
+    auto each = [&](auto use) {                 // (row, magnitude) of this thread's weights
+        for (int e = tid; e < G * O * KQ; e += 256)
+            use(e / KQ % O, __float_as_uint(wh[(long long)d * G * O * KQ + e]) & 0x7fffffffu);
+        for (int e = tid; e < G * Cx * KQ; e += 256) {
+            const int gu = e / (Cx * KQ), c = e / KQ % Cx, tap = e % KQ;
+            use(16 + c, __float_as_uint(wx[(((long long)d * G + gu) * C + c) * KQ + tap]) & 0x7fffffffu);
+        }
+    };
+    each([&](int row, unsigned m) { atomicMax(&mx[row], m); });
     __syncthreads();
-    if (tid < 32) rinv[d * 32 + tid] = tid < 20 ? exp2i(-scale_exp(mx[tid])) : 0.0f;
+    bool any = false;
+    each([&](int row, unsigned m) { any |= m != 0 && m + kStatRange < mx[row]; });
+    if (__syncthreads_or(any)) {                // (seldom)
+        each([&](int row, unsigned m) {
+            if (m) atomicAdd(&nonzero[row], 1u);
+            if (m && m + kStatRange < mx[row]) atomicAdd(&small[row], 1u);
+        });
+        __syncthreads();
+    }
+    const int r20 = tid % 20;
+    const bool wild = mx[r20] >= 0x7f800000u || small[r20] > nonzero[r20] / 64u;
+    const bool rawh = __syncthreads_or(wild && r20 < 16) != 0, rawx = __syncthreads_or(wild && r20 >= 16) != 0;
+    auto exponent = [&](int row) { return (row < 16 ? rawh : rawx) ? 0 : scale_exp(mx[row]); };
+    if (tid < 32)
+        rinv[d * 32 + tid] = tid < 20 ? exp2i(-exponent(tid)) : (tid == 20 && rawh) || (tid == 21 && rawx) ? 1.0f : 0.0f;
     for (int e = tid; e < NK * 64; e += 256) {
         const int l = e & 63, kg = e >> 6, col = l & 15, g0 = 32 * (kg & 1) + 8 * (l >> 4);
         f4 w[2], v[2];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const long long gu = (long long)d * G + g0 + j;
-            w[j >> 2][j & 3] = wh[(gu * O + col) * KQ + (kg >> 1)] * exp2i(scale_exp(mx[col]));
+            w[j >> 2][j & 3] = wh[(gu * O + col) * KQ + (kg >> 1)] * exp2i(exponent(col));
             v[j >> 2][j & 3] = col < Cx ? wx[(gu * C + col) * KQ + (kg >> 1)] *
-                                              exp2i(scale_exp(mx[16 + (col & 3)]))
+                                              exp2i(exponent(16 + (col & 3)))
                                         : 0.0f;
         }
         const Split8 sw = split8(w[0], w[1]);
         h8 *o = frag + ((long long)d * NK + kg) * 128 + l;
-        o[0] = sw.hi;
-        o[64] = sw.lo;
+        o[0] = rawh ? __builtin_bit_cast(h8, w[0]) : sw.hi;
+        o[64] = rawh ? __builtin_bit_cast(h8, w[1]) : sw.lo;
         if (col < 4) {
             const Split8 sv = split8(v[0], v[1]);
             h8 *ox = fragx + ((long long)d * NK + kg) * 32 + (l >> 4) * 4 + col;
-            ox[0] = sv.hi;
-            ox[16] = sv.lo;
+            ox[0] = rawx ? __builtin_bit_cast(h8, v[0]) : sv.hi;
+            ox[16] = rawx ? __builtin_bit_cast(h8, v[1]) : sv.lo;
         }
     }
 }
@@ -1885,7 +1901,7 @@ k_line_bwd(LineBwdArgs a)
 {
     constexpr int O = 16, G = 64;
     __shared__ f4 gcb[kLineSlots][4];           // gc f, chunk ^ (slot & 3)
-    __shared__ unsigned lmx[2];                 // largest finite |dA| of a line, by parity
+    __shared__ unsigned lmx[2][2];              // range of |dA| of a line, by parity
     __shared__ f4 cl[kLineSlots][4];            // c_{t-1} read at line t: line t - 1's c
     __shared__ f4 dbr[4][4][4];                 // bias-gradient sums [wave][gate][q4]
     extern __shared__ f4 dyn[];
@@ -1918,19 +1934,23 @@ k_line_bwd(LineBwdArgs a)
     h8 *afr = (h8 *)dyn;                        // [NK][hi, lo][64 lanes]
     f4 *dab = dyn + NK * 128;                   // [kLineSlots][16], chunk ^ (slot & 15)
     h8 *xfr = (h8 *)(dab + kLineSlots * 16);    // [NK][hi, lo][4][4]
-    float top = 0.0f;                           // largest finite |dA| of this lane's segment
-    auto finite_max = [](float m, f4 v) {
+    float top = 0.0f;                           // largest |dA| of this lane's segment
+    auto max_of = [](float m, f4 v) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float x = fabsf(v[u]);
-            m = x < __builtin_inff() ? fmaxf(m, x) : m;
-        }
+        for (int u = 0; u < 4; ++u) m = fmaxf(m, fabsf(v[u]));
         return m;
     };
-    auto wave_max = [&](float v) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-        return __float_as_uint(v);
+    const bool rawh = a.rinv[d * 32 + 20] != 0.0f, rawx = a.rinv[d * 32 + 21] != 0.0f;
+    bool f32;                                   // the line in dab is fp32
+    // joins the wave's range into line parity p's
+    auto leave_range = [&](int p, DaRange r) {
+        if (lane == 0) {
+            atomicMax(&lmx[p][0], (unsigned)r.x);
+            atomicMax(&lmx[p][1], (unsigned)r.y);
+        }
+    };
+    auto line_range = [&](int p) {
+        return DaRange{(unsigned short)lmx[p][0], (unsigned short)lmx[p][1]};
     };
     auto line_sign = [&](int t) { return (t + seg) & 1 ? -1.0f : 1.0f; };
     const f4 ri = *(const f4 *)(a.rinv + d * 32 + 4 * q4), rx = *(const f4 *)(a.rinv + d * 32 + 16);
@@ -1943,14 +1963,14 @@ k_line_bwd(LineBwdArgs a)
         for (int e = threadIdx.x; e < NK * 128; e += 256) afr[e] = src[e];
         if (want_dx)
             for (int e = threadIdx.x; e < NK * 32; e += 256) xfr[e] = a.fragx[(long long)d * NK * 32 + e];
-        if (threadIdx.x < 2) lmx[threadIdx.x] = 0u;
+        if (threadIdx.x < 4) lmx[threadIdx.x >> 1][threadIdx.x & 1] = 0u;
         __syncthreads();
         const int tn = T - r0;                  // line t + 1 for t = T - 1 - r0
         const int sn = dg.sign > 0 ? tn : T - 1 - tn;
         const int nsl = kLineSeg + 2 * (S + 1) * rq;
         constexpr int kIt = (kLineSlots * 8 + 255) / 256;
         f4 v[kIt][2];
-        float m = 0.0f;
+        DaRange wr = {0, 0};
 #pragma unroll
         for (int k = 0; k < kIt; ++k) {
             const int e = threadIdx.x + 256 * k, slot = e >> 3, ch = e & 7;
@@ -1958,35 +1978,59 @@ k_line_bwd(LineBwdArgs a)
             const bool ok = r0 > 0 && slot < nsl && (unsigned)qq < (unsigned)Q;
             const int vx = sn * ss + qq * sq;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < 2; ++h)
                 v[k][h] = bload4(rs_dA, sel_off(ok, (unsigned)((vx * G + 8 * ch + 4 * h) * 4)));
-                m = finite_max(m, v[k][h]);
-            }
             if (ch < 4 && slot < kLineSlots)
                 gcb[slot][ch ^ (slot & 3)] = bload4(rs_gcf, sel_off(ok, (unsigned)((vx * O + 4 * ch) * 4)));
         }
-        const unsigned wm = wave_max(m);
-        if (lane == 0) atomicMax(&lmx[1], wm);
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) {          // a pixel is eight lanes
+            float m = max_of(max_of(0.0f, v[k][0]), v[k][1]);
+#pragma unroll
+            for (int o = 4; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+            wr = da_join(wr, da_of(__float_as_uint(m)));
+        }
+#pragma unroll
+        for (int o = 32; o > 4; o >>= 1) wr = da_join(wr, da_shuffle(wr, o));
+        leave_range(1, wr);
         __syncthreads();
-        const int ex = scale_exp(lmx[1]);
+        const DaRange range = line_range(1);
+        const int ex = da_exp(range);
+        f32 = rawh || rawx || da_wide(range);
         scale = line_sign(tn) * exp2i(ex);
-        inv = line_sign(tn) * exp2i(-ex);
+        inv = f32 ? 1.0f : line_sign(tn) * exp2i(-ex);
 #pragma unroll
         for (int k = 0; k < kIt; ++k) {
             const int e = threadIdx.x + 256 * k, slot = e >> 3, ch = e & 7;
             if (slot >= kLineSlots) continue;
-            const Split8 sp = split8(v[k][0] * scale, v[k][1] * scale);
+            Split8 sp = split8(v[k][0] * scale, v[k][1] * scale);
+            if (f32) sp = {__builtin_bit_cast(h8, v[k][0]), __builtin_bit_cast(h8, v[k][1])};
             ((h8 *)dab)[slot * 16 + ((2 * ch) ^ (slot & 15))] = sp.hi;
             ((h8 *)dab)[slot * 16 + ((2 * ch + 1) ^ (slot & 15))] = sp.lo;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) lmx[1] = 0u;          // (line j = 0 uses lmx[0]; ordered by its barriers)
+    if (threadIdx.x < 2) lmx[1][threadIdx.x] = 0u;          // (line j = 0 uses lmx[0]; ordered by its barriers)
 
     const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     // sum over the taps of W^T dA[slot - (tap - r)], 64 gate-units of one line, scaled
-    auto contract = [&](int slot, auto weight) {
+    auto contract = [&](int slot, bool raw, auto weight) {
         f4 acc = zero, x0 = zero, x1 = zero;
+        if (__builtin_expect(f32, 0)) {
+#pragma unroll 1
+            for (int kg = 0; kg < NK; ++kg) {
+                const int sx = slot - ((kg >> 1) - rq);
+                const int o = sx * 16 + ((8 * (kg & 1) + 2 * q4) ^ (sx & 15));
+                const f4 b0 = dab[o], b1 = dab[o ^ 1];
+                const Wide8 w = widen8(weight(kg, 0), weight(kg, 1), raw);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    acc = mfma(w.a[i], b0[i], acc);
+                    acc = mfma(w.b[i], b1[i], acc);
+                }
+            }
+            return acc;
+        }
         for (int kg = 0; kg < NK; ++kg) {
             const int sx = slot - ((kg >> 1) - rq);
             const int o = sx * 16 + ((8 * (kg & 1) + 2 * q4) ^ (sx & 15));
@@ -2009,7 +2053,7 @@ k_line_bwd(LineBwdArgs a)
         // the one LDS buffer
         f4 dv[2][4];
         bool onv[2];
-        float lm = 0.0f;
+        unsigned pm[2] = {0u, 0u};              // largest |dA| of this lane's pixel of each tile (bits)
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int i = wave + 4 * k;
@@ -2033,7 +2077,7 @@ k_line_bwd(LineBwdArgs a)
             const f4 dhv = bload4(rs_dh, sel_off(on, (unsigned)((vox * O + 4 * q4) * 4)));
             f4 acc = zero;
             if (has_next)
-                acc = contract(slot, [&](int kg, int hl) { return afr[(kg * 2 + hl) * 64 + lane]; }) * ri;
+                acc = contract(slot, rawh, [&](int kg, int hl) { return afr[(kg * 2 + hl) * 64 + lane]; }) * ri;
             // gc f and c are read and rewritten by their own lane only
             const f4 gn = has_next ? gcb[slot][gsw] : zero;
             cl[slot][gsw] = cp;
@@ -2051,15 +2095,14 @@ k_line_bwd(LineBwdArgs a)
                 gco[u] = gc * gf;
             }
             gcb[slot][gsw] = on ? gco : zero;
-            if (on) {
+            float m = 0.0f;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) lm = finite_max(lm, dv[k][g]);
-            }
+            for (int g = 0; g < 4; ++g) m = max_of(m, dv[k][g]);
+            pm[k] = on ? __float_as_uint(m) : 0u;
             if (on && qq >= q0 && qq < q0 + kLineSeg) {
 #pragma unroll
                 for (int g = 0; g < 4; ++g) dbacc[g] += dv[k][g];
-#pragma unroll
-                for (int g = 0; g < 4; ++g) top = finite_max(top, dv[k][g]);
+                top = fmaxf(top, m);
                 const long long vo = sbase + vox;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) *(f4 *)(a.dA + vo * G + g * O + 4 * q4) = dv[k][g];
@@ -2067,12 +2110,21 @@ k_line_bwd(LineBwdArgs a)
                 if (j == nlines - 1) *(f4 *)(a.gcf + vo * O + 4 * q4) = gco;
             }
         }
-        const unsigned wm = wave_max(lm);
-        if (lane == 0) atomicMax(&lmx[j & 1], wm);
+        // (over the four lanes of a pixel, then both tiles' pixels)
+#pragma unroll
+        for (int o = 32; o > 8; o >>= 1)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) pm[k] = max(pm[k], (unsigned)__shfl_xor(pm[k], o));
+        DaRange wr = da_join(da_of(pm[0]), da_of(pm[1]));
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) wr = da_join(wr, da_shuffle(wr, o));
+        leave_range(j & 1, wr);
         __syncthreads();
-        const int ex = scale_exp(lmx[j & 1]);
+        const DaRange range = line_range(j & 1);
+        const int ex = da_exp(range);
+        f32 = rawh || rawx || da_wide(range);
         scale = line_sign(t) * exp2i(ex);
-        inv = line_sign(t) * exp2i(-ex);
+        inv = f32 ? 1.0f : line_sign(t) * exp2i(-ex);
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int i = wave + 4 * k;
@@ -2080,6 +2132,10 @@ k_line_bwd(LineBwdArgs a)
             const int slot = lo + 16 * i + col;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
+                if (f32) {
+                    dab[slot * 16 + ((4 * g + q4) ^ (slot & 15))] = onv[k] ? dv[k][g] : zero;
+                    continue;
+                }
                 const Split4 sp = split4(onv[k] ? dv[k][g] * scale : zero);
                 // gate-units 16 g + 4 q4 .. + 3: half of the chunks of units 8 (2 g + q4 / 2) .. + 7
                 const int ch = slot * 16 + ((4 * g + 2 * (q4 >> 1)) ^ (slot & 15));
@@ -2087,12 +2143,12 @@ k_line_bwd(LineBwdArgs a)
                 ((h4 *)&dab[ch ^ 1])[q4 & 1] = sp.lo;
             }
         }
-        if (threadIdx.x == 0) lmx[(j & 1) ^ 1] = 0u;    // (read before the barrier above)
+        if (threadIdx.x < 2) lmx[(j & 1) ^ 1][threadIdx.x] = 0u;    // (read before the barrier above)
         __syncthreads();
         if (want_dx) {
             // the segment's dL/dx of this line: channels are rows 0 .. 3 (lanes q4 = 0)
             const h8 none = {};
-            const f4 px = contract((S + 1) * rq + 16 * wave + col, [&](int kg, int hl) {
+            const f4 px = contract((S + 1) * rq + 16 * wave + col, rawx, [&](int kg, int hl) {
                 const h8 w = xfr[(kg * 2 + hl) * 16 + q4 * 4 + (col & 3)];
                 return col < 4 ? w : none;
             }) * rx;

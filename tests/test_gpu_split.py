@@ -330,7 +330,7 @@ def test_weight_gradients_of_an_infinite_dh(shape):
         assert (host(got)[np.isinf(want)] == want[np.isinf(want)]).all()
 
 
-@pytest.mark.parametrize("loud", [20, 28])
+@pytest.mark.parametrize("loud", [20, 28, 45, 100])
 @pytest.mark.parametrize("shape", [(1, 21, 30, 3, 3), (1, 12, 70, 1, 5), (2, 40, 9, 6, 3)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_line_reverse_beside_a_loud_pixel(shape, loud):
@@ -439,3 +439,21 @@ def test_line_forward_with_an_outlier_weight(shape, value):
     torch.cuda.synchronize()
     assert np.isfinite(ref).all()
     assert close(host(h), ref)
+
+
+@pytest.mark.parametrize("which, at", [("wh", (0, 3, 1)), ("wx", (2, 18, 0))], ids=["wh", "wx"])
+@pytest.mark.parametrize("shape", [(1, 21, 30, 3, 3), (2, 40, 9, 6, 5)], ids=lambda s: "x".join(map(str, s)))
+def test_line_reverse_with_an_outlier_weight(shape, which, at):
+    N, H, W, C, K = shape
+    x, wx, wh, b = synth.image2d(N, H, W, C, 16, K, 9920 + sum(shape), "f32")
+    {"wx": wx, "wh": wh}[which][at + (K // 2,)] = 1e30
+    dh = synth.upstream_grad((N, H, W, 16), 78)
+    with np.errstate(all="ignore"):
+        ref = o2d.backward2d(x, wx, wh, b, dh)
+    say("split line reverse outlier weight", shape, which)
+    xd, L = dev(x), LayerW(dev(wx), dev(wh), dev(b))
+    _, saved = layer2d_forward(xd, L, training=True)
+    dx, dwx, dwh, db = layer2d_backward(xd, L, saved, dev(dh))
+    torch.cuda.synchronize()
+    check_weights(ref, dwx, dwh, db)
+    assert np.abs(host(dx) - ref["dx"]).max() <= TOL * np.abs(ref["dx"]).max()
