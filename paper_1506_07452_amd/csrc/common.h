@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "index.h"
 #include "pyramid_lstm.h"
 
 namespace plstm {

@@ -46,10 +46,6 @@ __device__ inline bool on_plane(int p, int q, int P, int Q)
 {
     return ((unsigned)p < (unsigned)P) & ((unsigned)q < (unsigned)Q);
 }
-// floor(i / w) for 0 <= i < 2^20 from a float reciprocal (exact: the
-// fraction of (i + 0.5) / w is at least 0.5 / w from an integer, the
-// product's rounding error below 0.125 / w).
-__device__ inline int fdiv_floor(int i, float inv_w) { return (int)(((float)i + 0.5f) * inv_w); }
 
 // ---- statistics and packing -------------------------------------------------
 
@@ -670,7 +666,7 @@ struct BwdH2Args {
     float *gcp;               // dL/dc f of the last two planes, [N][min(T,2)][P Q][O] at coff
     float *dxd;               // [nd][N][V][C] or null
     long long coff[kDirs];
-    int bp[kDirs], bq[kDirs], nbq[kDirs], nblk[kDirs];
+    int bp[kDirs], bq[kDirs], nbp[kDirs], nbq[kDirs], nblk[kDirs];
     int base[kDirs + 1];
 };
 
@@ -768,11 +764,9 @@ k_step_bwd_h2(BwdH2Args a)
         // first wave now, the rest (wide halos) and the reduction beside the
         // staging loads
         const DaRange *const an = am + (long long)(t + 1) * a.nblk[d] * NW;
-        const int i0 = fdiv_floor(max(p0 - radp, 0), 1.0f / (float)BP);
-        const int i1 = fdiv_floor(min(p0 + BP - 1 + radp, P - 1), 1.0f / (float)BP);
-        const int j0 = fdiv_floor(max(q0 - radq, 0), 1.0f / (float)BQ);
-        const int j1 = fdiv_floor(min(q0 + BQ - 1 + radq, Q - 1), 1.0f / (float)BQ);
-        const int nj = (j1 - j0 + 1) * NW, cnt = (i1 - i0 + 1) * nj;
+        const Span si = blocks_touched(bi, BP, a.nbp[d], radp), sj = blocks_touched(bj, BQ, a.nbq[d], radq);
+        const int i0 = si.lo, j0 = sj.lo;
+        const int nj = (sj.hi - j0 + 1) * NW, cnt = (si.hi - i0 + 1) * nj;
         auto top_word = [&](int e) {
             const int i = fdiv_floor(e, 1.0f / (float)nj);
             return an[((i0 + i) * a.nbq[d] + j0) * NW + e - i * nj];
@@ -1233,6 +1227,7 @@ int launch_bwd_h2(const Geom &g, BwdH2Args &a, const PixBlocks &b, bool with_dx,
         return PLSTM_EHIP;
     for (int d = 0; d < kDirs; ++d) {
         a.bp[d] = b.bp[d]; a.bq[d] = b.bq[d]; a.nbq[d] = b.nbq[d]; a.nblk[d] = b.nblk[d];
+        a.nbp[d] = b.nbq[d] ? b.nblk[d] / b.nbq[d] : 0;
     }
     // with dL/dx, a last launch (t = -1) gives plane 0's share
     for (int t = max_T(g) - 1; t >= (with_dx ? -1 : 0); --t) {

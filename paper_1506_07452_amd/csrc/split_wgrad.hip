@@ -18,8 +18,6 @@ constexpr int kMaxWords = 32;            // maxima of |dA| per direction after k
 constexpr int kRowA = 288;               // bytes of a staged dA pixel: 64 gates as split tiles, 32 pad
 constexpr int kXB = 2;                   // staged 8-channel slots of [h | x] per thread
 
-__device__ inline int fdiv_floor(int i, float inv_w) { return (int)(((float)i + 0.5f) * inv_w); }
-
 // Transposed LDS read: within a group of 16 lanes lane l names 8 bytes (four
 // columns) of row l / 4 and receives rows 0 .. 3 of column l.
 __device__ inline h4 tr4(lds_char *base, int off)

@@ -54,8 +54,6 @@ constexpr int kWaitVmcnt0 = 0x0F70;   // s_waitcnt vmcnt(0), other counters unco
 __device__ inline float frcp(float v) { return __builtin_amdgcn_rcpf(v); }
 
 __device__ inline float ftanh(float a) { return 1.0f - 2.0f * frcp(__expf(2.0f * a) + 1.0f); }
-// floor(i / w) for 0 <= i < 2^20 (see the forward sweep for the error bound)
-__device__ inline int fdiv_floor(int i, float inv_w) { return (int)(((float)i + 0.5f) * inv_w); }
 
 struct BwdArgs {
     Geom g;

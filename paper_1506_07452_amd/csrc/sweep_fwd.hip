@@ -86,14 +86,6 @@ __device__ inline float frcp(float v) { return __builtin_amdgcn_rcpf(v); }
 __device__ inline float fsig(float a) { return frcp(1.0f + __expf(-a)); }
 __device__ inline float ftanh(float a) { return 1.0f - 2.0f * frcp(__expf(2.0f * a) + 1.0f); }
 
-// floor(i / w) for 0 <= i < 2^20, w >= 1, from a float reciprocal: the
-// fraction of (i + 0.5) / w is at least 0.5 / w away from an integer, while the
-// product's rounding error is below (i / w) 2^-23 <= 0.125 / w, so the
-// truncation is exact.
-__device__ inline int fdiv_floor(int i, float inv_w) {
-    return (int)(((float)i + 0.5f) * inv_w);
-}
-
 // Waits until the strip's neighbours have published `step` steps (bounded:
 // a wait that never ends raises the error flag and gives up).  Their shared
 // columns are then read at device coherence, so no cache invalidate is

@@ -380,3 +380,48 @@ def test_noalloc_validation_without_gpu(lib):
     assert f(ctypes.byref(small), None, FAKE, FAKE, FAKE, FAKE, None) == -1
     assert f(ctypes.byref(small), FAKE, FAKE, FAKE, FAKE, None, None) == -1
     assert f(None, FAKE, FAKE, FAKE, FAKE, FAKE, None) == -1
+
+
+def test_index_arithmetic(tmp_path):
+    """fdiv_floor over its range, and the blocks a widened block touches over planes up to the
+    largest extent a layer may have (2^23 voxels of 16 units in a row), against integer
+    division: the float reciprocal alone is one off from 4397273 / 63 on."""
+    import os
+    import subprocess
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src = tmp_path / "index.cpp"
+    src.write_text(r'''
+#define __host__
+#define __device__
+#include "index.h"
+#include <cstdio>
+using namespace plstm;
+int main()
+{
+    for (int w = 1; w <= 300; ++w)
+        for (int k = 0; k <= (1 << 22) / w; ++k)
+            for (int i = k * w - 1; i <= k * w; ++i)
+                if (i >= 0 && i < (1 << 22) && fdiv_floor(i, 1.0f / (float)w) != i / w)
+                    return printf("fdiv_floor(%d / %d)\n", i, w), 1;
+    if (fdiv_floor(4397273, 1.0f / 63.0f) == 4397273 / 63) return printf("range\n"), 1;
+    const int extents[] = {1, 5, 63, 64, 65, 4397273 + 64, (1 << 23) - 1};
+    for (int Q : extents)
+        for (int size = 1; size <= 64; ++size)
+            for (int r = 0; r <= 3; ++r) {
+                const int count = (Q + size - 1) / size, step = count > 4096 ? count / 4096 : 1;
+                for (int b0 = 0; b0 < count; b0 += step)
+                    for (int b = b0; b < count && b < b0 + 2; ++b) {
+                        const int lo = b * size - r, hi = b * size + size - 1 + r;
+                        const Span s = blocks_touched(b, size, count, r);
+                        if (s.lo != (lo > 0 ? lo : 0) / size || s.hi != (hi < Q - 1 ? hi : Q - 1) / size)
+                            return printf("blocks %d of %d, size %d, r %d\n", b, count, size, r), 1;
+                    }
+            }
+    return 0;
+}
+''')
+    exe = tmp_path / "index"
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(root, "paper_1506_07452_amd", "csrc"), str(src),
+                    "-o", str(exe)], check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout
