@@ -38,7 +38,7 @@ size_t forward_ws(const Geom &g, int dtype, bool training)
             cv.take<float>(saved_state_count(g));   // h^d
             cv.take<float>(saved_state_count(g));   // c^d
         }
-        const size_t s = align_up(cv.off, 256) + step_fwd_ws(g);
+        const size_t s = align_up(cv.off, 256) + step_fwd_ws(g, dtype, training);
         if (s > need) need = s;
     }
     return need;

@@ -1332,16 +1332,52 @@ int split_pad_x(long long nvox, int C, const float *x, float *xp, hipStream_t st
     return PLSTM_OK;
 }
 
-size_t split_fwd_ws(const Geom &g)
+// Packed weights, their scales and x's statistics.
+struct FwdPack {
+    h8 *frag;
+    float *bias, *rinv;
+    SplitScan *scan;
+    unsigned *ctl;
+};
+static FwdPack carve_pack(Carve &cv, const Geom &g, const FwdK &k)
+{
+    FwdPack p;
+    p.frag = cv.take<h8>((size_t)g.nd * (g.O / 16) * k.KG * 512);
+    p.bias = cv.take<float>((size_t)g.nd * 4 * g.O);
+    p.rinv = cv.take<float>((size_t)g.nd * 4 * g.O);
+    p.scan = cv.take<SplitScan>(1);
+    p.ctl = cv.take<unsigned>(2);
+    return p;
+}
+// Floats of the two-plane c^d buffer; the rest of the c^d array holds the packed weights
+// where it is large enough, so that inference needs no more than x's copy beside it.
+static size_t cell_planes(const Geom &g)
+{
+    size_t n = 0;
+    for (int d = 0; d < g.nd; ++d)
+        n += (size_t)g.N * (g.dir[d].T > 1 ? 2 : 1) * g.dir[d].P * g.dir[d].Q * g.O;
+    return n;
+}
+static bool pack_in_cell(const Geom &g, const FwdK &k)
+{
+    Carve cv(nullptr);
+    cv.take<float>(cell_planes(g));
+    carve_pack(cv, g, k);
+    return cv.off <= saved_state_count(g) * sizeof(float);
+}
+// fp32 input whose channels are a multiple of eight is read in place (bf16 input too
+// wide for its own path is widened).
+static bool fwd_in_place(const Geom &g, const FwdK &k, int dtype)
+{
+    return dtype == PLSTM_F32 && k.C8 == g.C;
+}
+
+size_t split_fwd_ws(const Geom &g, int dtype, bool cell_full)
 {
     const FwdK k = fwd_k(g);
     Carve cv(nullptr);
-    cv.take<float>((size_t)g.N * g.V * k.C8);          // (unless x is read in place)
-    cv.take<h8>((size_t)g.nd * (g.O / 16) * k.KG * 512);
-    cv.take<float>((size_t)g.nd * 4 * g.O);
-    cv.take<float>((size_t)g.nd * 4 * g.O);
-    cv.take<SplitScan>(1);
-    cv.take<unsigned>(2);
+    if (!fwd_in_place(g, k, dtype)) cv.take<float>((size_t)g.N * g.V * k.C8);
+    if (cell_full || !pack_in_cell(g, k)) carve_pack(cv, g, k);
     return cv.off;
 }
 
@@ -1352,15 +1388,15 @@ int split_fwd(const Geom &g, int dtype, const void *x, const void *wx, const voi
     const FwdK k = fwd_k(g);
     const int U = g.O / 16;
     Carve cv(ws);
-    // an fp32 input whose channels are a multiple of eight is read in place
-    // (bf16 input too wide for that path is widened)
-    const bool in_place = dtype == PLSTM_F32 && k.C8 == g.C;
+    const bool in_place = fwd_in_place(g, k, dtype);
     float *xp = !in_place ? cv.take<float>((size_t)g.N * g.V * k.C8) : nullptr;
-    h8 *frag = cv.take<h8>((size_t)g.nd * U * k.KG * 512);
-    float *bias = cv.take<float>((size_t)g.nd * 4 * g.O);
-    float *rinv = cv.take<float>((size_t)g.nd * 4 * g.O);
-    SplitScan *scan = cv.take<SplitScan>(1);
-    unsigned *ctl = cv.take<unsigned>(2);
+    Carve in_cell(cell);
+    in_cell.take<float>(cell_planes(g));
+    const FwdPack pk = carve_pack(cell_full || !pack_in_cell(g, k) ? cv : in_cell, g, k);
+    h8 *const frag = pk.frag;
+    float *const bias = pk.bias, *const rinv = pk.rinv;
+    SplitScan *const scan = pk.scan;
+    unsigned *const ctl = pk.ctl;
     const long long nvox = (long long)g.N * g.V;
     *launches = 2 + (in_place ? 0 : 1) + max_T(g);
 

@@ -502,10 +502,10 @@ struct WgWs {
     SplitStats *part;
     unsigned *dmax, *ctl;
 };
-WgWs carve_wg(Carve &cv, const Geom &g)
+WgWs carve_wg(Carve &cv, const Geom &g, bool room)
 {
     WgWs w;
-    w.xp = pad8(g.C) != g.C ? cv.take<float>((size_t)g.N * g.V * pad8(g.C)) : nullptr;
+    w.xp = pad8(g.C) != g.C && !room ? cv.take<float>((size_t)g.N * g.V * pad8(g.C)) : nullptr;
     w.part = cv.take<SplitStats>(1);
     w.dmax = cv.take<unsigned>((size_t)g.nd * kMaxWords);
     w.ctl = cv.take<unsigned>(kWgCtl);
@@ -520,19 +520,20 @@ WgradSplit split_wgrad_shape(const Geom &g)
     return {w.kch, (size_t)g.nd * w.kch * 4 * g.O * w.NTt * 16};
 }
 
-size_t split_wgrad_ws(const Geom &g)
+size_t split_wgrad_ws(const Geom &g, bool room)
 {
     Carve cv(nullptr);
-    carve_wg(cv, g);
+    carve_wg(cv, g, room);
     return cv.off;
 }
 
 int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-                const DaMaxima &am, float *partial, void *ws, const unsigned **ctl,
+                const DaMaxima &am, float *partial, float *room, void *ws, const unsigned **ctl,
                 hipStream_t st)
 {
     Carve cv(ws);
-    const WgWs s = carve_wg(cv, g);
+    WgWs s = carve_wg(cv, g, room != nullptr);
+    if (pad8(g.C) != g.C && room) s.xp = room;
     const WgPlan w = wg_plan(g);
     const long long nvox = (long long)g.N * g.V;
     int rc = split_stats(x, nvox * g.C, s.part, s.ctl, kWgCtl, st);

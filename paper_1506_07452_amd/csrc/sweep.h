@@ -27,7 +27,7 @@ bool step_supported(const Geom &g);
 // bf16 inference of a 16-unit layer on the macro-tiled bf16 step (packed taps),
 // taken before the persistent fp32 sweep
 bool step_b16_packed(const Geom &g, int dtype);
-size_t step_fwd_ws(const Geom &g);
+size_t step_fwd_ws(const Geom &g, int dtype, bool training);
 // Writes c^d, the gates when `gates` is set, h^d (fp32; bf16 storage on the
 // bf16 MFMA keeps h^d in bf16 in the workspace instead) and the direction sum h.
 int step_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void *wh,
@@ -40,9 +40,11 @@ struct DaMaxima {
     const unsigned *p = nullptr;
     long long off[kDirs + 1] = {};
 };
-size_t step_wgrad_ws(const Geom &g);
+// `room`: an array of at least N V max(8, C rounded up to 8) floats that the call may
+// overwrite, or null (then the workspace holds x padded to eight channels).
+size_t step_wgrad_ws(const Geom &g, bool room);
 int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-               const DaMaxima &am, void *ws, float *dwx, float *dwh, float *db,
+               const DaMaxima &am, float *room, void *ws, float *dwx, float *dwh, float *db,
                const char *phase, hipStream_t st);
 size_t step_bwd_ws(const Geom &g);
 int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, const Saved &sv,
@@ -50,8 +52,9 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
              hipStream_t st);
 // fp32 plane steps on the 16-bit matrix unit (split_step.hip, operands split
 // into two fp16 halves): the automatic choice of step_fwd outside the 2D line
-// blocks.  `cell`: c^d of every plane (cell_full) or room for the last two.
-size_t split_fwd_ws(const Geom &g);
+// blocks.  `cell`: c^d of every plane (cell_full), or the array that would hold them, used
+// for the last two and the packed weights.
+size_t split_fwd_ws(const Geom &g, int dtype, bool cell_full);
 int split_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void *wh,
               const void *b, float *hd, float *cell, bool cell_full, float *gates, void *ws,
               hipStream_t st, int *launches);
@@ -73,9 +76,9 @@ struct WgradSplit {
     size_t floats;            // of partial
 };
 WgradSplit split_wgrad_shape(const Geom &g);
-size_t split_wgrad_ws(const Geom &g);
+size_t split_wgrad_ws(const Geom &g, bool room);
 int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-                const DaMaxima &am, float *partial, void *ws, const unsigned **ctl,
+                const DaMaxima &am, float *partial, float *room, void *ws, const unsigned **ctl,
                 hipStream_t st);
 int split_pad_x(long long nvox, int C, const float *x, float *xp, hipStream_t st);
 // dL/dx from the gate gradients dA [6][N][V][4O] on the MFMA (step_supported

@@ -718,7 +718,7 @@ size_t sweep_bwd_ws(const Geom &g)
     cv.take<float>((size_t)kDirs * g.N * g.V * kO);                     // dL/dc * f
     cv.take<int>(2 * 1024 + 1);                                          // flags + err
     cv.take<unsigned>(1024 * kWaves);                                    // maxima of |dA|
-    cv.take<char>(step_wgrad_ws(g));                                     // weight gradients
+    cv.take<char>(step_wgrad_ws(g, true));                               // weight gradients
     cv.take<char>(step_dx_ws(g));                                        // dL/dx fragments
     return cv.off;
 }
@@ -745,7 +745,7 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
     float *gcf = cv.take<float>((size_t)kDirs * g.N * g.V * kO);
     int *flags = cv.take<int>(2 * 1024 + 1);     // (256-byte aligned: 64-bit words)
     unsigned *amax = cv.take<unsigned>(1024 * kWaves);
-    void *wgws = cv.take<char>(step_wgrad_ws(g));
+    void *wgws = cv.take<char>(step_wgrad_ws(g, true));
     float *fragx = (float *)cv.take<char>(step_dx_ws(g));
 
     BwdArgs args;
@@ -786,7 +786,7 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
     am.p = amax;
     for (int d = 0; d < kDirs; ++d) am.off[d] = (long long)pl.first[d] * kWaves;
     am.off[kDirs] = (long long)pl.blocks * kWaves;
-    int rc = step_wgrad(g, x, sv.hd, dA, am, wgws, dwx, dwh, db, "wgrad_mfma", st);
+    int rc = step_wgrad(g, x, sv.hd, dA, am, gcf, wgws, dwx, dwh, db, "wgrad_mfma", st);
     if (rc != PLSTM_OK) return rc;
     if (dx) {
         rc = step_dx(g, wx, dA, fragx, dx, st);

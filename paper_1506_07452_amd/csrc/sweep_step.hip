@@ -3015,13 +3015,18 @@ inline B16K b16_k(const Geom &g)
 
 bool step_b16_packed(const Geom &g, int dtype) { return use_b16(g, dtype) && g.O == 16; }
 
-size_t step_fwd_ws(const Geom &g)
+// Biases, and for the line blocks the row scales.
+inline size_t bias_floats(const Geom &g)
+{
+    return (size_t)g.nd * (g.nd == 4 && g.O == 16 ? 8 : 4) * g.O;
+}
+size_t step_fwd_ws(const Geom &g, int dtype, bool training)
 {
     const int U = g.O / 16, Cp = pad16(g.C), KK = g.KP * g.KQ, KG = KK * (Cp + g.O) / 16;
     Carve cv(nullptr);
     cv.take<float>((size_t)g.N * g.V * Cp);          // padded x
     cv.take<float>((size_t)g.nd * U * KG * 1024);    // A fragments
-    cv.take<float>((size_t)g.nd * 8 * g.O);          // bias, row scales
+    cv.take<float>(bias_floats(g));
     size_t need = cv.off;
     if (g.O % 32 == 0 || b16_packed(g)) {           // bf16 variant
         const B16K k = b16_k(g);
@@ -3038,7 +3043,7 @@ size_t step_fwd_ws(const Geom &g)
         }
         if (cb.off > need) need = cb.off;
     }
-    const size_t sp = split_fwd_ws(g);
+    const size_t sp = split_fwd_ws(g, dtype, training);
     return sp > need ? sp : need;
 }
 
@@ -3326,7 +3331,7 @@ int step_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void
     Carve cv(ws);
     float *xp = cv.take<float>((size_t)g.N * g.V * Cp);
     float *frag = cv.take<float>((size_t)g.nd * U * KG * 1024);
-    float *bias = cv.take<float>((size_t)g.nd * 8 * g.O);   // (line blocks: and row scales)
+    float *bias = cv.take<float>(bias_floats(g));
     const long long nvox = (long long)g.N * g.V;
     const long long nfrag = (long long)g.nd * U * KG * 1024;
 
@@ -3451,30 +3456,30 @@ inline int line_nsegmax(const Geom &g)
 }
 inline bool line_bwd_geom(const Geom &g) { return g.nd == 4 && g.KP == 1 && g.O == 16; }
 
-size_t step_wgrad_ws(const Geom &g)
+size_t step_wgrad_ws(const Geom &g, bool room)
 {
     Carve cv(nullptr);
     cv.take<float>(wg_partial_floats(g));
-    cv.take<char>(split_wgrad_ws(g));
+    cv.take<char>(split_wgrad_ws(g, room));
     return cv.off;
 }
 
 int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-               const DaMaxima &am, void *ws, float *dwx, float *dwh, float *db,
+               const DaMaxima &am, float *room, void *ws, float *dwx, float *dwh, float *db,
                const char *phase, hipStream_t st)
 {
     const int U = g.O / 16, KK = g.KP * g.KQ, G = 4 * g.O;
     const WgShape w = wg_shape(g);
     Carve cv(ws);
     float *partial = cv.take<float>(wg_partial_floats(g));
-    void *rest = cv.take<char>(split_wgrad_ws(g));
+    void *rest = cv.take<char>(split_wgrad_ws(g, room != nullptr));
     timing_begin(phase, st);
     // split products, and the fp32 kernel for an x or dA they do not serve (known
     // on the device only: it returns at once where it has no work)
     const unsigned *ctl = nullptr;
     const bool split = g_wgrad_staged && am.p;
     if (split) {
-        const int rc = split_wgrad(g, x, hd, dA, am, partial, rest, &ctl, st);
+        const int rc = split_wgrad(g, x, hd, dA, am, partial, room, rest, &ctl, st);
         if (rc != PLSTM_OK) return rc;
     }
     WgStepArgs wa;
@@ -3509,7 +3514,7 @@ size_t step_bwd_ws(const Geom &g)
     cv.take<float>((size_t)g.nd * g.N * g.V * G);                  // dA
     cv.take<float>((size_t)g.nd * g.N * g.V * g.O);                // dL/dc * f
     cv.take<float>((size_t)g.nd * U * KK * 4 * U * 256);           // W_h^T fragments
-    cv.take<char>(step_wgrad_ws(g));                                // weight gradients
+    cv.take<char>(step_wgrad_ws(g, true));                          // weight gradients
     cv.take<float>((size_t)g.nd * KK * 4 * U * (Cp / 16) * 256);   // W_x^T fragments
     if (line_bwd_dx(g)) cv.take<float>((size_t)g.nd * g.N * g.V * g.C);   // dL/dx per direction
     if (line_bwd_geom(g)) {
@@ -3518,7 +3523,7 @@ size_t step_bwd_ws(const Geom &g)
     }
     Carve sp(nullptr);                                             // split reverse steps
     sp.off = split_bwd_ws(g);
-    sp.take<char>(step_wgrad_ws(g));
+    sp.take<char>(step_wgrad_ws(g, false));
     return sp.off > cv.off ? sp.off : cv.off;
 }
 
@@ -3569,7 +3574,7 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
     float *dA = cv.take<float>((size_t)g.nd * g.N * g.V * G);
     float *gcf = cv.take<float>((size_t)g.nd * g.N * g.V * g.O);
     float *frag = cv.take<float>((size_t)g.nd * U * KK * 4 * U * 256);
-    void *wgws = cv.take<char>(step_wgrad_ws(g));
+    void *wgws = cv.take<char>(step_wgrad_ws(g, true));
     float *fragx = cv.take<float>((size_t)g.nd * KK * 4 * U * (Cp / 16) * 256);
     float *dxd = line_bwd_dx(g) ? cv.take<float>((size_t)g.nd * g.N * g.V * g.C) : nullptr;
     float *dbl = line_bwd_geom(g) ? cv.take<float>((size_t)g.nd * g.N * line_nsegmax(g) * 64)
@@ -3616,7 +3621,7 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         dA = sb.dA;
         Carve rest(ws);
         rest.off = sb.used;
-        wgws = rest.take<char>(step_wgrad_ws(g));
+        wgws = rest.take<char>(step_wgrad_ws(g, false));
         am = sb.am;
     } else if (lines) {
         // 2D layers with 16 units: line blocks, S lines per launch (S r <= 16)
@@ -3694,7 +3699,7 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         timing_end(1 + max_T(g), st);
     }
 
-    const int rc = step_wgrad(g, x, sv.hd, dA, am, wgws, dwx, dwh, db_done ? nullptr : db,
+    const int rc = step_wgrad(g, x, sv.hd, dA, am, split ? nullptr : gcf, wgws, dwx, dwh, db_done ? nullptr : db,
                               "wgrad_step", st);
     if (rc != PLSTM_OK) return rc;
     if (dx && !dx_done) return step_dx(g, wx, dA, fragx, dx, st);

@@ -425,3 +425,22 @@ int main()
                     "-o", str(exe)], check=True)
     res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stdout
+
+
+@pytest.mark.parametrize("N, D, H, W, C, O, dtype", [(1, 29, 29, 383, 16, 16, 0), (1, 22, 121, 121, 16, 16, 0),
+                                                     (1, 43, 25, 278, 24, 16, 1)])
+def test_workspace_just_below_the_scratch(lib, N, D, H, W, C, O, dtype):
+    """Shapes whose outputs and input copy leave a few KB of the no-allocation scratch: the
+    packed weights and statistics have to find room inside them."""
+    s = P.plstm_shape(N, D, H, W, C, O, dtype, 3)
+    need = P.pyramid_lstm_workspace_size(s, 0)
+    assert P.PLSTM_NOALLOC_SCRATCH_BYTES - 16384 < need <= P.PLSTM_NOALLOC_SCRATCH_BYTES
+
+
+def test_image_training_workspace(lib):
+    """Of a one-channel image layer: dA, dL/dc f and each direction's dL/dx, and no second
+    array of the input's size or more (x padded to eight channels lies in dL/dc f)."""
+    N, H, W = 30, 512, 512
+    per_voxel = 4 * (64 + 16 + 1) * 4
+    need = P.pyramid_lstm2d_workspace_size(P.plstm2d_shape(N, H, W, 1, 16, 0, 3), 1)
+    assert need <= N * H * W * per_voxel + (48 << 20)
