@@ -44,11 +44,8 @@
 // The weight gradients are sums whose size is not known beforehand: they keep the
 // fp32 instruction for an x that one scale does not serve (a value that is not
 // finite, or more than 1 in 1024 of its non-zero values below 2^-28 of the
-// largest, where the split starts to lose bits), and for a dA so: it has one
-// scale per direction, under which the rows of a gate shut by its bias lie far
-// below the rest.  That is counted while dA is staged, in groups of eight gate-units
-// of a pixel (more than 1 in 128 with a value so small), and the fp32 kernel
-// then runs after (wgrad_keeps_f32).
+// largest, where the split starts to lose bits).  dA has a scale per gate row there,
+// lowered as larger values come (split_wgrad.hip).
 // The reverse steps scale dA by the largest magnitude of the pixels they stage
 // and keep the fp32 instruction where the loudest gate-unit of some pixel is
 // below 2^-28 of it or a value is not finite (da_wide): a pixel's products are
@@ -142,8 +139,8 @@ struct SplitStat {
 struct SplitStats {
     SplitStat first[kStatBlocks], second[kStatBlocks];
 };
-// (of fp32 values; clears nctl words of ctl too)
-int split_stats(const float *x, long long n, SplitStats *part, unsigned *ctl, int nctl, hipStream_t st);
+// (of fp32 values; clears *ctl too)
+int split_stats(const float *x, long long n, SplitStats *part, unsigned *ctl, hipStream_t st);
 // What the forward's scales follow from, in one launch: x's largest finite
 // magnitude and whether it holds one that is not, and the largest |W_x| and |W_h| of
 // every gate row (bits; an infinity or NaN counts).
@@ -270,17 +267,6 @@ __device__ inline Wide8 widen8(h8 hi, h8 lo, bool raw)
         w.b[i] = __builtin_fmaf((float)lo[4 + i], kLoInv, (float)hi[4 + i]);
     }
     return w;
-}
-// Control words of the weight gradients: [0] 1: an input is not finite or x has no one
-// scale, [1] x's largest magnitude (bits), then per direction the groups of eight
-// values of dA that are not all zero, and those with a value below 2^-28 of the largest.
-constexpr int kWgCtl = 2 + 2 * kDirs;
-__device__ inline bool wgrad_keeps_f32(const unsigned *ctl)
-{
-    bool f32 = ctl[0] != 0;
-#pragma unroll
-    for (int d = 0; d < kDirs; ++d) f32 |= ctl[2 + kDirs + d] > ctl[2 + d] / 128u;
-    return f32;
 }
 // One scale serves the tensor.
 __device__ inline bool stat_fits(const SplitStat &max, const SplitStat &count)

@@ -93,7 +93,7 @@ __device__ SplitStat scan_values(long long n, const TS *__restrict__ x, unsigned
 template <bool COUNT>
 __global__ void __launch_bounds__(256)
 k_split_stats(long long n, const float *__restrict__ x, SplitStats *__restrict__ part,
-              unsigned *__restrict__ ctl, int nctl)
+              unsigned *__restrict__ ctl)
 {
     __shared__ SplitStat red[5];
     unsigned low = 0;                       // magnitudes below this are small
@@ -102,7 +102,7 @@ k_split_stats(long long n, const float *__restrict__ x, SplitStats *__restrict__
         low = m > kStatRange ? m - kStatRange : 0u;
     }
     const SplitStat s = scan_values<float, COUNT>(n, x, low, red);
-    if (!COUNT && blockIdx.x == 0 && (int)threadIdx.x < nctl) ctl[threadIdx.x] = 0u;
+    if (!COUNT && blockIdx.x == 0 && threadIdx.x == 0) *ctl = 0u;
     if (threadIdx.x == 0) (COUNT ? part->second : part->first)[blockIdx.x] = s;
 }
 // x's statistics (the first kStatBlocks workgroups) and the weights' row maxima, a row a
@@ -1302,11 +1302,11 @@ BwdWs carve_bwd(Carve &cv, const Geom &g, bool with_dx)
 
 }  // namespace
 
-int split_stats(const float *x, long long n, SplitStats *part, unsigned *ctl, int nctl, hipStream_t st)
+int split_stats(const float *x, long long n, SplitStats *part, unsigned *ctl, hipStream_t st)
 {
-    k_split_stats<false><<<kStatBlocks, 256, 0, st>>>(n, x, part, ctl, nctl);
+    k_split_stats<false><<<kStatBlocks, 256, 0, st>>>(n, x, part, ctl);
     PLSTM_LAUNCH_CHECK();
-    k_split_stats<true><<<kStatBlocks, 256, 0, st>>>(n, x, part, ctl, nctl);
+    k_split_stats<true><<<kStatBlocks, 256, 0, st>>>(n, x, part, ctl);
     PLSTM_LAUNCH_CHECK();
     return PLSTM_OK;
 }
@@ -1498,12 +1498,11 @@ int split_bwd(const Geom &g, const float *wx, const float *wh, const Saved &sv, 
         if (d < g.nd)
             off += (long long)g.N * (g.dir[d].T > 1 ? 2 : 1) * g.dir[d].P * g.dir[d].Q * g.O;
     }
-    for (int d = 0; d <= kDirs; ++d) a.aoff[d] = out->am.off[d] = w.aoff[d];
+    for (int d = 0; d <= kDirs; ++d) a.aoff[d] = w.aoff[d];
     const int rc = launch_bwd_shape(g, a, sh, w.blocks, with_dx, st);
     if (rc == PLSTM_OK) timing_end(1 + max_T(g) + (with_dx ? 1 : 0), st);
     out->dA = w.dA;
     out->dxd = w.dxd;
-    out->am.p = (const unsigned *)w.amax;
     out->used = cv.off;
     return rc;
 }

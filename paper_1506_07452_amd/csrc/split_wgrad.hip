@@ -14,8 +14,8 @@ typedef __attribute__((address_space(3))) g4 lds_g4;
 typedef __attribute__((address_space(3))) char lds_char;
 
 constexpr int kWaves = 8, kThreads = 64 * kWaves;
-constexpr int kMaxWords = 32;            // maxima of |dA| per direction after k_wg_prep
 constexpr int kRowA = 288;               // bytes of a staged dA pixel: 64 gates as split tiles, 32 pad
+constexpr int kStatic = 2048;            // LDS of k_wgrad_h2 beside its stage buffers, at most
 constexpr int kXB = 2;                   // staged 8-channel slots of [h | x] per thread
 
 // Transposed LDS read: within a group of 16 lanes lane l names 8 bytes (four
@@ -36,48 +36,6 @@ __device__ inline h8 tr8(lds_char *base, int o0, int o1)
     return r;
 }
 
-// Maxima of |dA| per direction (kMaxWords workgroups each) and, last workgroup,
-// whether one scale serves x and its exponent.  A dA that is not finite keeps fp32 too.
-struct PrepArgs {
-    int nd;
-    DaMaxima am;
-    const SplitStats *part;
-    unsigned *dmax;           // [nd][kMaxWords]
-    unsigned *ctl;            // [kWgCtl], cleared before
-};
-__global__ void __launch_bounds__(256) k_wg_prep(PrepArgs a)
-{
-    __shared__ SplitStat red[2];
-    __shared__ unsigned top[4];
-    const int d = blockIdx.x / kMaxWords, b = blockIdx.x % kMaxWords;
-    if (d == a.nd) {
-        const SplitStat m = stat_reduce(a.part->first, &red[0]);
-        const SplitStat c = stat_reduce(a.part->second, &red[1]);
-        if (threadIdx.x == 0) {
-            if (!stat_fits(m, c)) atomicOr(&a.ctl[0], 1u);
-            a.ctl[1] = m.max_bits;
-        }
-        return;
-    }
-    unsigned m = 0;
-    for (long long i = a.am.off[d] + b * 256 + threadIdx.x; i < a.am.off[d + 1]; i += kMaxWords * 256) {
-        const unsigned v = a.am.p[i] & 0xffffu;
-        m = v > m ? v : m;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned t = __shfl_xor(m, o);
-        m = t > m ? t : m;
-    }
-    if ((threadIdx.x & 63) == 0) top[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w) m = top[w] > m ? top[w] : m;
-        a.dmax[d * kMaxWords + b] = m << 23;
-        if (m == 255u) atomicOr(&a.ctl[0], 1u);
-    }
-}
-
 struct WgH2Args {
     Geom g;
     int C8;                   // channels of x in memory
@@ -85,8 +43,8 @@ struct WgH2Args {
     int nct;                  // parts along the column tiles
     int kch, NTt;             // voxel chunks per part, N-tiles of a row of partial
     const float *x, *hd, *dA;
-    const unsigned *dmax;
-    unsigned *ctl;            // [kWgCtl]
+    const SplitStats *part;   // x's statistics
+    unsigned *ctl;            // 1: left to the fp32 kernel (cleared before)
     float *partial;           // [nd][kch][4O][16 NTt]
     int rowB;                 // bytes of a staged [h | x] pixel
     int bufb;                 // bytes of one stage buffer
@@ -108,6 +66,12 @@ struct WgH2Args {
 // - The three products of a piece start from zero and are added to the
 //   accumulators in fp32 (round to nearest): over the millions of voxels of a
 //   direction the instruction's own rounding towards -inf would add up.
+// - dA has a scale per gate row, which is undone on the sums: rows of a shut gate or
+//   an idle unit lie far below the others.  A row's scale starts from its largest value in
+//   the workgroup's first block, brought to 2^10; a value that reaches 2^15 under it has
+//   the block's row maxima found, the scales of such rows lowered, their
+//   sums with them, and the block split again (a few times a workgroup).  What lies
+//   2^-24 or more below a row's largest loses bits only beside sums that size.
 // Bound by the waves' own instruction stream: of 9.5 kilocycles a block (32 -> 32
 // units, 3 x 3) the products are 3.8, each wave's loads, splits and LDS stores 3
 // and the transposed reads' latency most of the rest.  Measured against the fp32
@@ -125,7 +89,16 @@ __global__ void __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_e
 k_wgrad_h2(WgH2Args a)
 {
     extern __shared__ h8 wl_smem[];
-    if (a.ctl[0]) return;
+    __shared__ SplitStat red[2];
+    __shared__ float rscale[64], rlower[64];    // of each gate row: scale, and factor of its sums
+    __shared__ int rexp[64];                    // exponent of the scale
+    __shared__ unsigned rmax[64];               // largest |dA| of the block (bits)
+    __shared__ int raised[2];                   // a row's scale is too large for the block, by parity
+    const SplitStat xs = stat_reduce(a.part->first, &red[0]);
+    if (!stat_fits(xs, stat_reduce(a.part->second, &red[1]))) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) *a.ctl = 1u;
+        return;
+    }
     constexpr int TP = 64 * DB;
     const int tid = threadIdx.x, lane = tid & 63, q4 = lane >> 4, col = lane & 15;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -151,22 +124,14 @@ k_wgrad_h2(WgH2Args a)
     const int C8 = a.C8, rowB = a.rowB, NSL = PC * 2;
     char *const smem = (char *)wl_smem;
 
-    unsigned dm = 0;
-    {
-        const unsigned m = a.dmax[d * kMaxWords + (lane & (kMaxWords - 1))];
-        dm = m;
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) {
-            const unsigned t = __shfl_xor(dm, o);
-            dm = t > dm ? t : dm;
-        }
+    const int exx = scale_exp(xs.max_bits);
+    const float sx = exp2i(exx);
+    if (tid < 64) {
+        rexp[tid] = 110;
+        rscale[tid] = exp2i(110);
     }
-    const int ea = scale_exp(dm), exx = scale_exp(a.ctl[1]);
-    // groups of this wave's staged dA, and the bound below which a value is small, as
-    // (bits << 1) - 1, where zeros are the largest
-    const unsigned low = dm > kStatRange ? ((dm - kStatRange) << 1) - 1u : 0u;
-    int groups = 0, small = 0;
-    const float sa = exp2i(ea), sx = exp2i(exx);
+    if (tid < 2) raised[tid] = 0;
+    __syncthreads();
 
     // this wave's taps and its lane's rows of a piece (voxel 16 j + 4 q + i of the
     // piece for k = 8 q + 4 j + i)
@@ -238,25 +203,29 @@ k_wgrad_h2(WgH2Args a)
         }
     };
     const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    auto commit = [&](char *buf) {
-        const int ti = fresh(tid);
+    auto add_bias = [&]() {
 #pragma unroll
         for (int u = 0; u < DB; ++u) {
-            const f4 v0 = oka[u] ? ra[u][0] : zero, v1 = oka[u] ? ra[u][1] : zero;
-            dbs[0] += v0;
-            dbs[1] += v1;
-            unsigned least = ~0u;
+            dbs[0] += oka[u] ? ra[u][0] : zero;
+            dbs[1] += oka[u] ? ra[u][1] : zero;
+        }
+    };
+    auto commit = [&](char *buf, int *flag) {
+        const int ti = fresh(tid);
+        const int c = ti & 7;
+        const f4 s0 = *(const f4 *)&rscale[8 * c], s1 = *(const f4 *)&rscale[8 * c + 4];
+        float top = 0.0f;
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                least = min(least, min((__float_as_uint(v0[k]) << 1) - 1u, (__float_as_uint(v1[k]) << 1) - 1u));
-            groups += __popcll(__ballot(least != ~0u));
-            small += __popcll(__ballot(least < low));
-            const Split8 w = split8(v0 * sa, v1 * sa);
-            const int c = ti & 7;
+        for (int u = 0; u < DB; ++u) {
+            const f4 v0 = (oka[u] ? ra[u][0] : zero) * s0, v1 = (oka[u] ? ra[u][1] : zero) * s1;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) top = fmaxf(top, fmaxf(fabsf(v0[k]), fabsf(v1[k])));
+            const Split8 w = split8(v0, v1);
             char *p = buf + ((ti >> 3) + 64 * u) * kRowA + (c >> 1) * 64 + (c & 1) * 16;
             *(h8 *)p = w.hi;
             *(h8 *)(p + 32) = w.lo;
         }
+        if (top >= kHScale) *flag = 1;
 #pragma unroll
         for (int u = 0; u < kXB; ++u) {
             const int e = ti + kThreads * u;
@@ -311,6 +280,38 @@ k_wgrad_h2(WgH2Args a)
         }
     };
 
+    // after a commit and its barrier, where that found a scale too large: row maxima of
+    // the block in flight, the scales and sums that follow; false where it is not finite
+    auto lower_scales = [&](int *flag) {
+        if (tid < 64) rmax[tid] = 0u;
+        __syncthreads();
+        if (tid == 0) *flag = 0;
+#pragma unroll
+        for (int u = 0; u < DB; ++u)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const unsigned m = __float_as_uint(ra[u][k >> 2][k & 3]) & 0x7fffffffu;
+                if (oka[u]) atomicMax(&rmax[8 * (tid & 7) + k], m);
+            }
+        __syncthreads();
+        bool finite = true;
+        if (tid < 64) {
+            const int e = (int)(rmax[tid] >> 23) - 127, old = rexp[tid];
+            finite = e < 128;
+            const int now = e + old >= 15 ? 10 - e : old;
+            rexp[tid] = now;
+            rscale[tid] = exp2i(now);
+            rlower[tid] = now - old < -126 ? 0.0f : exp2i(now - old);
+        }
+        finite = __syncthreads_and(finite) != 0;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const f4 f = *(const f4 *)&rlower[m * 16 + 4 * q4];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[m][j] *= f;
+        }
+        return finite;
+    };
     // this workgroup's blocks: (n, t, blk), blk fastest
     const long long tot = (long long)a.g.N * dg.T * NBLK;
     // (fewer than 2^31 blocks)
@@ -319,12 +320,13 @@ k_wgrad_h2(WgH2Args a)
         int blk = uni((int)(u0 % NBLK));
         const int rest = uni((int)(u0 / NBLK));
         int t = uni(rest % dg.T), n = uni(rest / dg.T);
-        fetch(n, t, blk);
-        commit(smem);
-        __syncthreads();
-        for (int u = u0; u < u1; ++u) {
+        bool finite = true;
+        // block u's products beside block u + 1's loads (one pass of the loop before the first)
+        for (int u = u0 - 1; finite && u < u1; ++u) {
             const int buf = ((u - u0) & 1) * a.bufb;
-            if (u + 1 < u1) {
+            const bool more = u + 1 < u1;
+            if (more) {
+                fetch(n, t, blk);
                 if (++blk == NBLK) {
                     blk = 0;
                     if (++t == dg.T) {
@@ -332,32 +334,29 @@ k_wgrad_h2(WgH2Args a)
                         ++n;
                     }
                 }
-                fetch(n, t, blk);
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (busy)
+            if (busy && u >= u0)
 #pragma unroll 1
                 for (int pc = ks; pc < TP / 32; pc += KS) piece(buf, pc);
             __builtin_amdgcn_sched_barrier(0);
-            if (u + 1 < u1) commit(smem + (((u - u0) & 1) ^ 1) * a.bufb);
-            __syncthreads();
+            if (more) add_bias();
+            // (two flags: a wave may set the next block's before another has read this one's)
+            int *const flag = &raised[(u - u0) & 1];
+            for (bool again = true; again;) {
+                if (more) commit(smem + (((u - u0) & 1) ^ 1) * a.bufb, flag);
+                __syncthreads();
+                again = more && *(volatile int *)flag != 0;
+                if (__builtin_expect(again, 0)) {
+                    finite = lower_scales(flag);
+                    again = finite;
+                }
+            }
         }
-    }
-
-    // (one addition a workgroup: one a wave cost 15 us of 85 on 2 x 8 x 64 x 64)
-    if (cp == 0) {
-        int *const cnt = (int *)smem;
-        if (lane == 0) {
-            cnt[wv] = groups;
-            cnt[kWaves + wv] = small;
+        if (!finite) {
+            if (tid == 0) *a.ctl = 1u;
+            return;
         }
-        __syncthreads();
-        if (tid < 2) {
-            unsigned v = 0;
-            for (int k = 0; k < kWaves; ++k) v += (unsigned)cnt[tid * kWaves + k];
-            if (v) atomicAdd(&a.ctl[2 + tid * kDirs + d], v);
-        }
-        __syncthreads();
     }
 
     // the KS waves of an item, summed in order through LDS, one row tile at a time
@@ -382,7 +381,7 @@ k_wgrad_h2(WgH2Args a)
     float *const out = a.partial + (((long long)d * a.kch + kc) * G + mg * 64) * KCp;
     if (busy && ks == 0) {
         const bool is_h = ct < U;
-        const float inv = exp2i(-ea), inv2 = is_h ? 1.0f / kHScale : exp2i(-exx);
+        const float inv2 = is_h ? 1.0f / kHScale : exp2i(-exx);
         const int c = (is_h ? ct : ct - U) * 16 + col;
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
@@ -393,7 +392,8 @@ k_wgrad_h2(WgH2Args a)
             for (int m = 0; m < 4; ++m)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    out[(long long)(m * 16 + 4 * q4 + i) * KCp + column] = acc[m][j][i] * inv * inv2;
+                    out[(long long)(m * 16 + 4 * q4 + i) * KCp + column] =
+                        acc[m][j][i] * inv2 * exp2i(-rexp[m * 16 + 4 * q4 + i]);
         }
     }
     // bias sums: 64 threads hold slot s (gates 8 s .. 8 s + 7)
@@ -448,7 +448,7 @@ WgPlan wg_plan(const Geom &g)
     w.rowB = w.PC * 64 + 32;
     const DevInfo di = device_info();
     const int lim = di.max_lds > 0 ? di.max_lds : 65536;
-    int max_px = (lim / 2 - w.TP * kRowA) / w.rowB;
+    int max_px = ((lim - kStatic) / 2 - w.TP * kRowA) / w.rowB;
     if (max_px > kXB * kThreads / (2 * w.PC)) max_px = kXB * kThreads / (2 * w.PC);
     int staged = 0;
     for (int d = 0; d < g.nd; ++d) {
@@ -500,15 +500,14 @@ int launch_nt(const WgPlan &w, const WgH2Args &a, int grid, hipStream_t st)
 struct WgWs {
     float *xp;
     SplitStats *part;
-    unsigned *dmax, *ctl;
+    unsigned *ctl;
 };
 WgWs carve_wg(Carve &cv, const Geom &g, bool room)
 {
     WgWs w;
     w.xp = pad8(g.C) != g.C && !room ? cv.take<float>((size_t)g.N * g.V * pad8(g.C)) : nullptr;
     w.part = cv.take<SplitStats>(1);
-    w.dmax = cv.take<unsigned>((size_t)g.nd * kMaxWords);
-    w.ctl = cv.take<unsigned>(kWgCtl);
+    w.ctl = cv.take<unsigned>(1);
     return w;
 }
 
@@ -528,7 +527,7 @@ size_t split_wgrad_ws(const Geom &g, bool room)
 }
 
 int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-                const DaMaxima &am, float *partial, float *room, void *ws, const unsigned **ctl,
+                float *partial, float *room, void *ws, const unsigned **ctl,
                 hipStream_t st)
 {
     Carve cv(ws);
@@ -536,18 +535,12 @@ int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
     if (pad8(g.C) != g.C && room) s.xp = room;
     const WgPlan w = wg_plan(g);
     const long long nvox = (long long)g.N * g.V;
-    int rc = split_stats(x, nvox * g.C, s.part, s.ctl, kWgCtl, st);
+    int rc = split_stats(x, nvox * g.C, s.part, s.ctl, st);
     if (rc != PLSTM_OK) return rc;
     if (s.xp) {
         rc = split_pad_x(nvox, g.C, x, s.xp, st);
         if (rc != PLSTM_OK) return rc;
     }
-    PrepArgs pa;
-    pa.nd = g.nd;
-    pa.am = am;
-    pa.part = s.part; pa.dmax = s.dmax; pa.ctl = s.ctl;
-    k_wg_prep<<<g.nd * kMaxWords + 1, 256, 0, st>>>(pa);
-    PLSTM_LAUNCH_CHECK();
     *ctl = s.ctl;
     WgH2Args a;
     a.g = g;
@@ -555,7 +548,7 @@ int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
     a.CT = w.CT; a.PC = w.PC; a.TG = w.TG; a.nct = w.nct;
     a.kch = w.kch; a.NTt = w.NTt;
     a.x = s.xp ? s.xp : x; a.hd = hd; a.dA = dA;
-    a.dmax = s.dmax; a.ctl = s.ctl;
+    a.part = s.part; a.ctl = s.ctl;
     a.partial = partial;
     a.rowB = w.rowB; a.bufb = w.bufb;
     for (int d = 0; d < kDirs; ++d) {

@@ -33,18 +33,12 @@ size_t step_fwd_ws(const Geom &g, int dtype, bool training);
 int step_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void *wh,
              const void *b, float *hd, float *cell, float *gates, void *h, void *ws,
              hipStream_t st);
-// Weight and bias gradients (db may be null) from dA; `am`: the largest biased exponents
-// of dA (255: not finite), those of direction d in the lower halves of words am.off[d] ..
-// am.off[d + 1], or null for the fp32 kernel.
-struct DaMaxima {
-    const unsigned *p = nullptr;
-    long long off[kDirs + 1] = {};
-};
+// Weight and bias gradients (db may be null) from dA.
 // `room`: an array of at least N V max(8, C rounded up to 8) floats that the call may
 // overwrite, or null (then the workspace holds x padded to eight channels).
 size_t step_wgrad_ws(const Geom &g, bool room);
 int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-               const DaMaxima &am, float *room, void *ws, float *dwx, float *dwh, float *db,
+               float *room, void *ws, float *dwx, float *dwh, float *db,
                const char *phase, hipStream_t st);
 size_t step_bwd_ws(const Geom &g);
 int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, const Saved &sv,
@@ -58,19 +52,18 @@ size_t split_fwd_ws(const Geom &g, int dtype, bool cell_full);
 int split_fwd(const Geom &g, int dtype, const void *x, const void *wx, const void *wh,
               const void *b, float *hd, float *cell, bool cell_full, float *gates, void *ws,
               hipStream_t st, int *launches);
-// Reverse steps the same way: dA, with_dx each direction's share of dL/dx, and the
-// largest |dA| of each wave of each step, all in the workspace.
+// Reverse steps the same way: dA and, with_dx, each direction's share of dL/dx, in the
+// workspace.
 struct SplitBwd {
     float *dA, *dxd;
-    DaMaxima am;
     size_t used;              // workspace bytes taken
 };
 size_t split_bwd_ws(const Geom &g);
 int split_bwd(const Geom &g, const float *wx, const float *wh, const Saved &sv, const float *dh,
               bool with_dx, void *ws, SplitBwd *out, hipStream_t st);
 // Weight and bias gradients the same way (split_wgrad.hip): partial sums
-// [nd][kch][4O][16 NTt] of dA (x) [im2col(h) | im2col(x) | 1], and the control words
-// (device) that say whether the fp32 kernel is to make them instead (wgrad_keeps_f32).
+// [nd][kch][4O][16 NTt] of dA (x) [im2col(h) | im2col(x) | 1].  Where x has no one
+// scale or dA is not finite it leaves them to the fp32 kernel, and *ctl (device) is 1.
 struct WgradSplit {
     int kch;
     size_t floats;            // of partial
@@ -78,7 +71,7 @@ struct WgradSplit {
 WgradSplit split_wgrad_shape(const Geom &g);
 size_t split_wgrad_ws(const Geom &g, bool room);
 int split_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-                const DaMaxima &am, float *partial, float *room, void *ws, const unsigned **ctl,
+                float *partial, float *room, void *ws, const unsigned **ctl,
                 hipStream_t st);
 int split_pad_x(long long nvox, int C, const float *x, float *xp, hipStream_t st);
 // dL/dx from the gate gradients dA [6][N][V][4O] on the MFMA (step_supported

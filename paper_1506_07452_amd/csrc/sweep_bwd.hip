@@ -20,8 +20,7 @@
 //     keep the fp32 instruction on the same LDS.  The scale's sign alternates from step to step and strip to strip,
 //     so that the instruction's rounding towards -inf cancels in db.  The
 //     product gc_t f_t is what plane t - 1 needs, so that is what is kept.
-//     dA of every voxel is kept for (2) and for dL/dx, and each wave leaves the
-//     largest |dA| it stored, from which (2) scales its split operands.
+//     dA of every voxel is kept for (2) and for dL/dx.
 // (2) dW = sum over voxels of dA (x) [im2col(h_{t-1}), im2col(x_t), 1]: the
 //     plane-step path's kernels (split_wgrad.hip).
 #include "common.h"
@@ -62,7 +61,6 @@ struct BwdArgs {
     const float *dh;             // dL/dh [N][V][16]
     float *dA;                   // [6][N][V][64] gate pre-activation gradients
     float *gcf;                  // [6][N][V][16] dL/dc_t * f_t, carried to plane t - 1
-    unsigned *amax;              // [blocks][kWaves] exponent of the largest |dA|
     // [blocks] steps done << 32 | (range of the plane before the last) << 16 | of the last, a
     // range being DaRange's two exponents in a byte each
     unsigned long long *flags;
@@ -276,11 +274,6 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
         atomicMax(&m[1], (unsigned)v.y);
     };
     auto step_sign = [&](int r) { return (strip + r) & 1 ? -1.0f : 1.0f; };
-    auto wave_max = [&](float v) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-        return __float_as_uint(v);
-    };
     // fp32 slot `sl` of LDS pixel `pix`, split in place
     auto split_slot = [&](int pix, int sl, float scale) {
         float *p0 = &as[pix * kG + 4 * swz(2 * sl, pix)], *p1 = &as[pix * kG + 4 * swz(2 * sl + 1, pix)];
@@ -312,11 +305,6 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                ((pc == q1 - 1) & (nb_hi >= 0));
     };
 
-    float top = 0.0f;            // largest |dA| of this lane
-    auto leave_max = [&]() {
-        const unsigned m = wave_max(top);
-        if (lane == 0) a.amax[blockIdx.x * kWaves + wave] = m >> 23;
-    };
 
     if (a.resident[d]) {
         // ============ resident strip: dA of the whole strip stays in LDS ============
@@ -499,7 +487,6 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     // (beside the stores)
                     const float tm = top_of(dAi, dAf, dAg, dAo);
                     const DaRange tr = da_wave(__float_as_uint(tm));
-                    top = fmaxf(top, tm);
                     if (lane == 0) {
                         widen(&mx[2 * (r & 1)], tr);
                         if (k < n_edge) widen(&emx[2 * (r & 1)], tr);
@@ -525,7 +512,6 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
             }
             // (a strip without neighbours is waited for by none)
         }
-        leave_max();
         return;
     }
 
@@ -631,7 +617,6 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                 }
                 const float tm = top_of(dAi, dAf, dAg, dAo);
                 wave_range = da_join(wave_range, da_wave(__float_as_uint(tm)));
-                top = fmaxf(top, tm);
                 const int o4 = vo * kG + 4 * q4;
                 float *dst = &dA_dn[o4];
                 if (shared) {
@@ -674,7 +659,6 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
         __syncthreads();
         if (threadIdx.x == 0) publish(r, mx);
     }
-    leave_max();
 }
 
 __global__ void k_fill_zero(int *p, int n)
@@ -717,7 +701,6 @@ size_t sweep_bwd_ws(const Geom &g)
     cv.take<float>((size_t)kDirs * g.N * g.V * kG);                     // dA
     cv.take<float>((size_t)kDirs * g.N * g.V * kO);                     // dL/dc * f
     cv.take<int>(2 * 1024 + 1);                                          // flags + err
-    cv.take<unsigned>(1024 * kWaves);                                    // maxima of |dA|
     cv.take<char>(step_wgrad_ws(g, true));                               // weight gradients
     cv.take<char>(step_dx_ws(g));                                        // dL/dx fragments
     return cv.off;
@@ -744,7 +727,6 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
     float *dA = cv.take<float>((size_t)kDirs * g.N * g.V * kG);
     float *gcf = cv.take<float>((size_t)kDirs * g.N * g.V * kO);
     int *flags = cv.take<int>(2 * 1024 + 1);     // (256-byte aligned: 64-bit words)
-    unsigned *amax = cv.take<unsigned>(1024 * kWaves);
     void *wgws = cv.take<char>(step_wgrad_ws(g, true));
     float *fragx = (float *)cv.take<char>(step_dx_ws(g));
 
@@ -754,7 +736,6 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
     args.gates = sv.gates; args.cell = sv.cell;
     args.dh = dh;
     args.dA = dA; args.gcf = gcf;
-    args.amax = amax;
     args.flags = (unsigned long long *)flags; args.err = flags + 2 * 1024;
     args.max_spin = g_wait_spin_limit;
     args.wait_bias = g_wait_bias;
@@ -782,11 +763,7 @@ int sweep_bwd(const Geom &g, const float *x, const float *wx, const float *wh, c
         return PLSTM_EHIP;
     timing_end(1, st);
 
-    DaMaxima am;
-    am.p = amax;
-    for (int d = 0; d < kDirs; ++d) am.off[d] = (long long)pl.first[d] * kWaves;
-    am.off[kDirs] = (long long)pl.blocks * kWaves;
-    int rc = step_wgrad(g, x, sv.hd, dA, am, gcf, wgws, dwx, dwh, db, "wgrad_mfma", st);
+    int rc = step_wgrad(g, x, sv.hd, dA, gcf, wgws, dwx, dwh, db, "wgrad_mfma", st);
     if (rc != PLSTM_OK) return rc;
     if (dx) {
         rc = step_dx(g, wx, dA, fragx, dx, st);

@@ -1820,8 +1820,6 @@ struct LineBwdArgs {
     float *dxd;                 // [4][N][V][C] per-direction dL/dx, or null
     float *dbp;                 // [4][N][nsegmax][4O] bias-gradient partials, or null
     int nsegmax;                // segments of the longest line
-    unsigned *amax;             // exponent of the largest |dA| of each wave of a segment over
-    int aoff[kDirs];            // the launches so far, [N][nseg][4] at aoff
     int nseg[kDirs];
     int base[kDirs + 1];
 };
@@ -1934,7 +1932,6 @@ k_line_bwd(LineBwdArgs a)
     h8 *afr = (h8 *)dyn;                        // [NK][hi, lo][64 lanes]
     f4 *dab = dyn + NK * 128;                   // [kLineSlots][16], chunk ^ (slot & 15)
     h8 *xfr = (h8 *)(dab + kLineSlots * 16);    // [NK][hi, lo][4][4]
-    float top = 0.0f;                           // largest |dA| of this lane's segment
     auto max_of = [](float m, f4 v) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) m = fmaxf(m, fabsf(v[u]));
@@ -2102,7 +2099,6 @@ k_line_bwd(LineBwdArgs a)
             if (on && qq >= q0 && qq < q0 + kLineSeg) {
 #pragma unroll
                 for (int g = 0; g < 4; ++g) dbacc[g] += dv[k][g];
-                top = fmaxf(top, m);
                 const long long vo = sbase + vox;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) *(f4 *)(a.dA + vo * G + g * O + 4 * q4) = dv[k][g];
@@ -2158,13 +2154,6 @@ k_line_bwd(LineBwdArgs a)
                 for (int c = 0; c < C; ++c) out[c] = px[c];
             }
         }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
-    if (lane == 0) {
-        unsigned *e = a.amax + a.aoff[d] + (n * a.nseg[d] + seg) * 4 + wave;
-        const unsigned m = __float_as_uint(top) >> 23;
-        *e = r0 == 0 || m > *e ? m : *e;
     }
     if (a.dbp) {
         // over the 16 lanes of a unit group (pixels), then the four waves
@@ -2444,7 +2433,7 @@ struct WgStepArgs {
     int k_mul;                // ceil(2^16 / K)
     const float *xp, *hd, *dA;  // xp: the input x [N][V][Cp] (read one channel per lane)
     float *partial;           // [6][kch][4O][16 NTt]
-    const unsigned *ctl;      // run only where wgrad_keeps_f32 (null: always)
+    const unsigned *only_if;  // run only where this word is set (null: always)
 };
 
 // The wave's share: NTL tiles (compile time) of which `ntl` are real; ONES:
@@ -2608,7 +2597,7 @@ template <int U>
 __global__ void __launch_bounds__(64 * kSW) __attribute__((amdgpu_waves_per_eu(2)))
 k_wgrad_step(WgStepArgs a)
 {
-    if (a.ctl && !wgrad_keeps_f32(a.ctl)) return;
+    if (a.only_if && !*a.only_if) return;
     const int per_xcd = gridDim.x / kXcds;
     const int lblk = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
     const int item = lblk * kSW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -2671,7 +2660,7 @@ k_wgrad_step_reduce(int nd, int O, int C, int Cp, int KK, int NTt, int kch, int 
     const int gu = (int)((i / KC) % G);
     const int d = (int)(i / ((long long)KC * G));
     float acc = 0.0f;
-    if (ctl && wgrad_keeps_f32(ctl)) kch = kch_f32;        // the fp32 kernel's chunks
+    if (ctl && *ctl) kch = kch_f32;        // the fp32 kernel's chunks
     for (int c = 0; c < kch; ++c) acc += partial[(((long long)d * kch + c) * G + gu) * KCp + k];
     if (k < KK * O) {
         dwh[(((long long)d * G + gu) * O + k % O) * KK + k / O] = acc;
@@ -3465,7 +3454,7 @@ size_t step_wgrad_ws(const Geom &g, bool room)
 }
 
 int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
-               const DaMaxima &am, float *room, void *ws, float *dwx, float *dwh, float *db,
+               float *room, void *ws, float *dwx, float *dwh, float *db,
                const char *phase, hipStream_t st)
 {
     const int U = g.O / 16, KK = g.KP * g.KQ, G = 4 * g.O;
@@ -3477,9 +3466,9 @@ int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
     // split products, and the fp32 kernel for an x or dA they do not serve (known
     // on the device only: it returns at once where it has no work)
     const unsigned *ctl = nullptr;
-    const bool split = g_wgrad_staged && am.p;
+    const bool split = g_wgrad_staged != 0;
     if (split) {
-        const int rc = split_wgrad(g, x, hd, dA, am, partial, room, rest, &ctl, st);
+        const int rc = split_wgrad(g, x, hd, dA, partial, room, rest, &ctl, st);
         if (rc != PLSTM_OK) return rc;
     }
     WgStepArgs wa;
@@ -3489,7 +3478,7 @@ int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
     wa.xp = x; wa.hd = hd; wa.dA = dA;
     wa.partial = partial;
     wa.k_mul = k_mul_of(g);
-    wa.ctl = ctl;
+    wa.only_if = ctl;
     const long long witems = (long long)g.nd * U * w.nblk * w.kch;
     const long long wblocks = (blocks_for(witems, kSW) + kXcds - 1) / kXcds * kXcds;
     switch (U) {
@@ -3503,7 +3492,7 @@ int step_wgrad(const Geom &g, const float *x, const float *hd, const float *dA,
         g.nd, g.O, g.C, pad16(g.C), KK, w.NTt, split ? split_wgrad_shape(g).kch : w.kch, w.kch, ctl,
         partial, dwx, dwh, db);
     PLSTM_LAUNCH_CHECK();
-    timing_end(split ? 6 : 2, st);
+    timing_end(split ? 5 : 2, st);
     return PLSTM_OK;
 }
 
@@ -3517,10 +3506,7 @@ size_t step_bwd_ws(const Geom &g)
     cv.take<char>(step_wgrad_ws(g, true));                          // weight gradients
     cv.take<float>((size_t)g.nd * KK * 4 * U * (Cp / 16) * 256);   // W_x^T fragments
     if (line_bwd_dx(g)) cv.take<float>((size_t)g.nd * g.N * g.V * g.C);   // dL/dx per direction
-    if (line_bwd_geom(g)) {
-        cv.take<float>((size_t)g.nd * g.N * line_nsegmax(g) * 64);        // db partials
-        cv.take<unsigned>((size_t)g.nd * g.N * line_nsegmax(g) * 4);      // maxima of |dA|
-    }
+    if (line_bwd_geom(g)) cv.take<float>((size_t)g.nd * g.N * line_nsegmax(g) * 64);   // db partials
     Carve sp(nullptr);                                             // split reverse steps
     sp.off = split_bwd_ws(g);
     sp.take<char>(step_wgrad_ws(g, false));
@@ -3579,9 +3565,6 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
     float *dxd = line_bwd_dx(g) ? cv.take<float>((size_t)g.nd * g.N * g.V * g.C) : nullptr;
     float *dbl = line_bwd_geom(g) ? cv.take<float>((size_t)g.nd * g.N * line_nsegmax(g) * 64)
                                   : nullptr;
-    unsigned *aml = line_bwd_geom(g) ? cv.take<unsigned>((size_t)g.nd * g.N * line_nsegmax(g) * 4)
-                                     : nullptr;
-    DaMaxima am;                          // maxima of |dA| (split steps, line blocks)
     bool db_done = false;
     const long long nvox = (long long)g.N * g.V;
     bool dx_done = false;
@@ -3622,7 +3605,6 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         Carve rest(ws);
         rest.off = sb.used;
         wgws = rest.take<char>(step_wgrad_ws(g, false));
-        am = sb.am;
     } else if (lines) {
         // 2D layers with 16 units: line blocks, S lines per launch (S r <= 16)
         LineBwdArgs la;
@@ -3638,12 +3620,6 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         la.dbp = dbl;
         la.nsegmax = line_nsegmax(g);
         for (int d = 0; d < kDirs; ++d) la.nseg[d] = (g.dir[d].Q + kLineSeg - 1) / kLineSeg;
-        la.amax = aml;
-        for (int d = 0; d < kDirs; ++d) {
-            la.aoff[d] = (int)am.off[d];
-            am.off[d + 1] = am.off[d] + (d < g.nd ? (long long)g.N * la.nseg[d] * 4 : 0);
-        }
-        am.p = aml;
         const size_t dyn = line_dyn;
         if (hipFuncSetAttribute((const void *)k_line_bwd, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)dyn) != hipSuccess)
@@ -3699,7 +3675,7 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
         timing_end(1 + max_T(g), st);
     }
 
-    const int rc = step_wgrad(g, x, sv.hd, dA, am, split ? nullptr : gcf, wgws, dwx, dwh, db_done ? nullptr : db,
+    const int rc = step_wgrad(g, x, sv.hd, dA, split ? nullptr : gcf, wgws, dwx, dwh, db_done ? nullptr : db,
                               "wgrad_step", st);
     if (rc != PLSTM_OK) return rc;
     if (dx && !dx_done) return step_dx(g, wx, dA, fragx, dx, st);
