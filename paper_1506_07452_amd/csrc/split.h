@@ -46,14 +46,19 @@
 // finite, or more than 1 in 1024 of its non-zero values below 2^-28 of the
 // largest, where the split starts to lose bits).  dA has a scale per gate row there,
 // lowered as larger values come (split_wgrad.hip).
-// The reverse steps scale dA by the largest magnitude of the pixels they stage
-// and keep the fp32 instruction where the loudest gate-unit of some pixel is
-// below 2^-28 of it or a value is not finite (da_wide): a pixel's products are
-// then off by at most 2^-22 of its own largest.  The weights of a unit (a row of W_h^T,
-// W_x^T) count as x does, 1 in 64.
+// The reverse steps scale dA by the largest magnitude of the pixels they stage.  Where
+// the loudest gate-unit of some pixel is below 2^-28 of it (da_wide; away from the
+// labelled voxels of a masked loss dA falls off exponentially) each pixel has a
+// scale of its own instead: a tap's products then start from zero and its sums,
+// times 1 / its pixel's scale, are added up in fp32.  A pixel's products are so off by
+// at most 2^-22 of its own largest.  The fp32 instruction is kept where a value is
+// not finite, and for a unit's weights (a row of W_h^T, W_x^T) of which more than 1 in
+// 64 are below 2^-28 of the largest.
 #pragma once
 
 #include "common.h"
+
+#include <type_traits>
 
 namespace plstm {
 
@@ -226,6 +231,27 @@ __device__ inline DaRange da_join(DaRange a, DaRange b) { return __builtin_eleme
 __device__ inline DaRange da_shuffle(DaRange r, int o)
 {
     return __builtin_bit_cast(DaRange, __shfl_xor(__builtin_bit_cast(int, r), o));
+}
+// Scale exponent of a pixel's gate-units whose largest magnitude has these bits (zeros
+// take any).
+__device__ inline int pixel_exp(unsigned m) { return min(14 - ((int)(m >> 23) - 127), 110); }
+// The maximum over aligned groups of eight lanes, all of them active.
+__device__ inline float max8(float m)
+{
+    auto other = [](float v, auto ctrl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
+                                                                     decltype(ctrl)::value, 0xf, 0xf, false));
+    };
+    m = fmaxf(m, other(m, std::integral_constant<int, 0xB1>{}));     // lanes 1 0 3 2
+    m = fmaxf(m, other(m, std::integral_constant<int, 0x4E>{}));     // lanes 2 3 0 1
+    return fmaxf(m, other(m, std::integral_constant<int, 0x141>{})); // lanes 7 .. 0
+}
+__device__ inline float top8(v4 a, v4 b)
+{
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m = fmaxf(m, fmaxf(fabsf(a[i]), fabsf(b[i])));
+    return m;
 }
 // Of one pixel whose largest is `m` (bits).
 __device__ inline DaRange da_of(unsigned m)

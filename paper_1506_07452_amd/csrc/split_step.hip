@@ -673,7 +673,8 @@ struct BwdH2Args {
 // 1 KB fragment loads of a K-group: the row tiles' halves, rounded up to a
 // whole number per wave.
 constexpr int bwd_frags(int RTW, int WM) { return (RTW * WM * 2 + 4 * WM - 1) / (4 * WM) * (4 * WM); }
-constexpr int kBwdChunks = 18;           // staged pixel: 64 gate-units as 8 split slots, 2 pad
+// staged pixel: 64 gate-units as 8 split slots, 1 / their own scale, pad
+constexpr int kBwdChunks = 18, kBwdScale = 16;
 
 // Reverse plane step: dL/dh_t = dL/dh + sum_taps W_h^T dA_{t+1}[p - tap] and, with
 // CT channel tiles, dL/dx_{t+1} = sum_taps W_x^T dA_{t+1}[p - tap] of the same
@@ -684,8 +685,9 @@ constexpr int kBwdChunks = 18;           // staged pixel: 64 gate-units as 8 spl
 // largest magnitude of the blocks it touches, which the launch before left in
 // amax (one range a wave: an atomic maximum per plane cost 0.4 us a launch); the
 // fragments stream as in the forward step.  Blocks that one scale does not serve
-// (da_wide, raw weights) stage dA as it is and take the fp32 instruction, one
-// K-group at a time.
+// (da_wide) give each pixel its own; blocks with a value that is not finite, or
+// rows of weights that one scale does not serve, stage dA as it is and take the fp32
+// instruction.  Both run in a loop that reads a K-group's operands when it needs them.
 // Bound by the launches on small planes (37 us for 400 workgroups: staging twice
 // 4, K-groups 0.6 each, 36 of them, cell update 11 kilocycles) and by LDS reads and
 // barriers on large ones.  Measured against the fp32 instruction on 64-pixel
@@ -694,8 +696,11 @@ constexpr int kBwdChunks = 18;           // staged pixel: 64 gate-units as 8 spl
 // 25 -> 32 on 15 x 128 x 128 21.0 -> 8.5; 6 -> 16 on 19 x 101 x 75 1.39 -> 1.17.  Not
 // kept: 128-pixel blocks (15.7 ms on the first); the cell update's operands loaded
 // before the last pass (two instead of three workgroups a CU: 15.9).
+// (Registers for the three workgroups that a CU's LDS holds: left alone, the compiler counts
+// the rare loop's too and two of <4, 1> fit.  The same for <2, 1>, four, spills: 3 % slower on
+// small planes.)
 template <int RTW, int WM, int EU>
-__global__ void __launch_bounds__(256 * WM)
+__global__ void __launch_bounds__(256 * WM, WM == 1 && RTW >= 3 ? 3 : 1)
 k_step_bwd_h2(BwdH2Args a)
 {
     constexpr int NT = 1;                // pixel tiles of a wave
@@ -757,7 +762,8 @@ k_step_bwd_h2(BwdH2Args a)
     const float flip = (bi + bj + t) & 1 ? -1.0f : 1.0f;
     float unscale = 1.0f;
     unsigned raw = 0;                // row tiles with fp32 weights
-    bool f32 = false;
+    bool f32 = false, own = false;   // dA as it is; a scale per pixel
+    const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
 
     if (has_next) {
         // range of dA_{t+1} of the blocks the staged one touches: this lane's
@@ -833,19 +839,27 @@ k_step_bwd_h2(BwdH2Args a)
                     range = __builtin_bit_cast(
                         DaRange, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, range)));
                     raw = (unsigned)__ballot(raw_tile != 0 && lane < RT);
-                    f32 = raw != 0 || da_wide(range);
+                    f32 = raw != 0 || range.x == 255;
+                    own = !f32 && da_wide(range);
                 }
                 const float scale = flip * exp2i(da_exp(range));
 #pragma unroll
                 for (int u = 0; u < SB; ++u) {
-                    if (dst[u] < 0) continue;
-                    const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-                    if (f32) {
-                        stg[dst[u]] = __builtin_bit_cast(h8, ok[u] ? va[u] : zero);
-                        stg[dst[u] + 1] = __builtin_bit_cast(h8, ok[u] ? vb[u] : zero);
-                        continue;
+                    float sc = scale;
+                    if (f32 || own) {
+                        if (own) {                   // (a pixel is eight lanes)
+                            const float top = ok[u] ? top8(va[u], vb[u]) : 0.0f;
+                            const int ex = pixel_exp(__float_as_uint(max8(top)));
+                            sc = flip * exp2i(ex);
+                            if (dst[u] >= 0 && (tid & 7) == 0)
+                                *(float *)&stg[((e0 + u * THREADS) >> 3) * kBwdChunks + kBwdScale] = flip * exp2i(-ex);
+                        } else if (dst[u] >= 0) {
+                            stg[dst[u]] = __builtin_bit_cast(h8, ok[u] ? va[u] : zero);
+                            stg[dst[u] + 1] = __builtin_bit_cast(h8, ok[u] ? vb[u] : zero);
+                        }
                     }
-                    const Split8 w = split8(ok[u] ? va[u] * scale : zero, ok[u] ? vb[u] * scale : zero);
+                    if (dst[u] < 0 || f32) continue;
+                    const Split8 w = split8(ok[u] ? va[u] * sc : zero, ok[u] ? vb[u] * sc : zero);
                     stg[dst[u]] = w.hi;
                     stg[dst[u] + 1] = w.lo;
                 }
@@ -853,31 +867,64 @@ k_step_bwd_h2(BwdH2Args a)
             __builtin_amdgcn_s_waitcnt(kWaitAllLds);
             __syncthreads();
 
-            if (f32) {
-                // fp32 values: K-group kg is eight k-steps of the fp32 instruction
-                for (int kg = 0; kg < KG; ++kg) {
-                    __syncthreads();
-                    issue_a(kg, ring0);
-                    __builtin_amdgcn_s_waitcnt(kWaitAllLds);
-                    __syncthreads();
-                    const int bo = tab[kg >> 1] + 8 * (kg & 1);
+            if (__builtin_expect(f32 || own, 0)) {
+                // K-groups kg + 1 and kg + 2 are in flight beside kg
+                f4 tap[2][RTW][NT];          // sums of a tap, own scales
+                auto barrier = []() {        // (that waits for no load in flight)
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                };
+                auto slow = [&](int kg, h8 *slot) {
+                    if (kg + 2 < KG)
+                        __builtin_amdgcn_s_waitcnt(0x0070 | 2 * NDMA);
+                    else
+                        __builtin_amdgcn_s_waitcnt(kWaitAllLds);
+                    barrier();
+                    const int odd = kg & 1, bo = tab[kg >> 1];
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) {
-                        const f4 b0 = __builtin_bit_cast(f4, stg[spb[nt] + bo]);
-                        const f4 b1 = __builtin_bit_cast(f4, stg[spb[nt] + bo + 1]);
+                        const h8 *bp = &stg[spb[nt] + bo + 8 * odd];
+                        const h8 b0 = bp[0], b1 = bp[1];
+                        const float inv = *(const float *)&stg[spb[nt] - 2 * q4 + bo + kBwdScale];
 #pragma unroll
                         for (int i = 0; i < RTW; ++i) {
-                            const h8 *ap = &ring0[(i * WM * 2 + wm * 2) * 64 + lane];
-                            const Wide8 w = widen8(ap[0], ap[64], raw >> min(i * WM + wm, RT - 1) & 1);
+                            const h8 *ap = &slot[(i * WM * 2 + wm * 2) * 64 + lane];
+                            const h8 a0 = ap[0], a1 = ap[64];
+                            if (f32) {
+                                // eight k-steps of the fp32 instruction
+                                const f4 v0 = __builtin_bit_cast(f4, b0), v1 = __builtin_bit_cast(f4, b1);
+                                const Wide8 w = widen8(a0, a1, raw >> min(i * WM + wm, RT - 1) & 1);
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) {
-                                acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.a[j], b0[j],
-                                                                                  acc[i][nt], 0, 0, 0);
-                                acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.b[j], b1[j],
-                                                                                  acc[i][nt], 0, 0, 0);
+                                for (int j = 0; j < 4; ++j) {
+                                    acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.a[j], v0[j],
+                                                                                      acc[i][nt], 0, 0, 0);
+                                    acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.b[j], v1[j],
+                                                                                      acc[i][nt], 0, 0, 0);
+                                }
+                                continue;
                             }
+                            f4 x = odd ? tap[0][i][nt] : zero, y = odd ? tap[1][i][nt] : zero;
+                            x = mfma_h(a1, b0, x);
+                            y = mfma_h(a0, b0, y);
+                            x = mfma_h(a0, b1, x);
+                            tap[0][i][nt] = x;
+                            tap[1][i][nt] = y;
+                            if (odd) acc[i][nt] += join(y, x) * inv;
                         }
                     }
+                    barrier();
+                    if (kg + 3 < KG) issue_a(kg + 3, slot);
+                };
+#pragma unroll
+                for (int i = 0; i < RTW; ++i)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) tap[0][i][nt] = tap[1][i][nt] = zero;
+#pragma unroll 1
+                for (int kg = 0; kg < KG; kg += 3) {
+                    slow(kg, ring0);
+                    if (kg + 1 < KG) slow(kg + 1, ring1);
+                    if (kg + 2 < KG) slow(kg + 2, ring2);
                 }
                 continue;
             }
@@ -945,7 +992,7 @@ k_step_bwd_h2(BwdH2Args a)
         for (int i = 0; i < RTW; ++i)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) sum[1][i][nt] = join(sum[1][i][nt], sum[0][i][nt]);
-        unscale = f32 ? 1.0f : flip * exp2i(-da_exp(range));
+        unscale = f32 || own ? 1.0f : flip * exp2i(-da_exp(range));
     }
 
     const int np = dg.T > 1 ? 2 : 1;
