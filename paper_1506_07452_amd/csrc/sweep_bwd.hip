@@ -16,8 +16,10 @@
 //     lane ends with four consecutive units of one pixel, so every epilogue
 //     load and store is a 16-byte vector.  dA_{t+1} has one scale per strip and
 //     step, from its own range of |dA| and those its neighbours publish with
-//     their flags; a step that one scale does not serve (da_wide), or weights,
-//     keep the fp32 instruction on the same LDS.  The scale's sign alternates from step to step and strip to strip,
+//     their flags; in a step that one scale does not serve (da_wide) each
+//     pixel has its own, and a step with a value that is not finite, or weights
+//     that one scale does not serve, keep the fp32 instruction on the same LDS.
+//     The scale's sign alternates from step to step and strip to strip,
 //     so that the instruction's rounding towards -inf cancels in db.  The
 //     product gc_t f_t is what plane t - 1 needs, so that is what is kept.
 //     dA of every voxel is kept for (2) and for dL/dx.
@@ -123,6 +125,31 @@ __device__ __forceinline__ f4 contract_bwd(const float *as, const float *was, in
     return join(acc, x0 + x1);
 }
 
+// The same where each pixel has its own scale: a tap's sums start from zero and are
+// added up times 1 / its pixel's scale (`pinv`, by LDS pixel).
+__device__ __forceinline__ f4 contract_bwd_own(const float *as, const float *was, const float *pinv,
+                                               int base, int rs, int cs, int q4, int lane)
+{
+    f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int tap = 0; tap < 9; ++tap) {
+        const int ta = (tap * 11) >> 5, pp = base - ((ta - 1) * rs + (tap - 3 * ta - 1) * cs);
+        const int o0 = pp * kG + 4 * swz(2 * q4, pp);
+        f4 x = {0.0f, 0.0f, 0.0f, 0.0f}, y = x;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int o = o0 ^ (half * 32), kg = 2 * tap + half;
+            const h8 bh = *(const h8 *)&as[o], bl = *(const h8 *)&as[o ^ 4];
+            const h8 wh = *(const h8 *)&was[((kg * 2 + 0) * 64 + lane) * 4];
+            const h8 wl = *(const h8 *)&was[((kg * 2 + 1) * 64 + lane) * 4];
+            x = mfma_h(wl, bh, x);
+            y = mfma_h(wh, bh, y);
+            x = mfma_h(wh, bl, x);
+        }
+        acc += join(y, x) * pinv[pp];
+    }
+    return acc;
+}
 // The same of dA as it is, with the fp32 instruction: a gate-unit a lane group and step.
 // Seldom taken, so nothing is read ahead and little is kept in registers.
 __device__ __forceinline__ f4 contract_bwd_f32(const float *as, const float *was, bool raw, int base,
@@ -274,9 +301,15 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
         atomicMax(&m[1], (unsigned)v.y);
     };
     auto step_sign = [&](int r) { return (strip + r) & 1 ? -1.0f : 1.0f; };
-    // fp32 slot `sl` of LDS pixel `pix`, split in place
-    auto split_slot = [&](int pix, int sl, float scale) {
+    // fp32 slot `sl` of LDS pixel `pix`, split in place (by eight lanes a pixel; with `pinv`
+    // by a scale of the pixel's own, left there)
+    auto split_slot = [&](int pix, int sl, float scale, float *pinv) {
         float *p0 = &as[pix * kG + 4 * swz(2 * sl, pix)], *p1 = &as[pix * kG + 4 * swz(2 * sl + 1, pix)];
+        if (pinv) {
+            const int ex = pixel_exp(__float_as_uint(max8(top8(*(const f4 *)p0, *(const f4 *)p1))));
+            scale = exp2i(ex);
+            if (sl == 0) pinv[pix] = exp2i(-ex);
+        }
         const Split8 sp = split8(*(const f4 *)p0 * scale, *(const f4 *)p1 * scale);
         *(h8 *)p0 = sp.hi;
         *(h8 *)p1 = sp.lo;
@@ -320,7 +353,8 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
         const int npl = P2 * W2;
         const int npx = P * TQ;
         const int nmt = (npx + 15) >> 4;
-        int *order = (int *)(as + (size_t)npl * kG);   // tile order, edge tiles first
+        float *const px_inv = as + (size_t)npl * kG;    // 1 / scale of each pixel, where it has one
+        int *order = (int *)(px_inv + npl);            // tile order, edge tiles first
         int *cnt = order + nmt;                         // edge tiles stored this step
         const float inv_p = 1.0f / (float)P;
         for (int e = threadIdx.x; e < npl * (kG / 4); e += kThreads)
@@ -359,27 +393,37 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
             const int nplane = has_next ? (s + dg.sign) * ss : splane;
             const int pplane = has_prev ? (s - dg.sign) * ss : splane;
             float inv = 0.0f;
-            bool f32 = false;
+            bool f32 = false, own = false;
             if (r > 0) {
                 wait_neighbours(r);
                 __syncthreads();
                 const DaRange range = step_range(r);
                 const int ex = da_exp(range);
                 const float scale = step_sign(r) * exp2i(ex);
-                f32 = raw || da_wide(range);
-                inv = f32 ? 1.0f : step_sign(r) * exp2i(-ex);
+                f32 = raw || range.x == 255;
+                own = !f32 && da_wide(range);
+                inv = f32 || own ? 1.0f : step_sign(r) * exp2i(-ex);
                 // every contraction has read dA_{t+2}: overwrite it with dA_{t+1}
 #pragma unroll
                 for (int it = 0; it < 2; ++it) {
                     if (hbase[it] < 0) continue;
                     const int pb = hbase[it];
+                    float sc = scale;
+                    if (__builtin_expect(own, 0)) {
+                        float m = top_of(hold[it][0], hold[it][1], hold[it][2], hold[it][3]);
+#pragma unroll
+                        for (int o = 32; o > 8; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+                        const int px = pixel_exp(__float_as_uint(m));
+                        sc = exp2i(px);
+                        px_inv[pb] = exp2i(-px);
+                    }
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
                         if (f32) {
                             *(f4 *)&as[pb * kG + 4 * swz(4 * g + q4, pb)] = hold[it][g];
                             continue;
                         }
-                        const Split4 sp = split4(hold[it][g] * scale);
+                        const Split4 sp = split4(hold[it][g] * sc);
                         // gate-units 16 g + 4 q4 .. + 3: half of slot 2 g + q4 / 2
                         const int c = 2 * (2 * g + (q4 >> 1)), o = 2 * (q4 & 1);
                         *(h4 *)&as[pb * kG + 4 * swz(c, pb) + o] = sp.hi;
@@ -415,7 +459,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     const int side = i >= nslot ? 1 : 0;
                     const int row = 4 * (i - side * nslot) + (lane >> 3);
                     if ((side ? nb_hi : nb_lo) < 0 || lane >= 32 || row >= P) continue;
-                    split_slot((side ? TQ + 1 : 0) * P2 + 1 + row, lane & 7, scale);
+                    split_slot((side ? TQ + 1 : 0) * P2 + 1 + row, lane & 7, scale, own ? px_inv : nullptr);
                 }
                 if (threadIdx.x == 0) {
                     cnt[0] = 0;
@@ -453,6 +497,8 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                     if (has_next) {
                         if (__builtin_expect(f32, 0))
                             acc = contract_bwd_f32(as, was, raw, base, 1, P2, q4, lane);
+                        else if (__builtin_expect(own, 0))
+                            acc = contract_bwd_own(as, was, px_inv, base, 1, P2, q4, lane);
                         else
                             acc = contract_bwd(as, was, base, 1, P2, q4, lane);
                         acc = acc * inv * *(const f4 *)&winv[4 * q4];
@@ -515,6 +561,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
         return;
     }
 
+    float *const px_inv = as + (size_t)(chunk_rows + 2) * (a.max_w[d] + 2) * kG;
     for (int r = 0; r < dg.T; ++r) {
         const int t = dg.T - 1 - r;                   // plane processed at this step
         const int s = dg.sign > 0 ? t : dg.T - 1 - t;
@@ -522,15 +569,16 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
         // ---- wait for the neighbours' dA_{t+1} --------------------------
         float scale = 0.0f, inv = 0.0f;
         DaRange wave_range = {0, 0};        // of this wave's tiles
-        bool f32 = false;
+        bool f32 = false, own = false;
         if (r > 0) {
             wait_neighbours(r);
             __syncthreads();
             const DaRange range = step_range(r);
             const int ex = da_exp(range);
             scale = step_sign(r) * exp2i(ex);
-            f32 = raw || da_wide(range);
-            inv = f32 ? 1.0f : step_sign(r) * exp2i(-ex);
+            f32 = raw || range.x == 255;
+            own = !f32 && da_wide(range);
+            inv = f32 || own ? 1.0f : step_sign(r) * exp2i(-ex);
             if (threadIdx.x == 0) mx[2 * (r & 1)] = mx[2 * (r & 1) + 1] = 0u;
             // (ordered before this step's maxima by the chunks' barriers)
         }
@@ -572,7 +620,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
             if (has_next && !f32)
                 for (int i = wave + (lane >> 5) * kWaves; i < nslots; i += 2 * kWaves) {
                     const int pix = 4 * i + ((lane >> 3) & 3);
-                    if (pix < npl) split_slot(pix, lane & 7, scale);
+                    if (pix < npl) split_slot(pix, lane & 7, scale, own ? px_inv : nullptr);
                 }
             __syncthreads();
             // ---- 16-pixel tiles ------------------------------------------
@@ -645,6 +693,8 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
                 if (has_next) {
                     if (__builtin_expect(f32, 0))
                         acc = contract_bwd_f32(as, was, raw, base, W2, 1, q4, lane);
+                    else if (__builtin_expect(own, 0))
+                        acc = contract_bwd_own(as, was, px_inv, base, W2, 1, q4, lane);
                     else
                         acc = contract_bwd(as, was, base, W2, 1, q4, lane);
                     acc = acc * inv * *(const f4 *)&winv[4 * q4];
@@ -671,13 +721,13 @@ StripCostModel bwd_model(bool allow_resident)
 {
     StripCostModel m;
     m.fixed_bytes = kWaFloats * sizeof(float);
-    m.px_bytes = kG * sizeof(float);
+    m.px_bytes = (kG + 1) * sizeof(float);        // dA, 1 / scale
     m.c_sync = 3.0;
     m.c_tile = 2.9;
     m.c_stage0 = 1.0;
     m.c_stage_px = 0.008;
     m.allow_resident = allow_resident;
-    m.res_px_bytes = kG * sizeof(float);          // dA_{t+1} / dA_t, in place
+    m.res_px_bytes = (kG + 1) * sizeof(float);    // dA_{t+1} / dA_t, in place; 1 / scale
     m.res_own_bytes = 1;                          // tile order (4 bytes per 16 pixels)
     m.res_fixed_bytes = 16 * sizeof(int);         // counters
     m.res_max_staged = 1 << 30;
