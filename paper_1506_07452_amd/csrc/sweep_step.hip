@@ -1786,8 +1786,9 @@ struct BwdStepArgs {
 // back S lines per launch with overlapped tiles.  At reverse line j it
 // computes the segment widened by (S - j) r pixels on each side: line j + 1
 // reads all but the outer r of them (the outer r serve dL/dx).  dA_{t+1} (64
-// gate-units per pixel as split pairs (split.h) scaled by the line's largest |dA|, or as
-// they are where one scale does not serve the line (da_wide) or the weights, 16-byte
+// gate-units per pixel as split pairs (split.h) scaled by the line's largest |dA|, by the
+// pixel's own where that does not serve the line (da_wide), or as they are where a value
+// is not finite or one scale does not serve the weights, 16-byte
 // chunks XOR-swizzled by the pixel; overwritten after a barrier) and
 // gc_{t+1} f_{t+1} (in place) stay in LDS, and so does
 // the c_{t-1} read at line t, which is the next line's c.  The saved gates and
@@ -1902,6 +1903,7 @@ k_line_bwd(LineBwdArgs a)
     __shared__ unsigned lmx[2][2];              // range of |dA| of a line, by parity
     __shared__ f4 cl[kLineSlots][4];            // c_{t-1} read at line t: line t - 1's c
     __shared__ f4 dbr[4][4][4];                 // bias-gradient sums [wave][gate][q4]
+    __shared__ float pinv[kLineSlots];          // 1 / scale of each pixel, where it has its own
     extern __shared__ f4 dyn[];
     const int lane = threadIdx.x & 63, q4 = lane >> 4, col = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1938,7 +1940,7 @@ k_line_bwd(LineBwdArgs a)
         return m;
     };
     const bool rawh = a.rinv[d * 32 + 20] != 0.0f, rawx = a.rinv[d * 32 + 21] != 0.0f;
-    bool f32;                                   // the line in dab is fp32
+    bool f32, own;                              // the line in dab is fp32, has a scale per pixel
     // joins the wave's range into line parity p's
     auto leave_range = [&](int p, DaRange r) {
         if (lane == 0) {
@@ -1993,14 +1995,21 @@ k_line_bwd(LineBwdArgs a)
         __syncthreads();
         const DaRange range = line_range(1);
         const int ex = da_exp(range);
-        f32 = rawh || rawx || da_wide(range);
+        f32 = rawh || rawx || range.x == 255;
+        own = !f32 && da_wide(range);
         scale = line_sign(tn) * exp2i(ex);
-        inv = f32 ? 1.0f : line_sign(tn) * exp2i(-ex);
+        inv = f32 || own ? 1.0f : line_sign(tn) * exp2i(-ex);
 #pragma unroll
         for (int k = 0; k < kIt; ++k) {
             const int e = threadIdx.x + 256 * k, slot = e >> 3, ch = e & 7;
+            float sc = scale;
+            if (own) {
+                const int px = pixel_exp(__float_as_uint(max8(top8(v[k][0], v[k][1]))));
+                sc = exp2i(px);
+                if (ch == 0 && slot < kLineSlots) pinv[slot] = exp2i(-px);
+            }
             if (slot >= kLineSlots) continue;
-            Split8 sp = split8(v[k][0] * scale, v[k][1] * scale);
+            Split8 sp = split8(v[k][0] * sc, v[k][1] * sc);
             if (f32) sp = {__builtin_bit_cast(h8, v[k][0]), __builtin_bit_cast(h8, v[k][1])};
             ((h8 *)dab)[slot * 16 + ((2 * ch) ^ (slot & 15))] = sp.hi;
             ((h8 *)dab)[slot * 16 + ((2 * ch + 1) ^ (slot & 15))] = sp.lo;
@@ -2025,6 +2034,24 @@ k_line_bwd(LineBwdArgs a)
                     acc = mfma(w.a[i], b0[i], acc);
                     acc = mfma(w.b[i], b1[i], acc);
                 }
+            }
+            return acc;
+        }
+        if (__builtin_expect(own, 0)) {
+#pragma unroll 1
+            for (int tap = 0; tap < NK / 2; ++tap) {
+                const int sx = slot - (tap - rq);
+                f4 x = zero, y = zero;
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    const int o = sx * 16 + ((8 * half + 2 * q4) ^ (sx & 15));
+                    const h8 bh = ((const h8 *)dab)[o], bl = ((const h8 *)dab)[o ^ 1];
+                    const h8 wh = weight(2 * tap + half, 0), wl = weight(2 * tap + half, 1);
+                    x = mfma_h(wl, bh, x);
+                    y = mfma_h(wh, bh, y);
+                    x = mfma_h(wh, bl, x);
+                }
+                acc += join(y, x) * pinv[sx];
             }
             return acc;
         }
@@ -2118,21 +2145,28 @@ k_line_bwd(LineBwdArgs a)
         __syncthreads();
         const DaRange range = line_range(j & 1);
         const int ex = da_exp(range);
-        f32 = rawh || rawx || da_wide(range);
+        f32 = rawh || rawx || range.x == 255;
+        own = !f32 && da_wide(range);
         scale = line_sign(t) * exp2i(ex);
-        inv = f32 ? 1.0f : line_sign(t) * exp2i(-ex);
+        inv = f32 || own ? 1.0f : line_sign(t) * exp2i(-ex);
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int i = wave + 4 * k;
             if (i >= ntl) continue;
             const int slot = lo + 16 * i + col;
+            float sc = scale;
+            if (own) {                          // (pm[k]: over the pixel's four lanes)
+                const int px = pixel_exp(pm[k]);
+                sc = exp2i(px);
+                pinv[slot] = exp2i(-px);
+            }
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 if (f32) {
                     dab[slot * 16 + ((4 * g + q4) ^ (slot & 15))] = onv[k] ? dv[k][g] : zero;
                     continue;
                 }
-                const Split4 sp = split4(onv[k] ? dv[k][g] * scale : zero);
+                const Split4 sp = split4(onv[k] ? dv[k][g] * sc : zero);
                 // gate-units 16 g + 4 q4 .. + 3: half of the chunks of units 8 (2 g + q4 / 2) .. + 7
                 const int ch = slot * 16 + ((4 * g + 2 * (q4 >> 1)) ^ (slot & 15));
                 ((h4 *)&dab[ch])[q4 & 1] = sp.hi;
@@ -3573,7 +3607,7 @@ int step_bwd(const Geom &g, const float *x, const float *wh, const float *wx, co
     const size_t line_dyn = line_bwd_dyn_lds(g.KQ, fuse_dx);
     const bool lines =
         g.nd == 4 && g.KP == 1 && g.O == 16 && (g_step_split == 0 || g_step_split == 2) &&
-        line_dyn + 2 * kLineSlots * 64 + 4 * 4 * 4 * 16 + 16 <= (size_t)device_info().max_lds;
+        line_dyn + 2 * kLineSlots * 64 + 4 * 4 * 4 * 16 + kLineSlots * 4 + 16 <= (size_t)device_info().max_lds;
     const bool split = !lines && g_step_split == 0;
     if (!split) {
         timing_begin("sweep_bwd_step", st);
