@@ -502,12 +502,11 @@ k_step_fwd_h2(FwdH2Args a)
     } else {
         // fp32 channels: K-group kg is eight k-steps of the fp32 instruction,
         // lane group q supplying channel j of its slot
-        for (int kg = 0; kg < KG; ++kg) {
-            __syncthreads();
-            issue_a(kg, ring0);
-            __builtin_amdgcn_s_waitcnt(kWaitAllLds);
-            __syncthreads();
+        auto products = [&](int kg, auto masked) {
             const int bo = tab[4 * kg + q4];
+            // (h slots of the last group with input slots at t = 0: no product with an
+            // infinite weight where there is no h)
+            const bool real = !decltype(masked)::value || 4 * kg + q4 < a.NSX;
 #pragma unroll
             for (int hl = 0; hl < 2; ++hl)
 #pragma unroll
@@ -516,15 +515,23 @@ k_step_fwd_h2(FwdH2Args a)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         f4 av = __builtin_bit_cast(f4, ring0[(wm * 8 + 2 * i + hl) * 64 + lane]);
-                        // (h slots of the last group with input slots: no product with
-                        // an infinite weight where there is no h)
-                        if (t == 0 && 4 * kg + q4 >= a.NSX) av = f4{0.0f, 0.0f, 0.0f, 0.0f};
+                        if (!real) av = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
                             acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[j], bv[j],
                                                                               acc[i][nt], 0, 0, 0);
                     }
                 }
+        };
+        for (int kg = 0; kg < KG; ++kg) {
+            __syncthreads();
+            issue_a(kg, ring0);
+            __builtin_amdgcn_s_waitcnt(kWaitAllLds);
+            __syncthreads();
+            if (t == 0 && kg == KG - 1)
+                products(kg, std::true_type{});
+            else
+                products(kg, std::false_type{});
         }
     }
 
