@@ -162,8 +162,7 @@ struct SlotOff {
     int xlo;       // plane distance of x
 };
 __device__ __forceinline__ void tile_preact(const float *afr, const char *h, const char *x,
-                                            const SlotOff &o, int q4, int lane, bool f32,
-                                            f4 (&acc)[4])
+                                            const SlotOff &o, int q4, int lane, f4 (&acc)[4])
 {
     f4 cross[4];
 #pragma unroll
@@ -181,34 +180,54 @@ __device__ __forceinline__ void tile_preact(const float *afr, const char *h, con
             bh = read_pair(p);
             bl = read_pair(p + (is_h ? 16 : o.xlo));
         }
-        if (!f32) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const h8 ah = ap[(kg * 4 + g) * 128], al = ap[(kg * 4 + g) * 128 + 64];
-                cross[g] = mfma_h(al, bh, cross[g]);
-                acc[g] = mfma_h(ah, bh, acc[g]);
-                cross[g] = mfma_h(ah, bl, cross[g]);
-            }
-        } else {
-            f4 b0 = __builtin_bit_cast(f4, bh), b1 = __builtin_bit_cast(f4, bl);
-            // (the pixel with zero weights may hold an infinity)
-            const bool one = kg == 5 ? (q4 & 1) : kg == 4 && q4 == 3;
-            if (kg >= 4) b0[2] = one ? 0.0f : b0[2], b0[3] = one ? 0.0f : b0[3];
-            if (kg >= 4) b1[2] = one ? 0.0f : b1[2], b1[3] = one ? 0.0f : b1[3];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f4 a0 = __builtin_bit_cast(f4, ap[(kg * 4 + g) * 128]);
-                const f4 a1 = __builtin_bit_cast(f4, ap[(kg * 4 + g) * 128 + 64]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[i], b0[i], acc[g], 0, 0, 0);
-                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[i], b1[i], acc[g], 0, 0, 0);
-                }
-            }
+        for (int g = 0; g < 4; ++g) {
+            const h8 ah = ap[(kg * 4 + g) * 128], al = ap[(kg * 4 + g) * 128 + 64];
+            cross[g] = mfma_h(al, bh, cross[g]);
+            acc[g] = mfma_h(ah, bh, acc[g]);
+            cross[g] = mfma_h(ah, bl, cross[g]);
         }
     }
 #pragma unroll
     for (int g = 0; g < 4; ++g) acc[g] = join(acc[g], cross[g]);
+}
+// The same of fp32 channels with the fp32 instruction, eight k-steps a K-group.  In a loop
+// that works the slots out again: unrolled beside the other it cost the kernel, whose
+// waves have 128 registers, up to 13 spilled.
+__device__ __forceinline__ void tile_preact_f32(const float *afr, const char *h, const char *x, int xlo,
+                                                int rs, int cs, bool resident, int q4, int lane,
+                                                f4 (&acc)[4])
+{
+#pragma unroll
+    for (int g = 0; g < 4; ++g) acc[g] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int kg = 0; kg < kKG; ++kg) {
+        int q = q4;
+        asm volatile("" : "+v"(q));          // (nothing of it kept over the steps)
+        const int slot = 4 * kg + q, tap = slot >> 1, ta = (tap * 11) >> 5, xsl = slot - 18;
+        const bool is_h = slot < 18;
+        const char *p = is_h ? h + ((ta - 1) * rs + (tap - 3 * ta - 1) * cs) * kHS * 4 + (slot & 1) * 32
+                             : x + (((xsl >> 1) - 1) * (resident ? cs : rs) + ((xsl & 1) ? 1 : -1)) * 8;
+        f4 b0 = __builtin_bit_cast(f4, read_pair(p));
+        f4 b1 = __builtin_bit_cast(f4, read_pair(p + (is_h ? 16 : xlo)));
+        // (the pixel with zero weights may hold an infinity)
+        const bool one = !is_h && (xsl & 1);
+#pragma unroll
+        for (int i = 2; i < 4; ++i) {
+            b0[i] = one ? 0.0f : b0[i];
+            b1[i] = one ? 0.0f : b1[i];
+        }
+        const h8 *ap = (const h8 *)afr + kg * 512 + lane;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f4 a0 = __builtin_bit_cast(f4, ap[g * 128]), a1 = __builtin_bit_cast(f4, ap[g * 128 + 64]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[i], b0[i], acc[g], 0, 0, 0);
+                acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[i], b1[i], acc[g], 0, 0, 0);
+            }
+        }
+    }
 }
 
 // A fragments and row scales (split.h), one workgroup per (direction, gate); x
@@ -466,7 +485,11 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
                 const int v = splane + ra * sp + (q0 + ca) * sq;
                 const f4 cv = *(const f4 *)&cb[pa * kCS + 4 * q4];
                 f4 acc[4];
-                tile_preact(whs, (const char *)&hprev[base * kHS], xs + base * 8, so, q4, lane, f32, acc);
+                if (__builtin_expect(f32, 0))
+                    tile_preact_f32(whs, (const char *)&hprev[base * kHS], xs + base * 8, so.xlo, rs, cs,
+                                    true, q4, lane, acc);
+                else
+                    tile_preact(whs, (const char *)&hprev[base * kHS], xs + base * 8, so, q4, lane, acc);
                 f4 gi, gf, gg, go, cn, hn;
                 lstm_cell(acc, bs, q4, cv, t > 0, gi, gf, gg, go, cn, hn);
                 if (mt * 16 + col < npx) {
@@ -588,7 +611,11 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
                 // otherwise sink it to its use and expose its latency)
                 __builtin_amdgcn_sched_barrier(0);
                 f4 acc[4];
-                tile_preact(whs, (const char *)&hs[base * kHS], xs + base * 8, so, q4, lane, f32, acc);
+                if (__builtin_expect(f32, 0))
+                    tile_preact_f32(whs, (const char *)&hs[base * kHS], xs + base * 8, so.xlo, rs, cs,
+                                    false, q4, lane, acc);
+                else
+                    tile_preact(whs, (const char *)&hs[base * kHS], xs + base * 8, so, q4, lane, acc);
                 if (mt * 16 + col >= npx) continue;
                 f4 gi, gf, gg, go, cn, hn;
                 lstm_cell(acc, bs, q4, cv, t > 0, gi, gf, gg, go, cn, hn);
