@@ -359,6 +359,8 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
         const float inv_p = 1.0f / (float)P;
         for (int e = threadIdx.x; e < npl * (kG / 4); e += kThreads)
             *(f4 *)&as[e * 4] = f4{0.0f, 0.0f, 0.0f, 0.0f};   // dA_T = 0, halo rows
+        // (pixels off the plane stay zero: their scale is only to be finite)
+        for (int e = threadIdx.x; e < npl; e += kThreads) px_inv[e] = 0.0f;
         if (threadIdx.x == 0) {
             int k = 0, ne = 0;
             for (int pass = 0; pass < 2; ++pass)
