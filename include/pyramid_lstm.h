@@ -409,16 +409,15 @@ int pyramid_lstm_set_forward_path(int path);
 int pyramid_lstm_set_backward_path(int path);
 
 /* Launch shape of the plane-step MFMA path, for testing and tuning
- * (process-wide): 0 = automatic (default): the reverse step (16 or 32 units)
- * runs on 64-pixel blocks with dA_{t+1} staged in LDS, its K split over a
- * workgroup's four waves; a forward step whose tiles would give fewer than
- * about two waves per SIMD splits each tile's K dimension over the four
- * waves of a workgroup, other steps give each wave its own tiles;
- * 1 = always split (the reverse step's operands read from L1); 2 = never
- * split; 3 = never split, and the forward's operands read from L1 per
- * filter tap instead of from 64-pixel blocks staged in LDS (the default for
- * fp32 steps that are not split).  Results are identical up to summation
- * order.  Returns PLSTM_EINVAL for other values. */
+ * (process-wide): 0 = the default: fp32 steps on the 16-bit matrix unit with
+ * operands split into two fp16 halves, in blocks of at most 128 pixels whose
+ * shape follows from the plane (2D layers of 16 units: line blocks).  The
+ * others select fp32 steps on the fp32 instruction instead: 1 = each tile's K
+ * dimension split over the four waves of a workgroup; 2 = each wave its own
+ * tiles, the forward's operands from 64-pixel blocks staged in LDS (2D layers
+ * of 16 units keep their line blocks); 3 = as 2, the forward's operands read
+ * from L1 per filter tap.  bf16 steps split or do not the same way.  Results
+ * are identical up to rounding.  Returns PLSTM_EINVAL for other values. */
 int pyramid_lstm_set_step_split(int mode);
 
 /* Contraction type of bf16-storage layers with 32 or 64 hidden units, for

@@ -515,9 +515,10 @@ def pyramid_lstm_set_backward_path(path: int) -> None:
 
 
 def pyramid_lstm_set_step_split(mode: int) -> None:
-    """Plane-step launch shape: 0 = automatic, 1 = always split each tile's K
-    over a workgroup's waves, 2 = never, 3 = never and the fp32 forward
-    reading its operands from L1 instead of LDS-staged pixel blocks."""
+    """Plane steps, for testing: 0 = the default (fp32: split products);
+    otherwise the fp32 steps on the fp32 instruction, 1 = each tile's K split
+    over a workgroup's waves, 2 = not, 3 = not and the forward's operands read
+    from L1 instead of LDS-staged pixel blocks."""
     _check("pyramid_lstm_set_step_split", load().pyramid_lstm_set_step_split(int(mode)))
 
 

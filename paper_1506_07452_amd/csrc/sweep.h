@@ -122,9 +122,11 @@ int backward_dispatch(const Geom &g, const float *x, const float *wx, const floa
 // supported.
 extern int g_forward_path;
 extern int g_backward_path;
-// Plane-step launches: 0 = automatic, 1 = always split each tile's K over a
-// workgroup's waves, 2 = never, 3 = never and the fp32 forward without LDS
-// staging.
+// Plane-step launches, for tests.  0: the default, for fp32 the split products of
+// split_step.hip (2D layers of 16 units: line blocks).  Otherwise the fp32 steps on the
+// fp32 instruction, which no other call reaches: 1 = always split each tile's K over a
+// workgroup's waves, 2 = never (line blocks kept), 3 = never and the fp32 forward
+// without LDS staging; bf16 steps split or not the same way.
 extern int g_step_split;
 // bf16 storage with 32 or 64 hidden units: 1 = contraction on the bf16 MFMA
 // with pixel blocks staged in LDS (default), 2 = bf16 MFMA with operands read

@@ -2888,7 +2888,8 @@ inline size_t wg_partial_floats(const Geom &g)
 }
 
 // Waves below which a step splits each tile's K over a workgroup's waves:
-// about two per SIMD (or always / never, when set for testing).
+// about two per SIMD (bf16), or always / never, when set for testing (fp32, whose
+// default steps are split_step.hip's).
 inline int split_threshold()
 {
     if (g_step_split == 1) return 1 << 30;
@@ -2939,9 +2940,7 @@ int launch_fwd_steps(const Geom &g, FwdStepArgs &a, hipStream_t st)
 template <int U>
 int launch_bwd_steps(const Geom &g, BwdStepArgs &a, hipStream_t st)
 {
-    // an item of the reverse step holds every unit group: split up to four
-    // waves per SIMD
-    const int few = g_step_split == 0 ? 2 * split_threshold() : split_threshold();
+    const int few = split_threshold();
     for (int t = max_T(g) - 1; t >= 0; --t) {
         a.t = t;
         int tot = 0;

@@ -168,9 +168,9 @@ STEP_SHAPES = [(1, 5, 37, 29, 3, 16), (2, 4, 9, 7, 1, 16), (1, 6, 5, 4, 20, 16),
 
 @pytest.fixture(params=[0, 1, 2, 3], ids=["auto", "split", "nosplit", "nosplit_l1"])
 def step_split(request):
-    """Every launch shape of the plane-step kernels: the default (staged pixel
-    blocks; the reverse step's K split over a workgroup's waves by gate-unit
-    block), K split over a workgroup's waves, or one tile group per wave."""
+    """The plane steps: the default (fp32 split products; bf16 by its own rule), or the
+    kernels on the fp32 instruction that only this knob selects, with K split over a
+    workgroup's waves, one tile group per wave, or that without LDS staging."""
     P.pyramid_lstm_set_step_split(request.param)
     yield request.param
     P.pyramid_lstm_set_step_split(0)
