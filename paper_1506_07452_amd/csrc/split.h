@@ -153,8 +153,9 @@ struct SplitScan {
     SplitStat x[kStatBlocks];
     unsigned row[kDirs * 4 * 64][2];
 };
+// Clears nclear words of `clear` too.
 int split_scan(int dtype, const void *x, long long n, int rows, int nx, int nh, const void *wx,
-               const void *wh, SplitScan *scan, hipStream_t st);
+               const void *wh, SplitScan *scan, int *clear, int nclear, hipStream_t st);
 
 __device__ inline SplitStat stat_combine(SplitStat a, SplitStat b)
 {

@@ -110,8 +110,9 @@ k_split_stats(long long n, const float *__restrict__ x, SplitStats *__restrict__
 template <typename TS>
 __global__ void __launch_bounds__(256)
 k_split_scan(long long n, int nx, int nh, const TS *__restrict__ x, const TS *__restrict__ wx,
-             const TS *__restrict__ wh, SplitScan *__restrict__ scan)
+             const TS *__restrict__ wh, SplitScan *__restrict__ scan, int *__restrict__ clear, int nclear)
 {
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < nclear; i += gridDim.x * 256) clear[i] = 0;
     if (blockIdx.x < kStatBlocks) {
         __shared__ SplitStat red[4];
         const SplitStat s = scan_values<TS, false>(n, x, 0u, red);
@@ -1366,15 +1367,16 @@ int split_stats(const float *x, long long n, SplitStats *part, unsigned *ctl, hi
 }
 
 int split_scan(int dtype, const void *x, long long n, int rows, int nx, int nh, const void *wx,
-               const void *wh, SplitScan *scan, hipStream_t st)
+               const void *wh, SplitScan *scan, int *clear, int nclear, hipStream_t st)
 {
     const unsigned grid = kStatBlocks + rows / 4;
     if (dtype == PLSTM_BF16)
         k_split_scan<uint16_t><<<grid, 256, 0, st>>>(n, nx, nh, (const uint16_t *)x,
-                                                     (const uint16_t *)wx, (const uint16_t *)wh, scan);
+                                                     (const uint16_t *)wx, (const uint16_t *)wh, scan,
+                                                     clear, nclear);
     else
         k_split_scan<float><<<grid, 256, 0, st>>>(n, nx, nh, (const float *)x, (const float *)wx,
-                                                  (const float *)wh, scan);
+                                                  (const float *)wh, scan, clear, nclear);
     PLSTM_LAUNCH_CHECK();
     return PLSTM_OK;
 }
@@ -1455,7 +1457,7 @@ int split_fwd(const Geom &g, int dtype, const void *x, const void *wx, const voi
     *launches = 2 + (in_place ? 0 : 1) + max_T(g);
 
     const int KK = g.KP * g.KQ, rows = g.nd * 4 * g.O;
-    int rc = split_scan(dtype, x, nvox * g.C, rows, g.C * KK, g.O * KK, wx, wh, scan, st);
+    int rc = split_scan(dtype, x, nvox * g.C, rows, g.C * KK, g.O * KK, wx, wh, scan, nullptr, 0, st);
     if (rc != PLSTM_OK) return rc;
     if (!in_place) {
         const unsigned nb = blocks_for(nvox * k.C8, 256);

@@ -643,12 +643,6 @@ __global__ void __launch_bounds__(kThreads, 1) k_sweep_fwd(SweepArgs a)
     }
 }
 
-__global__ void k_fill_zero(int *p, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
 // ---- launch planning ------------------------------------------------------
 StripCostModel fwd_model(int C)
 {
@@ -768,10 +762,8 @@ int sweep_fwd(const Geom &g, const float *x, const float *wx, const float *wh, c
         args.resident[d] = pl.resident[d];
     }
 
-    k_fill_zero<<<(1025 + 255) / 256, 256, 0, st>>>(flags, 1025);
-    PLSTM_LAUNCH_CHECK();
     int rc = split_scan(PLSTM_F32, x, (long long)g.N * g.V * g.C, kDirs * kG, g.C * 9, kO * 9, wx, wh,
-                        pk.scan, st);
+                        pk.scan, flags, 1024 + 1, st);   // (flags and the error word start from zero)
     if (rc != PLSTM_OK) return rc;
     PackSweepArgs pa;
     pa.C = g.C;
