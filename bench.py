@@ -44,10 +44,9 @@ sys.path.insert(0, ROOT)
 
 METRIC = "voxel-direction LSTM updates/sec (fwd, fwd+bwd) + % peak MFMA, 1 MI355X"
 UNIT = "voxel-direction updates/s"
-# fp32 layers are priced against the fp32 instruction's peak; their contractions run on the
-# 16-bit matrix unit with split operands (three products each), so a fraction may exceed 1
-PEAK_FP32_TFLOPS = 157.3     # MI355X dense fp32 MFMA
-PEAK_BF16_TFLOPS = 2500.0    # MI355X dense bf16 MFMA
+PEAK_BF16_TFLOPS = 2500.0    # MI355X dense bf16 (and fp16) MFMA
+# fp32 contractions run on the 16-bit matrix unit, three fp16 products for each of fp32
+PEAK_FP32_TFLOPS = PEAK_BF16_TFLOPS / 3
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E
 
 
@@ -88,11 +87,11 @@ def phase_work(name, V, C, O, K=3):
 # measured (comments and whitespace aside); a figure whose sources changed
 # since is reported as null.
 PROFILES = os.path.join(ROOT, "profiles")
-_STEP = ["sweep_step.hip", "split_step.hip", "split.h", "common.h"]
-_WGRAD = ["split_wgrad.hip", "sweep_step.hip", "split.h", "common.h"]
+_STEP = ["sweep_step.hip", "split_step.hip", "split.h", "common.h", "index.h"]
+_WGRAD = ["split_wgrad.hip", "sweep_step.hip", "split.h", "common.h", "index.h"]
 KERNEL_SOURCES = {
-    "sweep_fwd_mfma": ["sweep_fwd.hip", "split.h", "strip_plan.h", "common.h", "coherent.h"],
-    "sweep_bwd_mfma": ["sweep_bwd.hip", "split.h", "strip_plan.h", "common.h", "coherent.h"],
+    "sweep_fwd_mfma": ["sweep_fwd.hip", "split.h", "strip_plan.h", "common.h", "index.h", "coherent.h"],
+    "sweep_bwd_mfma": ["sweep_bwd.hip", "split.h", "strip_plan.h", "common.h", "index.h", "coherent.h"],
     "wgrad_mfma": _WGRAD,
     "sweep_fwd_step": _STEP, "sweep_bwd_step": _STEP, "wgrad_step": _WGRAD, "dx_step": _STEP,
     "sweep_fwd_step_bf16": _STEP,
