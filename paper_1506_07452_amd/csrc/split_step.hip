@@ -264,7 +264,7 @@ struct FwdH2Args {
 // Bound by each launch's latency on small planes (staging 8, cell update 2.5 of
 // 15-28 kilocycles) and by LDS reads and barriers on large ones (a K-group takes
 // 1.0 kilocycles for 0.77 of products).  Measured against the fp32 instruction on
-// 64-pixel blocks: 32 -> 32 units on 48 x 240 x 240, training, 24.1 -> 11.5 ms (213
+// 64-pixel blocks: 32 -> 32 units on 48 x 240 x 240, training, 24.1 -> 11.0 ms (223
 // TFLOP/s of fp32 products); 64 -> 64 on 20 x 64 x 64 6.0 -> 1.8; 7 x 7, 25 -> 32 on
 // 15 x 128 x 128 18.2 -> 5.5; 6 -> 16 on 19 x 101 x 75 1.35 -> 0.84.  Not kept: a ring
 // of two arrays with operands read in the step that uses them (8.0 against 7.4 ms

@@ -76,7 +76,7 @@ struct WgH2Args {
 // units, 3 x 3) the products are 3.8, each wave's loads, splits and LDS stores 3
 // and the transposed reads' latency most of the rest.  Measured against the fp32
 // GEMM it replaces (im2col columns staged per tap, or operands streamed from
-// memory), with the reduction: 32 -> 32 units on 48 x 240 x 240 24.1 -> 9.7 ms, on
+// memory), with the reduction: 32 -> 32 units on 48 x 240 x 240 24.1 -> 9.8 ms, on
 // 25 x 240 x 240 12.6 -> 5.7; 64 -> 64 on 20 x 64 x 64 3.2 -> 1.2; 7 x 7, 25 -> 32 on
 // 15 x 128 x 128 10.7 -> 4.5; 16 -> 16, 5 x 5 on 2 x 61 x 132 x 144 19.0 -> 5.1; error
 // against 64 bits 4.6e-6 -> 9e-7.  After the persistent reverse sweep (16 units, 3

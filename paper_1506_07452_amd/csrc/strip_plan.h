@@ -33,9 +33,10 @@ inline DevInfo device_info()
     return di;
 }
 
-// Per-step cost model of a strip (microseconds; fitted on MI355X): a
-// neighbour handshake, then per LDS chunk a staging round trip that grows
-// with the staged pixels and the 16-pixel tiles, shared by four SIMDs.
+// Per-step cost model of a strip (microseconds; fitted on MI355X, each sweep's
+// constants beside its kernel): a neighbour handshake, then per LDS chunk a
+// staging round trip that grows with the staged pixels and the 16-pixel tiles,
+// shared by four SIMDs.
 struct StripCostModel {
     size_t fixed_bytes;   // LDS independent of the strip size
     size_t px_bytes;      // LDS per staged pixel

@@ -175,8 +175,8 @@ __device__ __forceinline__ f4 contract_bwd_f32(const float *as, const float *was
 }
 
 // One launch, against the contraction on v_mfma_f32_16x16x4 (144 instructions of 32
-// cycles a tile; now 54 of 16): 48 x 240 x 240 3.75 -> 3.05 ms, which is 15.6 GB of
-// activations and dA at 5.1 TB/s; 2 x 8 x 64 x 64 x 1, forward and backward, 0.836 ->
+// cycles a tile; now 54 of 16): 48 x 240 x 240 3.75 -> 2.95 ms, which is 15.6 GB of
+// activations and dA at 5.3 TB/s; 2 x 8 x 64 x 64 x 1, forward and backward, 0.836 ->
 // 0.798 ms (bound by the hand-over between strips).
 __global__ void __launch_bounds__(kThreads, 1) k_sweep_bwd(BwdArgs a)
 {
@@ -725,7 +725,7 @@ StripCostModel bwd_model(bool allow_resident)
     m.fixed_bytes = kWaFloats * sizeof(float);
     m.px_bytes = (kG + 1) * sizeof(float);        // dA, 1 / scale
     m.c_sync = 3.0;
-    m.c_tile = 2.9;
+    m.c_tile = 2.9;         // of the fp32 instruction's 144 a tile; not fitted again for split operands
     m.c_stage0 = 1.0;
     m.c_stage_px = 0.008;
     m.allow_resident = allow_resident;

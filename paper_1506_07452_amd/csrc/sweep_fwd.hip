@@ -33,8 +33,9 @@
 // A tile is 72 products of 16 cycles (172 of 32 on the fp32 instruction), 60 LDS
 // reads of 16 bytes a lane and the cell update of about a thousand cycles, which
 // the four waves of a SIMD overlap.  Measured against the fp32 instruction, one
-// launch: 48 x 240 x 240 x 3 inference 3.67 -> 2.01 ms, training (with the stores of the gates) 4.0 -> 3.0; 30 x 512 x 512 x 1 8.9 -> 4.5 and
-// 10.6 -> 8.5; 2 x 8 x 64 x 64 x 1, bound by the hand-over between strips, 0.37 -> 0.32.
+// launch: 48 x 240 x 240 x 3 inference 3.67 -> 1.87 ms, training (with the stores of
+// the gates) 4.0 -> 2.7; 30 x 512 x 512 x 1 inference 8.9 -> 4.3; 2 x 8 x 64 x 64 x 1, bound by the
+// hand-over between strips, 0.37 -> 0.32.
 #include "common.h"
 #include "coherent.h"
 #include "sweep.h"

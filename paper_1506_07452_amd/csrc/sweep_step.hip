@@ -560,7 +560,7 @@ k_step_fwd_blk(FwdStepArgs a)
 // 3 x 16 products of a 3-tap recurrence are 24 matrix instructions of 16 cycles,
 // where the fp32 instruction took 48 of 32.  x, a K-group or two of few channels,
 // stays on the fp32 instruction.  Four workgroups a CU by LDS.  30 x 512 x 512 x 1: 5.35
-// -> 4.19 ms for the 32 launches, which write 12 GB.
+// -> 4.29 ms for the 32 launches, which write 12 GB.
 constexpr int kLineSeg = 64;       // stored pixels of a segment
 constexpr int kLineSlots = 112;    // LDS pixel slots: segment + 2 S r (S r <= 16) + a tile
 struct LineFwdArgs {
@@ -1805,7 +1805,7 @@ struct BwdStepArgs {
 // + 15 of the segment (channels are four of the instruction's 16 rows).
 // 18 matrix instructions of 16 cycles a tile, for gh as for dL/dx, where the fp32 ones
 // were 48 of 32 and dL/dx was summed on the vector unit by wave and gate: 30 x 512 x 512
-// x 1, forward and backward, 15.5 -> 15.0 ms (two workgroups a CU by LDS; 22 GB).
+// x 1, forward and backward, 15.5 -> 15.0 ms (two workgroups a CU by LDS; 27 GB).
 // The sign of a line's scale alternates from line to line and segment to segment, so
 // that the instruction's rounding towards -inf cancels in db.
 // With dbp the segment's dA_t columns are summed too (db): per lane over its
